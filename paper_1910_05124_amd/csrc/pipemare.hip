@@ -186,8 +186,8 @@ pm_status validate(int32_t P, int32_t L, const pm_layer_desc* layers, const int3
     if (!is(L - 2, PM_LAYERNORM, d, d) || !is(L - 1, PM_LINEAR, d, V)) return fail(PM_EINVAL, "the last two units must be the final LayerNorm and the output head (d -> vocabulary)");
     if (d > 1024) return fail(PM_EINVAL, "LayerNorm kernels support widths up to 1024");
     const int dh = d / o->n_heads;
-    const bool mfma_attn = o->dtype == PM_BF16 && pm_attn_mfma_fits(o->seq_len, dh);
-    if (!mfma_attn && !pm_attn_plain_fits(o->seq_len, dh))
+    const bool whole = o->dtype == PM_BF16 && pm_attn_whole_tiles(o->seq_len, dh);
+    if (!whole && !pm_attn_short_fits(o->seq_len, dh))
       return fail(PM_EINVAL, "attention: outside bf16 / head size 64 / seq_len multiple of 32, the head size must be 4, 8, 16, 32 or 64 and seq_len * (head size + 1) <= 8192");
   }
   for (int i = 0; i < P; ++i) {
@@ -889,7 +889,7 @@ pm_status launch_tfm(pm_ctx* c, const void* x_dev, const void* y_dev, int accumu
   };
   auto attn_fwd = [&](const Layout::TfmLayer& b) {
     ProfSpan span(c, PM_CLS_ATTN);
-    return pm_attn_fwd_launch<T>(st, B, S, H, dh, TT(b.q), TT(b.k), TT(b.v), TT(b.o), F(b.lse));
+    return pm_attn_fwd_launch(st, B, S, H, dh, TT(b.q), TT(b.k), TT(b.v), TT(b.o), F(b.lse));
   };
   embed_fwd();
   for (int l = 0; l < nl; ++l) {
@@ -1027,7 +1027,7 @@ pm_status launch_tfm(pm_ctx* c, const void* x_dev, const void* y_dev, int accumu
     dgrad_t(u + 4, TT(b.dzo), d, d, nullptr, PM_ACT_NONE, TT(lay.t_do));
     {
       ProfSpan span(c, PM_CLS_ATTN);
-      if (!pm_attn_bwd_launch<T>(st, B, S, H, dh, TT(b.q), TT(b.k), TT(b.v), TT(b.o), TT(lay.t_do), F(b.lse), TT(b.dzq),
+      if (!pm_attn_bwd_launch(st, B, S, H, dh, TT(b.q), TT(b.k), TT(b.v), TT(b.o), TT(lay.t_do), F(b.lse), TT(b.dzq),
                                  TT(b.dzk), TT(b.dzv)))
         return fail(PM_EINVAL, "attention shape not supported");
     }
@@ -2000,8 +2000,8 @@ pm_status pm_attention_fwd(void* stream, int32_t dtype, int32_t B, int32_t S, in
   if (!q_dev || !k_dev || !v_dev || !o_dev || !lse_dev) return fail(PM_EINVAL, "NULL argument");
   hipStream_t st = (hipStream_t)stream;
   const bool ok = dtype == PM_BF16
-      ? pm_attn_fwd_launch<bf16_t>(st, B, S, H, dh, (const bf16_t*)q_dev, (const bf16_t*)k_dev, (const bf16_t*)v_dev, (bf16_t*)o_dev, lse_dev)
-      : pm_attn_fwd_launch<float>(st, B, S, H, dh, (const float*)q_dev, (const float*)k_dev, (const float*)v_dev, (float*)o_dev, lse_dev);
+      ? pm_attn_fwd_launch(st, B, S, H, dh, (const bf16_t*)q_dev, (const bf16_t*)k_dev, (const bf16_t*)v_dev, (bf16_t*)o_dev, lse_dev)
+      : pm_attn_fwd_launch(st, B, S, H, dh, (const float*)q_dev, (const float*)k_dev, (const float*)v_dev, (float*)o_dev, lse_dev);
   if (!ok) return fail(PM_EINVAL, "attention shape (S %d, head size %d) not supported for this dtype", S, dh);
   PM_HIP(hipGetLastError());
   return PM_OK;
@@ -2015,9 +2015,9 @@ pm_status pm_attention_bwd(void* stream, int32_t dtype, int32_t B, int32_t S, in
   if (!q_dev || !k_dev || !v_dev || !o_dev || !do_dev || !lse_dev || !dq_dev || !dk_dev || !dv_dev) return fail(PM_EINVAL, "NULL argument");
   hipStream_t st = (hipStream_t)stream;
   const bool ok = dtype == PM_BF16
-      ? pm_attn_bwd_launch<bf16_t>(st, B, S, H, dh, (const bf16_t*)q_dev, (const bf16_t*)k_dev, (const bf16_t*)v_dev, (const bf16_t*)o_dev,
+      ? pm_attn_bwd_launch(st, B, S, H, dh, (const bf16_t*)q_dev, (const bf16_t*)k_dev, (const bf16_t*)v_dev, (const bf16_t*)o_dev,
                                    (const bf16_t*)do_dev, lse_dev, (bf16_t*)dq_dev, (bf16_t*)dk_dev, (bf16_t*)dv_dev)
-      : pm_attn_bwd_launch<float>(st, B, S, H, dh, (const float*)q_dev, (const float*)k_dev, (const float*)v_dev, (const float*)o_dev,
+      : pm_attn_bwd_launch(st, B, S, H, dh, (const float*)q_dev, (const float*)k_dev, (const float*)v_dev, (const float*)o_dev,
                                   (const float*)do_dev, lse_dev, (float*)dq_dev, (float*)dk_dev, (float*)dv_dev);
   if (!ok) return fail(PM_EINVAL, "attention shape (S %d, head size %d) not supported for this dtype", S, dh);
   PM_HIP(hipGetLastError());

@@ -1,8 +1,8 @@
-// Causal attention core on bf16 MFMA (v_mfma_f32_32x32x16_bf16), head size 64, gfx950.
+// Causal attention core on bf16 MFMA (v_mfma_f32_32x32x16_bf16), head sizes 64 and 32, any sequence length, gfx950.
 //
 // The attention core carries no weights (so no stale / corrected weight enters it); it is on the
 // path of the fine-grained Transformer stages because q, k, v come from three weight units and o
-// feeds a fourth.  q, k, v, o and their gradients are [tokens, H * 64] bf16, row t = b * S + s.
+// feeds a fourth.  q, k, v, o and their gradients are [tokens, H * DH] bf16, row t = b * S + s.
 //
 // One scheme serves the forward and both backward kernels.  A wave owns 32 rows of one index
 // (queries in the forward and the dQ kernel, keys in the dK/dV kernel) and streams 32-row tiles of
@@ -18,6 +18,17 @@
 // v of lane group g = l / 32 the streamed row 16 (v / 8) + 8 g + v % 8, i.e. values 8 s .. 8 s + 7 are
 // exactly the k-slots of lane group g in k-step s of the second MFMA.
 //
+// A sequence that is no multiple of 32 rows (RAGGED, a template argument so that whole tiles keep their plain loads):
+// loads past the end re-read the last row, so every value stays finite.  Owned rows past the end are not stored.
+// Streamed keys past the end lie behind every query that is stored and fall to the causal mask; only the dK/dV
+// kernel, whose streamed index is the query, masks its last tile explicitly.
+// (24 x 100 tokens, 5 heads of 64, on the one-thread-per-row kernels that these lengths took before: forward 511 us,
+// backward 2090 us per layer, one wave per 64 rows walking 100 dependent keys; here 7 us and 18 us.)
+//
+// SPLIT: the second products take the probabilities (and dS) as two bf16 terms instead of one.  Whole tiles of 64-wide
+// heads round them to one bf16 value; the shapes that used to run on fp32 arithmetic (32-wide heads, ragged lengths)
+// keep sixteen mantissa bits through these products, for two more matrix instructions per tile and head half.
+//
 // Probabilities are recomputed in the backward from q, k and the stored log-sum-exp of the scaled
 // scores; D_i = sum_c dO[i, c] O[i, c].  Two backward kernels (dQ; dK and dV) so that every output
 // has one owner and no atomics are needed.
@@ -26,22 +37,25 @@
 #include "pm_common.hpp"
 #include "pm_mfma_types.hpp"
 
-constexpr int PM_AT_ST = 72;          // LDS row stride (elements) of a [32][64] tile: 144 B, 16-byte aligned rows
+// LDS row stride (elements) of a [32][DH] tile: 16-byte aligned rows, 8 elements of padding keep the rows' banks apart
+template <int DH> constexpr int PM_AT_ST = DH + 8;
 
 __device__ __forceinline__ int pm_at_perm(int m) { return (m & 0x13) | ((m & 4) << 1) | ((m & 8) >> 1); }
 
 // A fragment, contraction index contiguous: tile row `row`, contraction indices kb + 8 * (lane / 32) .. + 7
+template <int DH>
 __device__ __forceinline__ pm_bf16x8 pm_at_frag(const bf16_t* s, int row, int kb, int lane) {
-  return *reinterpret_cast<const pm_bf16x8*>(s + row * PM_AT_ST + kb + (lane >> 5) * 8);
+  return *reinterpret_cast<const pm_bf16x8*>(s + row * PM_AT_ST<DH> + kb + (lane >> 5) * 8);
 }
 // A fragment of the transposed tile: MFMA row = tile column r32 + lane % 32, contraction = tile rows
 // kb + 8 * (lane / 32) .. + 7 (LDS transpose load; lane mapping as in the GEMM's row-contiguous operands)
+template <int DH>
 __device__ __forceinline__ pm_bf16x8 pm_at_frag_tr(const bf16_t* s, int r32, int kb, int lane) {
   const int g = lane >> 4, q = lane & 15;
-  const bf16_t* p = s + (kb + 8 * (g >> 1) + (q >> 2)) * PM_AT_ST + r32 + 16 * (g & 1) + 4 * (q & 3);
+  const bf16_t* p = s + (kb + 8 * (g >> 1) + (q >> 2)) * PM_AT_ST<DH> + r32 + 16 * (g & 1) + 4 * (q & 3);
   typedef pm_v4s __attribute__((address_space(3))) * lds_v4s;
   const pm_v4s lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)(p));
-  const pm_v4s hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)(p + 4 * PM_AT_ST));
+  const pm_v4s hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)(p + 4 * PM_AT_ST<DH>));
   union { pm_bf16x8 v; pm_v4s h[2]; } u;
   u.h[0] = lo;
   u.h[1] = hi;
@@ -53,12 +67,49 @@ __device__ __forceinline__ pm_bf16x8 pm_at_pack8(const float* x) {
   for (int e = 0; e < 4; ++e) u.w[e] = pm_pack_bf16(x[2 * e], x[2 * e + 1]);
   return u.v;
 }
-// result tile [64 x 32] held as two accumulators (MFMA rows = head dimension, column = owned row):
-// store transposed into out[row0 + lane % 32][0..63] (bf16), 4 consecutive head-dimension entries at a time
+// eight values as two bf16 terms (the rounded values and what the rounding left): sixteen mantissa bits
+__device__ __forceinline__ void pm_at_split8(const float* x, pm_bf16x8* hi, pm_bf16x8* lo) {
+  *hi = pm_at_pack8(x);
+  union { pm_bf16x8 v; uint32_t w[4]; } u;
+  u.v = *hi;
+  float r[8];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    r[2 * e] = x[2 * e] - __uint_as_float(u.w[e] << 16);
+    r[2 * e + 1] = x[2 * e + 1] - __uint_as_float(u.w[e] & 0xffff0000u);
+  }
+  *lo = pm_at_pack8(r);
+}
+// acc[dt] += X^T x: X the streamed tile in LDS (read transposed), x = 16 per-lane values of the second product's
+// contraction (the 32 streamed rows).  SPLIT: x in two bf16 terms, see below.
+template <int DH, bool SPLIT>
+__device__ __forceinline__ void pm_at_second(pm_f32x16* acc, const bf16_t* sX, const float* x, int lane) {
+  pm_bf16x8 h0, h1, l0, l1;
+  if (SPLIT) {
+    pm_at_split8(x, &h0, &l0);
+    pm_at_split8(x + 8, &h1, &l1);
+  } else {
+    h0 = pm_at_pack8(x);
+    h1 = pm_at_pack8(x + 8);
+  }
+#pragma unroll
+  for (int dt = 0; dt < DH / 32; ++dt) {
+    const pm_bf16x8 a0 = pm_at_frag_tr<DH>(sX, dt * 32, 0, lane), a1 = pm_at_frag_tr<DH>(sX, dt * 32, 16, lane);
+    acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, h0, acc[dt], 0, 0, 0);
+    acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, h1, acc[dt], 0, 0, 0);
+    if (SPLIT) {
+      acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, l0, acc[dt], 0, 0, 0);
+      acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, l1, acc[dt], 0, 0, 0);
+    }
+  }
+}
+// result tile [DH x 32] held as DH / 32 accumulators (MFMA rows = head dimension, column = owned row):
+// store transposed into out[row0 + lane % 32][0 .. DH - 1] (bf16), 4 consecutive head-dimension entries at a time
+template <int DH>
 __device__ __forceinline__ void pm_at_store_t(bf16_t* out_row, const pm_f32x16* acc, float mul, int lane) {
   const int g = lane >> 5;
 #pragma unroll
-  for (int dt = 0; dt < 2; ++dt)
+  for (int dt = 0; dt < DH / 32; ++dt)
 #pragma unroll
     for (int a = 0; a < 4; ++a) {
       uint2 w;
@@ -74,44 +125,49 @@ __device__ __forceinline__ void pm_at_store_t(bf16_t* out_row, const pm_f32x16* 
 // ---------------------------------------------------------------------------------------------
 // (register budget of four waves per SIMD: two values spill, and the fourth wave is worth more - 26.2 -> 24.7 us on
 // 16 x 512 tokens, 16 heads; the dQ kernel would spill 34 and is left at three)
+template <int DH, bool RAGGED, bool SPLIT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void pm_attn_mfma_fwd_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
                                                                const bf16_t* __restrict__ v, bf16_t* __restrict__ o,
                                                                float* __restrict__ lse, int S, int H, int BH, float scale) {
-  __shared__ __attribute__((aligned(16))) bf16_t sK[2][32 * PM_AT_ST];
-  __shared__ __attribute__((aligned(16))) bf16_t sV[2][32 * PM_AT_ST];
+  __shared__ __attribute__((aligned(16))) bf16_t sK[2][32 * PM_AT_ST<DH>];
+  __shared__ __attribute__((aligned(16))) bf16_t sV[2][32 * PM_AT_ST<DH>];
   const int qblocks = (S + 127) / 128;
   const int bh = blockIdx.x % BH, qb = qblocks - 1 - blockIdx.x / BH;      // long blocks first
-  const int b = bh / H, h = bh % H, d = H * 64;
-  const int64_t base = (int64_t)b * S * d + (int64_t)h * 64;
+  const int b = bh / H, h = bh % H, d = H * DH;
+  const int64_t base = (int64_t)b * S * d + (int64_t)h * DH;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, ql = lane & 31, g = lane >> 5;
   const int q0 = qb * 128 + wave * 32;
   const bool active = q0 < S;
   const int my_last = q0 >> 5;
-  const int n_tiles = (S < qb * 128 + 128 ? S : qb * 128 + 128) >> 5;
+  const int qr = RAGGED && q0 + ql >= S ? S - 1 : q0 + ql;                 // the row this lane reads
+  const int n_tiles = ((S < qb * 128 + 128 ? S : qb * 128 + 128) + 31) >> 5;
 
-  pm_bf16x8 fq[4];
+  pm_bf16x8 fq[DH / 16];
 #pragma unroll
-  for (int kk = 0; kk < 4; ++kk)
-    fq[kk] = active ? *reinterpret_cast<const pm_bf16x8*>(q + base + (int64_t)(q0 + ql) * d + kk * 16 + 8 * g) : pm_at_zero8();
-  pm_f32x16 acc[2];
+  for (int kk = 0; kk < DH / 16; ++kk)
+    fq[kk] = active ? *reinterpret_cast<const pm_bf16x8*>(q + base + (int64_t)qr * d + kk * 16 + 8 * g) : pm_at_zero8();
+  pm_f32x16 acc[DH / 32];
 #pragma unroll
-  for (int dt = 0; dt < 2; ++dt)
+  for (int dt = 0; dt < DH / 32; ++dt)
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[dt][e] = 0.f;
   float m = -3.0e38f, lsum = 0.f;
 
-  const int lrow = threadIdx.x >> 3, lcol = (threadIdx.x & 7) * 8;       // loader: 32 rows x 8 pieces of 16 bytes
+  // loader: 32 rows x DH / 8 pieces of 16 bytes (32-wide heads: the block's halves fetch and park the same pieces)
+  const int lrow = (threadIdx.x / (DH / 8)) & 31, lcol = (threadIdx.x & (DH / 8 - 1)) * 8;
   // Two register sets: while tile jt is consumed from LDS, tile jt + 1 (loaded an iteration earlier) waits
   // in one set for its LDS store at the end of the iteration and tile jt + 2 is being loaded into the other,
   // so a load has more than a whole iteration to arrive.
   uint4 rk0, rv0, rk1 = make_uint4(0, 0, 0, 0), rv1 = rk1;
   auto gload = [&](int t, uint4& rk, uint4& rv) __attribute__((always_inline)) {
-    rk = *reinterpret_cast<const uint4*>(k + base + (int64_t)(t * 32 + lrow) * d + lcol);
-    rv = *reinterpret_cast<const uint4*>(v + base + (int64_t)(t * 32 + lrow) * d + lcol);
+    int r = t * 32 + lrow;
+    if (RAGGED) r = r < S ? r : S - 1;
+    rk = *reinterpret_cast<const uint4*>(k + base + (int64_t)r * d + lcol);
+    rv = *reinterpret_cast<const uint4*>(v + base + (int64_t)r * d + lcol);
   };
   auto sstore = [&](int buf, const uint4& rk, const uint4& rv) __attribute__((always_inline)) {
-    *reinterpret_cast<uint4*>(&sK[buf][lrow * PM_AT_ST + lcol]) = rk;
-    *reinterpret_cast<uint4*>(&sV[buf][lrow * PM_AT_ST + lcol]) = rv;
+    *reinterpret_cast<uint4*>(&sK[buf][lrow * PM_AT_ST<DH> + lcol]) = rk;
+    *reinterpret_cast<uint4*>(&sV[buf][lrow * PM_AT_ST<DH> + lcol]) = rv;
   };
   gload(0, rk0, rv0);
   sstore(0, rk0, rv0);
@@ -125,8 +181,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
 #pragma unroll
       for (int e = 0; e < 16; ++e) s[e] = 0.f;
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk)
-        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pm_at_frag(sK[cur], prow, kk * 16, lane), fq[kk], s, 0, 0, 0);
+      for (int kk = 0; kk < DH / 16; ++kk)
+        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pm_at_frag<DH>(sK[cur], prow, kk * 16, lane), fq[kk], s, 0, 0, 0);
       float p[16], mx = -3.0e38f;
 #pragma unroll
       for (int e = 0; e < 16; ++e) p[e] = s[e] * c2;
@@ -151,17 +207,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
       lsum = lsum * corr + ps;
       if (__builtin_amdgcn_ballot_w64(mn != m) != 0) {      // some row's maximum moved (rare after the first tiles)
 #pragma unroll
-        for (int dt = 0; dt < 2; ++dt)
+        for (int dt = 0; dt < DH / 32; ++dt)
 #pragma unroll
           for (int e = 0; e < 16; ++e) acc[dt][e] *= corr;
       }
       m = mn;
-      const pm_bf16x8 pb0 = pm_at_pack8(p), pb1 = pm_at_pack8(p + 8);
-#pragma unroll
-      for (int dt = 0; dt < 2; ++dt) {
-        acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pm_at_frag_tr(sV[cur], dt * 32, 0, lane), pb0, acc[dt], 0, 0, 0);
-        acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pm_at_frag_tr(sV[cur], dt * 32, 16, lane), pb1, acc[dt], 0, 0, 0);
-      }
+      pm_at_second<DH, SPLIT>(acc, sV[cur], p, lane);
     }
   };
   // steady part: the loads are unconditional, so the compiler counts outstanding loads exactly and the
@@ -191,7 +242,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
   }
   if (active) {
     lsum += __shfl_xor(lsum, 32, 64);
-    pm_at_store_t(o + base + (int64_t)(q0 + ql) * d, acc, 1.f / lsum, lane);
+    if (RAGGED && q0 + ql >= S) return;
+    pm_at_store_t<DH>(o + base + (int64_t)(q0 + ql) * d, acc, 1.f / lsum, lane);
     if (g == 0) lse[((int64_t)b * H + h) * S + q0 + ql] = m * 0.693147181f + __logf(lsum);   // m is in base-2 units
   }
 }
@@ -200,33 +252,35 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
 // backward, dQ: block = 4 waves x 32 queries; streams key / value tiles.
 //   S^T = K Q^T, dP^T = V dO^T, dS^T = P^T (dP^T - D) / sqrt(dh), dQ^T += K^T dS^T
 // ---------------------------------------------------------------------------------------------
+template <int DH, bool RAGGED, bool SPLIT>
 __global__ __launch_bounds__(256) void pm_attn_mfma_dq_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
                                                               const bf16_t* __restrict__ v, const bf16_t* __restrict__ o,
                                                               const bf16_t* __restrict__ dO, const float* __restrict__ lse,
                                                               bf16_t* __restrict__ dq, int S, int H, int BH, float scale) {
-  __shared__ __attribute__((aligned(16))) bf16_t sK[2][32 * PM_AT_ST];
-  __shared__ __attribute__((aligned(16))) bf16_t sV[2][32 * PM_AT_ST];
+  __shared__ __attribute__((aligned(16))) bf16_t sK[2][32 * PM_AT_ST<DH>];
+  __shared__ __attribute__((aligned(16))) bf16_t sV[2][32 * PM_AT_ST<DH>];
   const int qblocks = (S + 127) / 128;
   const int bh = blockIdx.x % BH, qb = qblocks - 1 - blockIdx.x / BH;
-  const int b = bh / H, h = bh % H, d = H * 64;
-  const int64_t base = (int64_t)b * S * d + (int64_t)h * 64;
+  const int b = bh / H, h = bh % H, d = H * DH;
+  const int64_t base = (int64_t)b * S * d + (int64_t)h * DH;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, ql = lane & 31, g = lane >> 5;
   const int q0 = qb * 128 + wave * 32;
   const bool active = q0 < S;
   const int my_last = q0 >> 5;
-  const int n_tiles = (S < qb * 128 + 128 ? S : qb * 128 + 128) >> 5;
+  const int qr = RAGGED && q0 + ql >= S ? S - 1 : q0 + ql;                 // the row this lane reads
+  const int n_tiles = ((S < qb * 128 + 128 ? S : qb * 128 + 128) + 31) >> 5;
 
-  pm_bf16x8 fq[4], fdo[4];
+  pm_bf16x8 fq[DH / 16], fdo[DH / 16];
   float Dq = 0.f, lq = 0.f;
 #pragma unroll
-  for (int kk = 0; kk < 4; ++kk) {
+  for (int kk = 0; kk < DH / 16; ++kk) {
     fq[kk] = pm_at_zero8();
     fdo[kk] = pm_at_zero8();
   }
   if (active) {
-    const int64_t ro = base + (int64_t)(q0 + ql) * d;
+    const int64_t ro = base + (int64_t)qr * d;
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
+    for (int kk = 0; kk < DH / 16; ++kk) {
       fq[kk] = *reinterpret_cast<const pm_bf16x8*>(q + ro + kk * 16 + 8 * g);
       fdo[kk] = *reinterpret_cast<const pm_bf16x8*>(dO + ro + kk * 16 + 8 * g);
       float a[8], c[8];
@@ -236,24 +290,26 @@ __global__ __launch_bounds__(256) void pm_attn_mfma_dq_kernel(const bf16_t* __re
       for (int e = 0; e < 8; ++e) Dq += a[e] * c[e];
     }
     Dq += __shfl_xor(Dq, 32, 64);
-    lq = lse[((int64_t)b * H + h) * S + q0 + ql];
+    lq = lse[((int64_t)b * H + h) * S + qr];
   }
-  pm_f32x16 acc[2];
+  pm_f32x16 acc[DH / 32];
 #pragma unroll
-  for (int dt = 0; dt < 2; ++dt)
+  for (int dt = 0; dt < DH / 32; ++dt)
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[dt][e] = 0.f;
 
-  const int lrow = threadIdx.x >> 3, lcol = (threadIdx.x & 7) * 8;
+  const int lrow = (threadIdx.x / (DH / 8)) & 31, lcol = (threadIdx.x & (DH / 8 - 1)) * 8;
   // two register sets as in the forward kernel: a tile is loaded two iterations before its use
   uint4 rk0, rv0, rk1 = make_uint4(0, 0, 0, 0), rv1 = rk1;
   auto gload = [&](int t, uint4& rk, uint4& rv) __attribute__((always_inline)) {
-    rk = *reinterpret_cast<const uint4*>(k + base + (int64_t)(t * 32 + lrow) * d + lcol);
-    rv = *reinterpret_cast<const uint4*>(v + base + (int64_t)(t * 32 + lrow) * d + lcol);
+    int r = t * 32 + lrow;
+    if (RAGGED) r = r < S ? r : S - 1;
+    rk = *reinterpret_cast<const uint4*>(k + base + (int64_t)r * d + lcol);
+    rv = *reinterpret_cast<const uint4*>(v + base + (int64_t)r * d + lcol);
   };
   auto sstore = [&](int buf, const uint4& rk, const uint4& rv) __attribute__((always_inline)) {
-    *reinterpret_cast<uint4*>(&sK[buf][lrow * PM_AT_ST + lcol]) = rk;
-    *reinterpret_cast<uint4*>(&sV[buf][lrow * PM_AT_ST + lcol]) = rv;
+    *reinterpret_cast<uint4*>(&sK[buf][lrow * PM_AT_ST<DH> + lcol]) = rk;
+    *reinterpret_cast<uint4*>(&sV[buf][lrow * PM_AT_ST<DH> + lcol]) = rv;
   };
   gload(0, rk0, rv0);
   sstore(0, rk0, rv0);
@@ -270,9 +326,9 @@ __global__ __launch_bounds__(256) void pm_attn_mfma_dq_kernel(const bf16_t* __re
         dp[e] = 0.f;
       }
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pm_at_frag(sK[cur], prow, kk * 16, lane), fq[kk], s, 0, 0, 0);
-        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pm_at_frag(sV[cur], prow, kk * 16, lane), fdo[kk], dp, 0, 0, 0);
+      for (int kk = 0; kk < DH / 16; ++kk) {
+        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pm_at_frag<DH>(sK[cur], prow, kk * 16, lane), fq[kk], s, 0, 0, 0);
+        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pm_at_frag<DH>(sV[cur], prow, kk * 16, lane), fdo[kk], dp, 0, 0, 0);
       }
       float ds[16];
 #pragma unroll
@@ -284,12 +340,7 @@ __global__ __launch_bounds__(256) void pm_attn_mfma_dq_kernel(const bf16_t* __re
           if (kidx > q0 + ql) ds[e] = 0.f;
         }
       }
-      const pm_bf16x8 b0 = pm_at_pack8(ds), b1 = pm_at_pack8(ds + 8);
-#pragma unroll
-      for (int dt = 0; dt < 2; ++dt) {
-        acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pm_at_frag_tr(sK[cur], dt * 32, 0, lane), b0, acc[dt], 0, 0, 0);
-        acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pm_at_frag_tr(sK[cur], dt * 32, 16, lane), b1, acc[dt], 0, 0, 0);
-      }
+      pm_at_second<DH, SPLIT>(acc, sK[cur], ds, lane);
     }
   };
   // steady part: the loads are unconditional, so the compiler counts outstanding loads exactly and the
@@ -317,7 +368,7 @@ __global__ __launch_bounds__(256) void pm_attn_mfma_dq_kernel(const bf16_t* __re
       __syncthreads();
     }
   }
-  if (active) pm_at_store_t(dq + base + (int64_t)(q0 + ql) * d, acc, scale, lane);
+  if (active && (!RAGGED || q0 + ql < S)) pm_at_store_t<DH>(dq + base + (int64_t)(q0 + ql) * d, acc, scale, lane);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -325,41 +376,43 @@ __global__ __launch_bounds__(256) void pm_attn_mfma_dq_kernel(const bf16_t* __re
 // log-sum-exp and D, the latter computed while the tile is loaded).
 //   S = Q K^T, dP = dO V^T, dS = P (dP - D) / sqrt(dh), dV^T += dO^T P, dK^T += Q^T dS
 // ---------------------------------------------------------------------------------------------
+template <int DH, bool RAGGED, bool SPLIT>
 __global__ __launch_bounds__(256) void pm_attn_mfma_dkv_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
                                                                const bf16_t* __restrict__ v, const bf16_t* __restrict__ o,
                                                                const bf16_t* __restrict__ dO, const float* __restrict__ lse,
                                                                bf16_t* __restrict__ dk, bf16_t* __restrict__ dv, int S, int H,
                                                                int BH, float scale) {
-  __shared__ __attribute__((aligned(16))) bf16_t sQ[2][32 * PM_AT_ST];
-  __shared__ __attribute__((aligned(16))) bf16_t sO[2][32 * PM_AT_ST];     // dO
+  __shared__ __attribute__((aligned(16))) bf16_t sQ[2][32 * PM_AT_ST<DH>];
+  __shared__ __attribute__((aligned(16))) bf16_t sO[2][32 * PM_AT_ST<DH>];     // dO
   __shared__ __attribute__((aligned(16))) float sL[2][32];
   __shared__ __attribute__((aligned(16))) float sD[2][32];
   const int bh = blockIdx.x % BH, kb = blockIdx.x / BH;                    // long blocks (early keys) first
-  const int b = bh / H, h = bh % H, d = H * 64;
-  const int64_t base = (int64_t)b * S * d + (int64_t)h * 64;
+  const int b = bh / H, h = bh % H, d = H * DH;
+  const int64_t base = (int64_t)b * S * d + (int64_t)h * DH;
   const int64_t lbase = ((int64_t)b * H + h) * S;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, kl = lane & 31, g = lane >> 5;
   const int k0 = kb * 128 + wave * 32;
   const bool active = k0 < S;
   const int my_first = k0 >> 5;
-  const int first = kb * 4, n_tiles = S >> 5;
+  const int kr = RAGGED && k0 + kl >= S ? S - 1 : k0 + kl;                 // the row this lane reads
+  const int first = kb * 4, n_tiles = (S + 31) >> 5;
 
-  pm_bf16x8 fk[4], fv[4];
+  pm_bf16x8 fk[DH / 16], fv[DH / 16];
 #pragma unroll
-  for (int kk = 0; kk < 4; ++kk) {
-    fk[kk] = active ? *reinterpret_cast<const pm_bf16x8*>(k + base + (int64_t)(k0 + kl) * d + kk * 16 + 8 * g) : pm_at_zero8();
-    fv[kk] = active ? *reinterpret_cast<const pm_bf16x8*>(v + base + (int64_t)(k0 + kl) * d + kk * 16 + 8 * g) : pm_at_zero8();
+  for (int kk = 0; kk < DH / 16; ++kk) {
+    fk[kk] = active ? *reinterpret_cast<const pm_bf16x8*>(k + base + (int64_t)kr * d + kk * 16 + 8 * g) : pm_at_zero8();
+    fv[kk] = active ? *reinterpret_cast<const pm_bf16x8*>(v + base + (int64_t)kr * d + kk * 16 + 8 * g) : pm_at_zero8();
   }
-  pm_f32x16 ak[2], av[2];
+  pm_f32x16 ak[DH / 32], av[DH / 32];
 #pragma unroll
-  for (int dt = 0; dt < 2; ++dt)
+  for (int dt = 0; dt < DH / 32; ++dt)
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
       ak[dt][e] = 0.f;
       av[dt][e] = 0.f;
     }
 
-  const int lrow = threadIdx.x >> 3, lcol = (threadIdx.x & 7) * 8;
+  const int lrow = (threadIdx.x / (DH / 8)) & 31, lcol = (threadIdx.x & (DH / 8 - 1)) * 8;
   // two register sets (a query tile is loaded two iterations before its use); D of the tile's rows is
   // computed when the set moves to LDS
   struct Regs {
@@ -370,15 +423,20 @@ __global__ __launch_bounds__(256) void pm_attn_mfma_dkv_kernel(const bf16_t* __r
   r1.q = r1.dO = r1.o = make_uint4(0, 0, 0, 0);
   r0.L = r1.L = 0.f;
   auto gload = [&](int it, Regs& r) __attribute__((always_inline)) {
-    const int64_t ro = base + (int64_t)(it * 32 + lrow) * d + lcol;
+    int qrow = it * 32 + lrow, lrw = it * 32 + (threadIdx.x & 31);
+    if (RAGGED) {
+      qrow = qrow < S ? qrow : S - 1;
+      lrw = lrw < S ? lrw : S - 1;
+    }
+    const int64_t ro = base + (int64_t)qrow * d + lcol;
     r.q = *reinterpret_cast<const uint4*>(q + ro);
     r.dO = *reinterpret_cast<const uint4*>(dO + ro);
     r.o = *reinterpret_cast<const uint4*>(o + ro);
-    r.L = lse[lbase + it * 32 + (threadIdx.x & 31)];       // every thread (no load under a condition)
+    r.L = lse[lbase + lrw];       // every thread (no load under a condition)
   };
   auto sstore = [&](int buf, const Regs& r) __attribute__((always_inline)) {
-    *reinterpret_cast<uint4*>(&sQ[buf][lrow * PM_AT_ST + lcol]) = r.q;
-    *reinterpret_cast<uint4*>(&sO[buf][lrow * PM_AT_ST + lcol]) = r.dO;
+    *reinterpret_cast<uint4*>(&sQ[buf][lrow * PM_AT_ST<DH> + lcol]) = r.q;
+    *reinterpret_cast<uint4*>(&sO[buf][lrow * PM_AT_ST<DH> + lcol]) = r.dO;
     const uint32_t a[4] = {r.dO.x, r.dO.y, r.dO.z, r.dO.w}, c[4] = {r.o.x, r.o.y, r.o.z, r.o.w};
     float part = 0.f;
 #pragma unroll
@@ -388,8 +446,8 @@ __global__ __launch_bounds__(256) void pm_attn_mfma_dkv_kernel(const bf16_t* __r
     }
     part += __shfl_xor(part, 1, 64);
     part += __shfl_xor(part, 2, 64);
-    part += __shfl_xor(part, 4, 64);
-    if ((threadIdx.x & 7) == 0) sD[buf][lrow] = part;
+    if (DH == 64) part += __shfl_xor(part, 4, 64);
+    if ((threadIdx.x & (DH / 8 - 1)) == 0) sD[buf][lrow] = part;
     if (threadIdx.x < 32) sL[buf][threadIdx.x] = r.L * 1.44269504f;       // base-2 units
   };
   gload(first, r0);
@@ -407,9 +465,9 @@ __global__ __launch_bounds__(256) void pm_attn_mfma_dkv_kernel(const bf16_t* __r
         dp[e] = 0.f;
       }
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pm_at_frag(sQ[cur], prow, kk * 16, lane), fk[kk], s, 0, 0, 0);
-        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pm_at_frag(sO[cur], prow, kk * 16, lane), fv[kk], dp, 0, 0, 0);
+      for (int kk = 0; kk < DH / 16; ++kk) {
+        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pm_at_frag<DH>(sQ[cur], prow, kk * 16, lane), fk[kk], s, 0, 0, 0);
+        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pm_at_frag<DH>(sO[cur], prow, kk * 16, lane), fv[kk], dp, 0, 0, 0);
       }
       float p[16], ds[16], lv[16], Dv[16];
 #pragma unroll
@@ -430,16 +488,15 @@ __global__ __launch_bounds__(256) void pm_attn_mfma_dkv_kernel(const bf16_t* __r
           if (qidx < k0 + kl) p[e] = 0.f;
         }
       }
+      if (RAGGED && it * 32 + 32 > S) {           // the last tile: queries past the end
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+          if (it * 32 + 16 * (e >> 3) + 8 * g + (e & 7) >= S) p[e] = 0.f;
+      }
 #pragma unroll
       for (int e = 0; e < 16; ++e) ds[e] = p[e] * (dp[e] - Dv[e]);       // the factor 1 / sqrt(dh) goes into the final store
-      const pm_bf16x8 p0 = pm_at_pack8(p), p1 = pm_at_pack8(p + 8), s0 = pm_at_pack8(ds), s1 = pm_at_pack8(ds + 8);
-#pragma unroll
-      for (int dt = 0; dt < 2; ++dt) {
-        av[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pm_at_frag_tr(sO[cur], dt * 32, 0, lane), p0, av[dt], 0, 0, 0);
-        av[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pm_at_frag_tr(sO[cur], dt * 32, 16, lane), p1, av[dt], 0, 0, 0);
-        ak[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pm_at_frag_tr(sQ[cur], dt * 32, 0, lane), s0, ak[dt], 0, 0, 0);
-        ak[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pm_at_frag_tr(sQ[cur], dt * 32, 16, lane), s1, ak[dt], 0, 0, 0);
-      }
+      pm_at_second<DH, SPLIT>(av, sO[cur], p, lane);
+      pm_at_second<DH, SPLIT>(ak, sQ[cur], ds, lane);
     }
   };
   int it = first;
@@ -464,9 +521,9 @@ __global__ __launch_bounds__(256) void pm_attn_mfma_dkv_kernel(const bf16_t* __r
       __syncthreads();
     }
   }
-  if (active) {
-    pm_at_store_t(dk + base + (int64_t)(k0 + kl) * d, ak, scale, lane);
-    pm_at_store_t(dv + base + (int64_t)(k0 + kl) * d, av, 1.f, lane);
+  if (active && (!RAGGED || k0 + kl < S)) {
+    pm_at_store_t<DH>(dk + base + (int64_t)(k0 + kl) * d, ak, scale, lane);
+    pm_at_store_t<DH>(dv + base + (int64_t)(k0 + kl) * d, av, 1.f, lane);
   }
 }
 

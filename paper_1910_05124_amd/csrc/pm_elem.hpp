@@ -222,12 +222,13 @@ __global__ __launch_bounds__(256) void pm_zero_f32_kernel(float* p, int64_t n) {
 
 // ---------------------------------------------------------------------------------------------
 // Epilogues shared by the plain and the MFMA GEMMs.  acc is the fp32 contraction result for
-// output element (i, j).
+// output element (i, j).  kAKC / kBKC: whether the product this epilogue belongs to reads its A / B operand with the
+// contraction index contiguous (forward: both; data gradient: A; weight gradient: neither).
 // ---------------------------------------------------------------------------------------------
 // forward: z = acc + b[j]; stores z (compute dtype and/or fp32) and a = act(z)
 template <typename T>
 struct PmEpiFwd {
-  static constexpr bool kColSumA = false;
+  static constexpr bool kColSumA = false, kAKC = true, kBKC = true;
   __device__ __forceinline__ bool wants_colsum() const { return false; }
   __device__ __forceinline__ void colsum(int, float) const {}
   PmWLoc<T> bias;   // the bias lives in the same ring slot as its weight matrix
@@ -263,7 +264,7 @@ struct PmEpiFwd {
 // backward data: dz_prev = acc * act'(z_prev)   (act == 0: dz_prev = acc, z_prev is not read)
 template <typename T>
 struct PmEpiBwdData {
-  static constexpr bool kColSumA = false;
+  static constexpr bool kColSumA = false, kAKC = true, kBKC = false;
   __device__ __forceinline__ bool wants_colsum() const { return false; }
   __device__ __forceinline__ void colsum(int, float) const {}
   const T* zprev; T* dzprev; int ld; int act;
@@ -295,7 +296,7 @@ struct PmEpiBwdData {
 // backward weight: g[i, j] (+)= acc, fp32; db[i] (+)= column sum of the A operand (MFMA path only)
 // (runs in table-driven launches: its accesses name the global address space, see pm_ldg16)
 struct PmEpiBwdWeight {
-  static constexpr bool kColSumA = true;
+  static constexpr bool kColSumA = true, kAKC = false, kBKC = false;
   float* g; int ld; int accumulate;
   float* db;   // bias gradient, or nullptr when a separate kernel produces it
   __device__ __forceinline__ bool wants_colsum() const { return db != nullptr; }

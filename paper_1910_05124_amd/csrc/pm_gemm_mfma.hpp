@@ -375,12 +375,9 @@ template <class Epi>
 inline bool pm_mfma_gemm_try(hipStream_t st, int I, int J, int K, const bf16_t* A, int64_t sai, int64_t sak,
                              PmWLoc<bf16_t> B, int64_t sbj, int64_t sbk, const Epi& epi, const PmPrefetch* pf = nullptr) {
   if (!pm_mfma_takes(I, J, K, A, sai, sak, B.base, B.stride, sbj, sbk)) return false;
-  const bool akc = sak == 1, bkc = sbk == 1;
-  PmGemmProb<Epi> pr{I, J, K, A, akc ? sai : sak, B, bkc ? sbj : sbk, epi};
-  if (akc && bkc) pm_mfma_pick<true, true>(st, pr, pf);
-  else if (akc && !bkc) pm_mfma_pick<true, false>(st, pr, pf);
-  else if (!akc && bkc) pm_mfma_pick<false, true>(st, pr, pf);
-  else pm_mfma_pick<false, false>(st, pr, pf);
+  if ((sak == 1) != Epi::kAKC || (sbk == 1) != Epi::kBKC) return false;
+  PmGemmProb<Epi> pr{I, J, K, A, Epi::kAKC ? sai : sak, B, Epi::kBKC ? sbj : sbk, epi};
+  pm_mfma_pick<Epi::kAKC, Epi::kBKC>(st, pr, pf);
   return true;
 }
 

@@ -20,7 +20,7 @@ constexpr float PM_LN_EPS = 1e-5f;
 // out[i, j] = res[i, j] + acc + b[j], fp32: the residual stream after an attention / feed-forward block
 template <typename T>
 struct PmEpiFwdRes {
-  static constexpr bool kColSumA = false;
+  static constexpr bool kColSumA = false, kAKC = true, kBKC = true;
   __device__ __forceinline__ bool wants_colsum() const { return false; }
   __device__ __forceinline__ void colsum(int, float) const {}
   PmWLoc<T> bias;
@@ -51,7 +51,7 @@ struct PmEpiFwdRes {
 // out[i, j] (+)= acc, fp32: data gradients that enter a LayerNorm backward (summed over the
 // consumers of the LayerNorm output)
 struct PmEpiF32 {
-  static constexpr bool kColSumA = false;
+  static constexpr bool kColSumA = false, kAKC = true, kBKC = false;
   __device__ __forceinline__ bool wants_colsum() const { return false; }
   __device__ __forceinline__ void colsum(int, float) const {}
   float* out; int ld; int accumulate;
@@ -302,154 +302,6 @@ __global__ __launch_bounds__(256) void pm_cast_kernel(const float* __restrict__ 
 }
 
 // ---------------------------------------------------------------------------------------------
-// Causal attention core, one block per (sequence, head), one thread per query row.
-// q, k, v, o: [tokens, d_model] in T, head h in columns h*DH .. h*DH+DH-1.  lse: fp32 [B, H, S].
-// K and V of the head sit in LDS as fp32 (S * DH * 8 bytes <= ~140 KB); all lanes read the same
-// key row at a time (LDS broadcast), scores are never materialised (running max / sum).
-// ---------------------------------------------------------------------------------------------
-template <typename T, int DH>
-__global__ void pm_attn_fwd_kernel(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
-                                   T* __restrict__ o, float* __restrict__ lse, int S, int H, float scale) {
-  extern __shared__ float sm[];
-  float* sK = sm;
-  float* sV = sm + (size_t)S * DH;
-  const int b = blockIdx.x / H, h = blockIdx.x % H;
-  const int d = H * DH;
-  const int64_t base = (int64_t)b * S * d + (int64_t)h * DH;
-  for (int e = threadIdx.x; e < S * DH; e += blockDim.x) {
-    const int r = e / DH, c = e % DH;
-    sK[e] = ldf(k + base + (int64_t)r * d + c);
-    sV[e] = ldf(v + base + (int64_t)r * d + c);
-  }
-  __syncthreads();
-  const int i = threadIdx.x;
-  if (i >= S) return;
-  float qi[DH], acc[DH];
-#pragma unroll
-  for (int c = 0; c < DH; ++c) {
-    qi[c] = ldf(q + base + (int64_t)i * d + c) * scale;
-    acc[c] = 0.f;
-  }
-  float m = -3.0e38f, l = 0.f;
-  for (int j = 0; j <= i; ++j) {
-    float s = 0.f;
-#pragma unroll
-    for (int c = 0; c < DH; ++c) s += qi[c] * sK[j * DH + c];
-    const float mn = fmaxf(m, s);
-    const float corr = __expf(m - mn), p = __expf(s - mn);
-    l = l * corr + p;
-#pragma unroll
-    for (int c = 0; c < DH; ++c) acc[c] = acc[c] * corr + p * sV[j * DH + c];
-    m = mn;
-  }
-  const float inv = 1.f / l;
-#pragma unroll
-  for (int c = 0; c < DH; ++c) stf(o + base + (int64_t)i * d + c, acc[c] * inv);
-  lse[((int64_t)b * H + h) * S + i] = m + __logf(l);
-}
-
-// Backward of the attention core.  Pass 1 (thread = query row i): dq_i.  Pass 2 (thread = key
-// row j): dk_j, dv_j.  Probabilities are recomputed from q, k and the stored log-sum-exp;
-// D_i = do_i . o_i is the row term of the softmax Jacobian.
-template <typename T, int DH>
-__global__ void pm_attn_bwd_kernel(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
-                                   const T* __restrict__ o, const T* __restrict__ dO, const float* __restrict__ lse,
-                                   T* __restrict__ dq, T* __restrict__ dk, T* __restrict__ dv, int S, int H, float scale) {
-  extern __shared__ float sm[];
-  float* sA = sm;                          // pass 1: K      pass 2: Q
-  float* sB = sm + (size_t)S * DH;         // pass 1: V      pass 2: dO
-  float* sL = sm + (size_t)2 * S * DH;     // log-sum-exp per row
-  float* sD = sL + S;                      // D per row
-  const int b = blockIdx.x / H, h = blockIdx.x % H;
-  const int d = H * DH;
-  const int64_t base = (int64_t)b * S * d + (int64_t)h * DH;
-  const int i = threadIdx.x;
-  for (int e = threadIdx.x; e < S * DH; e += blockDim.x) {
-    const int r = e / DH, c = e % DH;
-    sA[e] = ldf(k + base + (int64_t)r * d + c);
-    sB[e] = ldf(v + base + (int64_t)r * d + c);
-  }
-  float qi[DH], doi[DH];
-  float Di = 0.f, li = 0.f;
-  if (i < S) {
-#pragma unroll
-    for (int c = 0; c < DH; ++c) {
-      qi[c] = ldf(q + base + (int64_t)i * d + c);
-      doi[c] = ldf(dO + base + (int64_t)i * d + c);
-      Di += doi[c] * ldf(o + base + (int64_t)i * d + c);
-    }
-    li = lse[((int64_t)b * H + h) * S + i];
-    sL[i] = li;
-    sD[i] = Di;
-  }
-  __syncthreads();
-  if (i < S) {
-    float acc[DH];
-#pragma unroll
-    for (int c = 0; c < DH; ++c) acc[c] = 0.f;
-    for (int j = 0; j <= i; ++j) {
-      float s = 0.f, dp = 0.f;
-#pragma unroll
-      for (int c = 0; c < DH; ++c) {
-        s += qi[c] * sA[j * DH + c];
-        dp += doi[c] * sB[j * DH + c];
-      }
-      const float p = __expf(s * scale - li);
-      const float ds = p * (dp - Di) * scale;
-#pragma unroll
-      for (int c = 0; c < DH; ++c) acc[c] += ds * sA[j * DH + c];
-    }
-#pragma unroll
-    for (int c = 0; c < DH; ++c) stf(dq + base + (int64_t)i * d + c, acc[c]);
-  }
-  __syncthreads();
-  // pass 2: this thread is key row j = threadIdx.x; Q and dO of the head go to LDS
-  float kj[DH], vj[DH];
-  if (i < S) {
-#pragma unroll
-    for (int c = 0; c < DH; ++c) {
-      kj[c] = sA[i * DH + c];
-      vj[c] = sB[i * DH + c];
-    }
-  }
-  __syncthreads();
-  for (int e = threadIdx.x; e < S * DH; e += blockDim.x) {
-    const int r = e / DH, c = e % DH;
-    sA[e] = ldf(q + base + (int64_t)r * d + c);
-    sB[e] = ldf(dO + base + (int64_t)r * d + c);
-  }
-  __syncthreads();
-  if (i < S) {
-    float ak[DH], av[DH];
-#pragma unroll
-    for (int c = 0; c < DH; ++c) {
-      ak[c] = 0.f;
-      av[c] = 0.f;
-    }
-    for (int r = i; r < S; ++r) {
-      float s = 0.f, dp = 0.f;
-#pragma unroll
-      for (int c = 0; c < DH; ++c) {
-        s += sA[r * DH + c] * kj[c];
-        dp += sB[r * DH + c] * vj[c];
-      }
-      const float p = __expf(s * scale - sL[r]);
-      const float ds = p * (dp - sD[r]) * scale;
-#pragma unroll
-      for (int c = 0; c < DH; ++c) {
-        av[c] += p * sB[r * DH + c];
-        ak[c] += ds * sA[r * DH + c];
-      }
-    }
-#pragma unroll
-    for (int c = 0; c < DH; ++c) {
-      stf(dk + base + (int64_t)i * d + c, ak[c]);
-      stf(dv + base + (int64_t)i * d + c, av[c]);
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------------------------
 // host-side dispatch
 // ---------------------------------------------------------------------------------------------
 template <typename T>
@@ -480,61 +332,5 @@ inline bool pm_ln_bwd_launch(hipStream_t st, const float* dy, const float* x, co
   else if (d <= 1024) PM_LNB(4);
   else return false;
 #undef PM_LNB
-  return true;
-}
-
-// plain attention kernels: one thread per query / key row, K and V (Q and dO) of a head in LDS as fp32
-inline bool pm_attn_plain_fits(int S, int dh) {
-  // K, V (Q, dO) + two row vectors as fp32 in 64 KB of LDS
-  return (int64_t)S * (dh + 1) * 8 <= 65536 && S <= 1024 && (dh == 4 || dh == 8 || dh == 16 || dh == 32 || dh == 64);
-}
-
-template <typename T>
-inline bool pm_attn_fwd_launch(hipStream_t st, int B, int S, int H, int dh, const T* q, const T* k, const T* v, T* o,
-                               float* lse) {
-  if constexpr (sizeof(T) == 2) {
-    if (pm_attn_mfma_fits(S, dh)) {
-      pm_attn_mfma_fwd(st, B, S, H, q, k, v, o, lse);
-      return true;
-    }
-  }
-  if (!pm_attn_plain_fits(S, dh)) return false;
-  const float scale = 1.f / sqrtf((float)dh);
-  const dim3 grid(B * H), blk((S + 63) / 64 * 64);
-  const size_t lds = (size_t)2 * S * dh * 4;
-#define PM_AF(DH) hipLaunchKernelGGL((pm_attn_fwd_kernel<T, DH>), grid, blk, lds, st, q, k, v, o, lse, S, H, scale)
-  switch (dh) {
-    case 4: PM_AF(4); break;
-    case 8: PM_AF(8); break;
-    case 16: PM_AF(16); break;
-    case 32: PM_AF(32); break;
-    default: PM_AF(64); break;
-  }
-#undef PM_AF
-  return true;
-}
-
-template <typename T>
-inline bool pm_attn_bwd_launch(hipStream_t st, int B, int S, int H, int dh, const T* q, const T* k, const T* v, const T* o,
-                               const T* dO, const float* lse, T* dq, T* dk, T* dv) {
-  if constexpr (sizeof(T) == 2) {
-    if (pm_attn_mfma_fits(S, dh)) {
-      pm_attn_mfma_bwd(st, B, S, H, q, k, v, o, dO, lse, dq, dk, dv);
-      return true;
-    }
-  }
-  if (!pm_attn_plain_fits(S, dh)) return false;
-  const float scale = 1.f / sqrtf((float)dh);
-  const dim3 grid(B * H), blk((S + 63) / 64 * 64);
-  const size_t lds = (size_t)2 * S * dh * 4 + (size_t)2 * S * 4;
-#define PM_AB(DH) hipLaunchKernelGGL((pm_attn_bwd_kernel<T, DH>), grid, blk, lds, st, q, k, v, o, dO, lse, dq, dk, dv, S, H, scale)
-  switch (dh) {
-    case 4: PM_AB(4); break;
-    case 8: PM_AB(8); break;
-    case 16: PM_AB(16); break;
-    case 32: PM_AB(32); break;
-    default: PM_AB(64); break;
-  }
-#undef PM_AB
   return true;
 }

@@ -120,6 +120,18 @@ def test_attention_primitives(torch_cuda, dtype, B, S, H, dh):
         assert err <= tol, (name, err)
 
 
+# lengths around the 32-row tiles and the 128-row blocks, two rows, the longest each head size takes; every head size of
+# the fp32 arithmetic in both element types
+@pytest.mark.parametrize("dtype,B,S,H,dh", [("bf16", 2, 100, 5, 64), ("bf16", 1, 2, 2, 64), ("bf16", 2, 31, 1, 64), ("bf16", 2, 33, 3, 64),
+                                            ("bf16", 1, 126, 2, 64), ("bf16", 3, 32, 2, 32), ("bf16", 2, 65, 3, 32),
+                                            ("bf16", 1, 129, 2, 32), ("bf16", 2, 248, 2, 32), ("bf16", 2, 33, 2, 16),
+                                            ("bf16", 1, 100, 3, 8), ("bf16", 2, 65, 2, 4), ("f32", 1, 2, 2, 4), ("f32", 2, 33, 3, 4),
+                                            ("f32", 1, 64, 2, 8), ("f32", 2, 96, 2, 16), ("f32", 2, 65, 3, 32), ("f32", 1, 248, 2, 32),
+                                            ("f32", 2, 126, 2, 64), ("f32", 1, 1024, 1, 4)])
+def test_attention_ragged_lengths_and_narrow_heads(torch_cuda, dtype, B, S, H, dh):
+    test_attention_primitives(torch_cuda, dtype, B, S, H, dh)
+
+
 # ------------------------------------------------------------------------------- whole training runs
 def run_pair(torch, w, steps, tau=None, N=1, gpu_kw=None, check_tables=True, **kw):
     params = wl.init_params(w)
