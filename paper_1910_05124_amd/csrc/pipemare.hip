@@ -17,6 +17,7 @@
 
 #include "pm_common.hpp"
 #include "pm_elem.hpp"
+#include "pm_gemm_f32.hpp"
 #include "pm_gemm_mfma.hpp"
 #include "pm_update.hpp"
 #include "pm_chain.hpp"
@@ -92,7 +93,7 @@ struct Layout {
   int64_t n_chunks = 0;
   size_t esz = 4;         // bytes per element of the compute dtype
   // byte offsets
-  size_t w_off, g_off, v_off, s_off, d_off, ub_off, ur_off, cdf_off, ring_off, chunk_off, ls_off, ld_off, hdr_off, probs_off, x_off;
+  size_t w_off, g_off, v_off, s_off, d_off, ub_off, ur_off, cdf_off, ring_off, chunk_off, ls_off, ld_off, hdr_off, probs_off, first_off, x_off;
   size_t chain_f_off, chain_b_off;                         // unit tables of the chained launches
   size_t act_begin, act_end, total;
   // Transformer activations (byte offsets; see launch_tfm).  Per layer: index [layer]
@@ -278,7 +279,9 @@ void make_layout(int32_t L, const pm_layer_desc* layers, const int32_t* tau_fwd,
   lay.ls_off = take(sizeof(PmLayerStatic) * L);
   lay.ld_off = take(sizeof(PmLayerStep) * L * 2);
   lay.hdr_off = take(sizeof(PmStepHdr));
+  static_assert(sizeof(PmF32Prob<PmEpiBwdWeight>) == sizeof(PmGemmProb<PmEpiBwdWeight>), "one table size for both types");
   lay.probs_off = take(sizeof(PmGemmProb<PmEpiBwdWeight>) * 2 * L);
+  lay.first_off = take(o->dtype == PM_F32 ? sizeof(int32_t) * L : 0);
   lay.chain_f_off = take(sizeof(PmChainFwd) * L);
   lay.chain_b_off = take(sizeof(PmChainBwd) * L);
   const int M = o->microbatch;
@@ -394,7 +397,8 @@ struct pm_ctx {
   int dw_nprob = 0, dw_ntiles = 0;   // Transformer: problems and grid size (8 x the longest XCD list) of the grouped launch
   int dw_max_segs = 0;
   bool dw_aligned = false;           // no tile of the grouped launch needs a bounds test
-  int dw_tile = 128;                 // block tile of the grouped launch (128 or 256)
+  int dw_tile = 128;                 // block tile of the grouped launch (128 or 256; fp32: 16, 32 or 64)
+  bool dw_vector = false;            // fp32: every operand of the grouped launch allows vector accesses
   // MLP chain with few rows: units 0 .. chain_nf - 1 run forward as one chained launch, the data gradients of
   // units chain_hb .. 1 as another (0: the launch-per-product path)
   int chain_nf = 0, chain_hb = 0, chain_grid = 0;
@@ -553,9 +557,11 @@ void launch_gemm_on(hipStream_t st, int I, int J, int K, const T* A, int64_t sai
                     int64_t sbk, const Epi& epi, const PmPrefetch* pf = nullptr) {
   if constexpr (sizeof(T) == 2) {
     if (pm_mfma_gemm_try(st, I, J, K, A, sai, sak, B, sbj, sbk, epi, pf)) return;
+    dim3 grid((J + 15) / 16, (I + 15) / 16);
+    hipLaunchKernelGGL((pm_gemm_plain_kernel<T, T, Epi>), grid, dim3(256), 0, st, I, J, K, A, sai, sak, B, sbj, sbk, epi);
+  } else {
+    pm_gemm_f32_launch(st, PmF32Prob<Epi>{I, J, K, A, Epi::kAKC ? sai : sak, B, Epi::kBKC ? sbj : sbk, epi});
   }
-  dim3 grid((J + 15) / 16, (I + 15) / 16);
-  hipLaunchKernelGGL((pm_gemm_plain_kernel<T, T, Epi>), grid, dim3(256), 0, st, I, J, K, A, sai, sak, B, sbj, sbk, epi);
 }
 
 // Bias gradient db = column sums of dz as its own launch (when the GEMM does not fuse it).
@@ -570,11 +576,33 @@ void launch_bias_grad(hipStream_t st, const T* dz, float* db, int M, int N, int 
   }
 }
 
+// Weight and bias gradient of one unit: dW[n_out, n_in] (+)= dz^T a, db (+)= column sums of dz.  The matrix
+// kernels produce the bias gradient on the way: fp32 always; bf16 for few rows (with many the column sums would sit on
+// the critical path of the blocks that own them, and a chunked reduction over the whole chip is faster).
+template <typename T>
+void launch_wgrad(hipStream_t st, int M, int n_out, int n_in, const T* dz, int ld_dz, const T* a, int ld_a, float* dW, float* db,
+                  int accumulate) {
+  const bool fused_db = db && (sizeof(T) == 4 || (M <= 512 && pm_mfma_takes(n_out, n_in, M, dz, 1, ld_dz, a, 0, 1, ld_a)));
+  PmEpiBwdWeight epi{dW, n_in, accumulate, fused_db ? db : nullptr};
+  launch_gemm_on<T>(st, n_out, n_in, M, dz, 1, ld_dz, PmWLoc<T>{a, nullptr, 0}, 1, ld_a, epi);
+  if constexpr (sizeof(T) == 2) {
+    if (db && !fused_db) launch_bias_grad<T>(st, dz, db, M, n_out, ld_dz, accumulate);
+  }
+}
+
 template <typename T, class Epi>
 void launch_gemm(pm_ctx* c, int I, int J, int K, const T* A, int64_t sai, int64_t sak, PmWLoc<T> B, int64_t sbj,
                  int64_t sbk, const Epi& epi, const PmPrefetch* pf = nullptr) {
   ProfSpan span(c, PM_CLS_GEMM);
   launch_gemm_on<T>(c->stream, I, J, K, A, sai, sak, B, sbj, sbk, epi, pf);
+}
+
+// All weight and bias gradients of an fp32 step in one launch (problem tables built by pm_create).
+void launch_f32_wgrads(pm_ctx* c, int accumulate) {
+  ProfSpan span(c, PM_CLS_GEMM);
+  pm_gemm_f32_grouped_launch(c->stream, c->dw_tile, c->dw_vector,
+                             c->at<PmF32Prob<PmEpiBwdWeight>>(c->lay.probs_off) + (accumulate ? c->dw_nprob : 0),
+                             c->at<int32_t>(c->lay.first_off), c->dw_nprob, c->dw_ntiles);
 }
 
 // What the extra blocks of a small product should read ahead: the weight matrix W [n_out, n_in] of a
@@ -749,15 +777,17 @@ pm_status launch_fwd_bwd(pm_ctx* c, const void* x_dev, const void* y_dev, int ac
                            tab);
       grouped = true;
     }
+  } else {
+    launch_f32_wgrads(c, accumulate);
+    grouped = true;
   }
   if (!grouped) {
     for (int l = L - 1; l >= 0; --l) {
       const Unit& u = lay.units[l];
       const T* a_in = l == 0 ? c->at<T>(lay.x_off) : c->at<T>(lay.units[l - 1].a_off);
       const T* dz = c->at<T>(u.dz_off);
-      PmEpiBwdWeight ew{g + u.off, u.d.n_in, accumulate, nullptr};
-      launch_gemm<T>(c, u.d.n_out, u.d.n_in, M, dz, 1, u.ld_out, PmWLoc<T>{a_in, nullptr, 0}, 1, u.ld_in, ew);
-      launch_bias_grad<T>(st, dz, g + u.off + u.boff, M, u.d.n_out, u.ld_out, accumulate);
+      ProfSpan span(c, PM_CLS_GEMM);
+      launch_wgrad<T>(st, M, u.d.n_out, u.d.n_in, dz, u.ld_out, a_in, u.ld_in, g + u.off, g + u.off + u.boff, accumulate);
     }
   }
   PM_HIP(hipGetLastError());
@@ -818,9 +848,8 @@ pm_status launch_tfm(pm_ctx* c, const void* x_dev, const void* y_dev, int accumu
   };
   // dW = dz^T a_in, db = column sums of dz
   auto wgrad = [&](int u, const T* dz, int ld_dz, const T* a_in, int n_out, int n_in) {
-    PmEpiBwdWeight ew{g + U(u).off, n_in, accumulate, nullptr};
-    launch_gemm<T>(c, n_out, n_in, Tk, dz, 1, ld_dz, PmWLoc<T>{a_in, nullptr, 0}, 1, n_in, ew);
-    launch_bias_grad<T>(st, dz, g + U(u).off + U(u).boff, Tk, n_out, ld_dz, accumulate);
+    ProfSpan span(c, PM_CLS_GEMM);
+    launch_wgrad<T>(st, Tk, n_out, n_in, dz, ld_dz, a_in, n_in, g + U(u).off, g + U(u).off + U(u).boff, accumulate);
   };
   // fp32 out (+)= dz W_bkwd
   auto dgrad_f32 = [&](int u, const T* dz, int ld_dz, int n_out, int n_in, float* out, int acc) {
@@ -1067,6 +1096,8 @@ pm_status launch_tfm(pm_ctx* c, const void* x_dev, const void* y_dev, int accumu
                            dim3(PmBig128::NT), 0, st, tab, c->at<PmXcdSeg>(lay.t_wsegs), c->at<int32_t>(lay.t_wtiles),
                            c->dw_max_segs);
     }
+  } else if (grouped) {
+    launch_f32_wgrads(c, accumulate);
   }
   {
     const int64_t tot = (int64_t)Tk * d;
@@ -1163,9 +1194,10 @@ pm_status launch_resnet(pm_ctx* c, const void* x_dev, const void* y_dev, int acc
   };
   enter(fc);
   {
-    PmEpiBwdWeight ew{g + U(fc).off, C, accumulate, nullptr};
-    launch_gemm<T>(c, ncls, C, B, TT(lay.r_dlogits), 1, ldc, PmWLoc<T>{TT(lay.r_pool), nullptr, 0}, 1, C, ew);
-    launch_bias_grad<T>(st, TT(lay.r_dlogits), g + U(fc).off + U(fc).boff, B, ncls, ldc, accumulate);
+    {
+      ProfSpan span(c, PM_CLS_GEMM);
+      launch_wgrad<T>(st, B, ncls, C, TT(lay.r_dlogits), ldc, TT(lay.r_pool), C, g + U(fc).off, g + U(fc).off + U(fc).boff, accumulate);
+    }
     PmEpiBwdData<T> ed{nullptr, TT(lay.r_dpool), C, PM_ACT_NONE};
     launch_gemm<T>(c, B, C, ncls, TT(lay.r_dlogits), ldc, 1, Wb(fc, 0), 1, C, ed);
     const int64_t tot = (int64_t)B * HW * C;
@@ -1268,14 +1300,7 @@ pm_status linear_bwd_data_t(hipStream_t st, int M, int n_in, int n_out, const vo
 template <typename T>
 pm_status linear_bwd_weight_t(hipStream_t st, int M, int n_in, int n_out, const void* dz, const void* a, float* dW,
                               float* db, int accumulate) {
-  // the MFMA kernels produce the bias gradient themselves (column sums of the dz tile in LDS)
-  // (for few rows; with many rows the column sums would sit on the critical path of the blocks
-  // that own them, and a chunked reduction over the whole chip is faster)
-  bool fused_db = false;
-  if constexpr (sizeof(T) == 2) fused_db = M <= 512 && pm_mfma_takes(n_out, n_in, M, dz, 1, n_out, a, 0, 1, n_in);
-  PmEpiBwdWeight epi{dW, n_in, accumulate, fused_db ? db : nullptr};
-  launch_gemm_on<T>(st, n_out, n_in, M, (const T*)dz, 1, n_out, PmWLoc<T>{(const T*)a, nullptr, 0}, 1, n_in, epi);
-  if (db && !fused_db) launch_bias_grad<T>(st, (const T*)dz, db, M, n_out, n_out, accumulate);
+  launch_wgrad<T>(st, M, n_out, n_in, (const T*)dz, n_out, (const T*)a, n_in, dW, db, accumulate);
   PM_HIP(hipGetLastError());
   return PM_OK;
 }
@@ -1643,6 +1668,55 @@ pm_status pm_create(int32_t P, int32_t L, const pm_layer_desc* layers, const int
   if (c->o.arch == PM_ARCH_RESNET) {
     for (int l = 0; l < L - 1; ++l) { zero_tab.push_back(lay.units[l].off); zero_tab.push_back(lay.units[l].n_pad); }
     if ((e = hipMemcpyAsync(c->arena + lay.t_zero, zero_tab.data(), zero_tab.size() * 8, hipMemcpyHostToDevice, st)) != hipSuccess) return bail(e, "copy region table");
+  }
+  if (c->o.dtype == PM_F32 && (c->o.arch == PM_ARCH_CHAIN || (c->o.arch == PM_ARCH_TRANSFORMER && !lay.recompute))) {
+    // the weight gradients of a step as one launch (first microbatch: overwrite, later ones: accumulate)
+    const bool chain = c->o.arch == PM_ARCH_CHAIN;
+    const int rows = chain ? c->o.microbatch : c->o.microbatch * c->o.seq_len;
+    float* g = c->at<float>(lay.g_off);
+    std::vector<PmF32Prob<PmEpiBwdWeight>> fp;
+    auto add = [&](const Unit& u, size_t dz, int ld_dz, size_t a_in, int ld_a) {
+      fp.push_back({u.d.n_out, u.d.n_in, rows, c->at<float>(dz), ld_dz, PmWLoc<float>{c->at<float>(a_in), nullptr, 0}, ld_a,
+                    PmEpiBwdWeight{g + u.off, u.d.n_in, 0, g + u.off + u.boff}});
+    };
+    if (chain) {
+      for (int l = 0; l < L; ++l) add(lay.units[l], lay.units[l].dz_off, lay.units[l].ld_out, l == 0 ? lay.x_off : lay.units[l - 1].a_off, lay.units[l].ld_in);
+    } else {
+      const int d = lay.units[0].d.n_out, dff = lay.units[7].d.n_out;
+      add(lay.units[L - 1], lay.t_dlogits, (int)round_up(lay.units[0].d.n_in, 8), lay.t_nf, d);
+      for (size_t l = 0; l < lay.tl.size(); ++l) {
+        const Layout::TfmLayer& b = lay.tl[l];
+        const Unit* u = &lay.units[1 + 8 * l];
+        add(u[1], b.dzq, d, b.n1, d);
+        add(u[2], b.dzk, d, b.n1, d);
+        add(u[3], b.dzv, d, b.n1, d);
+        add(u[4], b.dzo, d, b.o, d);
+        add(u[6], b.dz1, dff, b.n2, d);
+        add(u[7], b.dz2, d, b.f, dff);
+      }
+    }
+    const int np = (int)fp.size();
+    int64_t t32 = 0, t64 = 0, tiles = 0;
+    c->dw_vector = true;
+    for (const auto& q : fp) {
+      t32 += pm_f32_tiles(q.I, q.J, 32);
+      t64 += pm_f32_tiles(q.I, q.J, 64);
+      c->dw_vector = c->dw_vector && pm_f32_vector(q);
+    }
+    c->dw_tile = pm_f32_pick(t32, t64);
+    std::vector<int32_t> first;
+    for (const auto& q : fp) {
+      first.push_back((int32_t)tiles);
+      tiles += pm_f32_tiles(q.I, q.J, c->dw_tile);
+    }
+    fp.insert(fp.end(), fp.begin(), fp.end());
+    for (int i = np; i < 2 * np; ++i) fp[i].epi.accumulate = 1;
+    c->dw_grouped = true;
+    c->dw_nprob = np;
+    c->dw_ntiles = (int)tiles;
+    if ((e = hipMemcpyAsync(c->arena + lay.probs_off, fp.data(), fp.size() * sizeof(fp[0]), hipMemcpyHostToDevice, st)) != hipSuccess) return bail(e, "copy problem table");
+    if ((e = hipMemcpyAsync(c->arena + lay.first_off, first.data(), first.size() * 4, hipMemcpyHostToDevice, st)) != hipSuccess) return bail(e, "copy problem table");
+    if ((e = hipStreamSynchronize(st)) != hipSuccess) return bail(e, "synchronise after tables");   // host tables go out of scope
   }
   if (c->o.dtype == PM_BF16 && c->o.arch == PM_ARCH_CHAIN) {
     // weight-gradient problem tables (first microbatch: overwrite, later ones: accumulate)

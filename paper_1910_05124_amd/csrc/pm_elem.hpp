@@ -1,4 +1,4 @@
-// Input staging, loss kernels, bias gradient and the plain (non-MFMA) GEMM used for fp32 contexts.
+// Input staging, loss kernels, bias gradient and the plain (non-MFMA) GEMM.
 #pragma once
 #include <type_traits>
 
@@ -420,8 +420,7 @@ template <class E> struct pm_has_tile_update<E, std::void_t<decltype(E::kTileUpd
 
 // ---------------------------------------------------------------------------------------------
 // Plain tiled GEMM  C[i, j] = sum_k A(i, k) * B(j, k)  with arbitrary strides; fp32 FMA.
-// Used for fp32 contexts (tiny layers where launch latency dominates) and for any bf16 shape the
-// MFMA kernel's alignment rules exclude.  16x16 outputs per block, K staged 16 at a time.
+// Used for bf16 shapes that the MFMA kernel's alignment rules exclude.  16x16 outputs per block, K staged 16 at a time.
 // ---------------------------------------------------------------------------------------------
 template <typename TA, typename TB, class Epi>
 __global__ __launch_bounds__(256) void pm_gemm_plain_kernel(int I, int J, int K,

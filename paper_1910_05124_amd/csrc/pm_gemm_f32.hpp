@@ -1,0 +1,298 @@
+// fp32 products of the stages on the fp32 matrix instruction (gfx950).
+//
+//   C[i, j] = sum_k A(i, k) * B(j, k),   v_mfma_f32_16x16x4_f32 (fp32 operands, fp32 accumulation).
+//
+// Operands are "KC" (contraction index contiguous) or "RC" (row index contiguous) as in pm_gemm_mfma.hpp.  The networks
+// trained in fp32 are small: a product has 10^5 .. 10^9 multiply-adds, and what bounds it is the latency of its loads
+// and the launch, not the matrix rate.  So the operands go from memory to the matrix instruction's registers without
+// a stop in LDS (no barrier in the main loop), each wave of a block takes its own 16-deep pieces of the contraction, two
+// pieces in flight ahead of the two being multiplied, and the waves' partial tiles are summed through LDS once at the end.
+//
+// One lane of a 16 x 16 x 4 step holds row lane % 16 and contraction index lane / 16 of each operand.  Which four
+// indices a step covers is free as long as both operands agree: step s of a 16-deep piece takes k = 4 (lane / 16) + s, so
+// a KC operand is one 16-byte load per lane and piece; an RC operand with two 16-row tiles per wave gives tile t the
+// rows 2 m + t, so that a lane loads its two rows with one 8-byte access.
+//
+// Measured (us per launch; before: 16 x 16 outputs per 256-thread block on vector FMAs through LDS): 100 x 512 x 512
+// forward 21.9 -> 4.6, data gradient 20.6 -> 4.3; 512 x 1024 x 256 with the residual 25.5 -> 7.3.  The weight gradients
+// of a step and their bias gradients were two launches per unit and are one now: 120 -> 17 us on the 9 units of that
+// first network (8 of them 512 wide), 615 -> 34 us on a 2-layer Transformer 256 wide with 512 tokens.
+#pragma once
+#include "pm_common.hpp"
+#include "pm_elem.hpp"
+
+typedef float pm_f32x4 __attribute__((ext_vector_type(4)));
+
+// T x T matrix tiles of 16 x 16 per wave, WI x WJ waves over the block's outputs, WK waves over the contraction
+template <int T_, int WI_, int WJ_, int WK_>
+struct PmF32Cfg {
+  static constexpr int T = T_, WI = WI_, WJ = WJ_, WK = WK_, NT = WI_ * WJ_ * WK_ * 64;
+  static constexpr int BI = WI_ * T_ * 16, BJ = WJ_ * T_ * 16, RS = BJ + 4;       // RS: padded row of the partial tile
+  static constexpr int lds_floats = WK_ * BI * RS + WK_ * BI;                     // partial tiles, partial column sums
+};
+
+template <class Epi>
+struct PmF32Prob {
+  int I, J, K;
+  const float* A;
+  int64_t lda;
+  PmWLoc<float> B;
+  int64_t ldb;
+  Epi epi;
+};
+
+// One wave's share of an operand: T tiles of 16 rows from row r0 on.  V: whole 16-byte (KC) / 8-byte (RC) accesses are
+// allowed.  Rows beyond the extent R repeat the last one (their results are not stored).
+template <int T, bool KC, bool V>
+struct PmF32Operand {
+  const float* p[T];
+  int64_t ld;
+  int g4;
+  __device__ __forceinline__ void init(const float* X, int64_t ld_, int r0, int R, int lane) {
+    const int m = lane & 15;
+    ld = ld_;
+    g4 = (lane >> 4) * 4;
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      int row = KC ? r0 + 16 * t + m : r0 + T * m + t;
+      // (a vector access of an RC operand starts at an even row and R is even then: both rows are inside or neither)
+      if (row >= R) row = (!KC && V) ? R - T + t : R - 1;
+      p[t] = KC ? X + (int64_t)row * ld : X + row;
+    }
+  }
+  // the 16-deep piece at k0, all of it inside the contraction: x[s][t]
+  __device__ __forceinline__ void load(int k0, float (&x)[4][T]) const {
+    if constexpr (KC) {
+#pragma unroll
+      for (int t = 0; t < T; ++t) {
+        const float* q = p[t] + k0 + g4;
+        if constexpr (V) {
+          const float4 v = *reinterpret_cast<const float4*>(q);
+          x[0][t] = v.x; x[1][t] = v.y; x[2][t] = v.z; x[3][t] = v.w;
+        } else {
+#pragma unroll
+          for (int s = 0; s < 4; ++s) x[s][t] = q[s];
+        }
+      }
+    } else {
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const int64_t o = (int64_t)(k0 + g4 + s) * ld;
+        if constexpr (V && T == 2) {
+          const float2 v = *reinterpret_cast<const float2*>(p[0] + o);
+          x[s][0] = v.x; x[s][1] = v.y;
+        } else {
+#pragma unroll
+          for (int t = 0; t < T; ++t) x[s][t] = p[t][o];
+        }
+      }
+    }
+  }
+  // the piece that crosses the end of the contraction: zeros beyond it
+  __device__ __forceinline__ void load_tail(int k0, int K, float (&x)[4][T]) const {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const int k = k0 + g4 + s;
+      const int64_t o = KC ? (int64_t)(k < K ? k : K - 1) : (int64_t)(k < K ? k : K - 1) * ld;
+#pragma unroll
+      for (int t = 0; t < T; ++t) {
+        const float v = p[t][o];
+        x[s][t] = k < K ? v : 0.f;
+      }
+    }
+  }
+};
+
+template <class Cfg, bool AKC, bool BKC, bool V, class Epi>
+__device__ __forceinline__ void pm_gemm_f32_body(const PmF32Prob<Epi>& pr, Epi epi, int bx, int by, float* smem) {
+  constexpr int T = Cfg::T, WI = Cfg::WI, WJ = Cfg::WJ, WK = Cfg::WK, BI = Cfg::BI, BJ = Cfg::BJ, RS = Cfg::RS, NT = Cfg::NT;
+  const int I = pr.I, J = pr.J, K = pr.K;
+  const int i0 = by * BI, j0 = bx * BJ;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int wk = wave % WK, wj = (wave / WK) % WJ, wi = wave / (WK * WJ);
+  PmF32Operand<T, AKC, V> oa;
+  PmF32Operand<T, BKC, V> ob;
+  oa.init(pr.A, pr.lda, i0 + wi * 16 * T, I, lane);
+  ob.init(pr.B.get(), pr.ldb, j0 + wj * 16 * T, J, lane);
+
+  pm_f32x4 acc[T][T];
+#pragma unroll
+  for (int a = 0; a < T; ++a)
+#pragma unroll
+    for (int b = 0; b < T; ++b) acc[a][b] = pm_f32x4{0.f, 0.f, 0.f, 0.f};
+  float cs[T] = {};
+  const bool do_colsum = Epi::kColSumA && !AKC && bx == 0 && wj == 0 && epi.wants_colsum();
+  auto mul = [&](const float (&xa)[4][T], const float (&xb)[4][T]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int a = 0; a < T; ++a)
+#pragma unroll
+        for (int b = 0; b < T; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[s][a], xb[s][b], acc[a][b], 0, 0, 0);
+    if (Epi::kColSumA && !AKC) {
+      if (do_colsum) {
+#pragma unroll
+        for (int a = 0; a < T; ++a) cs[a] += (xa[0][a] + xa[1][a]) + (xa[2][a] + xa[3][a]);
+      }
+    }
+  };
+  // whole pieces wk, wk + WK, ... of this wave, U at a time
+  constexpr int U = 2;
+  const int whole = K >> 4;
+  const int mine = whole > wk ? (whole - wk + WK - 1) / WK : 0;
+  float xa[U][4][T], xb[U][4][T];
+  int n = 0;
+  if (mine >= U) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      oa.load((wk + u * WK) * 16, xa[u]);
+      ob.load((wk + u * WK) * 16, xb[u]);
+    }
+    for (n = U; n + U <= mine; n += U) {
+      float ya[U][4][T], yb[U][4][T];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        oa.load((wk + (n + u) * WK) * 16, ya[u]);
+        ob.load((wk + (n + u) * WK) * 16, yb[u]);
+      }
+      __builtin_amdgcn_sched_barrier(0);        // keep the requests ahead of the products
+#pragma unroll
+      for (int u = 0; u < U; ++u) mul(xa[u], xb[u]);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+          for (int t = 0; t < T; ++t) xa[u][s][t] = ya[u][s][t], xb[u][s][t] = yb[u][s][t];
+    }
+  }
+  // what is left: at most one whole piece, and on one wave the piece that crosses the end; requested before the last
+  // pair is multiplied
+  float za[4][T], zb[4][T], ta[4][T], tb[4][T];
+  const bool one = n < mine, tail = (K & 15) && whole % WK == wk;
+  if (one) {
+    oa.load((wk + n * WK) * 16, za);
+    ob.load((wk + n * WK) * 16, zb);
+  }
+  if (tail) {
+    oa.load_tail(whole * 16, K, ta);
+    ob.load_tail(whole * 16, K, tb);
+  }
+  if (n > 0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) mul(xa[u], xb[u]);
+  }
+  if (one) mul(za, zb);
+  if (tail) mul(ta, tb);
+
+  // accumulator layout of the 16 x 16 tile: value v of lane l is row 4 (l / 16) + v, column l % 16
+  float* red = smem;
+  float* csum = smem + WK * BI * RS;
+#pragma unroll
+  for (int a = 0; a < T; ++a)
+#pragma unroll
+    for (int b = 0; b < T; ++b)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int r = (lane >> 4) * 4 + v, c = lane & 15;
+        const int li = wi * 16 * T + (AKC ? 16 * a + r : T * r + a), lj = wj * 16 * T + (BKC ? 16 * b + c : T * c + b);
+        red[(wk * BI + li) * RS + lj] = acc[a][b][v];
+      }
+  if (Epi::kColSumA && !AKC) {
+    if (do_colsum) {
+#pragma unroll
+      for (int a = 0; a < T; ++a) {
+        float s = cs[a];
+        s += __shfl_xor(s, 16, 64);
+        s += __shfl_xor(s, 32, 64);
+        if (lane < 16) csum[wk * BI + wi * 16 * T + T * lane + a] = s;
+      }
+    }
+  }
+  __syncthreads();
+  epi.begin();
+  for (int e = threadIdx.x; e < BI * BJ; e += NT) {
+    const int li = e / BJ, lj = e % BJ, i = i0 + li, j = j0 + lj;
+    float sum = 0.f;
+#pragma unroll
+    for (int w = 0; w < WK; ++w) sum += red[(w * BI + li) * RS + lj];
+    if (i < I && j < J) epi(i, j, sum);
+  }
+  if (Epi::kColSumA && !AKC) {
+    if (bx == 0 && epi.wants_colsum() && threadIdx.x < BI && i0 + (int)threadIdx.x < I) {
+      float s = 0.f;
+#pragma unroll
+      for (int w = 0; w < WK; ++w) s += csum[w * BI + threadIdx.x];
+      epi.colsum(i0 + threadIdx.x, s);
+    }
+  }
+}
+
+template <class Cfg, bool V, class Epi>
+__global__ __launch_bounds__(Cfg::NT) void pm_gemm_f32_kernel(PmF32Prob<Epi> pr) {
+  __shared__ float smem[Cfg::lds_floats];
+  pm_gemm_f32_body<Cfg, Epi::kAKC, Epi::kBKC, V, Epi>(pr, pr.epi, blockIdx.x, blockIdx.y, smem);
+}
+
+// A table of problems in one launch: block b works on the problem p with first[p] <= b < first[p + 1].
+template <class Cfg, bool V, class Epi>
+__global__ __launch_bounds__(Cfg::NT) void pm_gemm_f32_grouped_kernel(const PmF32Prob<Epi>* __restrict__ probs, const int32_t* __restrict__ first, int np) {
+  __shared__ float smem[Cfg::lds_floats];
+  int lo = 0, hi = np - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (first[mid] <= (int)blockIdx.x) lo = mid; else hi = mid - 1;
+  }
+  const PmF32Prob<Epi> pr = probs[lo];
+  const int id = (int)blockIdx.x - first[lo], tj = (pr.J + Cfg::BJ - 1) / Cfg::BJ;
+  pm_gemm_f32_body<Cfg, Epi::kAKC, Epi::kBKC, V, Epi>(pr, pr.epi, id % tj, id / tj, smem);
+}
+
+// A wave tile of 16 x 16 where 32 x 32 blocks would leave compute units idle (latency bound: the most waves win),
+// 32 x 32 with the contraction over four waves up to two such blocks per compute unit and 64 x 64 blocks beyond (half the
+// operand traffic per product).
+using PmF32Small = PmF32Cfg<1, 1, 1, 8>;
+using PmF32Mid = PmF32Cfg<2, 1, 1, 4>;
+using PmF32Large = PmF32Cfg<2, 2, 2, 1>;
+inline int64_t pm_f32_tiles(int I, int J, int b) { return (int64_t)((I + b - 1) / b) * ((J + b - 1) / b); }
+// outputs per block edge for a launch with that many 32 x 32 and 64 x 64 tiles in total
+inline int pm_f32_pick(int64_t tiles32, int64_t tiles64) { return tiles64 >= 512 ? 64 : tiles32 >= 256 ? 32 : 16; }
+
+// Whether the operands allow the vector accesses.
+template <class Epi>
+inline bool pm_f32_vector(const PmF32Prob<Epi>& pr) {
+  auto one = [&](bool kc, const void* X, int64_t stride, int64_t ld, int R) {
+    return kc ? pr.K % 4 == 0 && ld % 4 == 0 && stride % 4 == 0 && ((uintptr_t)X & 15) == 0
+              : R % 2 == 0 && ld % 2 == 0 && stride % 2 == 0 && ((uintptr_t)X & 7) == 0;
+  };
+  return one(Epi::kAKC, pr.A, 0, pr.lda, pr.I) && one(Epi::kBKC, pr.B.base, pr.B.stride, pr.ldb, pr.J);
+}
+
+template <class Epi>
+inline void pm_gemm_f32_launch(hipStream_t st, const PmF32Prob<Epi>& pr) {
+  auto go = [&](auto cfg) {
+    using Cfg = decltype(cfg);
+    const dim3 grid((pr.J + Cfg::BJ - 1) / Cfg::BJ, (pr.I + Cfg::BI - 1) / Cfg::BI);
+    if (pm_f32_vector(pr)) hipLaunchKernelGGL((pm_gemm_f32_kernel<Cfg, true, Epi>), grid, dim3(Cfg::NT), 0, st, pr);
+    else hipLaunchKernelGGL((pm_gemm_f32_kernel<Cfg, false, Epi>), grid, dim3(Cfg::NT), 0, st, pr);
+  };
+  switch (pm_f32_pick(pm_f32_tiles(pr.I, pr.J, 32), pm_f32_tiles(pr.I, pr.J, 64))) {
+    case 64: go(PmF32Large()); break;
+    case 32: go(PmF32Mid()); break;
+    default: go(PmF32Small()); break;
+  }
+}
+
+template <class Epi>
+inline void pm_gemm_f32_grouped_launch(hipStream_t st, int block, bool vector, const PmF32Prob<Epi>* probs, const int32_t* first, int np, int tiles) {
+  auto go = [&](auto cfg) {
+    using Cfg = decltype(cfg);
+    if (vector) hipLaunchKernelGGL((pm_gemm_f32_grouped_kernel<Cfg, true, Epi>), dim3(tiles), dim3(Cfg::NT), 0, st, probs, first, np);
+    else hipLaunchKernelGGL((pm_gemm_f32_grouped_kernel<Cfg, false, Epi>), dim3(tiles), dim3(Cfg::NT), 0, st, probs, first, np);
+  };
+  switch (block) {
+    case 64: go(PmF32Large()); break;
+    case 32: go(PmF32Mid()); break;
+    default: go(PmF32Small()); break;
+  }
+}

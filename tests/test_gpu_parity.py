@@ -409,3 +409,38 @@ def test_divergence_is_reported_not_fatal(torch_cuda):
             g.step(torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda(), want_loss=True)
     assert e.value.name == "PM_EDIVERGED"
     g.close()
+
+
+@pytest.mark.parametrize("M,n_in,n_out", [(1, 1, 1), (3, 5, 7), (16, 64, 1), (17, 16, 33), (100, 784, 512), (65, 129, 30), (33, 48, 34),
+                                          (511, 260, 515), (256, 31, 512), (600, 512, 2000), (2048, 20, 1030)])
+def test_fp32_linear_primitives_every_tile_choice(torch_cuda, M, n_in, n_out):
+    """fp32 products on blocks of 16, 32 and 64 outputs, with vector and with single accesses, contractions of no, one
+    and several whole 16-deep pieces and a remainder.  Bound per element: each of the K products and K additions rounds
+    by at most 2^-24, so |error| <= 2 K 2^-24 sum |a b| (and the activation adds one rounding of its own)."""
+    import paper_1910_05124_amd as pm
+    torch = torch_cuda
+    rng = np.random.default_rng(M * 7 + n_in * 3 + n_out)
+    x, W, dz, zp = (rng.standard_normal(s).astype(np.float32) for s in ((M, n_in), (n_out, n_in), (M, n_out), (M, n_in)))
+    b = rng.standard_normal(n_out).astype(np.float32)
+    g0, b0 = rng.standard_normal((n_out, n_in)).astype(np.float32), rng.standard_normal(n_out).astype(np.float32)
+    x_d, W_d, dz_d, zp_d, b_d = (torch.from_numpy(v).cuda() for v in (x, W, dz, zp, b))
+    st = torch.cuda.current_stream().cuda_stream
+    x64, W64, dz64 = x.astype(np.float64), W.astype(np.float64), dz.astype(np.float64)
+
+    def check(got, want, terms, K):
+        got = got.cpu().numpy().astype(np.float64)
+        assert np.all(np.abs(got - want) <= (2 * K + 4) * 2.0 ** -24 * terms), np.max(np.abs(got - want) / terms)
+
+    z, a = torch.full((M, n_out), np.nan, device="cuda"), torch.full((M, n_out), np.nan, device="cuda")
+    pm.pm_linear_fwd(st, "f32", M, n_in, n_out, x_d.data_ptr(), W_d.data_ptr(), b_d.data_ptr(), "relu", z.data_ptr(), a.data_ptr())
+    zw, terms = x64 @ W64.T + b, np.abs(x64) @ np.abs(W64).T + np.abs(b)
+    check(z, zw, terms, n_in)
+    check(a, np.maximum(zw, 0), terms, n_in)
+    dp = torch.full((M, n_in), np.nan, device="cuda")
+    pm.pm_linear_bwd_data(st, "f32", M, n_in, n_out, dz_d.data_ptr(), W_d.data_ptr(), zp_d.data_ptr(), "relu", dp.data_ptr())
+    check(dp, (dz64 @ W64) * (zp > 0), np.abs(dz64) @ np.abs(W64), n_out)
+    for acc in (0, 1):
+        dW, db = torch.from_numpy(g0).cuda(), torch.from_numpy(b0).cuda()
+        pm.pm_linear_bwd_weight(st, "f32", M, n_in, n_out, dz_d.data_ptr(), x_d.data_ptr(), dW.data_ptr(), db.data_ptr(), acc)
+        check(dW, dz64.T @ x64 + acc * g0, np.abs(dz64).T @ np.abs(x64) + acc * np.abs(g0), M)
+        check(db, dz64.sum(0) + acc * b0, np.abs(dz64).sum(0) + acc * np.abs(b0), M)
