@@ -390,6 +390,7 @@ struct pm_ctx {
   std::vector<StepGraph> graphs;
   // all weight-gradient products as one grouped MFMA launch (problem tables live in the arena)
   bool dw_grouped = false;
+  std::vector<char> dw_defer;    // Transformer: per unit, 1 if its weight gradient goes out with the grouped launch
   bool fuse_upd = false;         // the grouped weight-gradient launch applies the update of its units' weight matrices
   int upd_nblocks = 0;           // blocks left to the update pass then
   int64_t upd_fused_params = 0;  // parameters updated in the epilogues
@@ -577,12 +578,11 @@ void launch_bias_grad(hipStream_t st, const T* dz, float* db, int M, int N, int 
 }
 
 // Weight and bias gradient of one unit: dW[n_out, n_in] (+)= dz^T a, db (+)= column sums of dz.  The matrix
-// kernels produce the bias gradient on the way: fp32 always; bf16 for few rows (with many the column sums would sit on
-// the critical path of the blocks that own them, and a chunked reduction over the whole chip is faster).
+// kernels produce the bias gradient on the way, from the operand fragments they multiply.
 template <typename T>
 void launch_wgrad(hipStream_t st, int M, int n_out, int n_in, const T* dz, int ld_dz, const T* a, int ld_a, float* dW, float* db,
                   int accumulate) {
-  const bool fused_db = db && (sizeof(T) == 4 || (M <= 512 && pm_mfma_takes(n_out, n_in, M, dz, 1, ld_dz, a, 0, 1, ld_a)));
+  const bool fused_db = db && (sizeof(T) == 4 || pm_mfma_takes(n_out, n_in, M, dz, 1, ld_dz, a, 0, 1, ld_a));
   PmEpiBwdWeight epi{dW, n_in, accumulate, fused_db ? db : nullptr};
   launch_gemm_on<T>(st, n_out, n_in, M, dz, 1, ld_dz, PmWLoc<T>{a, nullptr, 0}, 1, ld_a, epi);
   if constexpr (sizeof(T) == 2) {
@@ -959,15 +959,16 @@ pm_status launch_tfm(pm_ctx* c, const void* x_dev, const void* y_dev, int accumu
   // end computes all dW and db.  Otherwise each unit's products go out as they become available.
   const bool grouped = c->dw_grouped;
   auto wg = [&](int u, const T* dz, int ld_dz, const T* a_in, int n_out, int n_in) {
-    if (!grouped) wgrad(u, dz, ld_dz, a_in, n_out, n_in);
+    if (!grouped || !c->dw_defer[u]) wgrad(u, dz, ld_dz, a_in, n_out, n_in);
   };
   // Recomputation (App. on recompute; "T2 for Recompute"): the forward pass is taken to have kept only the
   // tensors that cross a segment boundary.  Units are walked backwards; on entering a segment, all its units
   // first run again in order with the weights Wr, overwriting their outputs in place.  At that moment every
   // later segment has finished its backward pass, and no earlier one has been rebuilt: so a unit - in the
   // rebuild and in its backward alike - sees rebuilt tensors exactly where the producer sits in its own segment
-  // and the kept forward tensors where it sits in an earlier one.  Weight gradients go out as soon as their unit
-  // is reached (their inputs may be overwritten by an earlier segment's rebuild).  The head is not rebuilt (the
+  // and the kept forward tensors where it sits in an earlier one.  A weight gradient whose input comes out of an
+  // earlier segment goes out as soon as its unit is reached (that segment's rebuild will overwrite the input); all others
+  // wait for the grouped launch like those of a pass that rebuilds nothing.  The head is not rebuilt (the
   // loss gradient comes from the forward pass).
   auto seg_of = [&](int u) { return (U(u).d.stage - 1) / c->o.segment_size; };
   auto rebuild_unit = [&](int u) -> bool {
@@ -1520,6 +1521,15 @@ pm_status pm_create(int32_t P, int32_t L, const pm_layer_desc* layers, const int
       if (lay.units[l].d.kind != PM_LINEAR) { zero_tab.push_back(lay.units[l].off); zero_tab.push_back(lay.units[l].n_pad); }
     if ((e = hipMemcpyAsync(c->arena + lay.t_pos, pos.data(), pos.size() * 4, hipMemcpyHostToDevice, st)) != hipSuccess) return bail(e, "copy positions");
     if ((e = hipMemcpyAsync(c->arena + lay.t_zero, zero_tab.data(), zero_tab.size() * 8, hipMemcpyHostToDevice, st)) != hipSuccess) return bail(e, "copy region table");
+    // Which weight gradients can wait for the grouped launch: all, but those whose forward input another segment of a
+    // recomputing backward pass will overwrite before (the producer of the input sits in an earlier segment).
+    c->dw_defer.assign(L, 0);
+    for (int u = 0; u < L; ++u) {
+      if (lay.units[u].d.kind != PM_LINEAR) continue;
+      const int j = (u - 1) % 8;
+      const int producer = u == L - 1 ? u - 1 : j <= 3 ? u - j : j == 4 ? u : u - 1;      // projections: ln1; Wo: its own attention
+      c->dw_defer[u] = !lay.recompute || (lay.units[producer].d.stage - 1) / c->o.segment_size == (lay.units[u].d.stage - 1) / c->o.segment_size;
+    }
     if (c->o.dtype == PM_BF16) {
       // grouped weight-gradient launch: one problem per Linear unit, largest first
       const int nl = (L - 3) / 8, Tk = c->o.microbatch * S, V = lay.units[0].d.n_in;
@@ -1538,6 +1548,7 @@ pm_status pm_create(int32_t P, int32_t L, const pm_layer_desc* layers, const int
         wp.push_back({u + 6, c->at<bf16_t>(b.dz1), lay.units[u + 6].d.n_out, c->at<bf16_t>(b.n2)});
         wp.push_back({u + 7, c->at<bf16_t>(b.dz2), d, c->at<bf16_t>(b.f)});
       }
+      wp.erase(std::remove_if(wp.begin(), wp.end(), [&](const WP& w) { return !c->dw_defer[w.u]; }), wp.end());
       // 256 x 256 block tiles (half the LDS traffic per MFMA) when every problem is a whole number of
       // them and there are enough to balance 256 compute units; else 128 x 128
       int TB = 256;
@@ -1604,13 +1615,13 @@ pm_status pm_create(int32_t P, int32_t L, const pm_layer_desc* layers, const int
         }
       }
       const int32_t longest = *std::max_element(load, load + 8);
-      c->dw_grouped = fits && !lay.recompute;   // a recomputing backward needs each weight gradient at its unit's turn
+      c->dw_grouped = fits && np > 0;
       c->dw_aligned = aligned;
       c->dw_tile = TB;
       c->dw_nprob = np;
       c->dw_ntiles = longest * 8;
       c->dw_max_segs = max_segs;
-      if ((e = hipMemcpyAsync(c->arena + lay.t_wprobs, probs.data(), probs.size() * sizeof(probs[0]), hipMemcpyHostToDevice, st)) != hipSuccess) return bail(e, "copy problem table");
+      if (np > 0 && (e = hipMemcpyAsync(c->arena + lay.t_wprobs, probs.data(), probs.size() * sizeof(probs[0]), hipMemcpyHostToDevice, st)) != hipSuccess) return bail(e, "copy problem table");
       if ((e = hipMemcpyAsync(c->arena + lay.t_wtiles, load, sizeof load, hipMemcpyHostToDevice, st)) != hipSuccess) return bail(e, "copy tile table");
       if ((e = hipMemcpyAsync(c->arena + lay.t_wsegs, segs.data(), segs.size() * sizeof(PmXcdSeg), hipMemcpyHostToDevice, st)) != hipSuccess) return bail(e, "copy segment table");
       // The update inside the weight-gradient epilogue: possible when the gradient a tile holds is final (one
@@ -1622,7 +1633,7 @@ pm_status pm_create(int32_t P, int32_t L, const pm_layer_desc* layers, const int
       // steps; 1.99 against 1.99 - 2.01 ms on the 6-layer one, whose pass is cache assisted: hence the default)
       const bool in_launch = c->o.update_placement == 2 || (c->o.update_placement == 0 && nontemporal);
       if (in_launch && c->dw_grouped && aligned && c->o.n_microbatches == 1 && c->o.clip_norm <= 0.0 &&
-          !c->overlap && !lay.has_ur) {
+          !c->overlap && !lay.recompute) {
         const int per_block = nontemporal ? PmAcc<2>::PER_BLOCK : PmAcc<1>::PER_BLOCK;
         std::vector<char> fused((size_t)(lay.n_flat / per_block), 0);
         fprobs.resize(np);
@@ -1669,13 +1680,14 @@ pm_status pm_create(int32_t P, int32_t L, const pm_layer_desc* layers, const int
     for (int l = 0; l < L - 1; ++l) { zero_tab.push_back(lay.units[l].off); zero_tab.push_back(lay.units[l].n_pad); }
     if ((e = hipMemcpyAsync(c->arena + lay.t_zero, zero_tab.data(), zero_tab.size() * 8, hipMemcpyHostToDevice, st)) != hipSuccess) return bail(e, "copy region table");
   }
-  if (c->o.dtype == PM_F32 && (c->o.arch == PM_ARCH_CHAIN || (c->o.arch == PM_ARCH_TRANSFORMER && !lay.recompute))) {
+  if (c->o.dtype == PM_F32 && (c->o.arch == PM_ARCH_CHAIN || c->o.arch == PM_ARCH_TRANSFORMER)) {
     // the weight gradients of a step as one launch (first microbatch: overwrite, later ones: accumulate)
     const bool chain = c->o.arch == PM_ARCH_CHAIN;
     const int rows = chain ? c->o.microbatch : c->o.microbatch * c->o.seq_len;
     float* g = c->at<float>(lay.g_off);
     std::vector<PmF32Prob<PmEpiBwdWeight>> fp;
     auto add = [&](const Unit& u, size_t dz, int ld_dz, size_t a_in, int ld_a) {
+      if (!chain && !c->dw_defer[&u - lay.units.data()]) return;
       fp.push_back({u.d.n_out, u.d.n_in, rows, c->at<float>(dz), ld_dz, PmWLoc<float>{c->at<float>(a_in), nullptr, 0}, ld_a,
                     PmEpiBwdWeight{g + u.off, u.d.n_in, 0, g + u.off + u.boff}});
     };
@@ -1711,11 +1723,11 @@ pm_status pm_create(int32_t P, int32_t L, const pm_layer_desc* layers, const int
     }
     fp.insert(fp.end(), fp.begin(), fp.end());
     for (int i = np; i < 2 * np; ++i) fp[i].epi.accumulate = 1;
-    c->dw_grouped = true;
+    c->dw_grouped = np > 0;
     c->dw_nprob = np;
     c->dw_ntiles = (int)tiles;
-    if ((e = hipMemcpyAsync(c->arena + lay.probs_off, fp.data(), fp.size() * sizeof(fp[0]), hipMemcpyHostToDevice, st)) != hipSuccess) return bail(e, "copy problem table");
-    if ((e = hipMemcpyAsync(c->arena + lay.first_off, first.data(), first.size() * 4, hipMemcpyHostToDevice, st)) != hipSuccess) return bail(e, "copy problem table");
+    if (np > 0 && (e = hipMemcpyAsync(c->arena + lay.probs_off, fp.data(), fp.size() * sizeof(fp[0]), hipMemcpyHostToDevice, st)) != hipSuccess) return bail(e, "copy problem table");
+    if (np > 0 && (e = hipMemcpyAsync(c->arena + lay.first_off, first.data(), first.size() * 4, hipMemcpyHostToDevice, st)) != hipSuccess) return bail(e, "copy problem table");
     if ((e = hipStreamSynchronize(st)) != hipSuccess) return bail(e, "synchronise after tables");   // host tables go out of scope
   }
   if (c->o.dtype == PM_BF16 && c->o.arch == PM_ARCH_CHAIN) {

@@ -22,8 +22,8 @@
 //
 // A launch covers either one problem (passed by value) or a table of problems in device memory
 // indexed by blockIdx.z (all weight-gradient products of a step go out as one launch).  The
-// weight-gradient epilogue can also emit the bias gradient: column sums of the (RC) A tile,
-// accumulated by the blocks of the first column of tiles while the tile sits in LDS.
+// weight-gradient epilogue can also emit the bias gradient: column sums of the (RC) A operand,
+// added up by the blocks of the first column of tiles from the fragments they multiply.
 //
 // Requirements (checked by the dispatcher, which otherwise declines): leading dimensions and
 // base pointers multiples of 8 elements; memory readable up to the next multiple of 8 along the
@@ -107,6 +107,25 @@ __device__ __forceinline__ pm_bf16x8 pm_read_frag(const bf16_t* s, int r32, int 
   }
 }
 
+// Sum of the eight contraction indices a lane holds of its operand row: what a bias gradient (column sums of dz) adds up
+// from the fragments that the products read anyway.  (Reading the tile from LDS a second time, one 2-byte access per
+// index and row, kept the blocks of the first tile column behind all others.)
+__device__ __forceinline__ float pm_frag_sum(const pm_bf16x8& f) {
+  const uint4 u = __builtin_bit_cast(uint4, f);
+  auto two = [](uint32_t w) { return __uint_as_float(w << 16) + __uint_as_float(w & 0xffff0000u); };
+  return (two(u.x) + two(u.y)) + (two(u.z) + two(u.w));
+}
+// Partial sums cs[t] of operand rows row0 + 32 t + lane % 32 -> part[row]: the two halves of a wave meet here,
+// waves that share rows after the caller's barrier.
+template <int T>
+__device__ __forceinline__ void pm_frag_colsum_park(const float (&cs)[T], float* part, int row0, int lane) {
+#pragma unroll
+  for (int t = 0; t < T; ++t) {
+    const float s = cs[t] + __shfl_xor(cs[t], 32, 64);
+    if (lane < 32) part[row0 + t * 32 + lane] = s;
+  }
+}
+
 template <class Epi>
 struct PmGemmProb {
   int I, J, K;
@@ -158,7 +177,7 @@ __device__ __forceinline__ void pm_gemm_body(const PmGemmProb<Epi>& pr, Epi epi,
     for (int b = 0; b < TJ; ++b)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
-  float colsum = 0.f;                                     // bias gradient (weight-gradient epilogue only)
+  float cs[TI] = {};                                      // bias gradient (weight-gradient epilogue only)
   const bool do_colsum = Epi::kColSumA && !AKC && bx == 0 && epi.wants_colsum();
 
   PmTileLoader<BI, AKC, BK, NT> la;
@@ -174,18 +193,18 @@ __device__ __forceinline__ void pm_gemm_body(const PmGemmProb<Epi>& pr, Epi epi,
       la.load(A, lda, i0, (kt + 1) * BK, I, K);
       lb.load(B, ldb, j0, (kt + 1) * BK, J, K);
     }
-    if (Epi::kColSumA && !AKC) {
-      if (do_colsum && threadIdx.x < BI) {
-#pragma unroll 8
-        for (int k = 0; k < BK; ++k) colsum += bf16_to_f32(sA[k * SA::stride + threadIdx.x]);
-      }
-    }
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
       const int kb = (wk * KS + ks) * 16;
       pm_bf16x8 fa[TI], fb[TJ];
 #pragma unroll
       for (int a = 0; a < TI; ++a) fa[a] = pm_read_frag<BI, AKC, BK>(sA, (wi * TI + a) * 32, kb, lane);
+      if (Epi::kColSumA && !AKC) {
+        if (do_colsum && ks % WJ == wj) {                  // waves that hold the same rows take turns
+#pragma unroll
+          for (int a = 0; a < TI; ++a) cs[a] += pm_frag_sum(fa[a]);
+        }
+      }
 #pragma unroll
       for (int b = 0; b < TJ; ++b) fb[b] = pm_read_frag<BJ, BKC, BK>(sB, (wj * TJ + b) * 32, kb, lane);
 #pragma unroll
@@ -199,7 +218,18 @@ __device__ __forceinline__ void pm_gemm_body(const PmGemmProb<Epi>& pr, Epi epi,
 
   epi.begin();
   if (Epi::kColSumA && !AKC) {
-    if (do_colsum && threadIdx.x < BI && i0 + (int)threadIdx.x < I) epi.colsum(i0 + threadIdx.x, colsum);
+    if (do_colsum) {                                       // uniform over the block
+      float* part = reinterpret_cast<float*>(smem);        // [WK * WJ][BI]
+      pm_frag_colsum_park<TI>(cs, part + (wk * WJ + wj) * BI, wi * TI * 32, lane);
+      __syncthreads();
+      if (threadIdx.x < BI && i0 + (int)threadIdx.x < I) {
+        float sum = 0.f;
+#pragma unroll
+        for (int w = 0; w < WK * WJ; ++w) sum += part[w * BI + threadIdx.x];
+        epi.colsum(i0 + threadIdx.x, sum);
+      }
+      __syncthreads();
+    }
   }
   if (WK == 1) {
     // accumulator layout of the 32x32 tile: value v of lane l is row 8*(v/4) + 4*(l/32) + v%4, column l%32
@@ -535,7 +565,10 @@ __device__ __forceinline__ void pm_gemm_big_body(const PmGemmProb<Epi>& pr, int 
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
   Epi epi = pr.epi;
-  float colsum = 0.f;
+  // column sums from the fragments where the registers allow it; the 128 x 64 wave tile is full (they would spill: 0.35
+  // and 3.6 ms slower on the weight gradients of 6 x 512 and 12 x 1024 layers) and re-reads the tile from LDS
+  constexpr bool FRAG_SUM = TI <= 2;
+  float cs[FRAG_SUM ? TI : 1] = {};
   const bool do_colsum = Epi::kColSumA && !AKC && bx == 0 && epi.wants_colsum();
 
   using LA = PmBigLoader<BI, AKC, NT>;
@@ -597,10 +630,10 @@ __device__ __forceinline__ void pm_gemm_big_body(const PmGemmProb<Epi>& pr, int 
       // them to the end of the slab to shorten register live ranges, which costs the latency cover)
       __builtin_amdgcn_sched_barrier(0);
     }
-    if (Epi::kColSumA && !AKC) {
+    if constexpr (Epi::kColSumA && !AKC && !FRAG_SUM) {
       if (do_colsum && threadIdx.x < BI) {
 #pragma unroll 8
-        for (int k = 0; k < BK; ++k) colsum += bf16_to_f32(cA[k * SA::stride + threadIdx.x]);
+        for (int k = 0; k < BK; ++k) cs[0] += bf16_to_f32(cA[k * SA::stride + threadIdx.x]);
       }
     }
     // fragments are double-buffered in registers: the LDS reads of k-step ks+1 are in flight
@@ -613,6 +646,12 @@ __device__ __forceinline__ void pm_gemm_big_body(const PmGemmProb<Epi>& pr, int 
 #pragma unroll
     for (int ks = 0; ks < BK / 16; ++ks) {
       const int c = ks & 1, n = c ^ 1;
+      if constexpr (Epi::kColSumA && !AKC && FRAG_SUM) {
+        if (do_colsum && ks % WJ == wj) {                  // waves that hold the same rows take turns
+#pragma unroll
+          for (int a = 0; a < TI; ++a) cs[a] += pm_frag_sum(fa[c][a]);
+        }
+      }
       if (ks + 1 < BK / 16) {
 #pragma unroll
         for (int a = 0; a < TI; ++a) fa[n][a] = pm_big_frag<BI, AKC>(cA, (wi * TI + a) * 32, (ks + 1) * 16, lane);
@@ -651,7 +690,20 @@ __device__ __forceinline__ void pm_gemm_big_body(const PmGemmProb<Epi>& pr, int 
 
   epi.begin();
   if (Epi::kColSumA && !AKC) {
-    if (do_colsum && threadIdx.x < BI && (!CHECK || i0 + (int)threadIdx.x < I)) epi.colsum(i0 + threadIdx.x, colsum);
+    if (!FRAG_SUM) {
+      if (do_colsum && threadIdx.x < BI && (!CHECK || i0 + (int)threadIdx.x < I)) epi.colsum(i0 + threadIdx.x, cs[0]);
+    } else if (do_colsum) {                                // uniform over the block
+      float* part = reinterpret_cast<float*>(smem);        // [WJ][BI]
+      pm_frag_colsum_park(cs, part + wj * BI, wi * TI * 32, lane);
+      __syncthreads();
+      if (threadIdx.x < BI && (!CHECK || i0 + (int)threadIdx.x < I)) {
+        float sum = 0.f;
+#pragma unroll
+        for (int w = 0; w < WJ; ++w) sum += part[w * BI + threadIdx.x];
+        epi.colsum(i0 + threadIdx.x, sum);
+      }
+      __syncthreads();
+    }
   }
   // Epilogue through LDS (the operand stages are dead after the last barrier): each wave parks one
   // 32-row stripe of its fp32 tile at a time, row-major in a private region, then every lane takes 8
