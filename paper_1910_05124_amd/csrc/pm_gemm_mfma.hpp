@@ -29,6 +29,7 @@
 // base pointers multiples of 8 elements; memory readable up to the next multiple of 8 along the
 // contiguous index, holding zeros beyond the logical extent.
 #pragma once
+#include <algorithm>
 #include <type_traits>
 
 #include "pm_common.hpp"
@@ -788,16 +789,20 @@ __global__ __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(Cfg::WP
   pm_gemm_big_body<Cfg, AKC, BKC, CHECK, Epi>(p == 0 ? p0 : p == 1 ? p1 : p2, id, tiles_i, tiles_j, smem);
 }
 
-// One product with a very long contraction and too few output tiles to fill the chip, cut into two halves of
-// the contraction that run side by side: block b works on half b / (tiles_i * tiles_j); each half writes its
-// own fp32 output and the consumer adds the two.  (256 x 256 tiles: the only block shape whose main loop gets
-// past 1.1 PFLOP/s needs K >= 8192 to amortise its start and end.)
-template <class Cfg, bool AKC, bool BKC, class Epi>
-__global__ __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(Cfg::WPE, Cfg::WPE))) void pm_gemm_big_khalves_kernel(PmGemmProb<Epi> p0, PmGemmProb<Epi> p1, int tiles_i, int tiles_j) {
-  __shared__ __attribute__((aligned(16))) bf16_t smem[PmBigLds<Cfg, AKC, BKC>::elems];
+// One product with a long contraction and too few output tiles to fill the chip, its contraction cut into parts that
+// run side by side: block b works on part b / (tiles_i * tiles_j), indices part * kpart on, and writes that part's fp32
+// output at part * part_stride; the consumer adds the parts in order.  kpart is a multiple of 64.
+template <class Cfg, bool CHECK, class Epi>
+__global__ __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(Cfg::WPE, Cfg::WPE))) void pm_gemm_big_ksplit_kernel(PmGemmProb<Epi> pr, int kpart, int64_t part_stride, int tiles_i, int tiles_j) {
+  __shared__ __attribute__((aligned(16))) bf16_t smem[PmBigLds<Cfg, Epi::kAKC, Epi::kBKC>::elems];
   const int nt = tiles_i * tiles_j;
   const int p = blockIdx.x / nt, id = blockIdx.x - p * nt;      // uniform over the block
-  pm_gemm_big_body<Cfg, AKC, BKC, false, Epi>(p == 0 ? p0 : p1, id, tiles_i, tiles_j, smem);
+  const int k0 = p * kpart;
+  pr.A += (int64_t)k0 * (Epi::kAKC ? 1 : pr.lda);
+  pr.B.base += (int64_t)k0 * (Epi::kBKC ? 1 : pr.ldb);
+  pr.K = pr.K - k0 < kpart ? pr.K - k0 : kpart;
+  pr.epi.out += p * part_stride;
+  pm_gemm_big_body<Cfg, Epi::kAKC, Epi::kBKC, CHECK, Epi>(pr, id, tiles_i, tiles_j, smem);
 }
 
 // One product whose contraction runs over three operand pairs (PmKSeg3); pr.K = 3 * Kseg, pr.A / pr.B = pair 0.
@@ -998,5 +1003,38 @@ inline bool pm_gemm_kseg3_try(hipStream_t st, int I, int J, int Kseg, const bf16
   if (pick == 128) go(PmBig128());
   else if (pick == 64) go(PmBig64());
   else return false;
+  return true;
+}
+
+// How a product with K >> I, J is cut (pm_gemm_big_ksplit_kernel): block tile, parts and indices per part; parts = 1: not
+// at all.  Two halves on 256 x 256 tiles where those fill half to all of the chip (their main loop is the fastest from
+// 8192 indices on: 502 us on 8192 x 1024 x 32000); else as many parts on 128 x 128 tiles as give every compute unit two
+// blocks, of at least 512 indices each (below that the parts' start and the extra outputs cost
+// what they gain): 4096 x 512 x 8192 110 -> 49 us, 2048 x 768 x 16000 170 -> 68, 2400 x 320 x 10007 174 -> 42.
+struct PmKSplit { int tile, parts, kpart; };
+inline PmKSplit pm_ksplit_plan(int I, int J, int K, int max_parts) {
+  const PmKSplit none{0, 1, K};
+  if (K < 2048 || max_parts < 2) return none;
+  const int t256 = (I / 256) * (J / 256);
+  if (pm_big_aligned<PmBig256>(I, J, K) && K % 128 == 0 && K >= 16384 && 2 * t256 <= 256 && 2 * t256 >= 128) return {256, 2, K / 2};
+  const int t128 = ((I + 127) / 128) * ((J + 127) / 128);
+  int parts = std::min({8, max_parts, 512 / t128, K / 512});
+  if (parts < 2) return none;
+  const int kpart = (K + 64 * parts - 1) / (64 * parts) * 64;
+  parts = (K + kpart - 1) / kpart;
+  return {128, parts, kpart};
+}
+template <class Epi>
+inline bool pm_gemm_ksplit_try(hipStream_t st, const PmGemmProb<Epi>& pr, const PmKSplit& s, int64_t part_stride) {
+  if (s.parts < 2 || !pm_mfma_fits(pr.I, pr.J, pr.K, pr.A, pr.lda, 1, pr.B.base, pr.B.stride, 1, pr.ldb)) return false;
+  auto go = [&](auto cfg, auto check) {
+    using Cfg = decltype(cfg);
+    const int ti = (pr.I + Cfg::BI - 1) / Cfg::BI, tj = (pr.J + Cfg::BJ - 1) / Cfg::BJ;
+    hipLaunchKernelGGL((pm_gemm_big_ksplit_kernel<Cfg, decltype(check)::value, Epi>), dim3(s.parts * ti * tj), dim3(Cfg::NT), 0, st,
+                       pr, s.kpart, part_stride, ti, tj);
+  };
+  if (s.tile == 256) go(PmBig256(), std::false_type());
+  else if (pm_big_aligned<PmBig128>(pr.I, pr.J, pr.K)) go(PmBig128(), std::false_type());
+  else go(PmBig128(), std::true_type());
   return true;
 }

@@ -189,12 +189,12 @@ __global__ __launch_bounds__(256) void pm_ln_fwd_kernel(const float* __restrict_
 // Block = 8 waves x 4 rows; lane l owns columns 256 c + 4 l .. + 3 (16-byte accesses), d <= 256 NC,
 // d a multiple of 4.
 // ---------------------------------------------------------------------------------------------
-template <typename T, int NC>
+template <typename T, int NC, int R>
 __global__ __launch_bounds__(512) void pm_ln_bwd_kernel(const float* __restrict__ dy, const float* __restrict__ x,
                                                         const float* __restrict__ mean, const float* __restrict__ rstd,
                                                         PmWLoc<T> gain_bkwd, const float* dx_res, float* dx_out,
                                                         T* dx_out_t, float* __restrict__ dgain, float* __restrict__ dbias,
-                                                        int rows, int d, const float* dy2) {
+                                                        int rows, int d, int parts, int64_t part_stride) {
   __shared__ float4 red[8][2][64 * NC];                       // per wave: gain and bias partial sums
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const T* g = gain_bkwd.get();
@@ -207,13 +207,13 @@ __global__ __launch_bounds__(512) void pm_ln_bwd_kernel(const float* __restrict_
     ag[c] = zero4;
     ab[c] = zero4;
   }
-  // all loads of the wave's four rows go out first (rows past the end re-read the last row and are
+  // all loads of the wave's R rows go out first (rows past the end re-read the last row and are
   // masked out below), so the wave pays the memory latency once instead of once per row
-  float4 dyr[4][NC], xr[4][NC], rrr[4][NC];
-  float mur[4], rsr[4];
+  float4 dyr[R][NC], xr[R][NC], rrr[R][NC];
+  float mur[R], rsr[R];
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int row = blockIdx.x * 32 + wave * 4 + r;
+  for (int r = 0; r < R; ++r) {
+    const int row = blockIdx.x * (8 * R) + wave * R + r;
     const int rowc = row < rows ? row : rows - 1;
     const int64_t ro = (int64_t)rowc * d;
     mur[r] = mean[rowc];
@@ -222,18 +222,26 @@ __global__ __launch_bounds__(512) void pm_ln_bwd_kernel(const float* __restrict_
     for (int c = 0; c < NC; ++c) {
       const int j = 256 * c + 4 * lane;
       dyr[r][c] = j < d ? pm_ld4(dy + ro + j) : zero4;
-      if (dy2 && j < d) {       // the gradient arrives as two addends (dy2 may be the buffer dx_out is written to below)
-        const float4 e = pm_ld4(dy2 + ro + j);
-        dyr[r][c].x += e.x; dyr[r][c].y += e.y; dyr[r][c].z += e.z; dyr[r][c].w += e.w;
-      }
       xr[r][c] = j < d ? pm_ld4(x + ro + j) : zero4;
       // (requested here, not row by row below: a load issued behind the stores of the row before would wait for them)
       rrr[r][c] = (dx_res && j < d) ? pm_ld4(dx_res + ro + j) : zero4;
     }
   }
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int row = blockIdx.x * 32 + wave * 4 + r;
+  for (int r = 0; r < R; ++r)
+    for (int p = 1; p < parts; ++p) {                         // the gradient arrives as several addends
+      const int row = blockIdx.x * (8 * R) + wave * R + r;
+      const float* dyp = dy + p * part_stride + (int64_t)(row < rows ? row : rows - 1) * d;
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        const int j = 256 * c + 4 * lane;
+        const float4 e = j < d ? pm_ld4(dyp + j) : zero4;
+        dyr[r][c].x += e.x; dyr[r][c].y += e.y; dyr[r][c].z += e.z; dyr[r][c].w += e.w;
+      }
+    }
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int row = blockIdx.x * (8 * R) + wave * R + r;
     if (row >= rows) break;                                   // wave-uniform
     const float mu = mur[r], rs = rsr[r];
     const int64_t ro = (int64_t)row * d;
@@ -322,15 +330,17 @@ inline bool pm_ln_fwd_launch(hipStream_t st, const float* x, PmWLoc<T> gb, int b
 template <typename T>
 inline bool pm_ln_bwd_launch(hipStream_t st, const float* dy, const float* x, const float* mean, const float* rstd,
                              PmWLoc<T> gain_bkwd, const float* dx_res, float* dx_out, T* dx_out_t, float* dgain,
-                             float* dbias, int rows, int d, const float* dy2 = nullptr) {
+                             float* dbias, int rows, int d, int parts = 1, int64_t part_stride = 0) {
   if (d & 3) return false;
-  const dim3 grid((rows + 31) / 32), blk(512);
-#define PM_LNB(NC) hipLaunchKernelGGL((pm_ln_bwd_kernel<T, NC>), grid, blk, 0, st, dy, x, mean, rstd, gain_bkwd, dx_res, dx_out, dx_out_t, dgain, dbias, rows, d, dy2)
-  if (d <= 256) PM_LNB(1);
-  else if (d <= 512) PM_LNB(2);
-  else if (d <= 768) PM_LNB(3);
-  else if (d <= 1024) PM_LNB(4);
+  const dim3 blk(512);
+#define PM_LNB(NC, R) hipLaunchKernelGGL((pm_ln_bwd_kernel<T, NC, R>), dim3((rows + 8 * R - 1) / (8 * R)), blk, 0, st, dy, x, mean, rstd, gain_bkwd, dx_res, dx_out, dx_out_t, dgain, dbias, rows, d, parts, part_stride)
+#define PM_LNR(NC) PM_LNB(NC, 4)
+  if (d <= 256) PM_LNR(1);
+  else if (d <= 512) PM_LNR(2);
+  else if (d <= 768) PM_LNR(3);
+  else if (d <= 1024) PM_LNR(4);
   else return false;
+#undef PM_LNR
 #undef PM_LNB
   return true;
 }
