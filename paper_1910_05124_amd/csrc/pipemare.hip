@@ -768,13 +768,15 @@ pm_status launch_fwd_bwd(pm_ctx* c, const void* x_dev, const void* y_dev, int ac
     if (c->dw_grouped) {
       ProfSpan span(c, PM_CLS_GEMM);
       const auto* tab = c->at<PmGemmProb<PmEpiBwdWeight>>(lay.probs_off) + (accumulate ? L : 0);
-      dim3 grid((c->dw_maxJ + 63) / 64, (c->dw_maxI + 63) / 64, L);
       if (M <= 128)
-        hipLaunchKernelGGL((pm_gemm_mfma_grouped_kernel<PmCfgShortK, false, false, PmEpiBwdWeight>), grid, dim3(256), 0,
-                           st, tab);
+        hipLaunchKernelGGL((pm_gemm_mfma_grouped_kernel<PmCfgShortK, false, false, PmEpiBwdWeight>),
+                           dim3((c->dw_maxJ + 63) / 64, (c->dw_maxI + 63) / 64, L), dim3(256), 0, st, tab);
+      else if (c->dw_tile == 128)
+        hipLaunchKernelGGL((pm_gemm_big_table_kernel<PmBig128, false, false, PmEpiBwdWeight>), dim3(c->dw_ntiles, L),
+                           dim3(PmBig128::NT), 0, st, tab);
       else
-        hipLaunchKernelGGL((pm_gemm_mfma_grouped_kernel<PmCfgMid, false, false, PmEpiBwdWeight>), grid, dim3(256), 0, st,
-                           tab);
+        hipLaunchKernelGGL((pm_gemm_big_table_kernel<PmBig64, false, false, PmEpiBwdWeight>), dim3(c->dw_ntiles, L),
+                           dim3(PmBig64::NT), 0, st, tab);
       grouped = true;
     }
   } else {
@@ -1743,6 +1745,12 @@ pm_status pm_create(int32_t P, int32_t L, const pm_layer_desc* layers, const int
         c->dw_maxJ = std::max(c->dw_maxJ, (int)u.d.n_in);
       }
     c->dw_grouped = fits;
+    // more than 128 rows: the pipelined kernel, on 128 x 128 tiles where these give every compute unit two
+    auto tiles = [&](const Unit& u, int b) { return (int64_t)((u.d.n_out + b - 1) / b) * ((u.d.n_in + b - 1) / b); };
+    int64_t t128 = 0;
+    for (int l = 0; l < L; ++l) t128 += tiles(lay.units[l], 128);
+    c->dw_tile = t128 >= 512 ? 128 : 64;
+    for (int l = 0; l < L; ++l) c->dw_ntiles = std::max(c->dw_ntiles, (int)tiles(lay.units[l], c->dw_tile));
     if ((e = hipMemcpyAsync(c->arena + lay.probs_off, probs.data(), probs.size() * sizeof(probs[0]), hipMemcpyHostToDevice, st)) != hipSuccess) return bail(e, "copy problem table");
     // chained launches (see pm_chain.hpp): few rows, no recomputation, one step-table set
     std::vector<PmChainFwd> cf;
