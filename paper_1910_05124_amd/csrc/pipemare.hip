@@ -106,9 +106,12 @@ struct Layout {
   struct ConvBuf {
     PmConvGeom g;
     size_t z, y, da, dz, dy;
+    bool fused;                // the data gradient carries the affine backward of the unit below
+    int parts;                 // partials of the weight gradient (0: summed in one kernel)
+    size_t wpart, apart, wt;
   };
   std::vector<ConvBuf> cv;
-  size_t r_x, r_pool, r_logits, r_dlogits, r_dpool, r_wscratch, r_ascratch;
+  size_t r_x, r_pool, r_logits, r_dlogits, r_dpool;
   size_t t_xf, t_muf, t_rsf, t_nf, t_logits, t_dlogits;      // final LayerNorm and head
   size_t t_dx, t_dn, t_do;                                   // backward scratch, reused by every layer
   size_t t_pos, t_zero;                                      // positions fp32 [S, d]; zero-region table
@@ -338,12 +341,22 @@ void make_layout(int32_t L, const pm_layer_desc* layers, const int32_t* tau_fwd,
     lay.r_logits = take((size_t)M * round_up(ncls, 8) * 4);
     lay.r_dlogits = take((size_t)M * round_up(ncls, 8) * e);
     lay.r_dpool = take((size_t)M * C * e);
-    size_t ws = 0;
-    for (int u = 0; u < nconv; ++u)
-      ws = std::max(ws, o->dtype == PM_BF16 ? pm_conv_wgrad_scratch_elems<bf16_t>(lay.cv[u].g)
-                                            : pm_conv_wgrad_scratch_elems<float>(lay.cv[u].g));
-    lay.r_wscratch = take(ws * 4);
-    lay.r_ascratch = take((size_t)PM_CONV_AFFINE_MAX_BLOCKS * 2 * 256 * 4);     // per-block channel sums of the affine backward
+    // per unit: the weight gradient's partials, the channel sums of its affine backward, the transposed kernel
+    // tensor of the fused data gradient (all units' partials live until the reduce that ends the backward pass)
+    for (int u = 0; u < nconv; ++u) {
+      Layout::ConvBuf& b = lay.cv[u];
+      const bool bf = o->dtype == PM_BF16;
+      b.fused = bf && u > 0 && pm_conv_mfma_fits(b.g.Cin, b.g.Cout);
+      b.parts = bf ? pm_conv_wgrad_parts<bf16_t>(b.g) : pm_conv_wgrad_parts<float>(b.g);
+      b.wpart = take((size_t)b.parts * lay.units[u].nw * 4);
+      b.wt = b.fused ? take((size_t)lay.units[u].nw * e) : 0;
+    }
+    for (int u = 0; u < nconv; ++u) {
+      Layout::ConvBuf& b = lay.cv[u];
+      const size_t blocks = u + 1 < nconv && lay.cv[u + 1].fused ? pm_conv_dgrad_affine_blocks(lay.cv[u + 1].g)
+                                                                 : PM_CONV_AFFINE_MAX_BLOCKS;
+      b.apart = take(blocks * 2 * b.g.Cout * 4);
+    }
     lay.n_zero = nconv;
     lay.zero_max = 0;
     for (int u = 0; u < nconv; ++u) lay.zero_max = std::max(lay.zero_max, lay.units[u].n_pad);
@@ -1174,15 +1187,35 @@ pm_status launch_resnet(pm_ctx* c, const void* x_dev, const void* y_dev, int acc
     const unsigned bx = (unsigned)std::max<int64_t>(1, std::min<int64_t>(64, lay.zero_max / 4 / 256));
     hipLaunchKernelGGL(pm_zero_regions_kernel, dim3(bx, lay.n_zero), dim3(256), 0, st, g, c->at<int64_t>(lay.t_zero));
   }
+  if constexpr (sizeof(T) == 2) {
+    std::vector<PmCvTransposeJob> tr;
+    for (int u = 1; u < nconv; ++u)
+      if (lay.cv[u].fused) tr.push_back(PmCvTransposeJob{Wb(u, 0), TT(lay.cv[u].wt), U(u).d.n_in, U(u).d.n_out});
+    if (!tr.empty()) pm_conv_transpose_launch(st, tr.data(), (int)tr.size());
+  }
   // Recomputation: on entering a segment (walking the units backwards) its convolutions run again in order with
   // the weights Wr, overwriting their outputs in place; a unit then sees rebuilt tensors where the producer sits in
   // its own segment and kept forward tensors where it sits in an earlier one (see launch_tfm).  The classifier is
   // not rebuilt; its pooled input is, when the last convolution shares its segment.
+  // Weight gradients wait here until the end of the pass, or until recomputation is about to overwrite what they
+  // read; the reductions of their partials and of the channel sums wait until the end.
+  std::vector<PmCvWgradJob> wjobs;
+  std::vector<PmReduceJob> rjobs;
+  auto flush = [&]() {
+    if (wjobs.empty()) return;
+    ProfSpan span(c, PM_CLS_GEMM);
+    pm_conv_wgrad_group_launch(st, wjobs.data(), (int)wjobs.size());
+    wjobs.clear();
+  };
   auto seg_of = [&](int u) { return (U(u).d.stage - 1) / c->o.segment_size; };
-  auto enter = [&](int u) {                 // called before the backward of unit u
+  int entered = L;
+  auto enter = [&](int u) {                 // called before the backward of unit u, or earlier
+    if (u >= entered) return;
+    entered = u;
     if (!lay.recompute || (u < L - 1 && seg_of(u) == seg_of(u + 1))) return;
     int lo = u;
     while (lo > 0 && seg_of(lo - 1) == seg_of(u)) --lo;
+    flush();                                // the weight gradient of unit u + 1 reads the kept output of unit u
     for (int v = lo; v <= u; ++v)
       if (v < nconv) conv_fwd(v, Wr(v, 0));
     if (u == fc && lo <= nconv - 1) pm_pool_fwd_launch<T>(st, TT(lay.cv[nconv - 1].y), TT(lay.r_pool), B, HW, C);
@@ -1199,29 +1232,53 @@ pm_status launch_resnet(pm_ctx* c, const void* x_dev, const void* y_dev, int acc
     hipLaunchKernelGGL((pm_pool_bwd_kernel<T>), dim3((unsigned)std::min<int64_t>(2048, (tot + 255) / 256)), dim3(256), 0, st,
                        TT(lay.r_dpool), TT(lay.cv[nconv - 1].dy), B, HW, C);
   }
+  bool have_dz = false;                               // the unit above has written this unit's dz and channel sums
   for (int u = nconv - 1; u >= 0; --u) {
     enter(u);
     const Layout::ConvBuf& b = lay.cv[u];
     const int64_t nw = U(u).nw, tot = (int64_t)B * b.g.Ho * b.g.Wo * b.g.Cout;
-    // the per-channel sums of the affine backward ride on the weight gradient's reduce launch when it has one
-    PmReduceJob sums{nullptr, 0, 0, nullptr, 1};
-    float* apart = pm_conv_wgrad_has_reduce<T>(b.g) ? c->at<float>(lay.r_ascratch) : nullptr;
-    if (!pm_conv_affine_bwd_launch<T>(st, TT(b.dy), TT(b.y), TT(b.z), Wb(u, nw), TT(b.da), TT(b.dz), g + U(u).off + nw,
-                                      g + U(u).off + nw + b.g.Cout, tot, b.g.Cout, apart, &sums))
-      return fail(PM_EINVAL, "unit %d: channel count not supported", u);
-    // the reduce that ends the weight gradient rides on the data gradient's launch (none for the first layer)
-    PmReducePending pend{};
-    ProfSpan span(c, PM_CLS_GEMM);      // weight gradient and data gradient of this convolution
-    pm_conv_wgrad_launch<T>(st, b.g, TT(b.dz), input_of(u), g + U(u).off, accumulate, c->at<float>(lay.r_wscratch), sums,
-                            u > 0 ? &pend : nullptr);
+    if (!have_dz) {
+      // the per-channel sums join the final reduction where the weight gradient has one
+      float* apart = b.parts ? c->at<float>(b.apart) : nullptr;
+      PmReduceJob sums{nullptr, 0, 0, nullptr, 1};
+      if (!pm_conv_affine_bwd_launch<T>(st, TT(b.dy), TT(b.y), TT(b.z), Wb(u, nw), TT(b.da), TT(b.dz), g + U(u).off + nw,
+                                        g + U(u).off + nw + b.g.Cout, tot, b.g.Cout, apart, &sums))
+        return fail(PM_EINVAL, "unit %d: channel count not supported", u);
+      if (sums.part) rjobs.push_back(sums);
+    }
+    have_dz = false;
+    ProfSpan span(c, PM_CLS_GEMM);      // weight gradient (where it does not wait) and data gradient of this convolution
+    if (!b.parts) {
+      pm_conv_wgrad_plain_launch<T>(st, b.g, TT(b.dz), input_of(u), g + U(u).off, accumulate);
+    } else {
+      rjobs.push_back(PmReduceJob{c->at<float>(b.wpart), b.parts, (int)nw, g + U(u).off, accumulate});
+      if (pm_conv_thin_fits(b.g)) pm_conv_wgrad_thin_launch<T>(st, b.g, TT(b.dz), input_of(u), c->at<float>(b.wpart));
+      else if constexpr (sizeof(T) == 2) wjobs.push_back(PmCvWgradJob{b.g, TT(b.dz), input_of(u), c->at<float>(b.wpart), 0});
+    }
     if (u == 0) break;
     PmShortcutBwd<T> sb{nullptr, 0, 0, 0, 1};
     if ((u % 2) == 1) {                               // first convolution of a block: its input also feeds the shortcut
       const PmConvGeom& g2 = lay.cv[u + 1].g;
       sb = PmShortcutBwd<T>{TT(lay.cv[u + 1].da), g2.Ho, g2.Wo, g2.Cout, b.g.stride};
     }
-    pm_conv_dgrad_launch<T>(st, b.g, TT(b.dz), Wb(u, 0), sb, TT(lay.cv[u - 1].dy), &pend);
+    if constexpr (sizeof(T) == 2) {
+      if (b.fused) {
+        const Layout::ConvBuf& d = lay.cv[u - 1];
+        enter(u - 1);                                 // y and z of the unit below, rebuilt where they are to be
+        const int64_t nwd = U(u - 1).nw;
+        // shortcuts read da of second convolutions only
+        pm_conv_dgrad_affine_launch(st, b.g, TT(b.dz), TT(b.wt), sb, TT(d.y), TT(d.z), Wb(u - 1, nwd),
+                                    u >= 3 && ((u - 1) % 2) == 0 ? TT(d.da) : nullptr, TT(d.dz), c->at<float>(d.apart));
+        rjobs.push_back(PmReduceJob{c->at<float>(d.apart), pm_conv_dgrad_affine_blocks(b.g), 2 * d.g.Cout,
+                                    g + U(u - 1).off + nwd, 1});
+        have_dz = true;
+        continue;
+      }
+    }
+    pm_conv_dgrad_launch<T>(st, b.g, TT(b.dz), Wb(u, 0), sb, TT(lay.cv[u - 1].dy));
   }
+  flush();
+  if (!rjobs.empty()) pm_conv_reduce_launch(st, rjobs.data(), (int)rjobs.size());
   PM_HIP(hipGetLastError());
   return PM_OK;
 }
@@ -2177,8 +2234,8 @@ pm_status pm_conv3x3_bwd_weight(void* stream, int32_t dtype, int32_t B, int32_t 
   const size_t need = 4 * (dtype == PM_BF16 ? pm_conv_wgrad_scratch_elems<bf16_t>(g) : pm_conv_wgrad_scratch_elems<float>(g));
   if (need && (!scratch_dev || scratch_bytes < need)) return fail(PM_ENOMEM, "scratch has %zu bytes, %zu needed", scratch_bytes, need);
   hipStream_t st = (hipStream_t)stream;
-  if (dtype == PM_BF16) pm_conv_wgrad_launch<bf16_t>(st, g, (const bf16_t*)dz_dev, (const bf16_t*)x_dev, dW_dev, 0, (float*)scratch_dev);
-  else pm_conv_wgrad_launch<float>(st, g, (const float*)dz_dev, (const float*)x_dev, dW_dev, 0, (float*)scratch_dev);
+  if (dtype == PM_BF16) pm_conv_wgrad_launch<bf16_t>(st, g, (const bf16_t*)dz_dev, (const bf16_t*)x_dev, dW_dev, (float*)scratch_dev);
+  else pm_conv_wgrad_launch<float>(st, g, (const float*)dz_dev, (const float*)x_dev, dW_dev, (float*)scratch_dev);
   PM_HIP(hipGetLastError());
   return PM_OK;
 }
@@ -2237,8 +2294,8 @@ pm_status pm_conv3x3_bwd_weight_static(void* stream, int32_t dtype, int32_t B, i
   // every block of the kernels writes all of its slice of the partial results before the reduce reads
   // it, so nothing left by an earlier call needs clearing
   hipStream_t st = (hipStream_t)stream;
-  if (dtype == PM_BF16) pm_conv_wgrad_launch<bf16_t>(st, g, (const bf16_t*)dz_dev, (const bf16_t*)x_dev, dW_dev, 0, (float*)scratch);
-  else pm_conv_wgrad_launch<float>(st, g, (const float*)dz_dev, (const float*)x_dev, dW_dev, 0, (float*)scratch);
+  if (dtype == PM_BF16) pm_conv_wgrad_launch<bf16_t>(st, g, (const bf16_t*)dz_dev, (const bf16_t*)x_dev, dW_dev, (float*)scratch);
+  else pm_conv_wgrad_launch<float>(st, g, (const float*)dz_dev, (const float*)x_dev, dW_dev, (float*)scratch);
   PM_HIP(hipGetLastError());
   return PM_OK;
 }

@@ -21,6 +21,7 @@
 // no block-level barriers in the hot loops.  fp32 contexts and odd channel counts (the 3-channel
 // input convolution) use the plain kernels below.
 #pragma once
+#include <type_traits>
 #include "pm_common.hpp"
 #include "pm_mfma_types.hpp"
 
@@ -254,7 +255,7 @@ constexpr int PM_CONV_THIN_GROUPS = 64;
 
 // da = dy * [y > 0];  dz = da * scale_bkwd;  dscale += sum da * z;  dshift += sum da.  The caller zeroes
 // dscale / dshift at the start of a minibatch.  With `part` the block writes its sums to
-// part[block][0 = scale | 1 = shift][C] and the weight-gradient reduce kernel that follows adds them up
+// part[block][0 = scale | 1 = shift][C] and the reduce launch that ends the backward pass adds them up
 // (hundreds of blocks adding into the same few dozen addresses with fp32 atomics serialise: that tail
 // cost more than the streaming part of the kernel); without it, fp32 atomics.  Thread t of a block always
 // sees channel (t * 8 .. t * 8 + 7) mod C because a block's span is a multiple of C elements.
@@ -365,124 +366,336 @@ __global__ __launch_bounds__(256) void pm_pool_bwd_kernel(const T* __restrict__ 
   }
 }
 
+// out[e] (+)= sum over nparts partial vectors of n elements each (part[p][e]); one launch takes a list of jobs.
 struct PmReduceJob {
   const float* part;
-  int nparts;
-  int64_t n;
+  int nparts, n;
   float* out;
   int accumulate;
 };
-// work of block `bid` (256 threads) of a reduce over two jobs; blocks0 = blocks of the first job
-__device__ __forceinline__ void pm_conv_reduce_block(const PmReduceJob& j0, const PmReduceJob& j1, int blocks0, int bid) {
-  const bool second = bid >= blocks0;
-  const PmReduceJob jb = second ? j1 : j0;
+constexpr int PM_CONV_JOBS = 24;       // jobs of one launch (they travel as kernel arguments)
+struct PmReduceList {
+  PmReduceJob job[PM_CONV_JOBS];
+  int end[PM_CONV_JOBS];               // first block behind each job
+  int count;
+};
+// Block = 16 slices of the partial range x 64 elements, four per thread: many short chains of independent
+// loads instead of a few long ones (the arrays are small; what matters is the latency of the longest chain).
+__global__ __launch_bounds__(256) void pm_conv_reduce_kernel(PmReduceList list) {
+  int k = 0;
+  while (k + 1 < list.count && (int)blockIdx.x >= list.end[k]) ++k;
+  const PmReduceJob jb = list.job[k];
   const int el = threadIdx.x & 15, sl = threadIdx.x >> 4;
-  const int64_t e = (int64_t)(second ? bid - blocks0 : bid) * 16 + el;
-  float acc = 0.f;
-  if (e < jb.n) {
-    int p = sl;
+  const int e0 = ((int)blockIdx.x - (k ? list.end[k - 1] : 0)) * 64;
+  float acc[4] = {0.f, 0.f, 0.f, 0.f};
+  int off[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) off[q] = min(e0 + 16 * q + el, jb.n - 1);
+  int p = sl;
+  auto rows = [&](auto count) __attribute__((always_inline)) {
+    constexpr int R = decltype(count)::value;
+    float v[R][4];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) v[r][q] = jb.part[(int64_t)(p + 16 * r) * jb.n + off[q]];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) acc[q] += v[r][q];
+  };
 #pragma unroll 1
-    for (; p + 48 < jb.nparts; p += 64) {
-      const float a0 = jb.part[(int64_t)p * jb.n + e], a1 = jb.part[(int64_t)(p + 16) * jb.n + e];
-      const float a2 = jb.part[(int64_t)(p + 32) * jb.n + e], a3 = jb.part[(int64_t)(p + 48) * jb.n + e];
-      acc += (a0 + a1) + (a2 + a3);
-    }
-    for (; p < jb.nparts; p += 16) acc += jb.part[(int64_t)p * jb.n + e];
-  }
-  __shared__ float s[16][16];
-  s[sl][el] = acc;
+  for (; p + 112 < jb.nparts; p += 128) rows(std::integral_constant<int, 8>());
+#pragma unroll 1
+  for (; p + 16 < jb.nparts; p += 32) rows(std::integral_constant<int, 2>());
+  if (p < jb.nparts) rows(std::integral_constant<int, 1>());
+  __shared__ float s[16][64];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) s[sl][16 * q + el] = acc[q];
   __syncthreads();
-  if (sl == 0 && e < jb.n) {
+  if (threadIdx.x < 64 && e0 + (int)threadIdx.x < jb.n) {
     float v = 0.f;
 #pragma unroll
-    for (int q = 0; q < 16; ++q) v += s[q][el];
-    jb.out[e] = jb.accumulate ? jb.out[e] + v : v;
+    for (int q = 0; q < 16; ++q) v += s[q][threadIdx.x];
+    float* o = jb.out + e0 + threadIdx.x;
+    *o = jb.accumulate ? *o + v : v;
   }
 }
-__global__ __launch_bounds__(256) void pm_conv_wgrad_reduce_kernel(PmReduceJob j0, PmReduceJob j1, int blocks0) {
-  pm_conv_reduce_block(j0, j1, blocks0, blockIdx.x);
+// the jobs of `v`, in launches of up to PM_CONV_JOBS
+inline void pm_conv_reduce_launch(hipStream_t st, const PmReduceJob* v, int count) {
+  for (int at = 0; at < count; at += PM_CONV_JOBS) {
+    PmReduceList l{};
+    l.count = std::min(PM_CONV_JOBS, count - at);
+    int blocks = 0;
+    for (int k = 0; k < l.count; ++k) {
+      l.job[k] = v[at + k];
+      l.end[k] = blocks += (v[at + k].n + 63) / 64;
+    }
+    hipLaunchKernelGGL(pm_conv_reduce_kernel, dim3((unsigned)blocks), dim3(256), 0, st, l);
+  }
 }
-// a reduce that has not been launched yet: it can ride as extra blocks on the next independent launch
-struct PmReducePending {
-  PmReduceJob j0, j1;
-  bool valid;
-  int blocks0() const { return (int)((j0.n + 15) / 16); }
-  int blocks() const { return blocks0() + (j1.part ? (int)((j1.n + 15) / 16) : 0); }
-};
 
 // ---------------------------------------------------------------------------------------------
 // implicit-GEMM kernels (bf16, Cin and Cout multiples of 16, at most 64)
 // ---------------------------------------------------------------------------------------------
 __device__ __forceinline__ pm_bf16x8 pm_cv_ld8(const bf16_t* p) { return *reinterpret_cast<const pm_bf16x8*>(p); }
 
-// forward.  One wave = 32 output pixels x all output channels; blockDim.x / 64 waves per block (4 on large
-// maps, 1 on small ones so that the few pixel groups still spread over the chip), no LDS.
-template <int NCT>   // output-channel tiles of 32 (Cout <= 32 NCT)
+// Pixel index -> (image, row, column) of a W x H map (32-bit divisions but for maps beyond 2^31 pixels).
+__device__ __forceinline__ void pm_cv_split(int64_t p, int W, int H, int& b, int& y, int& x) {
+  if (p < ((int64_t)1 << 31)) {
+    const unsigned u = (unsigned)p, r = u / (unsigned)W;
+    x = (int)(u - r * (unsigned)W);
+    b = (int)(r / (unsigned)H);
+    y = (int)(r - (unsigned)b * (unsigned)H);
+  } else {
+    const int64_t r = p / W;
+    x = (int)(p - r * W);
+    b = (int)(r / H);
+    y = (int)(r - (int64_t)b * H);
+  }
+}
+
+// Product of one wave: 32 pixels (lane % 32) x the 32 channels rows[.] of the weights, contraction over 9 taps
+// of 16 KC channels.  BWD: the source is dz and the weights are [ci][tap][co].  All loads are unconditional (a tap
+// outside the map reads pixel 0 and is masked when it arrives) and are requested ahead of the products: all of
+// them up to 32 channels, a tap row ahead with more (registers).  Under a predicate each load came out with a wait
+// of its own, 9 KC round trips to memory one behind the other, and the kernels spent nearly all their time there.
+template <int KC, bool BWD>
+__device__ __forceinline__ void pm_cv_core(const PmConvGeom& g, const bf16_t* __restrict__ src, const bf16_t* __restrict__ wrow,
+                                           bool pv, int b, int y, int x, int kg, pm_f32x16& acc) {
+  constexpr int C = 16 * KC, AHEAD = KC <= 2 ? 3 : 2;     // tap rows in registers
+  const int SH = BWD ? g.Ho : g.H, SW = BWD ? g.Wo : g.W;
+  union Frag { pm_bf16x8 v; uint4 q; };
+  Frag fx[AHEAD][3][KC], fw[AHEAD][3][KC];
+  unsigned m[AHEAD][3];
+  auto load = [&](int r, int at) __attribute__((always_inline)) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      int iy, ix;
+      bool ok = pv;
+      if (BWD) {
+        const int sh = g.stride - 1;                      // stride 1 or 2
+        iy = y + 1 - r;
+        ix = x + 1 - c;
+        ok = ok && iy >= 0 && ix >= 0 && !((iy | ix) & sh);
+        iy >>= sh;
+        ix >>= sh;
+        ok = ok && iy < SH && ix < SW;
+      } else {
+        iy = y * g.stride + r - 1;
+        ix = x * g.stride + c - 1;
+        ok = ok && iy >= 0 && iy < SH && ix >= 0 && ix < SW;
+      }
+      m[at][c] = ok ? 0xffffffffu : 0u;
+      const bf16_t* sp = src + (ok ? (((int64_t)b * SH + iy) * SW + ix) * C : (int64_t)0) + 8 * kg;
+      const bf16_t* wp = wrow + (r * 3 + c) * C + 8 * kg;
+#pragma unroll
+      for (int k = 0; k < KC; ++k) {
+        fx[at][c][k].q = *reinterpret_cast<const uint4*>(sp + 16 * k);
+        fw[at][c][k].q = *reinterpret_cast<const uint4*>(wp + 16 * k);
+      }
+    }
+  };
+  auto mma = [&](int at) __attribute__((always_inline)) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+#pragma unroll
+      for (int k = 0; k < KC; ++k) {
+        Frag f = fx[at][c][k];
+        const unsigned w = m[at][c];
+        f.q = make_uint4(f.q.x & w, f.q.y & w, f.q.z & w, f.q.w & w);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[at][c][k].v, f.v, acc, 0, 0, 0);
+      }
+  };
+  // (scheduling barriers: left to itself the compiler moves each load down to its use)
+  load(0, 0);
+  load(1, 1);
+  if (AHEAD == 3) load(2, 2 % AHEAD);
+  __builtin_amdgcn_sched_barrier(0);
+  mma(0);
+  if (AHEAD == 2) {
+    load(2, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  mma(1);
+  mma(2 % AHEAD);
+}
+__device__ __forceinline__ float4 pm_cv_unpack(uint2 a) {
+  return make_float4(__uint_as_float(a.x << 16), __uint_as_float(a.x & 0xffff0000u), __uint_as_float(a.y << 16),
+                     __uint_as_float(a.y & 0xffff0000u));
+}
+__device__ __forceinline__ uint2 pm_cv_mask(uint2 a, bool on) {
+  const unsigned m = on ? 0xffffffffu : 0u;
+  return make_uint2(a.x & m, a.y & m);
+}
+
+// forward.  One wave = 32 output pixels x 32 output channels (blockIdx.y: which 32); blockDim.x / 64 waves per
+// block, no LDS.  What the epilogue reads is requested before the contraction.
+// 128 x 32 x 32 x 16 channels 10.4 -> 7.8 us, 128 x 8 x 8 x 64 channels 19.0 -> 7.5 us.
+template <int KC>    // Cin = 16 KC
 __global__ __launch_bounds__(256) void pm_conv_fwd_mfma_kernel(PmConvGeom g, const bf16_t* __restrict__ x,
                                                                PmWLoc<bf16_t> wloc, PmShortcut<bf16_t> sc,
                                                                bf16_t* __restrict__ z, bf16_t* __restrict__ y) {
   const bf16_t* Wt = wloc.get();
   const bf16_t* scale = Wt + (int64_t)g.Cout * 9 * g.Cin;
   const bf16_t* shift = scale + g.Cout;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, pl = lane & 31, kg = lane >> 5;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, pl = lane & 31, kg = lane >> 5, c0 = blockIdx.y * 32;
   const int64_t npix = (int64_t)g.B * g.Ho * g.Wo;
   const int64_t p = ((int64_t)blockIdx.x * (blockDim.x >> 6) + wave) * 32 + pl;
   const bool pv = p < npix;
-  const int ox = (int)(p % g.Wo), oy = (int)((p / g.Wo) % g.Ho), b = (int)(p / ((int64_t)g.Wo * g.Ho));
-  pm_f32x16 acc[NCT];
+  int b, oy, ox;
+  pm_cv_split(pv ? p : 0, g.Wo, g.Ho, b, oy, ox);
+  // a lane's channels: c0 + 8 a + 4 kg + 0 .. 3.  Groups past Cout read the first group's values and store nothing.
+  uint2 rs[4], rt[4], rc[4];
+  // (no shortcut: the shift's address, masked)
+  const bf16_t* sp = sc.src ? sc.src + (((int64_t)b * sc.Hs + oy * sc.stride) * sc.Ws + ox * sc.stride) * sc.Cs : shift;
 #pragma unroll
-  for (int t = 0; t < NCT; ++t)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) acc[t][e] = 0.f;
-  const int K9 = 9 * g.Cin;
-  for (int tap = 0; tap < 9; ++tap) {
-    const int iy = oy * g.stride + tap / 3 - 1, ix = ox * g.stride + tap % 3 - 1;
-    const bool ok = pv && iy >= 0 && iy < g.H && ix >= 0 && ix < g.W;
-    const bf16_t* xr = x + (((int64_t)b * g.H + iy) * g.W + ix) * g.Cin + 8 * kg;
-    for (int kc = 0; kc < g.Cin; kc += 16) {
-      const pm_bf16x8 fb = ok ? pm_cv_ld8(xr + kc) : pm_at_zero8();
-#pragma unroll
-      for (int t = 0; t < NCT; ++t) {
-        const int co = t * 32 + pl;
-        const pm_bf16x8 fa = co < g.Cout ? pm_cv_ld8(Wt + (int64_t)co * K9 + tap * g.Cin + kc + 8 * kg) : pm_at_zero8();
-        acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, fb, acc[t], 0, 0, 0);
-      }
-    }
+  for (int a = 0; a < 4; ++a) {
+    const int co = c0 + 8 * a + 4 * kg, cc = co < g.Cout ? co : 0;
+    rs[a] = *reinterpret_cast<const uint2*>(scale + cc);
+    rt[a] = *reinterpret_cast<const uint2*>(shift + cc);
+    // whole groups lie inside or outside the shortcut's channels (Cs is a multiple of 8)
+    rc[a] = *reinterpret_cast<const uint2*>(sp + (co < sc.Cs ? co : 0));
   }
+  pm_f32x16 acc;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+  // channels past Cout repeat the last one: their products are not stored
+  pm_cv_core<KC, false>(g, x, Wt + (int64_t)min(c0 + pl, g.Cout - 1) * 9 * g.Cin, pv, b, oy, ox, kg, acc);
   if (!pv) return;
 #pragma unroll
-  for (int t = 0; t < NCT; ++t)
+  for (int a = 0; a < 4; ++a) {
+    const int co = c0 + 8 * a + 4 * kg;
+    if (co >= g.Cout) continue;
+    const float4 s4 = pm_cv_unpack(rs[a]), t4 = pm_cv_unpack(rt[a]), c4 = pm_cv_unpack(pm_cv_mask(rc[a], sc.src && co < sc.Cs));
+    const float ss[4] = {s4.x, s4.y, s4.z, s4.w}, tt[4] = {t4.x, t4.y, t4.z, t4.w}, cc[4] = {c4.x, c4.y, c4.z, c4.w};
+    float yy[4];
 #pragma unroll
-    for (int a = 0; a < 4; ++a) {
-      const int co = t * 32 + 8 * a + 4 * kg;
-      if (co >= g.Cout) continue;
-      float zz[4], yy[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        zz[j] = acc[t][4 * a + j];
-        const float av = ldf(scale + co + j) * zz[j] + ldf(shift + co + j) + sc.at(b, oy, ox, co + j);
-        yy[j] = av > 0.f ? av : 0.f;
-      }
-      pm_st4(z + p * g.Cout + co, make_float4(zz[0], zz[1], zz[2], zz[3]));
-      pm_st4(y + p * g.Cout + co, make_float4(yy[0], yy[1], yy[2], yy[3]));
+    for (int j = 0; j < 4; ++j) {
+      const float av = ss[j] * acc[4 * a + j] + tt[j] + cc[j];
+      yy[j] = av > 0.f ? av : 0.f;
     }
+    pm_st4(z + p * g.Cout + co, make_float4(acc[4 * a], acc[4 * a + 1], acc[4 * a + 2], acc[4 * a + 3]));
+    pm_st4(y + p * g.Cout + co, make_float4(yy[0], yy[1], yy[2], yy[3]));
+  }
 }
 
-// data gradient.  One wave = 32 input pixels x all input channels.  The whole kernel tensor of the
+// The kernel tensors of the backward weights, transposed for the data gradient: [co][tap][ci] -> [ci][tap][co],
+// all units in one launch.
+struct PmCvTransposeJob {
+  PmWLoc<bf16_t> w;
+  bf16_t* wt;
+  int Cin, Cout;
+};
+struct PmCvTransposeList {
+  PmCvTransposeJob job[PM_CONV_JOBS];
+};
+__global__ __launch_bounds__(256) void pm_conv_transpose_kernel(PmCvTransposeList list) {
+  const PmCvTransposeJob jb = list.job[blockIdx.y];
+  const bf16_t* w = jb.w.get();
+  const int n = jb.Cin * 9 * jb.Cout;
+  for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) {
+    const int co = i % jb.Cout, r = i / jb.Cout, tap = r % 9, ci = r / 9;
+    jb.wt[i] = w[(co * 9 + tap) * jb.Cin + ci];
+  }
+}
+
+template <int O>
+__device__ __forceinline__ void pm_cv_exchange(float (&v)[32], int pl) {
+  const bool up = (pl & O) != 0;
+#pragma unroll
+  for (int i = 0; i < O; ++i) {
+    const float send = up ? v[i] : v[i + O], keep = up ? v[i + O] : v[i];
+    v[i] = keep + __shfl_xor(send, O, 64);
+  }
+}
+
+// data gradient of a unit with the affine backward of the unit below in its epilogue: the product is dy of that
+// unit; with its y and z at the same places
+//   da = dy [y > 0] (stored where a shortcut will read it),  dz = da * scale_bkwd,
+//   sums over the block's pixels of da z and of da -> part[block][0 = scale | 1 = shift][Cin].
+// Same scheme as the forward kernel, on the transposed kernel tensor.  One launch and no dy in memory in place of
+// the data gradient (11.6 us on 128 x 32 x 32 x 16 channels, 18.7 on 128 x 8 x 8 x 64: it parked the whole kernel
+// tensor in LDS first) and a pass over dy, y and z (7 us): 10.2 and 9.5 us.
+template <int KC>    // Cout = 16 KC
+__global__ __launch_bounds__(256) void pm_conv_dgrad_affine_kernel(PmConvGeom g, const bf16_t* __restrict__ dz,
+                                                                   const bf16_t* __restrict__ wt, PmShortcutBwd<bf16_t> sb,
+                                                                   const bf16_t* __restrict__ y, const bf16_t* __restrict__ z,
+                                                                   PmWLoc<bf16_t> scale_bkwd, bf16_t* __restrict__ da_out,
+                                                                   bf16_t* __restrict__ dz_out, float* __restrict__ part) {
+  const bf16_t* scale = scale_bkwd.get();
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, pl = lane & 31, kg = lane >> 5, c0 = blockIdx.y * 32;
+  const int64_t npix = (int64_t)g.B * g.H * g.W;
+  const int64_t p = ((int64_t)blockIdx.x * (blockDim.x >> 6) + wave) * 32 + pl;
+  const bool pv = p < npix;
+  int b, iy, ix;
+  pm_cv_split(pv ? p : 0, g.W, g.H, b, iy, ix);
+  const int64_t row = (pv ? p : 0) * g.Cin;
+  uint2 rs[4], ry[4], rz[4], rc[4];
+  const bool sv = sb.da && (sb.stride == 1 || !((iy | ix) & 1));
+  const bf16_t* sp = sb.da ? sb.da + (sv ? (((int64_t)b * sb.Ho + iy / sb.stride) * sb.Wo + ix / sb.stride) * sb.Co : (int64_t)0) : scale;
+#pragma unroll
+  for (int a = 0; a < 4; ++a) {
+    const int ci = c0 + 8 * a + 4 * kg, cc = ci < g.Cin ? ci : 0;
+    rs[a] = *reinterpret_cast<const uint2*>(scale + cc);
+    ry[a] = *reinterpret_cast<const uint2*>(y + row + cc);
+    rz[a] = *reinterpret_cast<const uint2*>(z + row + cc);
+    rc[a] = *reinterpret_cast<const uint2*>(sp + cc);      // (no shortcut: the scale's address, masked)
+  }
+  pm_f32x16 acc;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+  pm_cv_core<KC, true>(g, dz, wt + (int64_t)min(c0 + pl, g.Cin - 1) * 9 * g.Cout, pv, b, iy, ix, kg, acc);
+  float v[32];                                           // [which sum][a][j]
+#pragma unroll
+  for (int a = 0; a < 4; ++a) {
+    const int ci = c0 + 8 * a + 4 * kg;
+    const bool st = pv && ci < g.Cin;
+    const float4 s4 = pm_cv_unpack(rs[a]), y4 = pm_cv_unpack(ry[a]), z4 = pm_cv_unpack(rz[a]), c4 = pm_cv_unpack(pm_cv_mask(rc[a], sv));
+    const float ss[4] = {s4.x, s4.y, s4.z, s4.w}, yy[4] = {y4.x, y4.y, y4.z, y4.w}, zz[4] = {z4.x, z4.y, z4.z, z4.w};
+    // dy is rounded to bf16 as an activation gradient in memory is
+    const float4 d4 = pm_cv_unpack(make_uint2(pm_pack_bf16(acc[4 * a] + c4.x, acc[4 * a + 1] + c4.y),
+                                              pm_pack_bf16(acc[4 * a + 2] + c4.z, acc[4 * a + 3] + c4.w)));
+    const float dd[4] = {d4.x, d4.y, d4.z, d4.w};
+    float d[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      d[j] = yy[j] > 0.f ? dd[j] : 0.f;
+      v[4 * a + j] = st ? d[j] * zz[j] : 0.f;
+      v[16 + 4 * a + j] = st ? d[j] : 0.f;
+    }
+    if (st) {
+      if (da_out) pm_st4(da_out + row + ci, make_float4(d[0], d[1], d[2], d[3]));
+      pm_st4(dz_out + row + ci, make_float4(d[0] * ss[0], d[1] * ss[1], d[2] * ss[2], d[3] * ss[3]));
+    }
+  }
+  // 32 sums over 32 lanes: each exchange adds the half that the partner keeps, 31 exchanges in all, and lane pl
+  // ends with sum number pl
+  pm_cv_exchange<16>(v, pl);
+  pm_cv_exchange<8>(v, pl);
+  pm_cv_exchange<4>(v, pl);
+  pm_cv_exchange<2>(v, pl);
+  pm_cv_exchange<1>(v, pl);
+  __shared__ float red[4][64];
+  red[wave][(pl >> 4) * 32 + 8 * ((pl >> 2) & 3) + 4 * kg + (pl & 3)] = v[0];
+  __syncthreads();
+  if (threadIdx.x < 64) {
+    const int which = threadIdx.x >> 5, ci = c0 + (threadIdx.x & 31);
+    float t = red[0][threadIdx.x];
+    for (int w = 1; w < (int)(blockDim.x >> 6); ++w) t += red[w][threadIdx.x];
+    if (ci < g.Cin) part[((int64_t)blockIdx.x * 2 + which) * g.Cin + ci] = t;
+  }
+}
+
+// data gradient on the kernel tensor as it lies, for the entry point that has no room for a transposed one
+// and no unit below.  One wave = 32 input pixels x all input channels.  The whole kernel tensor of the
 // backward weights sits in LDS as it lies in memory ([co][tap * Cin + ci], padded rows); its
 // transposed fragments (row = ci, contraction = co) come from LDS transpose loads.
 template <int NCO, int NCT>   // channel tiles of 32: Cout <= 32 NCO, Cin <= 32 NCT
 __global__ __launch_bounds__(256) void pm_conv_dgrad_mfma_kernel(PmConvGeom g, const bf16_t* __restrict__ dz,
                                                                  PmWLoc<bf16_t> wloc, PmShortcutBwd<bf16_t> sb,
-                                                                 bf16_t* __restrict__ dx, PmReduceJob r0, PmReduceJob r1,
-                                                                 int rblocks0, int dgrad_blocks) {
+                                                                 bf16_t* __restrict__ dx) {
   __shared__ __attribute__((aligned(16))) bf16_t sW[(32 * NCO + 16) * (9 * 32 * NCT + 8)];
-  // blocks past the data gradient's own carry the pending reduce of the same layer's weight gradient
-  // (independent work: one launch less per layer on maps where a launch costs as much as the kernel)
-  if ((int)blockIdx.x >= dgrad_blocks) {
-    pm_conv_reduce_block(r0, r1, rblocks0, (int)blockIdx.x - dgrad_blocks);
-    return;
-  }
   const int K9 = 9 * g.Cin, WS = K9 + 8;                 // LDS row stride: 16-byte aligned rows
   {
     const bf16_t* Wt = wloc.get();
@@ -541,189 +754,170 @@ __global__ __launch_bounds__(256) void pm_conv_dgrad_mfma_kernel(PmConvGeom g, c
     }
 }
 
-// weight gradient.  Each wave owns a run of output pixels, 32 at a time ("chunk"): it parks the dz
-// rows and the (tap-shifted) input rows of the 32 pixels in a private LDS region and reads both
-// transposed (contraction = pixels).  Work items are (tap, chunk) pairs, tap outermost so that one
-// accumulator set serves a tap; the global loads of the next item are in flight in a second register
-// set while the current item is stored to LDS and multiplied (a wave has no other wave to hide its
-// load latency behind here).  At the end of a tap the four waves of the block park their accumulators
-// in LDS, the block sums them and writes ITS partial dW of that tap to a scratch area;
-// pm_conv_wgrad_reduce_kernel sums the blocks' partials.  (Measured alternatives: fp32 atomics of
-// every wave straight into dW, or LDS float atomics for the block sum, each cost several times the
-// rest of the kernel.)
-// TPB taps per block (9: all of them; 3: blockIdx.y picks the tap row dy = blockIdx.y - 1, for small
-// maps whose pixel chunks alone would leave most of the chip idle; the rows write disjoint entries of
-// the block's partial, so nothing else changes).
-template <int NTO, int NTI, int NCH, int TPB = 9>   // channel tiles of 32 of Cout and Cin; chunks of 32 pixels per wave
-__global__ __launch_bounds__(256) void pm_conv_wgrad_mfma_kernel(PmConvGeom g, const bf16_t* __restrict__ dz,
-                                                                 const bf16_t* __restrict__ x, float* __restrict__ part) {
-  const int tap0 = TPB == 9 ? 0 : (int)blockIdx.y * 3;
+// weight gradient.  Nothing of the backward chain waits for it, so the units of a step share one launch (one per
+// pair of channel tiles).  A block takes the three taps of one row (blockIdx.y) and a run of 32-pixel chunks
+// for each of its waves.  Per chunk a wave parks the dz rows and the three shifted sets of input rows in its own
+// LDS region and reads all of them transposed (contraction = pixels); the loads of the next chunk are in flight
+// meanwhile.  The taps' sums stay in registers until the end, when the four waves meet in LDS and the block
+// writes its partial of the three taps; pm_conv_reduce_kernel adds the blocks' partials.
+// Taking one tap of a chunk at a time left every load - park - multiply round trip exposed (36 of them in a row),
+// in a launch per unit that filled the chip once: 16 - 20 us per unit, 313 us for the 18 units of ResNet-20 on
+// 128 images; now 98 us.
+struct PmCvWgradJob {
+  PmConvGeom g;
+  const bf16_t* dz;
+  const bf16_t* x;
+  float* part;       // [block][Cout][9][Cin]
+  int nch;           // chunks of 32 pixels per wave
+};
+struct PmCvWgradList {
+  PmCvWgradJob job[PM_CONV_JOBS];
+  int end[PM_CONV_JOBS];               // first blockIdx.x behind each job
+  int count;
+};
+template <int NTO, int NTI>   // channel tiles of 32 of Cout and Cin
+__global__ __launch_bounds__(256) void pm_conv_wgrad_mfma_kernel(PmCvWgradList list) {
   constexpr int SA = NTO * 32 + 8, SB = NTI * 32 + 8;     // LDS row strides (elements)
   constexpr int PA = NTO * 2, PB = NTI * 2;               // 16-byte pieces per lane of a 32-pixel tile
   constexpr int RW = NTI * 32;                            // row width of the block's reduction tile
-  __shared__ __attribute__((aligned(16))) bf16_t sA[4][32 * SA];
-  __shared__ __attribute__((aligned(16))) bf16_t sB[4][32 * SB];
-  __shared__ float red[4][NTO * 32 * RW];                 // one accumulator image per wave
+  constexpr int WAVE = 32 * SA + 3 * 32 * SB;             // elements of a wave's region
+  constexpr size_t BYTES = sizeof(bf16_t) * 4 * WAVE > sizeof(float) * 4 * NTO * 32 * RW ? sizeof(bf16_t) * 4 * WAVE
+                                                                                         : sizeof(float) * 4 * NTO * 32 * RW;
+  __shared__ __attribute__((aligned(16))) unsigned char lds[BYTES];
+  int k = 0;
+  while (k + 1 < list.count && (int)blockIdx.x >= list.end[k]) ++k;
+  const PmCvWgradJob& jb = list.job[k];
+  const PmConvGeom g = jb.g;
+  const bf16_t* __restrict__ dz = jb.dz;
+  const bf16_t* __restrict__ x = jb.x;
+  const int bid = (int)blockIdx.x - (k ? list.end[k - 1] : 0), dy = (int)blockIdx.y - 1, nch = jb.nch;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  bf16_t* wa = sA[wave];
-  bf16_t* wb = sB[wave];
-  for (int c = lane; c < 32 * SA / 8; c += 64) *reinterpret_cast<uint4*>(wa + c * 8) = make_uint4(0, 0, 0, 0);
-  for (int c = lane; c < 32 * SB / 8; c += 64) *reinterpret_cast<uint4*>(wb + c * 8) = make_uint4(0, 0, 0, 0);
-  __syncthreads();
+  bf16_t* wa = reinterpret_cast<bf16_t*>(lds) + wave * WAVE;
+  bf16_t* wb = wa + 32 * SA;
+  for (int c = lane; c < WAVE / 8; c += 64) *reinterpret_cast<uint4*>(wa + c * 8) = make_uint4(0, 0, 0, 0);
   const int npix = g.B * g.Ho * g.Wo;                      // fits 32 bits (checked by the dispatcher)
-  const int p_begin = (blockIdx.x * 4 + wave) * NCH * 32;
   const int pa = g.Cout / 8, pb = g.Cin / 8;               // 16-byte pieces per row
-  const int64_t nW = (int64_t)g.Cout * 9 * g.Cin;
-  float* my_part = part + (int64_t)blockIdx.x * nW;
-
-  // Per chunk and piece, once: where this lane's piece comes from.  Loads are unconditional (clamped
-  // to a valid address) and zeroed by a select afterwards, so they issue back to back and the waits
-  // before the LDS stores count only the older register set.
-  int a_off[NCH][PA];        // element offset into dz, or -1 (piece not used / pixel past the end)
-  int b_ctr[NCH][PB];        // input pixel index of the centre tap, or -1
-  int b_yx[NCH][PB];         // (iy << 16 | ix) of the centre tap
+  const int first = (bid * 4 + wave) * nch * 32;           // (below npix + 4 * 32 * nch: fits as well)
+  // where this lane's pieces lie: pixel of the chunk and column
+  int ap[PA], ac[PA], bp[PB], bc[PB];
 #pragma unroll
-  for (int ch = 0; ch < NCH; ++ch) {
-#pragma unroll
-    for (int j = 0; j < PA; ++j) {
-      const int c = lane + 64 * j, p = p_begin + ch * 32 + c / pa;
-      a_off[ch][j] = (c < 32 * pa && p < npix) ? p * g.Cout + (c % pa) * 8 : -1;
-    }
-#pragma unroll
-    for (int j = 0; j < PB; ++j) {
-      const int c = lane + 64 * j, p = p_begin + ch * 32 + c / pb;
-      if (c < 32 * pb && p < npix) {
-        const unsigned up = (unsigned)p, wo = (unsigned)g.Wo, ho = (unsigned)g.Ho;
-        const int ox = (int)(up % wo), oy = (int)((up / wo) % ho), bb = (int)(up / (wo * ho));
-        const int iy = oy * g.stride, ix = ox * g.stride;
-        b_ctr[ch][j] = (bb * g.H + iy) * g.W + ix;
-        b_yx[ch][j] = (iy << 16) | ix;
-      } else {
-        b_ctr[ch][j] = -1;
-        b_yx[ch][j] = 0;
-      }
-    }
+  for (int j = 0; j < PA; ++j) {
+    const int c = lane + 64 * j;
+    ap[j] = c / pa;
+    ac[j] = (c - ap[j] * pa) * 8;
   }
-  int cbv[PB];                                             // column of this lane's j-th input piece
 #pragma unroll
-  for (int j = 0; j < PB; ++j) cbv[j] = ((lane + 64 * j) % pb) * 8;
-
-  auto load_regs = [&](int tl, int ch, uint4* ra, uint4* rb) __attribute__((always_inline)) {
-    const int dy = (tap0 + tl) / 3 - 1, dx = tl % 3 - 1;       // tap0 is a multiple of 3
+  for (int j = 0; j < PB; ++j) {
+    const int c = lane + 64 * j;
+    bp[j] = c / pb;
+    bc[j] = (c - bp[j] * pb) * 8;
+  }
+  uint4 ra[PA], rb[3][PB];
+  unsigned ma[PA], mb[3][PB];
+  // loads are unconditional (element 0 where there is nothing to read) and masked when they are parked
+  auto load = [&](int p0) __attribute__((always_inline)) {
 #pragma unroll
     for (int j = 0; j < PA; ++j) {
-      const int o = a_off[ch][j];
-      ra[j] = *reinterpret_cast<const uint4*>(dz + (o < 0 ? 0 : o));
+      const bool ok = ap[j] < 32 && p0 + ap[j] < npix;
+      ma[j] = ok ? 0xffffffffu : 0u;
+      ra[j] = *reinterpret_cast<const uint4*>(dz + (ok ? (p0 + ap[j]) * g.Cout + ac[j] : 0));
     }
 #pragma unroll
     for (int j = 0; j < PB; ++j) {
-      const int ctr = b_ctr[ch][j];
-      const int iy = (b_yx[ch][j] >> 16) + dy, ix = (b_yx[ch][j] & 0xffff) + dx;
-      const bool ok = ctr >= 0 && iy >= 0 && iy < g.H && ix >= 0 && ix < g.W;
-      rb[j] = *reinterpret_cast<const uint4*>(x + (ok ? (int64_t)(ctr + dy * g.W + dx) * g.Cin + cbv[j] : 0));
+      const int p = p0 + bp[j];
+      const bool in = bp[j] < 32 && p < npix;
+      const unsigned up = in ? (unsigned)p : 0u, r = up / (unsigned)g.Wo, bb = r / (unsigned)g.Ho;
+      const int iy = (int)(r - bb * (unsigned)g.Ho) * g.stride + dy, ix = (int)(up - r * (unsigned)g.Wo) * g.stride;
+      const bool iny = in && iy >= 0 && iy < g.H;
+#pragma unroll
+      for (int t = 0; t < 3; ++t) {
+        const bool ok = iny && ix + t - 1 >= 0 && ix + t - 1 < g.W;
+        mb[t][j] = ok ? 0xffffffffu : 0u;
+        rb[t][j] = *reinterpret_cast<const uint4*>(x + (ok ? (((int)bb * g.H + iy) * g.W + ix + t - 1) * g.Cin + bc[j] : 0));
+      }
     }
   };
-  // zero what must not contribute (after the data has arrived, right before it is parked)
-  auto store_regs = [&](int tl, int ch, const uint4* ra, const uint4* rb) __attribute__((always_inline)) {
-    const int dy = (tap0 + tl) / 3 - 1, dx = tl % 3 - 1;
-    // (component-wise selects: a select between whole uint4 objects would go through memory)
+  auto park = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int j = 0; j < PA; ++j) {
-      const int c = lane + 64 * j;
-      const unsigned m = a_off[ch][j] < 0 ? 0u : 0xffffffffu;
-      if (c < 32 * pa)
-        *reinterpret_cast<uint4*>(wa + (c / pa) * SA + (c % pa) * 8) = make_uint4(ra[j].x & m, ra[j].y & m, ra[j].z & m, ra[j].w & m);
-    }
-#pragma unroll
-    for (int j = 0; j < PB; ++j) {
-      const int c = lane + 64 * j;
-      const int iy = (b_yx[ch][j] >> 16) + dy, ix = (b_yx[ch][j] & 0xffff) + dx;
-      const bool ok = b_ctr[ch][j] >= 0 && iy >= 0 && iy < g.H && ix >= 0 && ix < g.W;
-      const unsigned m = ok ? 0xffffffffu : 0u;
-      if (c < 32 * pb) *reinterpret_cast<uint4*>(wb + (c / pb) * SB + cbv[j]) = make_uint4(rb[j].x & m, rb[j].y & m, rb[j].z & m, rb[j].w & m);
-    }
-  };
-  pm_f32x16 acc[NTO][NTI];
-  auto mma = [&]() __attribute__((always_inline)) {
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-      pm_bf16x8 fa[NTO], fb[NTI];
-      const int ql = lane >> 4, q = lane & 15;
-      typedef pm_v4s __attribute__((address_space(3))) * lds_v4s;
-#pragma unroll
-      for (int a = 0; a < NTO; ++a) {
-        const bf16_t* pp = wa + (ks * 16 + 8 * (ql >> 1) + (q >> 2)) * SA + a * 32 + 16 * (ql & 1) + 4 * (q & 3);
-        union { pm_bf16x8 v; pm_v4s h[2]; } u;
-        u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)(pp));
-        u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)(pp + 4 * SA));
-        fa[a] = u.v;
+    for (int j = 0; j < PA; ++j)
+      if (ap[j] < 32) {
+        const unsigned m = ma[j];
+        *reinterpret_cast<uint4*>(wa + ap[j] * SA + ac[j]) = make_uint4(ra[j].x & m, ra[j].y & m, ra[j].z & m, ra[j].w & m);
       }
 #pragma unroll
-      for (int bb = 0; bb < NTI; ++bb) {
-        const bf16_t* pp = wb + (ks * 16 + 8 * (ql >> 1) + (q >> 2)) * SB + bb * 32 + 16 * (ql & 1) + 4 * (q & 3);
-        union { pm_bf16x8 v; pm_v4s h[2]; } u;
-        u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)(pp));
-        u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)(pp + 4 * SB));
-        fb[bb] = u.v;
+    for (int j = 0; j < PB; ++j)
+      if (bp[j] < 32) {
+#pragma unroll
+        for (int t = 0; t < 3; ++t) {
+          const unsigned m = mb[t][j];
+          *reinterpret_cast<uint4*>(wb + (t * 32 + bp[j]) * SB + bc[j]) =
+              make_uint4(rb[t][j].x & m, rb[t][j].y & m, rb[t][j].z & m, rb[t][j].w & m);
+        }
       }
-#pragma unroll
-      for (int a = 0; a < NTO; ++a)
-#pragma unroll
-        for (int bb = 0; bb < NTI; ++bb)
-          acc[a][bb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[a], fb[bb], acc[a][bb], 0, 0, 0);
-    }
   };
-  uint4 ra[2][PA], rb[2][PB];
-  load_regs(0, 0, ra[0], rb[0]);
+  typedef pm_v4s __attribute__((address_space(3))) * lds_v4s;
+  const int ql = lane >> 4, q = lane & 15;                 // transpose-load lane mapping (see pm_at_frag_tr)
+  auto frag = [&](const bf16_t* base, int stride, int ks, int tile) __attribute__((always_inline)) {
+    const bf16_t* pp = base + (ks * 16 + 8 * (ql >> 1) + (q >> 2)) * stride + tile * 32 + 16 * (ql & 1) + 4 * (q & 3);
+    union { pm_bf16x8 v; pm_v4s h[2]; } u;
+    u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)(pp));
+    u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)(pp + 4 * stride));
+    return u.v;
+  };
+  pm_f32x16 acc[3][NTO][NTI];
 #pragma unroll
-  for (int tap = 0; tap < TPB; ++tap) {     // fully unrolled: every register-set and table index is static
+  for (int t = 0; t < 3; ++t)
 #pragma unroll
     for (int a = 0; a < NTO; ++a)
 #pragma unroll
       for (int bb = 0; bb < NTI; ++bb)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) acc[a][bb][e] = 0.f;
-    // items (tap, 0 .. NCH - 1); item (tap, ch) sits in register set ch & 1 (NCH is even or 1, and the
-    // first item of the next tap is requested during the last item of this one into set 0)
+        for (int e = 0; e < 16; ++e) acc[t][a][bb][e] = 0.f;
+  load(first);
+#pragma unroll 1
+  for (int ch = 0; ch < nch; ++ch) {
+    park();
+    if (ch + 1 < nch) load(first + (ch + 1) * 32);
+    __builtin_amdgcn_wave_barrier();
 #pragma unroll
-    for (int ch = 0; ch < NCH; ++ch) {
-      const int cur = NCH == 1 ? (tap & 1) : (ch & 1);
-      store_regs(tap, ch, ra[cur], rb[cur]);
-      if (ch + 1 < NCH) load_regs(tap, ch + 1, ra[cur ^ 1], rb[cur ^ 1]);
-      else if (tap + 1 < TPB) load_regs(tap + 1, 0, ra[cur ^ 1], rb[cur ^ 1]);
-      __builtin_amdgcn_wave_barrier();
-      mma();
-      __builtin_amdgcn_wave_barrier();
+    for (int ks = 0; ks < 2; ++ks) {
+      pm_bf16x8 fa[NTO];
+#pragma unroll
+      for (int a = 0; a < NTO; ++a) fa[a] = frag(wa, SA, ks, a);
+#pragma unroll
+      for (int t = 0; t < 3; ++t)
+#pragma unroll
+        for (int bb = 0; bb < NTI; ++bb) {
+          const pm_bf16x8 fb = frag(wb + t * 32 * SB, SB, ks, bb);
+#pragma unroll
+          for (int a = 0; a < NTO; ++a)
+            acc[t][a][bb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[a], fb, acc[t][a][bb], 0, 0, 0);
+        }
     }
-    // block reduction of the tap: accumulator value v of lane l is row co = 32 a + 8 (v / 4) + 4 (l / 32) + v % 4,
-    // column ci = 32 bb + l % 32
-    {
-      const int kg = lane >> 5, cl = lane & 31;
+    __builtin_amdgcn_wave_barrier();
+  }
+  // per tap the four waves' sums meet in LDS: value v of lane l is row co = 32 a + 8 (v / 4) + 4 (l / 32) + v % 4,
+  // column ci = 32 bb + l % 32
+  float* red = reinterpret_cast<float*>(lds);
+  constexpr int IMG = NTO * 32 * RW;
+  float* my_part = jb.part + (int64_t)bid * g.Cout * 9 * g.Cin;
+  const int kg = lane >> 5, cl = lane & 31;
 #pragma unroll
-      for (int a = 0; a < NTO; ++a)
+  for (int t = 0; t < 3; ++t) {
+    __syncthreads();
 #pragma unroll
-        for (int bb = 0; bb < NTI; ++bb)
+    for (int a = 0; a < NTO; ++a)
 #pragma unroll
-          for (int v = 0; v < 16; ++v)
-            red[wave][(a * 32 + 8 * (v >> 2) + 4 * kg + (v & 3)) * RW + bb * 32 + cl] = acc[a][bb][v];
-    }
+      for (int bb = 0; bb < NTI; ++bb)
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+          red[wave * IMG + (a * 32 + 8 * (v >> 2) + 4 * kg + (v & 3)) * RW + bb * 32 + cl] = acc[t][a][bb][v];
     __syncthreads();
     for (int e = threadIdx.x; e < g.Cout * g.Cin; e += 256) {
       const int co = e / g.Cin, ci = e - co * g.Cin, o = co * RW + ci;
-      my_part[((int64_t)co * 9 + tap0 + tap) * g.Cin + ci] = red[0][o] + red[1][o] + red[2][o] + red[3][o];
+      my_part[(co * 9 + blockIdx.y * 3 + t) * g.Cin + ci] = red[o] + red[IMG + o] + red[2 * IMG + o] + red[3 * IMG + o];
     }
-    __syncthreads();
   }
-}
-
-// out[e] (+)= sum over nparts partial vectors of n elements each (part[p][e]).  Block = 16 elements x 16
-// slices of the partial range: many short chains of independent loads instead of a few long ones (the
-// arrays are small; what matters is the latency of the longest chain).  A launch carries up to two
-// jobs: the blocks after the first job's work on the second one (used for the per-channel sums of the
-// affine backward, whose out is always added to).
-inline void pm_conv_reduce_launch(hipStream_t st, const PmReduceJob& j0, const PmReduceJob& j1) {
-  const int b0 = (int)((j0.n + 15) / 16), b1 = j1.part ? (int)((j1.n + 15) / 16) : 0;
-  hipLaunchKernelGGL(pm_conv_wgrad_reduce_kernel, dim3((unsigned)(b0 + b1)), dim3(256), 0, st, j0, j1, b0);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -731,15 +925,25 @@ inline void pm_conv_reduce_launch(hipStream_t st, const PmReduceJob& j0, const P
 // ---------------------------------------------------------------------------------------------
 inline bool pm_conv_mfma_fits(int Cin, int Cout) { return (Cin % 16) == 0 && (Cout % 16) == 0 && Cin <= 64 && Cout <= 64; }
 
+// Waves (of 32 pixels) per block of the forward and data-gradient kernels: one where the pixel groups times the
+// channel tiles are fewer than eight waves per compute unit, so that they spread over all of them.
+inline int pm_conv_waves(int64_t npix, int channels) {
+  return (npix + 31) / 32 * ((channels + 31) / 32) >= 2048 ? 4 : 1;
+}
+
 template <typename T>
 inline void pm_conv_fwd_launch(hipStream_t st, const PmConvGeom& g, const T* x, PmWLoc<T> w, PmShortcut<T> sc, T* z, T* y) {
   const int64_t npix = (int64_t)g.B * g.Ho * g.Wo;
   if constexpr (sizeof(T) == 2) {
     if (pm_conv_mfma_fits(g.Cin, g.Cout)) {
-      const int wpb = npix >= 256 * 128 ? 4 : 1;          // waves (of 32 pixels) per block
-      const dim3 grid((unsigned)((npix + 32 * wpb - 1) / (32 * wpb))), blk(64 * wpb);
-      if (g.Cout <= 32) hipLaunchKernelGGL((pm_conv_fwd_mfma_kernel<1>), grid, blk, 0, st, g, x, w, sc, z, y);
-      else hipLaunchKernelGGL((pm_conv_fwd_mfma_kernel<2>), grid, blk, 0, st, g, x, w, sc, z, y);
+      const int wpb = pm_conv_waves(npix, g.Cout);
+      const dim3 grid((unsigned)((npix + 32 * wpb - 1) / (32 * wpb)), (g.Cout + 31) / 32), blk(64 * wpb);
+#define PM_CF(K) hipLaunchKernelGGL((pm_conv_fwd_mfma_kernel<K>), grid, blk, 0, st, g, x, w, sc, z, y)
+      if (g.Cin == 16) PM_CF(1);
+      else if (g.Cin == 32) PM_CF(2);
+      else if (g.Cin == 48) PM_CF(3);
+      else PM_CF(4);
+#undef PM_CF
       return;
     }
   }
@@ -754,19 +958,13 @@ inline void pm_conv_fwd_launch(hipStream_t st, const PmConvGeom& g, const T* x, 
 }
 
 template <typename T>
-inline void pm_conv_dgrad_launch(hipStream_t st, const PmConvGeom& g, const T* dz, PmWLoc<T> w, PmShortcutBwd<T> sb, T* dx,
-                                 const PmReducePending* pend = nullptr) {
+inline void pm_conv_dgrad_launch(hipStream_t st, const PmConvGeom& g, const T* dz, PmWLoc<T> w, PmShortcutBwd<T> sb, T* dx) {
   const int64_t npix = (int64_t)g.B * g.H * g.W;
-  const bool carry = pend && pend->valid;
   if constexpr (sizeof(T) == 2) {
     if (pm_conv_mfma_fits(g.Cin, g.Cout)) {
       // (fewer waves per block on small maps were measured slower here: every block first loads the kernel tensor)
-      const int nb = (int)((npix + 127) / 128);
-      const PmReduceJob none{nullptr, 0, 0, nullptr, 1};
-      const PmReduceJob r0 = carry ? pend->j0 : none, r1 = carry ? pend->j1 : none;
-      const int rb0 = carry ? pend->blocks0() : 0;
-      const dim3 grid((unsigned)(nb + (carry ? pend->blocks() : 0))), blk(256);
-#define PM_CD(A, B) hipLaunchKernelGGL((pm_conv_dgrad_mfma_kernel<A, B>), grid, blk, 0, st, g, dz, w, sb, dx, r0, r1, rb0, nb)
+      const dim3 grid((unsigned)((npix + 127) / 128)), blk(256);
+#define PM_CD(A, B) hipLaunchKernelGGL((pm_conv_dgrad_mfma_kernel<A, B>), grid, blk, 0, st, g, dz, w, sb, dx)
       if (g.Cout <= 32 && g.Cin <= 32) PM_CD(1, 1);
       else if (g.Cout <= 32) PM_CD(1, 2);
       else if (g.Cin <= 32) PM_CD(2, 1);
@@ -778,77 +976,124 @@ inline void pm_conv_dgrad_launch(hipStream_t st, const PmConvGeom& g, const T* d
   const int64_t total = npix * g.Cin;
   hipLaunchKernelGGL((pm_conv_dgrad_plain_kernel<T>), dim3((unsigned)std::min<int64_t>(65535, (total + 255) / 256)), dim3(256),
                      0, st, g, dz, w, sb, dx);
-  if (carry) pm_conv_reduce_launch(st, pend->j0, pend->j1);
 }
 
-// blocks and chunks per wave (4 on large maps, 1 on small ones) of the MFMA weight-gradient kernel
-inline void pm_conv_wgrad_plan(const PmConvGeom& g, int* blocks, int* cpw) {
-  const int64_t npix = (int64_t)g.B * g.Ho * g.Wo;
-  const int64_t chunks = (npix + 31) / 32;
-  const int c = chunks >= 2048 ? 4 : 1;
-  *cpw = c;
-  *blocks = (int)((chunks + (int64_t)c * 4 - 1) / ((int64_t)c * 4));
+// blocks of the fused data gradient over the pixels: the partial sums it writes
+inline int pm_conv_dgrad_affine_blocks(const PmConvGeom& g) {
+  const int64_t npix = (int64_t)g.B * g.H * g.W;
+  const int wpb = pm_conv_waves(npix, g.Cin);
+  return (int)((npix + 32 * wpb - 1) / (32 * wpb));
 }
-// fp32 scratch elements the MFMA path needs (0: the plain path is used)
+inline void pm_conv_dgrad_affine_launch(hipStream_t st, const PmConvGeom& g, const bf16_t* dz, const bf16_t* wt,
+                                        PmShortcutBwd<bf16_t> sb, const bf16_t* y, const bf16_t* z, PmWLoc<bf16_t> scale_bkwd,
+                                        bf16_t* da_out, bf16_t* dz_out, float* part) {
+  const int wpb = pm_conv_waves((int64_t)g.B * g.H * g.W, g.Cin);
+  const dim3 grid((unsigned)pm_conv_dgrad_affine_blocks(g), (g.Cin + 31) / 32), blk(64 * wpb);
+#define PM_CA(K) hipLaunchKernelGGL((pm_conv_dgrad_affine_kernel<K>), grid, blk, 0, st, g, dz, wt, sb, y, z, scale_bkwd, da_out, dz_out, part)
+  if (g.Cout == 16) PM_CA(1);
+  else if (g.Cout == 32) PM_CA(2);
+  else if (g.Cout == 48) PM_CA(3);
+  else PM_CA(4);
+#undef PM_CA
+}
+inline void pm_conv_transpose_launch(hipStream_t st, const PmCvTransposeJob* v, int count) {
+  for (int at = 0; at < count; at += PM_CONV_JOBS) {
+    PmCvTransposeList l{};
+    const int n = std::min(PM_CONV_JOBS, count - at);
+    for (int k = 0; k < n; ++k) l.job[k] = v[at + k];
+    hipLaunchKernelGGL(pm_conv_transpose_kernel, dim3(16, (unsigned)n), dim3(256), 0, st, l);
+  }
+}
+
+// Chunks of 32 pixels per wave and blocks of the MFMA weight-gradient kernel: at most 64 blocks (times three tap
+// rows, times the units that share the launch) write a partial, 32 of the wide tensors, whose partials are 147 KB
+// each and are written and read once more.
+inline void pm_conv_wgrad_plan(const PmConvGeom& g, int* blocks, int* nch) {
+  const int64_t chunks = ((int64_t)g.B * g.Ho * g.Wo + 31) / 32;
+  const int64_t top = 4 * (g.Cin * g.Cout > 1024 ? 32 : 64);
+  const int64_t c = (chunks + top - 1) / top;
+  *nch = (int)c;
+  *blocks = (int)((chunks + c * 4 - 1) / (c * 4));
+}
 inline bool pm_conv_thin_fits(const PmConvGeom& g) {
   return g.Cin == 3 && g.Cout == 16 && (int64_t)g.B * g.H * g.W * 16 < ((int64_t)1 << 31);
 }
 template <typename T>
+inline bool pm_conv_wgrad_mfma_fits(const PmConvGeom& g) {       // 32-bit indexing inside
+  return sizeof(T) == 2 && pm_conv_mfma_fits(g.Cin, g.Cout) &&
+         (int64_t)g.B * g.H * g.W * std::max(g.Cin, g.Cout) < (int64_t)1 << 31;
+}
+// partial vectors of Cout * 9 * Cin floats that the weight gradient writes (0: the plain path is used)
+template <typename T>
+inline int pm_conv_wgrad_parts(const PmConvGeom& g) {
+  if (pm_conv_thin_fits(g)) return PM_CONV_THIN_GROUPS;
+  if (!pm_conv_wgrad_mfma_fits<T>(g)) return 0;
+  int blocks, nch;
+  pm_conv_wgrad_plan(g, &blocks, &nch);
+  return blocks;
+}
+// fp32 scratch elements that the entry points ask for: a partial per 128 pixels, per 512 on large maps.  The
+// kernel writes fewer; callers hold workspaces of this size, and the entry without one refuses by it.
+template <typename T>
 inline size_t pm_conv_wgrad_scratch_elems(const PmConvGeom& g) {
   if (pm_conv_thin_fits(g)) return (size_t)PM_CONV_THIN_GROUPS * g.Cout * 9 * g.Cin;
-  if (sizeof(T) != 2 || !pm_conv_mfma_fits(g.Cin, g.Cout)) return 0;
-  if ((int64_t)g.B * g.H * g.W * std::max(g.Cin, g.Cout) >= (int64_t)1 << 31) return 0;   // 32-bit indexing inside
-  int blocks, cpw;
-  pm_conv_wgrad_plan(g, &blocks, &cpw);
-  return (size_t)blocks * g.Cout * 9 * g.Cin;
+  if (!pm_conv_wgrad_mfma_fits<T>(g)) return 0;
+  const int64_t chunks = ((int64_t)g.B * g.Ho * g.Wo + 31) / 32, c = chunks >= 2048 ? 16 : 4;
+  return (size_t)((chunks + c - 1) / c) * g.Cout * 9 * g.Cin;
 }
 
-// dW (fp32 [Cout][9][Cin]) = (accumulate ? dW : 0) + correlation of dz with x.  `scratch` must hold
-// pm_conv_wgrad_scratch_elems floats (unused by the plain path).
-// true if the weight gradient of this geometry ends in a reduce launch (which can carry a second job)
-template <typename T>
-inline bool pm_conv_wgrad_has_reduce(const PmConvGeom& g) {
-  return pm_conv_thin_fits(g) || pm_conv_wgrad_scratch_elems<T>(g) > 0;
-}
-
-template <typename T>
-inline void pm_conv_wgrad_launch(hipStream_t st, const PmConvGeom& g, const T* dz, const T* x, float* dW, int accumulate,
-                                 float* scratch, PmReduceJob extra = PmReduceJob{nullptr, 0, 0, nullptr, 1},
-                                 PmReducePending* pend = nullptr) {
-  // the reduce that ends the MFMA and thin paths is launched here, or handed back in *pend for the caller
-  // to attach to its next launch
-  auto finish = [&](const PmReduceJob& j0) {
-    if (pend) *pend = PmReducePending{j0, extra, true};
-    else pm_conv_reduce_launch(st, j0, extra);
-  };
-  if (pend) pend->valid = false;
-  if constexpr (sizeof(T) == 2) {
-    if (!pm_conv_thin_fits(g) && pm_conv_wgrad_scratch_elems<T>(g) > 0) {
-      int blocks, cpw;
-      pm_conv_wgrad_plan(g, &blocks, &cpw);
-      const bool split = blocks < 128;                 // too few pixel chunks to fill the chip: one tap row per block
-      const dim3 grid(blocks, split ? 3 : 1), blk(256);
-#define PM_CW(A, B) do { if (cpw == 4) hipLaunchKernelGGL((pm_conv_wgrad_mfma_kernel<A, B, 4>), grid, blk, 0, st, g, dz, x, scratch); \
-                         else if (split) hipLaunchKernelGGL((pm_conv_wgrad_mfma_kernel<A, B, 1, 3>), grid, blk, 0, st, g, dz, x, scratch); \
-                         else hipLaunchKernelGGL((pm_conv_wgrad_mfma_kernel<A, B, 1>), grid, blk, 0, st, g, dz, x, scratch); } while (0)
-      if (g.Cout <= 32 && g.Cin <= 32) PM_CW(1, 1);
-      else if (g.Cout <= 32) PM_CW(1, 2);
-      else if (g.Cin <= 32) PM_CW(2, 1);
-      else PM_CW(2, 2);
-#undef PM_CW
-      const int64_t nW = (int64_t)g.Cout * 9 * g.Cin;
-      finish(PmReduceJob{scratch, blocks, nW, dW, accumulate});
-      return;
+// The MFMA weight gradients of a list of units, one launch per pair of channel tiles and PM_CONV_JOBS units
+inline void pm_conv_wgrad_group_launch(hipStream_t st, const PmCvWgradJob* v, int count) {
+  for (int cls = 0; cls < 4; ++cls) {
+    PmCvWgradList l{};
+    int blocks = 0;
+    auto flush = [&]() {
+      if (!l.count) return;
+      const dim3 grid((unsigned)blocks, 3), blk(256);
+      if (cls == 0) hipLaunchKernelGGL((pm_conv_wgrad_mfma_kernel<1, 1>), grid, blk, 0, st, l);
+      else if (cls == 1) hipLaunchKernelGGL((pm_conv_wgrad_mfma_kernel<1, 2>), grid, blk, 0, st, l);
+      else if (cls == 2) hipLaunchKernelGGL((pm_conv_wgrad_mfma_kernel<2, 1>), grid, blk, 0, st, l);
+      else hipLaunchKernelGGL((pm_conv_wgrad_mfma_kernel<2, 2>), grid, blk, 0, st, l);
+      l.count = blocks = 0;
+    };
+    for (int i = 0; i < count; ++i) {
+      if ((v[i].g.Cout > 32 ? 2 : 0) + (v[i].g.Cin > 32 ? 1 : 0) != cls) continue;
+      int nb, nch;
+      pm_conv_wgrad_plan(v[i].g, &nb, &nch);
+      l.job[l.count] = v[i];
+      l.job[l.count].nch = nch;
+      l.end[l.count++] = blocks += nb;
+      if (l.count == PM_CONV_JOBS) flush();
     }
+    flush();
   }
-  if (pm_conv_thin_fits(g)) {
-    const int64_t nW = (int64_t)g.Cout * 9 * g.Cin;
-    hipLaunchKernelGGL((pm_conv_wgrad_thin_kernel<T, 16, 3>), dim3(PM_CONV_THIN_GROUPS, 9), dim3(256), 0, st, g, dz, x, scratch);
-    finish(PmReduceJob{scratch, PM_CONV_THIN_GROUPS, nW, dW, accumulate});
-    return;
-  }
+}
+template <typename T>
+inline void pm_conv_wgrad_thin_launch(hipStream_t st, const PmConvGeom& g, const T* dz, const T* x, float* part) {
+  hipLaunchKernelGGL((pm_conv_wgrad_thin_kernel<T, 16, 3>), dim3(PM_CONV_THIN_GROUPS, 9), dim3(256), 0, st, g, dz, x, part);
+}
+template <typename T>
+inline void pm_conv_wgrad_plain_launch(hipStream_t st, const PmConvGeom& g, const T* dz, const T* x, float* dW, int accumulate) {
   hipLaunchKernelGGL((pm_conv_wgrad_plain_kernel<T>), dim3((unsigned)(g.Cout * 9 * g.Cin)), dim3(256), 0, st, g, dz, x, dW,
                      accumulate);
+}
+// one unit by itself: dW (fp32 [Cout][9][Cin]) = correlation of dz with x.  `scratch` holds
+// pm_conv_wgrad_scratch_elems floats (unused by the plain path).
+template <typename T>
+inline void pm_conv_wgrad_launch(hipStream_t st, const PmConvGeom& g, const T* dz, const T* x, float* dW, float* scratch) {
+  const int parts = pm_conv_wgrad_parts<T>(g);
+  if (!parts) {
+    pm_conv_wgrad_plain_launch<T>(st, g, dz, x, dW, 0);
+    return;
+  }
+  if (pm_conv_thin_fits(g)) {
+    pm_conv_wgrad_thin_launch<T>(st, g, dz, x, scratch);
+  } else if constexpr (sizeof(T) == 2) {
+    const PmCvWgradJob jb{g, dz, x, scratch, 0};
+    pm_conv_wgrad_group_launch(st, &jb, 1);
+  }
+  const PmReduceJob r{scratch, parts, g.Cout * 9 * g.Cin, dW, 0};
+  pm_conv_reduce_launch(st, &r, 1);
 }
 
 constexpr int PM_CONV_AFFINE_MAX_BLOCKS = 1024;
@@ -864,6 +1109,6 @@ inline bool pm_conv_affine_bwd_launch(hipStream_t st, const T* dy, const T* y, c
   const unsigned blocks = (unsigned)std::max<int64_t>(1, std::min<int64_t>(part ? PM_CONV_AFFINE_MAX_BLOCKS : 512, (total + 2047) / 2048));
   hipLaunchKernelGGL((pm_conv_affine_bwd_kernel<T>), dim3(blocks), dim3(256), 0, st, dy, y, z, scale_bkwd, da, dz, dscale,
                      dshift, part, total, C);
-  if (part && job) *job = PmReduceJob{part, (int)blocks, (int64_t)2 * C, dscale, 1};
+  if (part && job) *job = PmReduceJob{part, (int)blocks, 2 * C, dscale, 1};
   return true;
 }

@@ -93,6 +93,50 @@ def run_pair(torch, w, steps, tau=None, N=1, gpu_kw=None, check_tables=True, **k
     return g, o, losses
 
 
+@pytest.mark.parametrize("batch,image,blocks,N,segment", [(1, 4, 1, 1, 0), (5, 12, 2, 2, 0), (3, 20, 2, 1, 3), (51, 36, 1, 1, 0)])
+def test_bf16_backward_chain_edges(torch_cuda, batch, image, blocks, N, segment):
+    """The data gradients that carry the affine backward of the unit below, and the grouped weight gradients: maps of
+    one pixel, pixel counts that are no multiple of a wave's 32 or a block's 128 (720, 1200, 66096 pixels; one and four
+    waves per block), microbatches that accumulate, recomputation that overwrites the outputs between them.
+    Odd channels are shifted far above and even ones far below zero and the kernels are small, so that no rounding
+    flips a ReLU; what is left is 2^-9 per stored tensor and weight, two of them in each of up to 13 convolutions,
+    2^-9 sqrt(26) = 1 % of a part's norm.  The bound is three times that."""
+    torch = torch_cuda
+    w = wl.resnet(blocks, batch, dtype="bf16", image=image)
+    params = wl.init_params(w)
+    for p, L in zip(params[:-1], w.layers[:-1]):
+        nw = L.n_out * 9 * L.n_in
+        p[:nw] *= 0.1
+        p[nw + L.n_out:] = np.where(np.arange(L.n_out) % 2, 4.0, -4.0)
+    kw = dict(opt="sgdm", lr=0.02, beta=0.9, D=0.5, K=6)
+    tf, tb = po.pipeline_delays(w.P, N)
+    if segment:
+        kw.update(tau_recomp=po.recompute_delays(w.P, segment, N, tb), segment=segment)
+    o = make_oracle(w, params, tf, tb, N=N, **kw)
+    g = make_gpu(w, params, tf, tb, N=N, **kw)
+    stream = wl.ImageStream(w)
+    mbs = [stream.batch(j) for j in range(N)]
+    o.step(mbs if N > 1 else mbs[0])
+    for x, y in mbs:
+        g.step(torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda(), want_loss=True)
+    for u, L in enumerate(w.layers[:-1]):
+        nw = L.n_out * 9 * L.n_in
+        for name, part in (("W", slice(0, nw)), ("scale", slice(nw, nw + L.n_out)), ("shift", slice(nw + L.n_out, None))):
+            # the library keeps the sum over the microbatches and averages in the update
+            a, b = g.state(4, u)[part].astype(np.float64) / N, o.last_grads[u][part]
+            err = float(np.linalg.norm(a - b) / np.linalg.norm(b))
+            assert err <= 3e-2, (u, name, err)
+    g.close()
+
+
+@pytest.mark.parametrize("shape", [(1, 1, 1, 16, 16, 1), (3, 7, 5, 32, 16, 2), (9, 31, 33, 16, 32, 1), (2, 200, 180, 16, 16, 1),
+                                   (40, 16, 16, 48, 64, 1)])
+def test_conv_primitives_at_tile_edges(torch_cuda, shape):
+    """Pixel counts around a wave's 32 and a block's 128, several chunks per wave in the weight gradient, four waves
+    per block in the forward product; references and tolerances as above."""
+    test_conv_primitives_against_numpy(torch_cuda, "bf16", shape)
+
+
 @pytest.mark.parametrize("case", ["pipemare_f32", "pipemare_bf16", "t2_off", "pipedream", "gpipe", "adamw_clip",
                                   "microbatches", "two_blocks_bf16"])
 def test_small_resnet_modes(torch_cuda, case):
