@@ -110,6 +110,8 @@ struct Layout {
     int parts;                 // partials of the weight gradient (0: summed in one kernel)
     size_t wpart, apart, wt;
   };
+  int img_pad;               // bf16 images of fewer than 16 channels are staged with 16, the first kernel tensor likewise
+  size_t r_wpad;
   std::vector<ConvBuf> cv;
   size_t r_x, r_pool, r_logits, r_dlogits, r_dpool;
   size_t t_xf, t_muf, t_rsf, t_nf, t_logits, t_dlogits;      // final LayerNorm and head
@@ -326,12 +328,15 @@ void make_layout(int32_t L, const pm_layer_desc* layers, const int32_t* tau_fwd,
     lay.x_off = 0;
     lay.cv.resize(nconv);
     int H = o->image_size;
-    lay.r_x = take((size_t)M * H * H * lay.units[0].d.n_in * e);
+    const pm_layer_desc& d0 = lay.units[0].d;
+    lay.img_pad = e == 2 && d0.n_in < 16 && pm_conv_wgrad_mfma_fits<bf16_t>(PmConvGeom{M, H, H, 16, d0.n_out, 1, H, H});
+    lay.r_x = take((size_t)M * H * H * (lay.img_pad ? 16 : d0.n_in) * e);
+    lay.r_wpad = lay.img_pad ? take((size_t)d0.n_out * (9 * 16 + 2) * e) : 0;
     for (int u = 0; u < nconv; ++u) {
       Layout::ConvBuf& b = lay.cv[u];
       const pm_layer_desc& dd = lay.units[u].d;
       const int stride = (u > 0 && (u % 2) == 1 && dd.n_out == 2 * dd.n_in) ? 2 : 1;
-      b.g = PmConvGeom{M, H, H, dd.n_in, dd.n_out, stride, (H - 1) / stride + 1, (H - 1) / stride + 1};
+      b.g = PmConvGeom{M, H, H, u == 0 && lay.img_pad ? 16 : dd.n_in, dd.n_out, stride, (H - 1) / stride + 1, (H - 1) / stride + 1};
       H = b.g.Ho;
       const size_t n = (size_t)M * H * H * dd.n_out * e;
       b.z = take(n); b.y = take(n); b.da = take(n); b.dz = take(n); b.dy = take(n);
@@ -348,7 +353,7 @@ void make_layout(int32_t L, const pm_layer_desc* layers, const int32_t* tau_fwd,
       const bool bf = o->dtype == PM_BF16;
       b.fused = bf && u > 0 && pm_conv_mfma_fits(b.g.Cin, b.g.Cout);
       b.parts = bf ? pm_conv_wgrad_parts<bf16_t>(b.g) : pm_conv_wgrad_parts<float>(b.g);
-      b.wpart = take((size_t)b.parts * lay.units[u].nw * 4);
+      b.wpart = take((size_t)b.parts * b.g.Cout * 9 * b.g.Cin * 4);
       b.wt = b.fused ? take((size_t)lay.units[u].nw * e) : 0;
     }
     for (int u = 0; u < nconv; ++u) {
@@ -1150,12 +1155,21 @@ pm_status launch_resnet(pm_ctx* c, const void* x_dev, const void* y_dev, int acc
   prof_mark(c, 0);
   hipLaunchKernelGGL(pm_begin_tokens_kernel, dim3(1), dim3(256), 0, st, c->hdr(), c->ls(), tab, accumulate ? 0 : L,
                      sched_dev(c), par);
-  {
-    const PmConvGeom& g0 = lay.cv[0].g;
+  const PmConvGeom& g0 = lay.cv[0].g;
+  // the first unit's kernel tensor as its convolution reads it, with the images (x) or by itself
+  auto image_stage = [&](const float* x, PmWLoc<T> W) {
+    if constexpr (sizeof(T) == 2) {
+      if (lay.img_pad) {
+        pm_image_stage16_launch(st, x, TT(lay.r_x), B, U(0).d.n_in, g0.H * g0.W, W, TT(lay.r_wpad), g0.Cout);
+        return;
+      }
+    }
+    if (!x) return;
     const int64_t tot = (int64_t)B * g0.H * g0.W * g0.Cin;
     hipLaunchKernelGGL((pm_image_stage_kernel<T>), dim3((unsigned)std::min<int64_t>(2048, (tot + 255) / 256)), dim3(256), 0, st,
-                       (const float*)x_dev, TT(lay.r_x), B, g0.Cin, g0.H, g0.W);
-  }
+                       x, TT(lay.r_x), B, g0.Cin, g0.H, g0.W);
+  };
+  image_stage((const float*)x_dev, Wf(0, 0));
   // ---- forward
   auto input_of = [&](int u) { return u == 0 ? TT(lay.r_x) : TT(lay.cv[u - 1].y); };
   auto conv_fwd = [&](int u, PmWLoc<T> W) {
@@ -1166,6 +1180,7 @@ pm_status launch_resnet(pm_ctx* c, const void* x_dev, const void* y_dev, int acc
       sc = PmShortcut<T>{input_of(u - 1), g1.H, g1.W, g1.Cin, g1.stride};
     }
     ProfSpan span(c, PM_CLS_GEMM);
+    if (u == 0 && lay.img_pad) W = PmWLoc<T>{TT(lay.r_wpad), nullptr, 0};
     pm_conv_fwd_launch<T>(st, b.g, input_of(u), W, sc, TT(b.z), TT(b.y));
   };
   for (int u = 0; u < nconv; ++u) conv_fwd(u, Wf(u, 0));
@@ -1216,6 +1231,7 @@ pm_status launch_resnet(pm_ctx* c, const void* x_dev, const void* y_dev, int acc
     int lo = u;
     while (lo > 0 && seg_of(lo - 1) == seg_of(u)) --lo;
     flush();                                // the weight gradient of unit u + 1 reads the kept output of unit u
+    if (lo == 0) image_stage(nullptr, Wr(0, 0));
     for (int v = lo; v <= u; ++v)
       if (v < nconv) conv_fwd(v, Wr(v, 0));
     if (u == fc && lo <= nconv - 1) pm_pool_fwd_launch<T>(st, TT(lay.cv[nconv - 1].y), TT(lay.r_pool), B, HW, C);
@@ -1247,13 +1263,19 @@ pm_status launch_resnet(pm_ctx* c, const void* x_dev, const void* y_dev, int acc
       if (sums.part) rjobs.push_back(sums);
     }
     have_dz = false;
-    ProfSpan span(c, PM_CLS_GEMM);      // weight gradient (where it does not wait) and data gradient of this convolution
+    // weight gradient, where it does not wait
     if (!b.parts) {
+      ProfSpan span(c, PM_CLS_GEMM);
       pm_conv_wgrad_plain_launch<T>(st, b.g, TT(b.dz), input_of(u), g + U(u).off, accumulate);
     } else {
-      rjobs.push_back(PmReduceJob{c->at<float>(b.wpart), b.parts, (int)nw, g + U(u).off, accumulate});
-      if (pm_conv_thin_fits(b.g)) pm_conv_wgrad_thin_launch<T>(st, b.g, TT(b.dz), input_of(u), c->at<float>(b.wpart));
-      else if constexpr (sizeof(T) == 2) wjobs.push_back(PmCvWgradJob{b.g, TT(b.dz), input_of(u), c->at<float>(b.wpart), 0});
+      const bool pad = u == 0 && lay.img_pad;
+      rjobs.push_back(PmReduceJob{c->at<float>(b.wpart), b.parts, (int)nw, g + U(u).off, accumulate, pad ? U(u).d.n_in : 0, pad ? 16 : 0});
+      if (pm_conv_thin_fits(b.g)) {
+        ProfSpan span(c, PM_CLS_GEMM);
+        pm_conv_wgrad_thin_launch<T>(st, b.g, TT(b.dz), input_of(u), c->at<float>(b.wpart));
+      } else if constexpr (sizeof(T) == 2) {
+        wjobs.push_back(PmCvWgradJob{b.g, TT(b.dz), input_of(u), c->at<float>(b.wpart), 0});
+      }
     }
     if (u == 0) break;
     PmShortcutBwd<T> sb{nullptr, 0, 0, 0, 1};
@@ -1266,6 +1288,7 @@ pm_status launch_resnet(pm_ctx* c, const void* x_dev, const void* y_dev, int acc
         const Layout::ConvBuf& d = lay.cv[u - 1];
         enter(u - 1);                                 // y and z of the unit below, rebuilt where they are to be
         const int64_t nwd = U(u - 1).nw;
+        ProfSpan span(c, PM_CLS_GEMM);
         // shortcuts read da of second convolutions only
         pm_conv_dgrad_affine_launch(st, b.g, TT(b.dz), TT(b.wt), sb, TT(d.y), TT(d.z), Wb(u - 1, nwd),
                                     u >= 3 && ((u - 1) % 2) == 0 ? TT(d.da) : nullptr, TT(d.dz), c->at<float>(d.apart));
@@ -1275,6 +1298,7 @@ pm_status launch_resnet(pm_ctx* c, const void* x_dev, const void* y_dev, int acc
         continue;
       }
     }
+    ProfSpan span(c, PM_CLS_GEMM);
     pm_conv_dgrad_launch<T>(st, b.g, TT(b.dz), Wb(u, 0), sb, TT(lay.cv[u - 1].dy));
   }
   flush();

@@ -70,6 +70,40 @@ __global__ __launch_bounds__(256) void pm_image_stage_kernel(const float* __rest
   }
 }
 
+// The same for bf16 images of fewer than 16 channels whose convolution takes the matrix path: pixels of 16 channels,
+// the missing ones zero.  The blocks from pix_blocks on pad the convolution's kernel tensor likewise
+// ([co][tap][C] -> [co][tap][16]) and copy its scale and shift behind it.
+__global__ __launch_bounds__(256) void pm_image_stage16_kernel(const float* __restrict__ x, bf16_t* __restrict__ out, int B, int C,
+                                                               int HW, int pix_blocks, PmWLoc<bf16_t> wloc,
+                                                               bf16_t* __restrict__ wpad, int Cout) {
+  if ((int)blockIdx.x >= pix_blocks) {
+    const bf16_t* w = wloc.get();
+    const int n = Cout * 9 * 16, first = ((int)blockIdx.x - pix_blocks) * 256 + threadIdx.x, step = ((int)gridDim.x - pix_blocks) * 256;
+    for (int i = first; i < n + 2 * Cout; i += step) {
+      const int c = i & 15;
+      wpad[i] = i >= n ? w[Cout * 9 * C + i - n] : c < C ? w[(i >> 4) * C + c] : (bf16_t)0;
+    }
+    return;
+  }
+  const int64_t total = (int64_t)B * HW;
+  for (int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x; p < total; p += (int64_t)pix_blocks * 256) {
+    const int64_t b = p / HW, at = p - b * HW;
+    float v[16];
+#pragma unroll
+    for (int c = 0; c < 16; ++c) v[c] = c < C ? x[(b * C + c) * HW + at] : 0.f;
+    pm_st8(out + p * 16, v);
+    pm_st8(out + p * 16 + 8, v + 8);
+  }
+}
+constexpr int PM_IMAGE_PAD_BLOCKS = 4;
+// x == nullptr: the kernel tensor only
+inline void pm_image_stage16_launch(hipStream_t st, const float* x, bf16_t* out, int B, int C, int HW, PmWLoc<bf16_t> w, bf16_t* wpad,
+                                    int Cout) {
+  const int pb = x ? (int)std::min<int64_t>(2048, ((int64_t)B * HW + 255) / 256) : 0;
+  hipLaunchKernelGGL(pm_image_stage16_kernel, dim3((unsigned)(pb + PM_IMAGE_PAD_BLOCKS)), dim3(256), 0, st, x, out, B, C, HW, pb, w,
+                     wpad, Cout);
+}
+
 template <typename T>
 __global__ __launch_bounds__(256) void pm_conv_fwd_plain_kernel(PmConvGeom g, const T* __restrict__ x, PmWLoc<T> wloc,
                                                                 PmShortcut<T> sc, T* __restrict__ z, T* __restrict__ y) {
@@ -99,7 +133,7 @@ __global__ __launch_bounds__(256) void pm_conv_fwd_plain_kernel(PmConvGeom g, co
   }
 }
 
-// Forward of the image layer (3 input channels, 16 output channels): one thread per output pixel
+// Forward of the image layer (3 input channels, 16 output channels; fp32, and bf16 at the stand-alone entry): one thread per output pixel
 // computes all 16 channels from the 27 inputs of its window, with the kernel tensor, scale and shift
 // held in LDS as fp32 (every lane reads the same entry: a broadcast); outputs go out as 16-byte pieces.
 // The one-thread-per-output-element kernel above spends 61 us on the 128 x 32 x 32 images of the
@@ -372,6 +406,7 @@ struct PmReduceJob {
   int nparts, n;
   float* out;
   int accumulate;
+  int cin, cpad;     // rows of cin elements lie cpad apart in the partials (0: they lie as in the output)
 };
 constexpr int PM_CONV_JOBS = 24;       // jobs of one launch (they travel as kernel arguments)
 struct PmReduceList {
@@ -389,8 +424,12 @@ __global__ __launch_bounds__(256) void pm_conv_reduce_kernel(PmReduceList list) 
   const int e0 = ((int)blockIdx.x - (k ? list.end[k - 1] : 0)) * 64;
   float acc[4] = {0.f, 0.f, 0.f, 0.f};
   int off[4];
+  const int ns = jb.cpad ? jb.n / jb.cin * jb.cpad : jb.n;
 #pragma unroll
-  for (int q = 0; q < 4; ++q) off[q] = min(e0 + 16 * q + el, jb.n - 1);
+  for (int q = 0; q < 4; ++q) {
+    off[q] = min(e0 + 16 * q + el, jb.n - 1);
+    if (jb.cpad) off[q] = off[q] / jb.cin * jb.cpad + off[q] % jb.cin;
+  }
   int p = sl;
   auto rows = [&](auto count) __attribute__((always_inline)) {
     constexpr int R = decltype(count)::value;
@@ -398,7 +437,7 @@ __global__ __launch_bounds__(256) void pm_conv_reduce_kernel(PmReduceList list) 
 #pragma unroll
     for (int r = 0; r < R; ++r)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) v[r][q] = jb.part[(int64_t)(p + 16 * r) * jb.n + off[q]];
+      for (int q = 0; q < 4; ++q) v[r][q] = jb.part[(int64_t)(p + 16 * r) * ns + off[q]];
 #pragma unroll
     for (int r = 0; r < R; ++r)
 #pragma unroll
@@ -616,9 +655,9 @@ __device__ __forceinline__ void pm_cv_exchange(float (&v)[32], int pl) {
 //   sums over the block's pixels of da z and of da -> part[block][0 = scale | 1 = shift][Cin].
 // Same scheme as the forward kernel, on the transposed kernel tensor.  One launch and no dy in memory in place of
 // the data gradient (11.6 us on 128 x 32 x 32 x 16 channels, 18.7 on 128 x 8 x 8 x 64: it parked the whole kernel
-// tensor in LDS first) and a pass over dy, y and z (7 us): 10.2 and 9.5 us.
+// tensor in LDS first) and a pass over dy, y and z (7 us): 10.0 and 9.4 us.
 template <int KC>    // Cout = 16 KC
-__global__ __launch_bounds__(256) void pm_conv_dgrad_affine_kernel(PmConvGeom g, const bf16_t* __restrict__ dz,
+__global__ __launch_bounds__(256, KC == 1 ? 4 : 1) void pm_conv_dgrad_affine_kernel(PmConvGeom g, const bf16_t* __restrict__ dz,
                                                                    const bf16_t* __restrict__ wt, PmShortcutBwd<bf16_t> sb,
                                                                    const bf16_t* __restrict__ y, const bf16_t* __restrict__ z,
                                                                    PmWLoc<bf16_t> scale_bkwd, bf16_t* __restrict__ da_out,
@@ -762,7 +801,7 @@ __global__ __launch_bounds__(256) void pm_conv_dgrad_mfma_kernel(PmConvGeom g, c
 // writes its partial of the three taps; pm_conv_reduce_kernel adds the blocks' partials.
 // Taking one tap of a chunk at a time left every load - park - multiply round trip exposed (36 of them in a row),
 // in a launch per unit that filled the chip once: 16 - 20 us per unit, 313 us for the 18 units of ResNet-20 on
-// 128 images; now 98 us.
+// 128 images; now 93 us with the image layer.
 struct PmCvWgradJob {
   PmConvGeom g;
   const bf16_t* dz;
@@ -775,12 +814,15 @@ struct PmCvWgradList {
   int end[PM_CONV_JOBS];               // first blockIdx.x behind each job
   int count;
 };
-template <int NTO, int NTI>   // channel tiles of 32 of Cout and Cin
+// PA, PB: 16-byte pieces per lane of 32 pixels of Cout and Cin channels: 1 (both 16), 2 (up to 32), 4 (up to 64).
+// With 16 channels a transposed read of 32 columns runs into the next row; those rows of the product are not
+// stored.  That takes 24 KB of LDS a block instead of 40, and half the loads.
+template <int PA, int PB>
 __global__ __launch_bounds__(256) void pm_conv_wgrad_mfma_kernel(PmCvWgradList list) {
-  constexpr int SA = NTO * 32 + 8, SB = NTI * 32 + 8;     // LDS row strides (elements)
-  constexpr int PA = NTO * 2, PB = NTI * 2;               // 16-byte pieces per lane of a 32-pixel tile
+  constexpr int NTO = (PA + 1) / 2, NTI = (PB + 1) / 2;   // channel tiles of 32
+  constexpr int SA = PA * 16 + 8, SB = PB * 16 + 8;       // LDS row strides (elements)
   constexpr int RW = NTI * 32;                            // row width of the block's reduction tile
-  constexpr int WAVE = 32 * SA + 3 * 32 * SB;             // elements of a wave's region
+  constexpr int WAVE = 32 * SA + 3 * 32 * SB + (PB == 1 ? 16 : 0);   // elements of a wave's region, with what a read of the last row runs into
   constexpr size_t BYTES = sizeof(bf16_t) * 4 * WAVE > sizeof(float) * 4 * NTO * 32 * RW ? sizeof(bf16_t) * 4 * WAVE
                                                                                          : sizeof(float) * 4 * NTO * 32 * RW;
   __shared__ __attribute__((aligned(16))) unsigned char lds[BYTES];
@@ -1044,20 +1086,22 @@ inline size_t pm_conv_wgrad_scratch_elems(const PmConvGeom& g) {
 
 // The MFMA weight gradients of a list of units, one launch per pair of channel tiles and PM_CONV_JOBS units
 inline void pm_conv_wgrad_group_launch(hipStream_t st, const PmCvWgradJob* v, int count) {
-  for (int cls = 0; cls < 4; ++cls) {
+  for (int cls = 0; cls < 5; ++cls) {
     PmCvWgradList l{};
     int blocks = 0;
     auto flush = [&]() {
       if (!l.count) return;
       const dim3 grid((unsigned)blocks, 3), blk(256);
-      if (cls == 0) hipLaunchKernelGGL((pm_conv_wgrad_mfma_kernel<1, 1>), grid, blk, 0, st, l);
-      else if (cls == 1) hipLaunchKernelGGL((pm_conv_wgrad_mfma_kernel<1, 2>), grid, blk, 0, st, l);
-      else if (cls == 2) hipLaunchKernelGGL((pm_conv_wgrad_mfma_kernel<2, 1>), grid, blk, 0, st, l);
-      else hipLaunchKernelGGL((pm_conv_wgrad_mfma_kernel<2, 2>), grid, blk, 0, st, l);
+      if (cls == 0) hipLaunchKernelGGL((pm_conv_wgrad_mfma_kernel<2, 2>), grid, blk, 0, st, l);
+      else if (cls == 1) hipLaunchKernelGGL((pm_conv_wgrad_mfma_kernel<2, 4>), grid, blk, 0, st, l);
+      else if (cls == 2) hipLaunchKernelGGL((pm_conv_wgrad_mfma_kernel<4, 2>), grid, blk, 0, st, l);
+      else if (cls == 3) hipLaunchKernelGGL((pm_conv_wgrad_mfma_kernel<4, 4>), grid, blk, 0, st, l);
+      else hipLaunchKernelGGL((pm_conv_wgrad_mfma_kernel<1, 1>), grid, blk, 0, st, l);
       l.count = blocks = 0;
     };
     for (int i = 0; i < count; ++i) {
-      if ((v[i].g.Cout > 32 ? 2 : 0) + (v[i].g.Cin > 32 ? 1 : 0) != cls) continue;
+      const bool thin = v[i].g.Cin == 16 && v[i].g.Cout == 16;
+      if ((thin ? 4 : (v[i].g.Cout > 32 ? 2 : 0) + (v[i].g.Cin > 32 ? 1 : 0)) != cls) continue;
       int nb, nch;
       pm_conv_wgrad_plan(v[i].g, &nb, &nch);
       l.job[l.count] = v[i];
