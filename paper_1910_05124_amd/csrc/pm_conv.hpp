@@ -14,12 +14,12 @@
 // accumulator group: the gathered operand (8 consecutive channels of one input pixel of one tap) is
 // a single 16-byte global load, and results leave as 8-byte pieces of NHWC rows.
 //   forward   out^T [co][pixel]    = sum_{tap, ci} W[co][tap][ci] x[pixel + tap][ci]
-//   data      dx^T  [ci][in pixel] = sum_{tap, co} W[co][tap][ci] dz[pixel - tap][co]   (W^T via LDS transpose loads)
+//   data      dx^T  [ci][in pixel] = sum_{tap, co} W[co][tap][ci] dz[pixel - tap][co]   (W transposed once per step)
 //   weight    dW    [co][tap, ci]  = sum_{pixel}   dz[pixel][co] x[pixel + tap][ci]     (both operands via LDS transpose loads)
-// These layers are bound by launch latency and HBM traffic, not by MFMA rate (channel counts of
-// 16 .. 64 give 70 - 300 flop per byte of activation traffic), so the kernels favour simplicity:
-// no block-level barriers in the hot loops.  fp32 contexts and odd channel counts (the 3-channel
-// input convolution) use the plain kernels below.
+// These layers are bound by the latency of their loads and launches, not by the MFMA rate (channel counts of
+// 16 .. 64 give 70 - 300 flop per byte of activation traffic): what counts is that a wave's loads are in flight
+// together and that a step has few launches in a row.  fp32 contexts and channel counts beyond 64 or no multiple
+// of 16 use the plain kernels below.
 #pragma once
 #include <type_traits>
 #include "pm_common.hpp"
