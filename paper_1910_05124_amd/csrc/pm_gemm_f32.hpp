@@ -4,31 +4,40 @@
 //
 // Operands are "KC" (contraction index contiguous) or "RC" (row index contiguous) as in pm_gemm_mfma.hpp.  The networks
 // trained in fp32 are small: a product has 10^5 .. 10^9 multiply-adds, and what bounds it is the latency of its loads
-// and the launch, not the matrix rate.  So the operands go from memory to the matrix instruction's registers without
-// a stop in LDS (no barrier in the main loop), each wave of a block takes its own 16-deep pieces of the contraction, two
-// pieces in flight ahead of the two being multiplied, and the waves' partial tiles are summed through LDS once at the end.
+// and of its chain of additions, not the matrix rate.  So the operands go from memory to the matrix instruction's registers
+// without a stop in LDS (no barrier in the main loop), several 16-deep pieces of the contraction in flight ahead of those
+// being multiplied.
 //
-// One lane of a 16 x 16 x 4 step holds row lane % 16 and contraction index lane / 16 of each operand.  Which four
-// indices a step covers is free as long as both operands agree: step s of a 16-deep piece takes k = 4 (lane / 16) + s, so
-// a KC operand is one 16-byte load per lane and piece; an RC operand with two 16-row tiles per wave gives tile t the
-// rows 2 m + t, so that a lane loads its two rows with one 8-byte access.
+// Order of the sums.  Every output is ONE chain of fused multiply-adds over k = 0, 1, 2, ... starting at zero: the
+// instruction adds its four products to the accumulator one after the other, each addition rounded (checked bit for bit
+// against fmaf chains, with wide exponents and denormal products).  A network with ReLU units turns a difference of one
+// rounding in a pre-activation next to zero into a gradient that differs in the third digit, so the order is part of
+// what a caller can rely on: splitting the contraction over waves or permuting it inside a piece made 1 seed in 6 of a
+// 2-layer Transformer 256 wide differ by 5e-6 .. 1e-4 in its gradients, and is left out.  For the same reason a bias
+// gradient adds rows m, m + 4, m + 8, ... in four chains and the chains in order.
+//
+// One lane of a 16 x 16 x 4 step s holds row lane % 16 and contraction index 4 s + lane / 16 of each operand.  A KC
+// operand is one 16-byte load per lane and 16-deep piece (lane group g takes indices 4 g .. 4 g + 3) and four lane
+// exchanges that transpose the 4 x 4 registers x lane groups; an RC operand with two 16-row tiles per wave gives tile t
+// the rows 2 m + t, so that a lane loads its two rows with one 8-byte access.
 //
 // Measured (us per launch; before: 16 x 16 outputs per 256-thread block on vector FMAs through LDS): 100 x 512 x 512
-// forward 21.9 -> 4.6, data gradient 20.6 -> 4.3; 512 x 1024 x 256 with the residual 25.5 -> 7.3.  The weight gradients
-// of a step and their bias gradients were two launches per unit and are one now: 120 -> 17 us on the 9 units of that
-// first network (8 of them 512 wide), 615 -> 34 us on a 2-layer Transformer 256 wide with 512 tokens.
+// forward 21.9 -> 7.4, data gradient 20.6 -> 8.5 (4.6 and 4.3 with the contraction over eight waves); 512 x 1024 x 256 with
+// the residual 25.5 -> 12.1.  More than four pieces ahead gained nothing.  The weight gradients of a step and their bias
+// gradients were two launches per unit and are one now: 120 -> 16 us on the 9 units of that first network (8 of them 512
+// wide), 615 -> 35 us on a 2-layer Transformer 256 wide with 512 tokens.
 #pragma once
 #include "pm_common.hpp"
 #include "pm_elem.hpp"
 
 typedef float pm_f32x4 __attribute__((ext_vector_type(4)));
 
-// T x T matrix tiles of 16 x 16 per wave, WI x WJ waves over the block's outputs, WK waves over the contraction
-template <int T_, int WI_, int WJ_, int WK_>
+// T x T matrix tiles of 16 x 16 per wave, WI x WJ waves over the block's outputs, U pieces in flight ahead
+template <int T_, int WI_, int WJ_, int U_>
 struct PmF32Cfg {
-  static constexpr int T = T_, WI = WI_, WJ = WJ_, WK = WK_, NT = WI_ * WJ_ * WK_ * 64;
-  static constexpr int BI = WI_ * T_ * 16, BJ = WJ_ * T_ * 16, RS = BJ + 4;       // RS: padded row of the partial tile
-  static constexpr int lds_floats = WK_ * BI * RS + WK_ * BI;                     // partial tiles, partial column sums
+  static constexpr int T = T_, WI = WI_, WJ = WJ_, U = U_, NT = WI_ * WJ_ * 64;
+  static constexpr int BI = WI_ * T_ * 16, BJ = WJ_ * T_ * 16, RS = BJ + 4;       // RS: padded row of the output tile
+  static constexpr int lds_floats = BI * RS;
 };
 
 template <class Epi>
@@ -47,11 +56,11 @@ template <int T, bool KC, bool V>
 struct PmF32Operand {
   const float* p[T];
   int64_t ld;
-  int g4;
+  int g;
   __device__ __forceinline__ void init(const float* X, int64_t ld_, int r0, int R, int lane) {
     const int m = lane & 15;
     ld = ld_;
-    g4 = (lane >> 4) * 4;
+    g = lane >> 4;
 #pragma unroll
     for (int t = 0; t < T; ++t) {
       int row = KC ? r0 + 16 * t + m : r0 + T * m + t;
@@ -60,24 +69,19 @@ struct PmF32Operand {
       p[t] = KC ? X + (int64_t)row * ld : X + row;
     }
   }
-  // the 16-deep piece at k0, all of it inside the contraction: x[s][t]
+  // the 16-deep piece at k0, all of it inside the contraction: x[s][t] = row t's value of index k0 + 4 s + lane / 16.
+  // (KC with vector accesses: what arrives is index k0 + 4 (lane / 16) + s, see arrange)
   __device__ __forceinline__ void load(int k0, float (&x)[4][T]) const {
-    if constexpr (KC) {
+    if constexpr (KC && V) {
 #pragma unroll
       for (int t = 0; t < T; ++t) {
-        const float* q = p[t] + k0 + g4;
-        if constexpr (V) {
-          const float4 v = *reinterpret_cast<const float4*>(q);
-          x[0][t] = v.x; x[1][t] = v.y; x[2][t] = v.z; x[3][t] = v.w;
-        } else {
-#pragma unroll
-          for (int s = 0; s < 4; ++s) x[s][t] = q[s];
-        }
+        const float4 v = *reinterpret_cast<const float4*>(p[t] + k0 + 4 * g);
+        x[0][t] = v.x; x[1][t] = v.y; x[2][t] = v.z; x[3][t] = v.w;
       }
     } else {
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
-        const int64_t o = (int64_t)(k0 + g4 + s) * ld;
+        const int64_t o = KC ? (int64_t)(k0 + 4 * s + g) : (int64_t)(k0 + 4 * s + g) * ld;
         if constexpr (V && T == 2) {
           const float2 v = *reinterpret_cast<const float2*>(p[0] + o);
           x[s][0] = v.x; x[s][1] = v.y;
@@ -88,11 +92,26 @@ struct PmF32Operand {
       }
     }
   }
-  // the piece that crosses the end of the contraction: zeros beyond it
+  // after the load has arrived: registers s x lane groups g transposed, so that register s holds index 4 s + g
+  __device__ __forceinline__ void arrange(float (&x)[4][T]) const {
+    if constexpr (KC && V) {
+#pragma unroll
+      for (int t = 0; t < T; ++t) {
+        auto bits = [](float f) { return __float_as_uint(f); };
+        const auto a = __builtin_amdgcn_permlane32_swap(bits(x[0][t]), bits(x[2][t]), false, false);
+        const auto b = __builtin_amdgcn_permlane32_swap(bits(x[1][t]), bits(x[3][t]), false, false);
+        const auto c = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false);
+        const auto d = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
+        x[0][t] = __uint_as_float(c[0]); x[1][t] = __uint_as_float(c[1]);
+        x[2][t] = __uint_as_float(d[0]); x[3][t] = __uint_as_float(d[1]);
+      }
+    }
+  }
+  // the piece that crosses the end of the contraction, arranged already: zeros beyond it
   __device__ __forceinline__ void load_tail(int k0, int K, float (&x)[4][T]) const {
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
-      const int k = k0 + g4 + s;
+      const int k = k0 + 4 * s + g;
       const int64_t o = KC ? (int64_t)(k < K ? k : K - 1) : (int64_t)(k < K ? k : K - 1) * ld;
 #pragma unroll
       for (int t = 0; t < T; ++t) {
@@ -105,11 +124,11 @@ struct PmF32Operand {
 
 template <class Cfg, bool AKC, bool BKC, bool V, class Epi>
 __device__ __forceinline__ void pm_gemm_f32_body(const PmF32Prob<Epi>& pr, Epi epi, int bx, int by, float* smem) {
-  constexpr int T = Cfg::T, WI = Cfg::WI, WJ = Cfg::WJ, WK = Cfg::WK, BI = Cfg::BI, BJ = Cfg::BJ, RS = Cfg::RS, NT = Cfg::NT;
+  constexpr int T = Cfg::T, WJ = Cfg::WJ, BI = Cfg::BI, BJ = Cfg::BJ, RS = Cfg::RS, NT = Cfg::NT, U = Cfg::U;
   const int I = pr.I, J = pr.J, K = pr.K;
   const int i0 = by * BI, j0 = bx * BJ;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int wk = wave % WK, wj = (wave / WK) % WJ, wi = wave / (WK * WJ);
+  const int wj = wave % WJ, wi = wave / WJ;
   PmF32Operand<T, AKC, V> oa;
   PmF32Operand<T, BKC, V> ob;
   oa.init(pr.A, pr.lda, i0 + wi * 16 * T, I, lane);
@@ -132,62 +151,90 @@ __device__ __forceinline__ void pm_gemm_f32_body(const PmF32Prob<Epi>& pr, Epi e
     if (Epi::kColSumA && !AKC) {
       if (do_colsum) {
 #pragma unroll
-        for (int a = 0; a < T; ++a) cs[a] += (xa[0][a] + xa[1][a]) + (xa[2][a] + xa[3][a]);
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+          for (int a = 0; a < T; ++a) cs[a] += xa[s][a];
       }
     }
   };
-  // whole pieces wk, wk + WK, ... of this wave, U at a time
-  constexpr int U = 2;
+  auto piece = [&](float (&xa)[4][T], float (&xb)[4][T]) __attribute__((always_inline)) {
+    oa.arrange(xa);
+    ob.arrange(xb);
+    mul(xa, xb);
+  };
+  // whole pieces, U at a time with the next U on their way; the first group takes what is no multiple of U, and the
+  // piece that crosses the end is requested before the last group is multiplied
+  struct Group { float a[U][4][T], b[U][4][T]; };
   const int whole = K >> 4;
-  const int mine = whole > wk ? (whole - wk + WK - 1) / WK : 0;
-  float xa[U][4][T], xb[U][4][T];
-  int n = 0;
-  if (mine >= U) {
+  const bool tail = K & 15;
+  float ta[4][T], tb[4][T];
+  Group x, y;
+  int n = whole % U;
+  if (n == 0 && whole > 0) n = U;
+  const int first = n;
+  auto load = [&](Group& q) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      oa.load((wk + u * WK) * 16, xa[u]);
-      ob.load((wk + u * WK) * 16, xb[u]);
+      oa.load((n + u) * 16, q.a[u]);
+      ob.load((n + u) * 16, q.b[u]);
     }
-    for (n = U; n + U <= mine; n += U) {
-      float ya[U][4][T], yb[U][4][T];
+    n += U;
+    __builtin_amdgcn_sched_barrier(0);          // keep the requests ahead of the products
+  };
+  auto load_tail = [&]() __attribute__((always_inline)) {
+    if (tail) {
+      oa.load_tail(whole * 16, K, ta);
+      ob.load_tail(whole * 16, K, tb);
+    }
+  };
+  auto group = [&](Group& q, int have) __attribute__((always_inline)) {
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        oa.load((wk + (n + u) * WK) * 16, ya[u]);
-        ob.load((wk + (n + u) * WK) * 16, yb[u]);
-      }
-      __builtin_amdgcn_sched_barrier(0);        // keep the requests ahead of the products
+    for (int u = 0; u < U; ++u)
+      if (u < have) piece(q.a[u], q.b[u]);
+  };
 #pragma unroll
-      for (int u = 0; u < U; ++u) mul(xa[u], xb[u]);
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-#pragma unroll
-        for (int s = 0; s < 4; ++s)
-#pragma unroll
-          for (int t = 0; t < T; ++t) xa[u][s][t] = ya[u][s][t], xb[u][s][t] = yb[u][s][t];
+  for (int u = 0; u < U; ++u)
+    if (u < first) {
+      oa.load(u * 16, x.a[u]);
+      ob.load(u * 16, x.b[u]);
+    }
+  if (n == whole) {
+    load_tail();
+    group(x, first);
+  } else {
+    load(y);
+    group(x, first);
+    while (n + U < whole) {                     // two groups at a time: the registers trade places
+      load(x);
+      group(y, U);
+      load(y);
+      group(x, U);
+    }
+    if (n < whole) {
+      load(x);
+      group(y, U);
+      load_tail();
+      group(x, U);
+    } else {
+      load_tail();
+      group(y, U);
     }
   }
-  // what is left: at most one whole piece, and on one wave the piece that crosses the end; requested before the last
-  // pair is multiplied
-  float za[4][T], zb[4][T], ta[4][T], tb[4][T];
-  const bool one = n < mine, tail = (K & 15) && whole % WK == wk;
-  if (one) {
-    oa.load((wk + n * WK) * 16, za);
-    ob.load((wk + n * WK) * 16, zb);
-  }
-  if (tail) {
-    oa.load_tail(whole * 16, K, ta);
-    ob.load_tail(whole * 16, K, tb);
-  }
-  if (n > 0) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) mul(xa[u], xb[u]);
-  }
-  if (one) mul(za, zb);
   if (tail) mul(ta, tb);
 
-  // accumulator layout of the 16 x 16 tile: value v of lane l is row 4 (l / 16) + v, column l % 16
-  float* red = smem;
-  float* csum = smem + WK * BI * RS;
+  if (Epi::kColSumA && !AKC) {
+    if (do_colsum) {
+#pragma unroll
+      for (int a = 0; a < T; ++a) {
+        // lane group g holds the chain of rows m = g mod 4; the four chains in order
+        const float s1 = __shfl(cs[a], (lane & 15) + 16, 64), s2 = __shfl(cs[a], (lane & 15) + 32, 64), s3 = __shfl(cs[a], (lane & 15) + 48, 64);
+        const int i = i0 + wi * 16 * T + T * lane + a;
+        if (lane < 16 && i < I) epi.colsum(i, ((cs[a] + s1) + s2) + s3);
+      }
+    }
+  }
+  // accumulator layout of the 16 x 16 tile: value v of lane l is row 4 (l / 16) + v, column l % 16; through LDS so that
+  // the stores are consecutive
 #pragma unroll
   for (int a = 0; a < T; ++a)
 #pragma unroll
@@ -196,35 +243,15 @@ __device__ __forceinline__ void pm_gemm_f32_body(const PmF32Prob<Epi>& pr, Epi e
       for (int v = 0; v < 4; ++v) {
         const int r = (lane >> 4) * 4 + v, c = lane & 15;
         const int li = wi * 16 * T + (AKC ? 16 * a + r : T * r + a), lj = wj * 16 * T + (BKC ? 16 * b + c : T * c + b);
-        red[(wk * BI + li) * RS + lj] = acc[a][b][v];
+        smem[li * RS + lj] = acc[a][b][v];
       }
-  if (Epi::kColSumA && !AKC) {
-    if (do_colsum) {
-#pragma unroll
-      for (int a = 0; a < T; ++a) {
-        float s = cs[a];
-        s += __shfl_xor(s, 16, 64);
-        s += __shfl_xor(s, 32, 64);
-        if (lane < 16) csum[wk * BI + wi * 16 * T + T * lane + a] = s;
-      }
-    }
-  }
   __syncthreads();
   epi.begin();
-  for (int e = threadIdx.x; e < BI * BJ; e += NT) {
+#pragma unroll
+  for (int q = 0; q < BI * BJ / NT; ++q) {
+    const int e = q * NT + threadIdx.x;
     const int li = e / BJ, lj = e % BJ, i = i0 + li, j = j0 + lj;
-    float sum = 0.f;
-#pragma unroll
-    for (int w = 0; w < WK; ++w) sum += red[(w * BI + li) * RS + lj];
-    if (i < I && j < J) epi(i, j, sum);
-  }
-  if (Epi::kColSumA && !AKC) {
-    if (bx == 0 && epi.wants_colsum() && threadIdx.x < BI && i0 + (int)threadIdx.x < I) {
-      float s = 0.f;
-#pragma unroll
-      for (int w = 0; w < WK; ++w) s += csum[w * BI + threadIdx.x];
-      epi.colsum(i0 + threadIdx.x, s);
-    }
+    if (i < I && j < J) epi(i, j, smem[li * RS + lj]);
   }
 }
 
@@ -248,12 +275,12 @@ __global__ __launch_bounds__(Cfg::NT) void pm_gemm_f32_grouped_kernel(const PmF3
   pm_gemm_f32_body<Cfg, Epi::kAKC, Epi::kBKC, V, Epi>(pr, pr.epi, id % tj, id / tj, smem);
 }
 
-// A wave tile of 16 x 16 where 32 x 32 blocks would leave compute units idle (latency bound: the most waves win),
-// 32 x 32 with the contraction over four waves up to two such blocks per compute unit and 64 x 64 blocks beyond (half the
-// operand traffic per product).
-using PmF32Small = PmF32Cfg<1, 1, 1, 8>;
-using PmF32Mid = PmF32Cfg<2, 1, 1, 4>;
-using PmF32Large = PmF32Cfg<2, 2, 2, 1>;
+// A wave tile of 16 x 16 takes 8 clocks per contraction index, one of 32 x 32 32 clocks with half the operand traffic per
+// product: small tiles, and so more waves with shorter chains, up to two 64 x 64 blocks per compute unit.  Blocks of
+// four such waves (which share operand lines in the first-level cache) once there is one for each compute unit.
+using PmF32Small = PmF32Cfg<1, 1, 1, 4>;
+using PmF32Mid = PmF32Cfg<1, 2, 2, 4>;
+using PmF32Large = PmF32Cfg<2, 2, 2, 2>;
 inline int64_t pm_f32_tiles(int I, int J, int b) { return (int64_t)((I + b - 1) / b) * ((J + b - 1) / b); }
 // outputs per block edge for a launch with that many 32 x 32 and 64 x 64 tiles in total
 inline int pm_f32_pick(int64_t tiles32, int64_t tiles64) { return tiles64 >= 512 ? 64 : tiles32 >= 256 ? 32 : 16; }

@@ -444,3 +444,43 @@ def test_fp32_linear_primitives_every_tile_choice(torch_cuda, M, n_in, n_out):
         pm.pm_linear_bwd_weight(st, "f32", M, n_in, n_out, dz_d.data_ptr(), x_d.data_ptr(), dW.data_ptr(), db.data_ptr(), acc)
         check(dW, dz64.T @ x64 + acc * g0, np.abs(dz64).T @ np.abs(x64) + acc * np.abs(g0), M)
         check(db, dz64.sum(0) + acc * b0, np.abs(dz64).sum(0) + acc * np.abs(b0), M)
+
+
+def _fma_chain(a, b, start=None):
+    """C[i, j] = chain of fp32 fused multiply-adds over k of a[i, k] b[j, k], one rounding each (the 64-bit significand of
+    the extended type holds a product exactly, so rounding the sum to fp32 is a fused multiply-add but for a double
+    rounding of one in 2^40)."""
+    if np.finfo(np.longdouble).nmant < 63:
+        pytest.skip("no extended precision on this machine")
+    c = np.zeros((a.shape[0], b.shape[0]), dtype=np.float32) if start is None else start
+    for k in range(a.shape[1]):
+        c = (np.multiply.outer(a[:, k].astype(np.longdouble), b[:, k].astype(np.longdouble)) + c).astype(np.float32)
+    return c
+
+
+@pytest.mark.parametrize("M,n_in,n_out", [(1, 1, 1), (3, 5, 7), (16, 64, 16), (17, 16, 33), (65, 129, 30), (33, 48, 34), (100, 203, 96),
+                                          (260, 31, 512), (300, 64, 1040)])
+def test_fp32_products_sum_in_index_order(torch_cuda, M, n_in, n_out):
+    """Every fp32 product is one chain of fused multiply-adds in the order of the contraction index, for all tile
+    choices: bit for bit.  (A ReLU network turns one rounding next to zero into another gradient, so the order of the
+    sums is part of the result.)  The bias gradient: rows m, m + 4, ... in four chains, added in order."""
+    import paper_1910_05124_amd as pm
+    torch = torch_cuda
+    rng = np.random.default_rng(M * 5 + n_in * 3 + n_out)
+    x, W, dz = (rng.standard_normal(s).astype(np.float32) for s in ((M, n_in), (n_out, n_in), (M, n_out)))
+    b = rng.standard_normal(n_out).astype(np.float32)
+    x_d, W_d, dz_d, b_d = (torch.from_numpy(v).cuda() for v in (x, W, dz, b))
+    st = torch.cuda.current_stream().cuda_stream
+    z = torch.full((M, n_out), np.nan, device="cuda")
+    pm.pm_linear_fwd(st, "f32", M, n_in, n_out, x_d.data_ptr(), W_d.data_ptr(), b_d.data_ptr(), "none", z.data_ptr(), 0)
+    assert np.array_equal(z.cpu().numpy(), _fma_chain(x, W) + b)
+    dp = torch.full((M, n_in), np.nan, device="cuda")
+    pm.pm_linear_bwd_data(st, "f32", M, n_in, n_out, dz_d.data_ptr(), W_d.data_ptr(), x_d.data_ptr(), "none", dp.data_ptr())
+    assert np.array_equal(dp.cpu().numpy(), _fma_chain(dz, np.ascontiguousarray(W.T)))
+    dW, db = torch.zeros((n_out, n_in), device="cuda"), torch.zeros(n_out, device="cuda")
+    pm.pm_linear_bwd_weight(st, "f32", M, n_in, n_out, dz_d.data_ptr(), x_d.data_ptr(), dW.data_ptr(), db.data_ptr(), 0)
+    assert np.array_equal(dW.cpu().numpy(), _fma_chain(np.ascontiguousarray(dz.T), np.ascontiguousarray(x.T)))
+    chains = [np.zeros(n_out, dtype=np.float32) for _ in range(4)]
+    for m in range(M):
+        chains[m % 4] = chains[m % 4] + dz[m]
+    assert np.array_equal(db.cpu().numpy(), ((chains[0] + chains[1]) + chains[2]) + chains[3])
