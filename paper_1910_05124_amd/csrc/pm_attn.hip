@@ -30,7 +30,7 @@ void mfma_bwd(hipStream_t st, int B, int S, int H, const bf16_t* q, const bf16_t
 }
 template <typename T, int DH>
 void f32_fwd(hipStream_t st, int B, int S, int H, const T* q, const T* k, const T* v, T* o, float* lse) {
-  hipLaunchKernelGGL((pm_attn_f32_fwd_kernel<T, DH>), dim3(B * H * ((S + 31) / 32)), dim3(64), 0, st, q, k, v, o, lse, S, H, B * H,
+  hipLaunchKernelGGL((pm_attn_f32_fwd_kernel<T, DH>), dim3(B * H * ((S + 15) / 16)), dim3(256), 0, st, q, k, v, o, lse, S, H, B * H,
                      1.f / sqrtf((float)DH));
 }
 template <typename T, int DH>

@@ -1,19 +1,27 @@
-// Causal attention core in fp32 arithmetic on v_mfma_f32_32x32x2_f32, for fp32 contexts and for bf16 tensors with
-// heads narrower than 32, gfx950.  T: element type of the tensors in memory; everything inside is fp32.
+// Causal attention core in fp32 arithmetic, for fp32 contexts and for bf16 tensors with heads narrower than 32, gfx950.
+// T: element type of the tensors in memory; everything inside is fp32.
 //
-// The scheme is that of pm_attn_mfma.hpp: a wave owns 32 rows of one index and streams 32-row tiles of the other; the
-// score-like products come out transposed, streamed index on the MFMA rows and owned index on the columns, so row
-// statistics are per-lane scalars and the probabilities are the second product's B operand without leaving their
-// lane.  The fp32 instruction contracts two indices at a time, lane group g = lane / 32 holding one of them, and the
-// order of a contraction is free as long as both operands agree, hence:
-//   * scores: group g holds head-dimension entries g DH / 2 .. + DH / 2 - 1 of its row, step c contracts the c-th of each
-//     half: both operands are read as 16-byte pieces;
-//   * second product: accumulator value v of group g is streamed row 8 (v / 4) + 4 g + v % 4, so step v contracts exactly
-//     the two rows that the groups' values v stand for; the A operand is read column-wise from the tile in LDS.
+// Order of the sums.  Scores are one chain of fused multiply-adds over the head dimension, the forward pass takes its keys
+// one after the other (running maximum and sum, every earlier value scaled when the maximum moves), and a gradient row is one
+// chain over its keys or queries in order.  Whole fp32 networks have ReLU units behind this core, whose gradients
+// hang on the rounding of a pre-activation next to zero, so the order is part of the result (see pm_gemm_f32.hpp).
+//
+// Forward: 16 lanes per query row.  A lane holds DH / 16 columns of the row's output; for 16 keys at a time each lane
+// computes one key's score, a scan over the lanes gives every key's running maximum (a maximum does not depend on
+// the order), so that the two exponentials of a key are computed once, and the 16 keys are then applied in order.
+//
+// Backward, on v_mfma_f32_32x32x2_f32: the scheme is that of pm_attn_mfma.hpp, a wave owns 32 rows of one index and
+// streams 32-row tiles of the other; the score-like products come out transposed, streamed index on the MFMA rows and
+// owned index on the columns, so row statistics are per-lane scalars and the probabilities are the second product's
+// B operand.  The instruction adds its two products one after the other, lane group 0's first, hence:
+//   * scores: step c contracts head-dimension entries 2 c and 2 c + 1.  The tile lies in LDS with the even entries of a row
+//     in front of the odd ones, so that a lane reads its share as 16-byte pieces;
+//   * second product: accumulator value v of group g is streamed row 8 (v / 4) + 4 g + v % 4, and a step is to contract rows
+//     r and r + 1: one lane exchange per two values brings them there.
 // One wave per block (the tiles are private, no barrier but the wave's own): a tile costs 64 clocks per contracted pair
 // - 2048 + 2048 clocks at DH = 64 - against 256 clocks to fetch it, so sharing tiles between waves would save nothing,
 // and these shapes (a few dozen heads, sequences of at most 8192 / (DH + 1) rows) need the blocks to fill the chip.
-// 8 sequences of 64 tokens, 8 heads of 32: forward 85 -> 5 us, backward 161 -> 15 us per layer against one thread per row.
+// 8 sequences of 64 tokens, 8 heads of 32: forward 85 -> 6 us, backward 161 -> 16 us per layer against one thread per row.
 #pragma once
 #include "pm_common.hpp"
 #include "pm_mfma_types.hpp"
@@ -27,7 +35,126 @@ struct PmAf {
   static constexpr int PER = (PIECES + 63) / 64;          // pieces per lane
   static constexpr int ELEMS = 32 * ST + 32;              // a narrow head's column reads run past its rows
 };
+__device__ __forceinline__ float pm_af_exp(float x) { return __builtin_amdgcn_exp2f(x * 1.44269504f); }
 
+// ---------------------------------------------------------------------------------------------
+// forward
+// ---------------------------------------------------------------------------------------------
+// lane N of each group of 16, to all of them
+template <int N>
+__device__ __forceinline__ float pm_row_bcast(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x150 + N, 0xf, 0xf, true));
+}
+// lane l - N of the group of 16, `out` where there is none
+template <int N>
+__device__ __forceinline__ float pm_row_shr(float x, float out) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(out), __float_as_int(x), 0x110 + N, 0xf, 0xf, false));
+}
+
+// Keys N .. 15 of a group, in order: l and acc scaled by the key's correction, then its probability added.  have: keys of
+// the group that the row sees (FULL: all).
+template <int N, int CPL, bool FULL>
+__device__ __forceinline__ void pm_af_keys(float corr, float p, const float* v, int st, int have, float& l, float (&acc)[CPL]) {
+  if constexpr (N < 16) {
+    const float c = pm_row_bcast<N>(corr), w = pm_row_bcast<N>(p);
+    float x[CPL];
+#pragma unroll
+    for (int e = 0; e < CPL; ++e) x[e] = v[N * st + e];
+    const bool on = FULL || N < have;
+    l = on ? fmaf(l, c, w) : l;
+#pragma unroll
+    for (int e = 0; e < CPL; ++e) acc[e] = on ? fmaf(acc[e], c, w * x[e]) : acc[e];
+    pm_af_keys<N + 1, CPL, FULL>(corr, p, v, st, have, l, acc);
+  }
+}
+
+// blockIdx.x = block of 16 query rows * BH + (sequence, head); wave w takes rows 4 w .. 4 w + 3, lanes 16 r .. 16 r + 15 row r
+template <typename T, int DH>
+__global__ __launch_bounds__(256) void pm_attn_f32_fwd_kernel(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
+                                                              T* __restrict__ o, float* __restrict__ lse, int S, int H, int BH,
+                                                              float scale) {
+  constexpr int ST = DH + 4, CPL = DH >= 16 ? DH / 16 : 1, PIECES = 32 * DH / 4, PER = (PIECES + 255) / 256;
+  __shared__ __attribute__((aligned(16))) float sK[32 * ST], sV[32 * ST + 16];       // narrow heads: lanes without a column read on
+  const int blocks = (S + 15) / 16;
+  const int bh = blockIdx.x % BH, qb = blocks - 1 - blockIdx.x / BH;                 // long blocks first
+  const int b = bh / H, h = bh % H, d = H * DH, wave = threadIdx.x >> 6, lane = threadIdx.x & 63, t = lane & 15;
+  const int64_t base = (int64_t)b * S * d + (int64_t)h * DH;
+  const int w0 = qb * 16 + wave * 4, row = w0 + (lane >> 4), i = row < S ? row : S - 1;
+  float qi[DH];
+#pragma unroll
+  for (int c = 0; c < DH; c += 4) {
+    const float4 x = pm_ld4(q + base + (int64_t)i * d + c);
+    qi[c] = x.x * scale; qi[c + 1] = x.y * scale; qi[c + 2] = x.z * scale; qi[c + 3] = x.w * scale;
+  }
+  float4 rk[PER], rv[PER];
+  auto fetch = [&](int tile) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const int c = ((int)threadIdx.x + 256 * j) % PIECES;           // (fewer pieces than threads: fetched more than once)
+      int r = tile * 32 + c / (DH / 4);
+      r = r < S ? r : S - 1;
+      const int64_t at = base + (int64_t)r * d + (c % (DH / 4)) * 4;
+      rk[j] = pm_ld4(k + at);
+      rv[j] = pm_ld4(v + at);
+    }
+  };
+  auto park = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const int c = ((int)threadIdx.x + 256 * j) % PIECES, at = (c / (DH / 4)) * ST + (c % (DH / 4)) * 4;
+      *reinterpret_cast<float4*>(sK + at) = rk[j];
+      *reinterpret_cast<float4*>(sV + at) = rv[j];
+    }
+  };
+  const int last = (qb * 16 + 15 < S ? qb * 16 + 15 : S - 1);        // last key that a row of the block sees
+  float m = -3.0e38f, l = 0.f, acc[CPL] = {};
+  fetch(0);
+  for (int tile = 0; tile <= last >> 5; ++tile) {
+    park();
+    __syncthreads();
+    if (tile < last >> 5) fetch(tile + 1);                           // on its way while this one is used
+    for (int jj = 0; jj < 32; jj += 16) {
+      const int j0 = tile * 32 + jj;
+      if (j0 > w0 + 3) break;                                        // uniform over the wave
+      float s = 0.f;
+      const float* kr = sK + (jj + t) * ST;
+#pragma unroll
+      for (int c = 0; c < DH; c += 4) {
+        const float4 x = *reinterpret_cast<const float4*>(kr + c);
+        s = fmaf(qi[c], x.x, s);
+        s = fmaf(qi[c + 1], x.y, s);
+        s = fmaf(qi[c + 2], x.z, s);
+        s = fmaf(qi[c + 3], x.w, s);
+      }
+      // running maximum behind each key; keys that the row does not see leave it alone
+      const float none = -__builtin_inff();
+      float mx = j0 + t <= i ? s : none;
+      mx = fmaxf(mx, pm_row_shr<1>(mx, none));
+      mx = fmaxf(mx, pm_row_shr<2>(mx, none));
+      mx = fmaxf(mx, pm_row_shr<4>(mx, none));
+      mx = fmaxf(mx, pm_row_shr<8>(mx, none));
+      const float mt = fmaxf(m, mx), mb = pm_row_shr<1>(mt, m);      // behind and before this lane's key
+      const float corr = pm_af_exp(mb - mt), p = pm_af_exp(s - mt);
+      m = pm_row_bcast<15>(mt);
+      const float* vc = sV + jj * ST + t * CPL;
+      if (j0 + 15 <= w0) pm_af_keys<0, CPL, true>(corr, p, vc, ST, 16, l, acc);
+      else pm_af_keys<0, CPL, false>(corr, p, vc, ST, i - j0 + 1, l, acc);
+    }
+    __syncthreads();
+  }
+  if (row >= S) return;
+  const float inv = 1.f / l;
+  if (t * CPL < DH) {
+    T* out = o + base + (int64_t)row * d + t * CPL;
+#pragma unroll
+    for (int e = 0; e < CPL; ++e) stf(out + e, acc[e] * inv);
+  }
+  if (t == 0) lse[((int64_t)b * H + h) * S + row] = m + __logf(l);
+}
+
+// ---------------------------------------------------------------------------------------------
+// backward
+// ---------------------------------------------------------------------------------------------
 // 32 rows of X (row stride d, rows past the end re-read the last one): registers first, LDS later
 template <typename T, int DH>
 __device__ __forceinline__ void pm_af_load(const T* X, int64_t d, int r0, int S, int lane, float4* r) {
@@ -40,21 +167,29 @@ __device__ __forceinline__ void pm_af_load(const T* X, int64_t d, int r0, int S,
     r[j] = pm_ld4(X + (int64_t)row * d + (c % (DH / 4)) * 4);
   }
 }
+// head-dimension entry c of a row in LDS: the even ones, then the odd ones
+template <int DH>
+__device__ __forceinline__ constexpr int pm_af_pos(int c) { return (c & 1) * PmAf<DH>::HALF + (c >> 1); }
 template <int DH>
 __device__ __forceinline__ void pm_af_park(float* s, int lane, const float4* r) {
   using A = PmAf<DH>;
 #pragma unroll
   for (int j = 0; j < A::PER; ++j) {
     const int c = (lane + 64 * j) % A::PIECES;
-    *reinterpret_cast<float4*>(s + (c / (DH / 4)) * A::ST + (c % (DH / 4)) * 4) = r[j];
+    float* p = s + (c / (DH / 4)) * A::ST + (c % (DH / 4)) * 2;
+    *reinterpret_cast<float2*>(p) = make_float2(r[j].x, r[j].z);
+    *reinterpret_cast<float2*>(p + A::HALF) = make_float2(r[j].y, r[j].w);
   }
 }
-// this lane's half of a row of X
+// this lane's entries 2 c + g of a row of X
 template <typename T, int DH>
 __device__ __forceinline__ void pm_af_own(const T* X, int64_t d, int row, int g, float* x) {
-  const T* p = X + (int64_t)row * d + g * PmAf<DH>::HALF;
 #pragma unroll
-  for (int c = 0; c < PmAf<DH>::HALF; ++c) x[c] = ldf(p + c);
+  for (int c = 0; c < DH; c += 4) {
+    const float4 v = pm_ld4(X + (int64_t)row * d + c);
+    x[c / 2] = g ? v.y : v.x;
+    x[c / 2 + 1] = g ? v.w : v.z;
+  }
 }
 // out^T [streamed row][owned row] = tile rows . owned rows
 template <int DH>
@@ -68,52 +203,71 @@ __device__ __forceinline__ pm_f32x16 pm_af_scores(const float* s, const float* o
   for (int c = 0; c < A::HALF; ++c) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(p[c], own[c], acc, 0, 0, 0);
   return acc;
 }
-// acc[dt] [head dimension][owned row] += tile^T . x
+// acc[dt] [head dimension][owned row] += tile^T . x, streamed rows in order
 template <int DH>
 __device__ __forceinline__ void pm_af_second(pm_f32x16* acc, const float* s, const float* x, int lane) {
   using A = PmAf<DH>;
-  const float* p = s + 4 * (lane >> 5) * A::ST + (lane & 31);
-#pragma unroll
-  for (int v = 0; v < 16; ++v)
+  const float* p = s + (lane >> 5) * A::ST + pm_af_pos<DH>(lane & 31);
+  auto step = [&](int r, float w) __attribute__((always_inline)) {              // rows r and r + 1
 #pragma unroll
     for (int dt = 0; dt < A::NDT; ++dt)
-      acc[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(p[(8 * (v >> 2) + (v & 3)) * A::ST + dt * 32], x[v], acc[dt], 0, 0, 0);
+      acc[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(p[r * A::ST + dt * 16], w, acc[dt], 0, 0, 0);
+  };
+#pragma unroll
+  for (int a = 0; a < 4; ++a) {
+    // values 4 a .. 4 a + 3: rows 8 a .. 8 a + 3 in group 0, 8 a + 4 .. 8 a + 7 in group 1
+    const auto w0 = __builtin_amdgcn_permlane32_swap(__float_as_uint(x[4 * a]), __float_as_uint(x[4 * a + 1]), false, false);
+    const auto w1 = __builtin_amdgcn_permlane32_swap(__float_as_uint(x[4 * a + 2]), __float_as_uint(x[4 * a + 3]), false, false);
+    step(8 * a, __uint_as_float(w0[0]));
+    step(8 * a + 2, __uint_as_float(w1[0]));
+    step(8 * a + 4, __uint_as_float(w0[1]));
+    step(8 * a + 6, __uint_as_float(w1[1]));
+  }
 }
 template <typename T, int DH>
-__device__ __forceinline__ void pm_af_store(T* out_row, const pm_f32x16* acc, float mul, int lane) {
+__device__ __forceinline__ void pm_af_store(T* out_row, const pm_f32x16* acc, int lane) {
 #pragma unroll
   for (int dt = 0; dt < PmAf<DH>::NDT; ++dt)
 #pragma unroll
     for (int a = 0; a < 4; ++a) {
       const int c = dt * 32 + 8 * a + 4 * (lane >> 5);
-      if (c < DH)
-        pm_st4(out_row + c, make_float4(acc[dt][4 * a] * mul, acc[dt][4 * a + 1] * mul, acc[dt][4 * a + 2] * mul, acc[dt][4 * a + 3] * mul));
+      if (c < DH) pm_st4(out_row + c, make_float4(acc[dt][4 * a], acc[dt][4 * a + 1], acc[dt][4 * a + 2], acc[dt][4 * a + 3]));
     }
 }
 
 // blockIdx.x = block of 32 owned rows * BH + (sequence, head)
 template <typename T, int DH>
-__global__ __launch_bounds__(64) void pm_attn_f32_fwd_kernel(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
-                                                             T* __restrict__ o, float* __restrict__ lse, int S, int H, int BH,
-                                                             float scale) {
+__global__ __launch_bounds__(64) void pm_attn_f32_dq_kernel(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
+                                                            const T* __restrict__ o, const T* __restrict__ dO,
+                                                            const float* __restrict__ lse, T* __restrict__ dq, int S, int H, int BH,
+                                                            float scale) {
   using A = PmAf<DH>;
   __shared__ __attribute__((aligned(16))) float sK[A::ELEMS], sV[A::ELEMS];
   const int bh = blockIdx.x % BH, qb = (S + 31) / 32 - 1 - blockIdx.x / BH;      // long blocks first
   const int b = bh / H, h = bh % H, d = H * DH, lane = threadIdx.x, ql = lane & 31, g = lane >> 5;
   const int64_t base = (int64_t)b * S * d + (int64_t)h * DH;
   const int q0 = qb * 32, qi = q0 + ql, qr = qi < S ? qi : S - 1;
-  float own[A::HALF];
+  float own[A::HALF], od[A::HALF], D = 0.f;
+#pragma unroll
+  for (int c = 0; c < DH; c += 4) {
+    const float4 x = pm_ld4(dO + base + (int64_t)qr * d + c), y = pm_ld4(o + base + (int64_t)qr * d + c);
+    D = fmaf(x.x, y.x, D);
+    D = fmaf(x.y, y.y, D);
+    D = fmaf(x.z, y.z, D);
+    D = fmaf(x.w, y.w, D);
+    od[c / 2] = g ? x.y : x.x;
+    od[c / 2 + 1] = g ? x.w : x.z;
+  }
   pm_af_own<T, DH>(q + base, d, qr, g, own);
+  const float L = lse[((int64_t)b * H + h) * S + qr];
   pm_f32x16 acc[A::NDT];
 #pragma unroll
   for (int dt = 0; dt < A::NDT; ++dt)
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[dt][e] = 0.f;
-  float m = -3.0e38f, lsum = 0.f;
   float4 rk[A::PER], rv[A::PER];
   pm_af_load<T, DH>(k + base, d, 0, S, lane, rk);
   pm_af_load<T, DH>(v + base, d, 0, S, lane, rv);
-  const float c2 = scale * 1.44269504f;            // scores in base-2 units
   for (int jt = 0; jt <= qb; ++jt) {
     pm_af_park<DH>(sK, lane, rk);
     pm_af_park<DH>(sV, lane, rv);
@@ -122,83 +276,18 @@ __global__ __launch_bounds__(64) void pm_attn_f32_fwd_kernel(const T* __restrict
       pm_af_load<T, DH>(k + base, d, (jt + 1) * 32, S, lane, rk);
       pm_af_load<T, DH>(v + base, d, (jt + 1) * 32, S, lane, rv);
     }
-    const pm_f32x16 s = pm_af_scores<DH>(sK, own, lane);
-    float p[16], mx = -3.0e38f;
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      p[e] = s[e] * c2;
-      if (jt == qb && jt * 32 + 8 * (e >> 2) + 4 * g + (e & 3) > qi) p[e] = -3.0e38f;      // causal mask (keys past the end too)
-      mx = fmaxf(mx, p[e]);
-    }
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    const float mn = fmaxf(m, mx), corr = __builtin_amdgcn_exp2f(m - mn);
-    float ps = 0.f;
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      p[e] = __builtin_amdgcn_exp2f(p[e] - mn);
-      ps += p[e];
-    }
-    lsum = lsum * corr + ps;
-#pragma unroll
-    for (int dt = 0; dt < A::NDT; ++dt)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[dt][e] *= corr;
-    m = mn;
-    pm_af_second<DH>(acc, sV, p, lane);
-    __syncthreads();
-  }
-  lsum += __shfl_xor(lsum, 32, 64);
-  if (qi >= S) return;
-  pm_af_store<T, DH>(o + base + (int64_t)qi * d, acc, 1.f / lsum, lane);
-  if (g == 0) lse[((int64_t)b * H + h) * S + qi] = m * 0.693147181f + __logf(lsum);
-}
-
-template <typename T, int DH>
-__global__ __launch_bounds__(64) void pm_attn_f32_dq_kernel(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
-                                                            const T* __restrict__ o, const T* __restrict__ dO,
-                                                            const float* __restrict__ lse, T* __restrict__ dq, int S, int H, int BH,
-                                                            float scale) {
-  using A = PmAf<DH>;
-  __shared__ __attribute__((aligned(16))) float sK[A::ELEMS], sV[A::ELEMS];
-  const int bh = blockIdx.x % BH, qb = (S + 31) / 32 - 1 - blockIdx.x / BH;
-  const int b = bh / H, h = bh % H, d = H * DH, lane = threadIdx.x, ql = lane & 31, g = lane >> 5;
-  const int64_t base = (int64_t)b * S * d + (int64_t)h * DH;
-  const int q0 = qb * 32, qi = q0 + ql, qr = qi < S ? qi : S - 1;
-  float own[A::HALF], od[A::HALF], D = 0.f;
-  pm_af_own<T, DH>(o + base, d, qr, g, own);
-  pm_af_own<T, DH>(dO + base, d, qr, g, od);
-#pragma unroll
-  for (int c = 0; c < A::HALF; ++c) D += own[c] * od[c];
-  D += __shfl_xor(D, 32, 64);
-  pm_af_own<T, DH>(q + base, d, qr, g, own);
-  const float c2 = scale * 1.44269504f, l2 = lse[((int64_t)b * H + h) * S + qr] * 1.44269504f;
-  pm_f32x16 acc[A::NDT];
-#pragma unroll
-  for (int dt = 0; dt < A::NDT; ++dt)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) acc[dt][e] = 0.f;
-  float4 rk[A::PER], rv[A::PER];
-  pm_af_load<T, DH>(k + base, d, 0, S, lane, rk);
-  pm_af_load<T, DH>(v + base, d, 0, S, lane, rv);
-  for (int jt = 0; jt <= qb; ++jt) {
-    pm_af_park<DH>(sK, lane, rk);
-    pm_af_park<DH>(sV, lane, rv);
-    __syncthreads();
-    if (jt < qb) {
-      pm_af_load<T, DH>(k + base, d, (jt + 1) * 32, S, lane, rk);
-      pm_af_load<T, DH>(v + base, d, (jt + 1) * 32, S, lane, rv);
-    }
     const pm_f32x16 s = pm_af_scores<DH>(sK, own, lane), dp = pm_af_scores<DH>(sV, od, lane);
     float ds[16];
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
-      ds[e] = __builtin_amdgcn_exp2f(fmaf(s[e], c2, -l2)) * (dp[e] - D);       // the factor 1 / sqrt(dh) goes into the store
-      if (jt == qb && jt * 32 + 8 * (e >> 2) + 4 * g + (e & 3) > qi) ds[e] = 0.f;
+      const float p = pm_af_exp(fmaf(s[e], scale, -L));
+      ds[e] = p * (dp[e] - D) * scale;
+      if (jt == qb && jt * 32 + 8 * (e >> 2) + 4 * g + (e & 3) > qi) ds[e] = 0.f;      // causal mask (keys past the end too)
     }
     pm_af_second<DH>(acc, sK, ds, lane);
     __syncthreads();
   }
-  if (qi < S) pm_af_store<T, DH>(dq + base + (int64_t)qi * d, acc, scale, lane);
+  if (qi < S) pm_af_store<T, DH>(dq + base + (int64_t)qi * d, acc, lane);
 }
 
 template <typename T, int DH>
@@ -207,7 +296,7 @@ __global__ __launch_bounds__(64) void pm_attn_f32_dkv_kernel(const T* __restrict
                                                              const float* __restrict__ lse, T* __restrict__ dk, T* __restrict__ dv,
                                                              int S, int H, int BH, float scale) {
   using A = PmAf<DH>;
-  __shared__ __attribute__((aligned(16))) float sQ[A::ELEMS], sO[A::ELEMS], sL[32], sD[32];
+  __shared__ __attribute__((aligned(16))) float sQ[A::ELEMS], sO[A::ELEMS], sX[32 * A::ST], sL[32], sD[32];
   const int bh = blockIdx.x % BH, kb = blockIdx.x / BH;                          // long blocks (early keys) first
   const int b = bh / H, h = bh % H, d = H * DH, lane = threadIdx.x, kl = lane & 31, g = lane >> 5;
   const int64_t base = (int64_t)b * S * d + (int64_t)h * DH;
@@ -224,7 +313,6 @@ __global__ __launch_bounds__(64) void pm_attn_f32_dkv_kernel(const T* __restrict
       av[dt][e] = 0.f;
     }
   const int n_tiles = (S + 31) / 32;
-  const float c2 = scale * 1.44269504f;
   float4 rq[A::PER], rd[A::PER], ro[A::PER];
   float L = 0.f;
   auto load = [&](int it) __attribute__((always_inline)) {
@@ -232,39 +320,42 @@ __global__ __launch_bounds__(64) void pm_attn_f32_dkv_kernel(const T* __restrict
     pm_af_load<T, DH>(dO + base, d, it * 32, S, lane, rd);
     pm_af_load<T, DH>(o + base, d, it * 32, S, lane, ro);
     const int row = it * 32 + kl;
-    L = lse[((int64_t)b * H + h) * S + (row < S ? row : S - 1)] * 1.44269504f;
+    L = lse[((int64_t)b * H + h) * S + (row < S ? row : S - 1)];
   };
   load(kb);
   for (int it = kb; it < n_tiles; ++it) {
     pm_af_park<DH>(sQ, lane, rq);
     pm_af_park<DH>(sO, lane, rd);
-    // D of the tile's rows: the DH / 4 lanes that hold a row's pieces are neighbours
-#pragma unroll
-    for (int j = 0; j < A::PER; ++j) {
-      float part = rd[j].x * ro[j].x + rd[j].y * ro[j].y + rd[j].z * ro[j].z + rd[j].w * ro[j].w;
-#pragma unroll
-      for (int m = 1; m < DH / 4; m <<= 1) part += __shfl_xor(part, m, 64);
-      const int c = (lane + 64 * j) % A::PIECES;
-      if (c % (DH / 4) == 0) sD[c / (DH / 4)] = part;
-    }
+    pm_af_park<DH>(sX, lane, ro);
     if (lane < 32) sL[lane] = L;
     __syncthreads();
     if (it + 1 < n_tiles) load(it + 1);
+    {                                              // D of row kl: both lane groups compute it
+      const float *x = sO + kl * A::ST, *y = sX + kl * A::ST;
+      float D = 0.f;
+#pragma unroll
+      for (int c = 0; c < A::HALF; ++c) {
+        D = fmaf(x[c], y[c], D);
+        D = fmaf(x[A::HALF + c], y[A::HALF + c], D);
+      }
+      if (lane < 32) sD[lane] = D;
+    }
     const pm_f32x16 s = pm_af_scores<DH>(sQ, ok, lane), dp = pm_af_scores<DH>(sO, ov, lane);
+    __syncthreads();
     float p[16], ds[16];
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
       const int r = 8 * (e >> 2) + 4 * g + (e & 3), qi = it * 32 + r;
-      p[e] = __builtin_amdgcn_exp2f(fmaf(s[e], c2, -sL[r]));
-      if (qi < ki || qi >= S) p[e] = 0.f;
-      ds[e] = p[e] * (dp[e] - sD[r]);
+      p[e] = pm_af_exp(fmaf(s[e], scale, -sL[r]));
+      ds[e] = p[e] * (dp[e] - sD[r]) * scale;
+      if (qi < ki || qi >= S) p[e] = ds[e] = 0.f;
     }
     pm_af_second<DH>(av, sO, p, lane);
     pm_af_second<DH>(ak, sQ, ds, lane);
     __syncthreads();
   }
   if (ki < S) {
-    pm_af_store<T, DH>(dk + base + (int64_t)ki * d, ak, scale, lane);
-    pm_af_store<T, DH>(dv + base + (int64_t)ki * d, av, 1.f, lane);
+    pm_af_store<T, DH>(dk + base + (int64_t)ki * d, ak, lane);
+    pm_af_store<T, DH>(dv + base + (int64_t)ki * d, av, lane);
   }
 }

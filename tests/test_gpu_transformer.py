@@ -132,6 +132,77 @@ def test_attention_ragged_lengths_and_narrow_heads(torch_cuda, dtype, B, S, H, d
     test_attention_primitives(torch_cuda, dtype, B, S, H, dh)
 
 
+def _fma(a, b, c):
+    """fp32 fused multiply-add (a product is exact in the extended type's 64 bits)."""
+    return (a.astype(np.longdouble) * b.astype(np.longdouble) + c.astype(np.longdouble)).astype(np.float32)
+
+
+@pytest.mark.parametrize("dtype,B,S,H,dh", [("f32", 2, 5, 2, 64), ("f32", 1, 16, 2, 32), ("f32", 2, 33, 1, 16), ("f32", 1, 50, 2, 8),
+                                            ("f32", 1, 67, 1, 4), ("f32", 1, 70, 1, 64), ("bf16", 2, 35, 1, 16), ("bf16", 1, 18, 3, 4)])
+def test_fp32_attention_arithmetic_keeps_its_order(torch_cuda, dtype, B, S, H, dh):
+    """The fp32 core bit for bit: scores are chains of fused multiply-adds over the head dimension, the forward pass takes a
+    row's keys one after the other with a running maximum and sum, a gradient row is one chain over its keys or queries.
+    (In an fp32 network a ReLU input next to zero turns one rounding into another gradient.)  The exponentials are the
+    device's own; every argument lies in its normal range."""
+    import paper_1910_05124_amd as pm
+    torch = torch_cuda
+    if np.finfo(np.longdouble).nmant < 63:
+        pytest.skip("no extended precision on this machine")
+    tdt, f = _tdt(torch, dtype), np.float32
+    rng = np.random.default_rng(S * 11 + dh)
+    q, k, v, do = (torch.from_numpy(rng.standard_normal((B * S, H * dh)).astype(f)).cuda().to(tdt) for _ in range(4))
+    o, dq, dk, dv = (torch.empty_like(q) for _ in range(4))
+    lse = torch.empty(B * H * S, dtype=torch.float32, device="cuda")
+    st = torch.cuda.current_stream().cuda_stream
+    pm.pm_attention_fwd(st, dtype, B, S, H, dh, q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), lse.data_ptr())
+    pm.pm_attention_bwd(st, dtype, B, S, H, dh, q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), do.data_ptr(),
+                        lse.data_ptr(), dq.data_ptr(), dk.data_ptr(), dv.data_ptr())
+
+    def heads(t):                                           # [B, H, S, dh]
+        return t.float().cpu().numpy().reshape(B, S, H, dh).transpose(0, 2, 1, 3)
+
+    def exp(x):
+        with np.errstate(over="ignore"):                    # the first key's correction: exp of minus infinity
+            return torch.exp2(torch.from_numpy(x * f(1.44269504)).cuda()).cpu().numpy()
+
+    def stored(x):                                          # rounded to the element type
+        return torch.from_numpy(x).to(tdt).float().numpy()
+
+    def scores(a, b):                                       # [.., i, j]: chain over the head dimension
+        s = np.zeros((B, H, S, S), dtype=f)
+        for c in range(dh):
+            s = _fma(a[..., :, None, c], b[..., None, :, c], s)
+        return s
+
+    Q, K, V, DO, O = heads(q), heads(k), heads(v), heads(do), heads(o)
+    scale = f(1.0) / np.sqrt(f(dh))
+    s = scores(Q * scale, K)
+    m, l, acc = np.full((B, H, S), -3.0e38, dtype=f), np.zeros((B, H, S), dtype=f), np.zeros((B, H, S, dh), dtype=f)
+    rows = np.arange(S)
+    for j in range(S):
+        mn = np.maximum(m, s[..., j])
+        corr, p = exp(m - mn), exp(s[..., j] - mn)
+        on = rows >= j
+        l = np.where(on, _fma(l, corr, p), l)
+        acc = np.where(on[:, None], _fma(acc, corr[..., None], p[..., None] * V[..., j, None, :]), acc)
+        m = np.where(on, mn, m)
+    assert np.array_equal(O, stored(acc * (f(1.0) / l)[..., None]))
+    D = np.zeros((B, H, S), dtype=f)
+    for c in range(dh):
+        D = _fma(DO[..., c], O[..., c], D)
+    L = lse.cpu().numpy().reshape(B, H, S)
+    raw = scores(Q, K)
+    P = exp(_fma(raw, np.broadcast_to(scale, raw.shape), np.broadcast_to(-L[..., None], raw.shape)))
+    dS = P * (scores(DO, V) - D[..., None]) * scale
+    dq_, dk_, dv_ = (np.zeros((B, H, S, dh), dtype=f) for _ in range(3))
+    for j in range(S):
+        dq_ = np.where((rows >= j)[:, None], _fma(dS[..., j, None], K[..., j, None, :], dq_), dq_)
+        dv_ = np.where((rows <= j)[:, None], _fma(P[..., j, :, None], DO[..., j, None, :], dv_), dv_)
+        dk_ = np.where((rows <= j)[:, None], _fma(dS[..., j, :, None], Q[..., j, None, :], dk_), dk_)
+    for name, got, want in (("dq", dq, dq_), ("dk", dk, dk_), ("dv", dv, dv_)):
+        assert np.array_equal(heads(got), stored(want)), name
+
+
 # ------------------------------------------------------------------------------- whole training runs
 def run_pair(torch, w, steps, tau=None, N=1, gpu_kw=None, check_tables=True, **kw):
     params = wl.init_params(w)
