@@ -33,6 +33,7 @@
 #include <type_traits>
 
 #include "pm_common.hpp"
+#include "pm_slabs.hpp"
 #include "pm_elem.hpp"
 #include "pm_mfma_types.hpp"
 
@@ -420,7 +421,7 @@ inline bool pm_mfma_gemm_try(hipStream_t st, int I, int J, int K, const bf16_t* 
 // ---------------------------------------------------------------------------------------------
 template <int ROWS, bool KC>
 struct PmBigTile {                         // (ROWS x 64) operand slab in LDS
-  static constexpr int BK = 64;
+  static constexpr int BK = PM_SLAB;
   static constexpr int lds_rows = KC ? ROWS : BK;
   static constexpr int lds_cols = KC ? BK : ROWS;
   // KC: 16-byte fragment reads of 16 lanes cover all banks once with an 8-element pad.
@@ -443,14 +444,13 @@ struct PmBigLoader {
   // a wait behind every second one (1000 x 2048 x 2048 forward: 27.8 us against 20.8).
   template <bool CHECK, bool TAIL>
   __device__ __forceinline__ void load(const bf16_t* __restrict__ X, int64_t ld, int r0, int k0, int R, int K) {
-    const int Rl = KC ? R - 1 : ((R + 7) & ~7) - 8, Kl = KC ? ((K + 7) & ~7) - 8 : K - 1;     // last row / index (group of 8)
 #pragma unroll
     for (int p = 0; p < PER; ++p) {
       const int c = p * NT + threadIdx.x;
       const int lr = c / (S::lds_cols / 8), lc = (c % (S::lds_cols / 8)) * 8;
       int row = r0 + (KC ? lr : lc), k = k0 + (KC ? lc : lr);
-      if (CHECK && row > Rl) row = Rl;
-      if (CHECK && TAIL && k > Kl) k = Kl;
+      if (CHECK) row = pm_clamp_index<!KC>(row, R);
+      if (CHECK && TAIL) k = pm_clamp_index<KC>(k, K);
       r[p] = pm_ldg16(KC ? X + (int64_t)row * ld + k : X + (int64_t)k * ld + row);
     }
   }
@@ -531,7 +531,7 @@ struct PmKSeg3 {                     // pair 0 is the problem's own A and B
 template <class Cfg, bool AKC, bool BKC, bool CHECK, class Epi, class Seg = PmNoSeg>
 __device__ __forceinline__ void pm_gemm_big_body(const PmGemmProb<Epi>& pr, int id, int tiles_i, int tiles_j, bf16_t* smem,
                                                  bool xcd_remap = true, const Seg& sg = Seg()) {
-  constexpr int BI = Cfg::BI, BJ = Cfg::BJ, WI = Cfg::WI, WJ = Cfg::WJ, NT = Cfg::NT, BK = 64;
+  constexpr int BI = Cfg::BI, BJ = Cfg::BJ, WI = Cfg::WI, WJ = Cfg::WJ, NT = Cfg::NT, BK = PM_SLAB;
   constexpr int TI = BI / WI / 32, TJ = BJ / WJ / 32;
   using SA = PmBigTile<BI, AKC>;
   using SB = PmBigTile<BJ, BKC>;
@@ -616,12 +616,12 @@ __device__ __forceinline__ void pm_gemm_big_body(const PmGemmProb<Epi>& pr, int 
   __syncthreads();
 
   // one slab: fa / fb = register set that is free (refilled with slab kt + 2), na / nb = register set
-  // holding slab kt + 1 (moved to the other LDS stage).  steady (compile-time): slabs kt + 1 and
-  // kt + 2 exist and neither is the last one, so the loads and stores are unconditional and the compiler's wait counts before
-  // the LDS stores cover exactly the older register set.
-  auto slab = [&](auto steady, int kt, LA& fa_set, LB& fb_set, const LA& na_set, const LB& nb_set)
-                  __attribute__((always_inline)) {
-    constexpr bool STEADY = decltype(steady)::value;
+  // holding slab kt + 1 (moved to the other LDS stage).  Steady (compile-time, see pm_slab_walk): both exist and are whole,
+  // so the loads and stores are unconditional and the compiler's wait counts before the LDS stores cover exactly the
+  // older register set.
+  auto one_slab = [&](auto tag, int kt, LA& fa_set, LB& fb_set, const LA& na_set, const LB& nb_set)
+                      __attribute__((always_inline)) {
+    constexpr bool STEADY = decltype(tag)::STEADY;
     const int cur = kt & 1;
     const bf16_t* cA = smem + cur * STAGE;
     const bf16_t* cB = cA + SA::elems;
@@ -679,15 +679,10 @@ __device__ __forceinline__ void pm_gemm_big_body(const PmGemmProb<Epi>& pr, int 
     }
     __syncthreads();
   };
-  int kt = 0;
-  for (; kt + 3 < nk; kt += 2) {          // both slabs of the pair have successors kt + 2 and kt + 3
-    slab(std::true_type{}, kt, la0, lb0, la1, lb1);
-    slab(std::true_type{}, kt + 1, la1, lb1, la0, lb0);
-  }
-  for (; kt < nk; kt += 2) {              // the last one to three slabs
-    slab(std::false_type{}, kt, la0, lb0, la1, lb1);
-    if (kt + 1 < nk) slab(std::false_type{}, kt + 1, la1, lb1, la0, lb0);
-  }
+  pm_slab_walk(K, [&](auto tag, int kt) __attribute__((always_inline)) {
+    if constexpr (decltype(tag)::SET == 0) one_slab(tag, kt, la0, lb0, la1, lb1);
+    else one_slab(tag, kt, la1, lb1, la0, lb0);
+  });
 
   epi.begin();
   if (Epi::kColSumA && !AKC) {
