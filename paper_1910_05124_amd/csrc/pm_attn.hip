@@ -11,7 +11,7 @@
 
 namespace {
 // bf16 matrix instructions: whole tiles of 64-wide heads, or (ragged lengths, 32-wide heads) with the probabilities in
-// two terms
+// three terms
 template <int DH, bool RAGGED, bool SPLIT>
 void mfma_fwd(hipStream_t st, int B, int S, int H, const bf16_t* q, const bf16_t* k, const bf16_t* v, bf16_t* o, float* lse) {
   const int qblocks = (S + 127) / 128;

@@ -25,9 +25,10 @@
 // (24 x 100 tokens, 5 heads of 64, on the one-thread-per-row kernels that these lengths took before: forward 511 us,
 // backward 2090 us per layer, one wave per 64 rows walking 100 dependent keys; here 7 us and 18 us.)
 //
-// SPLIT: the second products take the probabilities (and dS) as two bf16 terms instead of one.  Whole tiles of 64-wide
-// heads round them to one bf16 value; the shapes that used to run on fp32 arithmetic (32-wide heads, ragged lengths)
-// keep sixteen mantissa bits through these products, for two more matrix instructions per tile and head half.
+// SPLIT: the second products take the probabilities (and dS) as three bf16 terms instead of one.  Whole tiles of 64-wide
+// heads round them to one bf16 value; the shapes that run on fp32 arithmetic otherwise (32-wide heads, ragged lengths)
+// keep all 24 mantissa bits through these products, for four more matrix instructions per tile and head half.  Two terms
+// (16 bits) took 6.6 + 16.2 us per layer of the example above against 7.1 + 17.7 and lost bits where a sum cancels.
 //
 // Probabilities are recomputed in the backward from q, k and the stored log-sum-exp of the scaled
 // scores; D_i = sum_c dO[i, c] O[i, c].  Two backward kernels (dQ; dK and dV) so that every output
@@ -67,39 +68,43 @@ __device__ __forceinline__ pm_bf16x8 pm_at_pack8(const float* x) {
   for (int e = 0; e < 4; ++e) u.w[e] = pm_pack_bf16(x[2 * e], x[2 * e + 1]);
   return u.v;
 }
-// eight values as two bf16 terms (the rounded values and what the rounding left): sixteen mantissa bits
-__device__ __forceinline__ void pm_at_split8(const float* x, pm_bf16x8* hi, pm_bf16x8* lo) {
-  *hi = pm_at_pack8(x);
-  union { pm_bf16x8 v; uint32_t w[4]; } u;
-  u.v = *hi;
+// eight values as three bf16 terms, each holding what the rounding of those before left: 24 mantissa bits
+__device__ __forceinline__ void pm_at_split8(const float* x, pm_bf16x8* t) {
   float r[8];
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    r[2 * e] = x[2 * e] - __uint_as_float(u.w[e] << 16);
-    r[2 * e + 1] = x[2 * e + 1] - __uint_as_float(u.w[e] & 0xffff0000u);
+  for (int e = 0; e < 8; ++e) r[e] = x[e];
+#pragma unroll
+  for (int n = 0; n < 3; ++n) {
+    t[n] = pm_at_pack8(r);
+    union { pm_bf16x8 v; uint32_t w[4]; } u;
+    u.v = t[n];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      r[2 * e] -= __uint_as_float(u.w[e] << 16);
+      r[2 * e + 1] -= __uint_as_float(u.w[e] & 0xffff0000u);
+    }
   }
-  *lo = pm_at_pack8(r);
 }
 // acc[dt] += X^T x: X the streamed tile in LDS (read transposed), x = 16 per-lane values of the second product's
-// contraction (the 32 streamed rows).  SPLIT: x in two bf16 terms, see below.
+// contraction (the 32 streamed rows).  SPLIT: x in three bf16 terms, the small ones first.
 template <int DH, bool SPLIT>
 __device__ __forceinline__ void pm_at_second(pm_f32x16* acc, const bf16_t* sX, const float* x, int lane) {
-  pm_bf16x8 h0, h1, l0, l1;
-  if (SPLIT) {
-    pm_at_split8(x, &h0, &l0);
-    pm_at_split8(x + 8, &h1, &l1);
+  constexpr int N = SPLIT ? 3 : 1;
+  pm_bf16x8 t0[N], t1[N];
+  if constexpr (SPLIT) {
+    pm_at_split8(x, t0);
+    pm_at_split8(x + 8, t1);
   } else {
-    h0 = pm_at_pack8(x);
-    h1 = pm_at_pack8(x + 8);
+    t0[0] = pm_at_pack8(x);
+    t1[0] = pm_at_pack8(x + 8);
   }
 #pragma unroll
   for (int dt = 0; dt < DH / 32; ++dt) {
     const pm_bf16x8 a0 = pm_at_frag_tr<DH>(sX, dt * 32, 0, lane), a1 = pm_at_frag_tr<DH>(sX, dt * 32, 16, lane);
-    acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, h0, acc[dt], 0, 0, 0);
-    acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, h1, acc[dt], 0, 0, 0);
-    if (SPLIT) {
-      acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, l0, acc[dt], 0, 0, 0);
-      acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, l1, acc[dt], 0, 0, 0);
+#pragma unroll
+    for (int n = N - 1; n >= 0; --n) {
+      acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, t0[n], acc[dt], 0, 0, 0);
+      acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, t1[n], acc[dt], 0, 0, 0);
     }
   }
 }

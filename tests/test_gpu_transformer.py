@@ -203,6 +203,48 @@ def test_fp32_attention_arithmetic_keeps_its_order(torch_cuda, dtype, B, S, H, d
         assert np.array_equal(heads(got), stored(want)), name
 
 
+def _cancelling(rng, p, n_cols):
+    """bf16 columns x with sum_j p[j] x[j] about 2^-17 of sum_j |p[j] x[j]|: a first value, its balance at the next
+    position, and what that leaves at the third."""
+    import torch
+    x = np.zeros((len(p), n_cols))
+    bf = lambda a: torch.from_numpy(a.astype(np.float32)).bfloat16().double().numpy()
+    x[0] = bf(rng.uniform(1, 2, n_cols) * rng.choice([-1, 1], n_cols))
+    x[1] = bf(-p[0] * x[0] / p[1])
+    x[2] = bf(-(p[0] * x[0] + p[1] * x[1]) / p[2])
+    return x
+
+
+@pytest.mark.parametrize("S,dh", [(33, 64), (20, 64), (126, 64), (32, 32), (65, 32), (248, 32)])
+def test_bf16_attention_outside_whole_tiles_keeps_fp32_probabilities(torch_cuda, S, dh):
+    """Ragged lengths and 32-wide heads in bf16 hold probabilities to 24 bits through the second products.  Seen where the sum
+    cancels: the last query's output, the first key's dv.  Bound: scores of up to 4, rounded in fp32, carry an absolute
+    error of about 2^-22 into an exponential, which is its relative one: 2^-21 of the sum of magnitudes; and the
+    output's own rounding, 2^-8 of it.  (Two bf16 terms leave up to 2^-17 per term, 2^-18.4 .. 2^-20 in these sums.)"""
+    import paper_1910_05124_amd as pm
+    torch = torch_cuda
+    rng = np.random.default_rng(S + dh)
+    bf = lambda a: torch.from_numpy(a.astype(np.float32)).cuda().bfloat16()
+    q, k = bf(rng.standard_normal((S, dh))), bf(rng.standard_normal((S, dh)))
+    Q, K = (t.double().cpu().numpy() for t in (q, k))
+    sc = Q @ K.T / math.sqrt(dh)
+    sc[np.triu_indices(S, 1)] = -np.inf
+    P = np.exp(sc - sc.max(-1, keepdims=True))
+    P /= P.sum(-1, keepdims=True)
+    V, DO = _cancelling(rng, P[-1], dh), _cancelling(rng, P[:, 0], dh)
+    v, do = bf(V), bf(DO)
+    o, dq, dk, dv = (torch.empty_like(q) for _ in range(4))
+    lse = torch.empty(S, dtype=torch.float32, device="cuda")
+    st = torch.cuda.current_stream().cuda_stream
+    pm.pm_attention_fwd(st, "bf16", 1, S, 1, dh, q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), lse.data_ptr())
+    pm.pm_attention_bwd(st, "bf16", 1, S, 1, dh, q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), do.data_ptr(),
+                        lse.data_ptr(), dq.data_ptr(), dk.data_ptr(), dv.data_ptr())
+    for name, got, w, x in (("o", o[-1], P[-1], V), ("dv", dv[0], P[:, 0], DO)):
+        want, size = w @ x, w @ np.abs(x)
+        err = np.abs(got.double().cpu().numpy() - want) - 2.0 ** -8 * np.abs(want)
+        assert np.all(err <= 2.0 ** -21 * size), (name, np.log2(np.max(err / size)))
+
+
 # ------------------------------------------------------------------------------- whole training runs
 def run_pair(torch, w, steps, tau=None, N=1, gpu_kw=None, check_tables=True, **kw):
     params = wl.init_params(w)
