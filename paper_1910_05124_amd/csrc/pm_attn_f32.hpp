@@ -21,6 +21,8 @@
 // One wave per block (the tiles are private, no barrier but the wave's own): a tile costs 64 clocks per contracted pair
 // - 2048 + 2048 clocks at DH = 64 - against 256 clocks to fetch it, so sharing tiles between waves would save nothing,
 // and these shapes (a few dozen heads, sequences of at most 8192 / (DH + 1) rows) need the blocks to fill the chip.
+// A masked row has probability zero, and zero times an infinity or NaN of its is NaN: where a tile with masked rows holds such
+// a value, its rows are added by hand (pm_at_add_row), each for the owned rows that see it.
 // 8 sequences of 64 tokens, 8 heads of 32: forward 85 -> 6 us, backward 161 -> 16 us per layer against one thread per row.
 #pragma once
 #include "pm_common.hpp"
@@ -153,6 +155,28 @@ __global__ __launch_bounds__(256) void pm_attn_f32_fwd_kernel(const T* __restric
 }
 
 // ---------------------------------------------------------------------------------------------
+// rows by hand, for tiles whose masked rows hold an infinity or NaN (also used by pm_attn_mfma.hpp)
+// ---------------------------------------------------------------------------------------------
+template <typename T, int DH>
+__device__ __forceinline__ float pm_at_dot(const T* a, const T* b) {
+  float s = 0.f;
+#pragma unroll 4
+  for (int c = 0; c < DH; ++c) s = fmaf(ldf(a + c), ldf(b + c), s);
+  return s;
+}
+// acc [head dimension][owned row] += w * row, in the lanes whose owned row sees it
+template <typename T, int DH>
+__device__ __forceinline__ void pm_at_add_row(pm_f32x16* acc, const T* row, float w, bool sees, int lane) {
+#pragma unroll
+  for (int dt = 0; dt < (DH + 31) / 32; ++dt)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int c = dt * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+      if (c < DH && sees) acc[dt][e] = fmaf(w, ldf(row + c), acc[dt][e]);
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
 // backward
 // ---------------------------------------------------------------------------------------------
 // 32 rows of X (row stride d, rows past the end re-read the last one): registers first, LDS later
@@ -166,6 +190,15 @@ __device__ __forceinline__ void pm_af_load(const T* X, int64_t d, int r0, int S,
     row = row < S ? row : S - 1;
     r[j] = pm_ld4(X + (int64_t)row * d + (c % (DH / 4)) * 4);
   }
+}
+// whether any lane's pieces hold a value that is not finite
+template <int N>
+__device__ __forceinline__ bool pm_af_odd(const float4* r) {
+  uint32_t top = 0;                                          // an exponent of all ones carries into the sign
+  auto carry = [](float f) { return (__float_as_uint(f) & 0x7f800000u) + 0x00800000u; };
+#pragma unroll
+  for (int j = 0; j < N; ++j) top |= carry(r[j].x) | carry(r[j].y) | carry(r[j].z) | carry(r[j].w);
+  return __builtin_amdgcn_ballot_w64((top & 0x80000000u) != 0) != 0;
 }
 // head-dimension entry c of a row in LDS: the even ones, then the odd ones
 template <int DH>
@@ -271,6 +304,7 @@ __global__ __launch_bounds__(64) void pm_attn_f32_dq_kernel(const T* __restrict_
   for (int jt = 0; jt <= qb; ++jt) {
     pm_af_park<DH>(sK, lane, rk);
     pm_af_park<DH>(sV, lane, rv);
+    const bool odd = jt == qb && pm_af_odd<A::PER>(rk);
     __syncthreads();
     if (jt < qb) {                                 // the next tile is on its way while this one is multiplied
       pm_af_load<T, DH>(k + base, d, (jt + 1) * 32, S, lane, rk);
@@ -284,7 +318,16 @@ __global__ __launch_bounds__(64) void pm_attn_f32_dq_kernel(const T* __restrict_
       ds[e] = p * (dp[e] - D) * scale;
       if (jt == qb && jt * 32 + 8 * (e >> 2) + 4 * g + (e & 3) > qi) ds[e] = 0.f;      // causal mask (keys past the end too)
     }
-    pm_af_second<DH>(acc, sK, ds, lane);
+    if (odd) {
+#pragma unroll 1
+      for (int j = q0; j < S && j < q0 + 32; ++j) {
+        const int64_t rj = base + (int64_t)j * d, ri = base + (int64_t)qr * d;
+        const float pj = pm_af_exp(fmaf(pm_at_dot<T, DH>(q + ri, k + rj), scale, -L));
+        pm_at_add_row<T, DH>(acc, k + rj, pj * (pm_at_dot<T, DH>(dO + ri, v + rj) - D) * scale, j <= qi, lane);
+      }
+    } else {
+      pm_af_second<DH>(acc, sK, ds, lane);
+    }
     __syncthreads();
   }
   if (qi < S) pm_af_store<T, DH>(dq + base + (int64_t)qi * d, acc, lane);
@@ -327,6 +370,7 @@ __global__ __launch_bounds__(64) void pm_attn_f32_dkv_kernel(const T* __restrict
     pm_af_park<DH>(sQ, lane, rq);
     pm_af_park<DH>(sO, lane, rd);
     pm_af_park<DH>(sX, lane, ro);
+    const bool odd = (it == kb || it * 32 + 32 > S) && (pm_af_odd<A::PER>(rq) | pm_af_odd<A::PER>(rd));
     if (lane < 32) sL[lane] = L;
     __syncthreads();
     if (it + 1 < n_tiles) load(it + 1);
@@ -350,8 +394,19 @@ __global__ __launch_bounds__(64) void pm_attn_f32_dkv_kernel(const T* __restrict
       ds[e] = p[e] * (dp[e] - sD[r]) * scale;
       if (qi < ki || qi >= S) p[e] = ds[e] = 0.f;
     }
-    pm_af_second<DH>(av, sO, p, lane);
-    pm_af_second<DH>(ak, sQ, ds, lane);
+    if (odd) {
+#pragma unroll 1
+      for (int i = it * 32; i < S && i < it * 32 + 32; ++i) {
+        const int64_t ri = base + (int64_t)i * d, rj = base + (int64_t)kr * d;
+        const float pi = pm_af_exp(fmaf(pm_at_dot<T, DH>(q + ri, k + rj), scale, -sL[i - it * 32]));
+        const float di = pi * (pm_at_dot<T, DH>(dO + ri, v + rj) - sD[i - it * 32]) * scale;
+        pm_at_add_row<T, DH>(av, dO + ri, pi, i >= ki, lane);
+        pm_at_add_row<T, DH>(ak, q + ri, di, i >= ki, lane);
+      }
+    } else {
+      pm_af_second<DH>(av, sO, p, lane);
+      pm_af_second<DH>(ak, sQ, ds, lane);
+    }
     __syncthreads();
   }
   if (ki < S) {

@@ -23,18 +23,24 @@
 // Streamed keys past the end lie behind every query that is stored and fall to the causal mask; only the dK/dV
 // kernel, whose streamed index is the query, masks its last tile explicitly.
 // (24 x 100 tokens, 5 heads of 64, on the one-thread-per-row kernels that these lengths took before: forward 511 us,
-// backward 2090 us per layer, one wave per 64 rows walking 100 dependent keys; here 7 us and 18 us.)
+// backward 2090 us per layer, one wave per 64 rows walking 100 dependent keys; here 8 us and 20 us.)
 //
 // SPLIT: the second products take the probabilities (and dS) as three bf16 terms instead of one.  Whole tiles of 64-wide
 // heads round them to one bf16 value; the shapes that run on fp32 arithmetic otherwise (32-wide heads, ragged lengths)
 // keep all 24 mantissa bits through these products, for four more matrix instructions per tile and head half.  Two terms
 // (16 bits) took 6.6 + 16.2 us per layer of the example above against 7.1 + 17.7 and lost bits where a sum cancels.
 //
+// A masked row has probability zero, and zero times an infinity or NaN of its is NaN.  The SPLIT shapes keep such a value from
+// rows that the mask keeps it from: where a tile with masked rows holds one, its second product is left out and its rows
+// are added by hand at the end (pm_at_add_row), each for the owned rows that see it.  (The look at those tiles and the
+// code behind it: 7.1 + 17.7 -> 7.7 + 19.7 us per layer of the example above.)
+//
 // Probabilities are recomputed in the backward from q, k and the stored log-sum-exp of the scaled
 // scores; D_i = sum_c dO[i, c] O[i, c].  Two backward kernels (dQ; dK and dV) so that every output
 // has one owner and no atomics are needed.
 #pragma once
 #include "pm_attn_api.hpp"
+#include "pm_attn_f32.hpp"
 #include "pm_common.hpp"
 #include "pm_mfma_types.hpp"
 
@@ -108,6 +114,18 @@ __device__ __forceinline__ void pm_at_second(pm_f32x16* acc, const bf16_t* sX, c
     }
   }
 }
+// whether the tile holds a value that is not finite (every lane looks at half a row; uniform over the wave)
+template <int DH>
+__device__ __forceinline__ bool pm_at_odd(const bf16_t* s, int lane) {
+  uint32_t top = 0;                                          // an exponent of all ones carries into the sign
+#pragma unroll
+  for (int c = 0; c < DH / 16; ++c) {
+    const uint4 u = *reinterpret_cast<const uint4*>(s + (lane & 31) * PM_AT_ST<DH> + (lane >> 5) * (DH / 2) + 8 * c);
+    auto carry = [](uint32_t w) { return (w & 0x7f807f80u) + 0x00800080u; };
+    top |= carry(u.x) | carry(u.y) | carry(u.z) | carry(u.w);
+  }
+  return __builtin_amdgcn_ballot_w64((top & 0x80008000u) != 0) != 0;
+}
 // result tile [DH x 32] held as DH / 32 accumulators (MFMA rows = head dimension, column = owned row):
 // store transposed into out[row0 + lane % 32][0 .. DH - 1] (bf16), 4 consecutive head-dimension entries at a time
 template <int DH>
@@ -129,9 +147,10 @@ __device__ __forceinline__ void pm_at_store_t(bf16_t* out_row, const pm_f32x16* 
 // double-buffered in LDS (one barrier per tile).
 // ---------------------------------------------------------------------------------------------
 // (register budget of four waves per SIMD: two values spill, and the fourth wave is worth more - 26.2 -> 24.7 us on
-// 16 x 512 tokens, 16 heads; the dQ kernel would spill 34 and is left at three)
+// 16 x 512 tokens, 16 heads; the dQ kernel would spill 34 and is left at three.  SPLIT, 64 wide: three as well, 9.3 -> 7.7 us
+// on 24 x 100 tokens, 5 heads; 32 wide four, 15.4 -> 12.9 us on 256 x 32 tokens, 16 heads)
 template <int DH, bool RAGGED, bool SPLIT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void pm_attn_mfma_fwd_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SPLIT && DH == 64 ? 3 : 4, SPLIT && DH == 64 ? 3 : 4))) void pm_attn_mfma_fwd_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
                                                                const bf16_t* __restrict__ v, bf16_t* __restrict__ o,
                                                                float* __restrict__ lse, int S, int H, int BH, float scale) {
   __shared__ __attribute__((aligned(16))) bf16_t sK[2][32 * PM_AT_ST<DH>];
@@ -180,6 +199,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
   __syncthreads();
   const int prow = pm_at_perm(ql);
   const float c2 = scale * 1.44269504f;            // scores in base-2 units: exp(x) = exp2(x log2 e)
+  bool odd = false;
   auto tile = [&](int jt, int cur) __attribute__((always_inline)) {
     if (active && jt <= my_last) {
       pm_f32x16 s;
@@ -195,7 +215,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
           const int kidx = jt * 32 + 16 * (e >> 3) + 8 * g + (e & 7);
-          if (kidx > q0 + ql) p[e] = -3.0e38f;
+          // (SPLIT: minus infinity, so that a row whose scores are all of them minus infinity takes nothing from it)
+          if (kidx > q0 + ql) p[e] = SPLIT ? -__builtin_inff() : -3.0e38f;
         }
       }
 #pragma unroll
@@ -217,7 +238,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
           for (int e = 0; e < 16; ++e) acc[dt][e] *= corr;
       }
       m = mn;
-      pm_at_second<DH, SPLIT>(acc, sV[cur], p, lane);
+      if (SPLIT && jt == my_last) odd = pm_at_odd<DH>(sV[cur], lane);
+      if (!SPLIT || !odd) pm_at_second<DH, SPLIT>(acc, sV[cur], p, lane);
     }
   };
   // steady part: the loads are unconditional, so the compiler counts outstanding loads exactly and the
@@ -247,6 +269,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
   }
   if (active) {
     lsum += __shfl_xor(lsum, 32, 64);
+    if (SPLIT && odd) {
+#pragma unroll 1
+      for (int j = q0; j < S && j < q0 + 32; ++j) {
+        const int64_t rj = base + (int64_t)j * d;
+        const float pj = __builtin_amdgcn_exp2f(pm_at_dot<bf16_t, DH>(q + base + (int64_t)qr * d, k + rj) * c2 - m);
+        pm_at_add_row<bf16_t, DH>(acc, v + rj, pj, j <= q0 + ql, lane);
+      }
+    }
     if (RAGGED && q0 + ql >= S) return;
     pm_at_store_t<DH>(o + base + (int64_t)(q0 + ql) * d, acc, 1.f / lsum, lane);
     if (g == 0) lse[((int64_t)b * H + h) * S + q0 + ql] = m * 0.693147181f + __logf(lsum);   // m is in base-2 units
@@ -322,6 +352,7 @@ __global__ __launch_bounds__(256) void pm_attn_mfma_dq_kernel(const bf16_t* __re
   __syncthreads();
   const int prow = pm_at_perm(ql);
   const float c2 = scale * 1.44269504f, lq2 = lq * 1.44269504f;       // base-2 units: exp(x) = exp2(x log2 e)
+  bool odd = false;
   auto tile = [&](int jt, int cur) __attribute__((always_inline)) {
     if (active && jt <= my_last) {
       pm_f32x16 s, dp;
@@ -345,7 +376,8 @@ __global__ __launch_bounds__(256) void pm_attn_mfma_dq_kernel(const bf16_t* __re
           if (kidx > q0 + ql) ds[e] = 0.f;
         }
       }
-      pm_at_second<DH, SPLIT>(acc, sK[cur], ds, lane);
+      if (SPLIT && jt == my_last) odd = pm_at_odd<DH>(sK[cur], lane);
+      if (!SPLIT || !odd) pm_at_second<DH, SPLIT>(acc, sK[cur], ds, lane);
     }
   };
   // steady part: the loads are unconditional, so the compiler counts outstanding loads exactly and the
@@ -371,6 +403,14 @@ __global__ __launch_bounds__(256) void pm_attn_mfma_dq_kernel(const bf16_t* __re
       tile(jt + 1, 1);
       if (jt + 2 < n_tiles) sstore(0, rk0, rv0);
       __syncthreads();
+    }
+  }
+  if (SPLIT && active && odd) {
+#pragma unroll 1
+    for (int j = q0; j < S && j < q0 + 32; ++j) {
+      const int64_t rj = base + (int64_t)j * d, ri = base + (int64_t)qr * d;
+      const float pj = __builtin_amdgcn_exp2f(fmaf(pm_at_dot<bf16_t, DH>(q + ri, k + rj), c2, -lq2));
+      pm_at_add_row<bf16_t, DH>(acc, k + rj, pj * (pm_at_dot<bf16_t, DH>(dO + ri, v + rj) - Dq), j <= q0 + ql, lane);
     }
   }
   if (active && (!RAGGED || q0 + ql < S)) pm_at_store_t<DH>(dq + base + (int64_t)(q0 + ql) * d, acc, scale, lane);
@@ -461,6 +501,7 @@ __global__ __launch_bounds__(256) void pm_attn_mfma_dkv_kernel(const bf16_t* __r
   __syncthreads();
   const int prow = pm_at_perm(kl);
   const float c2 = scale * 1.44269504f;
+  bool odd_first = false, odd_last = false;
   auto tile = [&](int it, int cur) __attribute__((always_inline)) {
     if (active && it >= my_first) {
       pm_f32x16 s, dp;
@@ -485,23 +526,31 @@ __global__ __launch_bounds__(256) void pm_attn_mfma_dkv_kernel(const bf16_t* __r
         Dv[4 * c4] = d4.x; Dv[4 * c4 + 1] = d4.y; Dv[4 * c4 + 2] = d4.z; Dv[4 * c4 + 3] = d4.w;
       }
 #pragma unroll
-      for (int e = 0; e < 16; ++e) p[e] = __builtin_amdgcn_exp2f(fmaf(s[e], c2, -lv[e]));
+      for (int e = 0; e < 16; ++e) {
+        p[e] = __builtin_amdgcn_exp2f(fmaf(s[e], c2, -lv[e]));
+        ds[e] = p[e] * (dp[e] - Dv[e]);           // the factor 1 / sqrt(dh) goes into the final store
+      }
       if (it == my_first) {                       // the diagonal tile (uniform over the wave): causal mask
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
           const int qidx = it * 32 + 16 * (e >> 3) + 8 * g + (e & 7);
-          if (qidx < k0 + kl) p[e] = 0.f;
+          if (qidx < k0 + kl) p[e] = ds[e] = 0.f;
         }
       }
       if (RAGGED && it * 32 + 32 > S) {           // the last tile: queries past the end
 #pragma unroll
         for (int e = 0; e < 16; ++e)
-          if (it * 32 + 16 * (e >> 3) + 8 * g + (e & 7) >= S) p[e] = 0.f;
+          if (it * 32 + 16 * (e >> 3) + 8 * g + (e & 7) >= S) p[e] = ds[e] = 0.f;
       }
-#pragma unroll
-      for (int e = 0; e < 16; ++e) ds[e] = p[e] * (dp[e] - Dv[e]);       // the factor 1 / sqrt(dh) goes into the final store
-      pm_at_second<DH, SPLIT>(av, sO[cur], p, lane);
-      pm_at_second<DH, SPLIT>(ak, sQ[cur], ds, lane);
+      bool by_hand = false;
+      if (SPLIT && (it == my_first || it * 32 + 32 > S)) {
+        by_hand = pm_at_odd<DH>(sO[cur], lane) | pm_at_odd<DH>(sQ[cur], lane);
+        if (by_hand) (it == my_first ? odd_first : odd_last) = true;
+      }
+      if (!SPLIT || !by_hand) {
+        pm_at_second<DH, SPLIT>(av, sO[cur], p, lane);
+        pm_at_second<DH, SPLIT>(ak, sQ[cur], ds, lane);
+      }
     }
   };
   int it = first;
@@ -525,6 +574,18 @@ __global__ __launch_bounds__(256) void pm_attn_mfma_dkv_kernel(const bf16_t* __r
       if (it + 2 < n_tiles) sstore(0, r0);
       __syncthreads();
     }
+  }
+  if (SPLIT && active && (odd_first || odd_last)) {
+#pragma unroll 1
+    for (int it2 = odd_first ? my_first : n_tiles - 1; it2 < n_tiles; it2 = it2 == n_tiles - 1 || !odd_last ? n_tiles : n_tiles - 1)
+#pragma unroll 1
+      for (int i = it2 * 32; i < S && i < it2 * 32 + 32; ++i) {
+        const int64_t ri = base + (int64_t)i * d, rj = base + (int64_t)kr * d;
+        const float pi = __builtin_amdgcn_exp2f(fmaf(pm_at_dot<bf16_t, DH>(q + ri, k + rj), c2, -lse[lbase + i] * 1.44269504f));
+        const float di = pi * (pm_at_dot<bf16_t, DH>(dO + ri, v + rj) - pm_at_dot<bf16_t, DH>(dO + ri, o + ri));
+        pm_at_add_row<bf16_t, DH>(av, dO + ri, pi, i >= k0 + kl, lane);
+        pm_at_add_row<bf16_t, DH>(ak, q + ri, di, i >= k0 + kl, lane);
+      }
   }
   if (active && (!RAGGED || k0 + kl < S)) {
     pm_at_store_t<DH>(dk + base + (int64_t)(k0 + kl) * d, ak, scale, lane);

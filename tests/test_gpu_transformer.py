@@ -245,6 +245,64 @@ def test_bf16_attention_outside_whole_tiles_keeps_fp32_probabilities(torch_cuda,
         assert np.all(err <= 2.0 ** -21 * size), (name, np.log2(np.max(err / size)))
 
 
+@pytest.mark.parametrize("bad", ["nan", "inf"])
+@pytest.mark.parametrize("dtype,S,dh", [("f32", 50, 64), ("f32", 33, 32), ("f32", 70, 16), ("f32", 20, 4), ("bf16", 45, 64), ("bf16", 165, 32),
+                                        ("bf16", 64, 32), ("bf16", 126, 64), ("bf16", 40, 8)])
+def test_attention_mask_stops_infinities_and_nans(torch_cuda, dtype, S, dh, bad):
+    """Outside whole bf16 tiles a later key or value, or an earlier query or output gradient, that is infinite or NaN reaches
+    no row that the causal mask keeps it from (its probability is zero there, and zero times infinity would be NaN); the
+    rows that see it are no longer finite.  fp32: the other rows keep their bits but for the order of a sum (2^-20 of the
+    largest value); bf16: one rounding of the output."""
+    import paper_1910_05124_amd as pm
+    torch = torch_cuda
+    tdt = _tdt(torch, dtype)
+    rng = np.random.default_rng(S * 3 + dh)
+    H, cut = 2, S - 7                                       # inside the last tile, with rows on both sides
+    val = float(bad)
+    st = torch.cuda.current_stream().cuda_stream
+
+    def fresh():
+        return [torch.from_numpy(a).cuda().to(tdt) for a in clean]
+
+    def fwd(t):
+        o, lse = torch.empty_like(t[0]), torch.empty(H * S, dtype=torch.float32, device="cuda")
+        pm.pm_attention_fwd(st, dtype, 1, S, H, dh, *(x.data_ptr() for x in t[:3]), o.data_ptr(), lse.data_ptr())
+        return o, lse
+
+    def bwd(t, o, lse):
+        out = [torch.empty_like(o) for _ in range(3)]
+        pm.pm_attention_bwd(st, dtype, 1, S, H, dh, *(x.data_ptr() for x in t[:3]), o.data_ptr(), t[3].data_ptr(), lse.data_ptr(),
+                            *(x.data_ptr() for x in out))
+        return out
+
+    def same(got, want):
+        got, want = got.float().cpu().numpy(), want.float().cpu().numpy()
+        tol = 2.0 ** (-20 if dtype == "f32" else -8)
+        assert np.all(np.isfinite(got)) and np.max(np.abs(got - want)) <= tol * np.max(np.abs(want))
+
+    clean = [rng.standard_normal((S, H * dh)).astype(np.float32) for _ in range(4)]
+    t = fresh()
+    o, lse = fwd(t)
+    grads = bwd(t, o, lse)
+    for which in (1, 2):                                    # keys, values from `cut` on
+        t = fresh()
+        t[which][cut:] = val
+        ob, lb = fwd(t)
+        same(ob[:cut], o[:cut])
+        assert not torch.isfinite(ob[cut:]).any()
+        dqb = bwd(t, o, lse)[0]
+        same(dqb[:cut], grads[0][:cut])
+        assert not torch.isfinite(dqb[cut:]).all()
+    for first in (3, S - 32 if S > 40 else 3):              # queries, output gradients, outputs up to `first`
+        for which in (0, 3, 4):
+            t, oo = fresh(), o.clone()
+            (t + [oo])[which][:first] = val
+            _, dkb, dvb = bwd(t, oo, lse)
+            same(dkb[first:], grads[1][first:])
+            same(dvb[first:], grads[2][first:])
+            assert not torch.isfinite(dkb[:first]).all()
+
+
 # ------------------------------------------------------------------------------- whole training runs
 def run_pair(torch, w, steps, tau=None, N=1, gpu_kw=None, check_tables=True, **kw):
     params = wl.init_params(w)
