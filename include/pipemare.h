@@ -347,7 +347,9 @@ pm_status pm_linear_bwd_weight(void* stream, int32_t dtype, int32_t M, int32_t n
  *                  are added to (caller zeroes them)
  *   attention_fwd: causal softmax(q k^T / sqrt(dh)) v per (sequence, head); q, k, v, o T [B*S, H*dh], head h in
  *                  columns h*dh..; lse fp32 [B, H, S] receives log-sum-exp of the scaled scores
- *   attention_bwd: gradients dq, dk, dv T [B*S, H*dh] from do, recomputing probabilities from q, k, lse */
+ *   attention_bwd: gradients dq, dk, dv T [B*S, H*dh] from do, recomputing probabilities from q, k, lse
+ *                  bf16 with dh = 64 and S a multiple of 32 needs 16-byte aligned tensors; otherwise they may start at any
+ *                  element */
 pm_status pm_layernorm_fwd(void* stream, int32_t dtype, int32_t rows, int32_t d, const float* x_dev,
                            const void* gain_dev, const void* bias_dev, void* y_dev, float* mean_dev, float* rstd_dev);
 pm_status pm_layernorm_bwd(void* stream, int32_t dtype, int32_t rows, int32_t d, const float* dy_dev,

@@ -1,5 +1,6 @@
-// Causal attention core in fp32 arithmetic, for fp32 contexts and for bf16 tensors with heads narrower than 32, gfx950.
-// T: element type of the tensors in memory; everything inside is fp32.
+// Causal attention core in fp32 arithmetic, for fp32 contexts and for bf16 tensors with heads narrower than 32
+// or off the alignment of the bf16 kernels, gfx950.
+// T: element type of the tensors in memory; everything inside is fp32.  VEC: see pm_af_ld4.
 //
 // Order of the sums.  Scores are one chain of fused multiply-adds over the head dimension, the forward pass takes its keys
 // one after the other (running maximum and sum, every earlier value scaled when the maximum moves), and a gradient row is one
@@ -37,6 +38,31 @@ struct PmAf {
   static constexpr int PER = (PIECES + 63) / 64;          // pieces per lane
   static constexpr int ELEMS = 32 * ST + 32;              // a narrow head's column reads run past its rows
 };
+// Four consecutive elements of a tensor that starts anywhere: fp32 tensors are read and written 16 bytes at a time (a
+// memory access of that width needs 4-byte alignment), bf16 ones 8 bytes with VEC (8-byte alignment), else element by element.
+typedef float pm_f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+template <bool VEC>
+__device__ __forceinline__ float4 pm_af_ld4(const float* p) {
+  const pm_f32x4_any v = *reinterpret_cast<const pm_f32x4_any*>(p);
+  return make_float4(v.x, v.y, v.z, v.w);
+}
+template <bool VEC>
+__device__ __forceinline__ float4 pm_af_ld4(const bf16_t* p) {
+  if constexpr (VEC) return pm_ld4(p);
+  else return make_float4(ldf(p), ldf(p + 1), ldf(p + 2), ldf(p + 3));
+}
+template <bool VEC>
+__device__ __forceinline__ void pm_af_st4(float* p, float4 x) {
+  *reinterpret_cast<pm_f32x4_any*>(p) = pm_f32x4_any{x.x, x.y, x.z, x.w};
+}
+template <bool VEC>
+__device__ __forceinline__ void pm_af_st4(bf16_t* p, float4 x) {
+  if constexpr (VEC) {
+    pm_st4(p, x);
+  } else {
+    stf(p, x.x); stf(p + 1, x.y); stf(p + 2, x.z); stf(p + 3, x.w);
+  }
+}
 __device__ __forceinline__ float pm_af_exp(float x) { return __builtin_amdgcn_exp2f(x * 1.44269504f); }
 
 // ---------------------------------------------------------------------------------------------
@@ -71,7 +97,7 @@ __device__ __forceinline__ void pm_af_keys(float corr, float p, const float* v, 
 }
 
 // blockIdx.x = block of 16 query rows * BH + (sequence, head); wave w takes rows 4 w .. 4 w + 3, lanes 16 r .. 16 r + 15 row r
-template <typename T, int DH>
+template <typename T, int DH, bool VEC>
 __global__ __launch_bounds__(256) void pm_attn_f32_fwd_kernel(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
                                                               T* __restrict__ o, float* __restrict__ lse, int S, int H, int BH,
                                                               float scale) {
@@ -85,7 +111,7 @@ __global__ __launch_bounds__(256) void pm_attn_f32_fwd_kernel(const T* __restric
   float qi[DH];
 #pragma unroll
   for (int c = 0; c < DH; c += 4) {
-    const float4 x = pm_ld4(q + base + (int64_t)i * d + c);
+    const float4 x = pm_af_ld4<VEC>(q + base + (int64_t)i * d + c);
     qi[c] = x.x * scale; qi[c + 1] = x.y * scale; qi[c + 2] = x.z * scale; qi[c + 3] = x.w * scale;
   }
   float4 rk[PER], rv[PER];
@@ -96,8 +122,8 @@ __global__ __launch_bounds__(256) void pm_attn_f32_fwd_kernel(const T* __restric
       int r = tile * 32 + c / (DH / 4);
       r = r < S ? r : S - 1;
       const int64_t at = base + (int64_t)r * d + (c % (DH / 4)) * 4;
-      rk[j] = pm_ld4(k + at);
-      rv[j] = pm_ld4(v + at);
+      rk[j] = pm_af_ld4<VEC>(k + at);
+      rv[j] = pm_af_ld4<VEC>(v + at);
     }
   };
   auto park = [&]() __attribute__((always_inline)) {
@@ -180,7 +206,7 @@ __device__ __forceinline__ void pm_at_add_row(pm_f32x16* acc, const T* row, floa
 // backward
 // ---------------------------------------------------------------------------------------------
 // 32 rows of X (row stride d, rows past the end re-read the last one): registers first, LDS later
-template <typename T, int DH>
+template <typename T, int DH, bool VEC>
 __device__ __forceinline__ void pm_af_load(const T* X, int64_t d, int r0, int S, int lane, float4* r) {
   using A = PmAf<DH>;
 #pragma unroll
@@ -188,7 +214,7 @@ __device__ __forceinline__ void pm_af_load(const T* X, int64_t d, int r0, int S,
     const int c = (lane + 64 * j) % A::PIECES;            // (fewer pieces than lanes: fetched more than once)
     int row = r0 + c / (DH / 4);
     row = row < S ? row : S - 1;
-    r[j] = pm_ld4(X + (int64_t)row * d + (c % (DH / 4)) * 4);
+    r[j] = pm_af_ld4<VEC>(X + (int64_t)row * d + (c % (DH / 4)) * 4);
   }
 }
 // whether any lane's pieces hold a value that is not finite
@@ -215,11 +241,11 @@ __device__ __forceinline__ void pm_af_park(float* s, int lane, const float4* r) 
   }
 }
 // this lane's entries 2 c + g of a row of X
-template <typename T, int DH>
+template <typename T, int DH, bool VEC>
 __device__ __forceinline__ void pm_af_own(const T* X, int64_t d, int row, int g, float* x) {
 #pragma unroll
   for (int c = 0; c < DH; c += 4) {
-    const float4 v = pm_ld4(X + (int64_t)row * d + c);
+    const float4 v = pm_af_ld4<VEC>(X + (int64_t)row * d + c);
     x[c / 2] = g ? v.y : v.x;
     x[c / 2 + 1] = g ? v.w : v.z;
   }
@@ -257,19 +283,19 @@ __device__ __forceinline__ void pm_af_second(pm_f32x16* acc, const float* s, con
     step(8 * a + 6, __uint_as_float(w1[1]));
   }
 }
-template <typename T, int DH>
+template <typename T, int DH, bool VEC>
 __device__ __forceinline__ void pm_af_store(T* out_row, const pm_f32x16* acc, int lane) {
 #pragma unroll
   for (int dt = 0; dt < PmAf<DH>::NDT; ++dt)
 #pragma unroll
     for (int a = 0; a < 4; ++a) {
       const int c = dt * 32 + 8 * a + 4 * (lane >> 5);
-      if (c < DH) pm_st4(out_row + c, make_float4(acc[dt][4 * a], acc[dt][4 * a + 1], acc[dt][4 * a + 2], acc[dt][4 * a + 3]));
+      if (c < DH) pm_af_st4<VEC>(out_row + c, make_float4(acc[dt][4 * a], acc[dt][4 * a + 1], acc[dt][4 * a + 2], acc[dt][4 * a + 3]));
     }
 }
 
 // blockIdx.x = block of 32 owned rows * BH + (sequence, head)
-template <typename T, int DH>
+template <typename T, int DH, bool VEC>
 __global__ __launch_bounds__(64) void pm_attn_f32_dq_kernel(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
                                                             const T* __restrict__ o, const T* __restrict__ dO,
                                                             const float* __restrict__ lse, T* __restrict__ dq, int S, int H, int BH,
@@ -283,7 +309,7 @@ __global__ __launch_bounds__(64) void pm_attn_f32_dq_kernel(const T* __restrict_
   float own[A::HALF], od[A::HALF], D = 0.f;
 #pragma unroll
   for (int c = 0; c < DH; c += 4) {
-    const float4 x = pm_ld4(dO + base + (int64_t)qr * d + c), y = pm_ld4(o + base + (int64_t)qr * d + c);
+    const float4 x = pm_af_ld4<VEC>(dO + base + (int64_t)qr * d + c), y = pm_af_ld4<VEC>(o + base + (int64_t)qr * d + c);
     D = fmaf(x.x, y.x, D);
     D = fmaf(x.y, y.y, D);
     D = fmaf(x.z, y.z, D);
@@ -291,7 +317,7 @@ __global__ __launch_bounds__(64) void pm_attn_f32_dq_kernel(const T* __restrict_
     od[c / 2] = g ? x.y : x.x;
     od[c / 2 + 1] = g ? x.w : x.z;
   }
-  pm_af_own<T, DH>(q + base, d, qr, g, own);
+  pm_af_own<T, DH, VEC>(q + base, d, qr, g, own);
   const float L = lse[((int64_t)b * H + h) * S + qr];
   pm_f32x16 acc[A::NDT];
 #pragma unroll
@@ -299,16 +325,16 @@ __global__ __launch_bounds__(64) void pm_attn_f32_dq_kernel(const T* __restrict_
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[dt][e] = 0.f;
   float4 rk[A::PER], rv[A::PER];
-  pm_af_load<T, DH>(k + base, d, 0, S, lane, rk);
-  pm_af_load<T, DH>(v + base, d, 0, S, lane, rv);
+  pm_af_load<T, DH, VEC>(k + base, d, 0, S, lane, rk);
+  pm_af_load<T, DH, VEC>(v + base, d, 0, S, lane, rv);
   for (int jt = 0; jt <= qb; ++jt) {
     pm_af_park<DH>(sK, lane, rk);
     pm_af_park<DH>(sV, lane, rv);
     const bool odd = jt == qb && pm_af_odd<A::PER>(rk);
     __syncthreads();
     if (jt < qb) {                                 // the next tile is on its way while this one is multiplied
-      pm_af_load<T, DH>(k + base, d, (jt + 1) * 32, S, lane, rk);
-      pm_af_load<T, DH>(v + base, d, (jt + 1) * 32, S, lane, rv);
+      pm_af_load<T, DH, VEC>(k + base, d, (jt + 1) * 32, S, lane, rk);
+      pm_af_load<T, DH, VEC>(v + base, d, (jt + 1) * 32, S, lane, rv);
     }
     const pm_f32x16 s = pm_af_scores<DH>(sK, own, lane), dp = pm_af_scores<DH>(sV, od, lane);
     float ds[16];
@@ -330,10 +356,10 @@ __global__ __launch_bounds__(64) void pm_attn_f32_dq_kernel(const T* __restrict_
     }
     __syncthreads();
   }
-  if (qi < S) pm_af_store<T, DH>(dq + base + (int64_t)qi * d, acc, lane);
+  if (qi < S) pm_af_store<T, DH, VEC>(dq + base + (int64_t)qi * d, acc, lane);
 }
 
-template <typename T, int DH>
+template <typename T, int DH, bool VEC>
 __global__ __launch_bounds__(64) void pm_attn_f32_dkv_kernel(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
                                                              const T* __restrict__ o, const T* __restrict__ dO,
                                                              const float* __restrict__ lse, T* __restrict__ dk, T* __restrict__ dv,
@@ -345,8 +371,8 @@ __global__ __launch_bounds__(64) void pm_attn_f32_dkv_kernel(const T* __restrict
   const int64_t base = (int64_t)b * S * d + (int64_t)h * DH;
   const int ki = kb * 32 + kl, kr = ki < S ? ki : S - 1;
   float ok[A::HALF], ov[A::HALF];
-  pm_af_own<T, DH>(k + base, d, kr, g, ok);
-  pm_af_own<T, DH>(v + base, d, kr, g, ov);
+  pm_af_own<T, DH, VEC>(k + base, d, kr, g, ok);
+  pm_af_own<T, DH, VEC>(v + base, d, kr, g, ov);
   pm_f32x16 ak[A::NDT], av[A::NDT];
 #pragma unroll
   for (int dt = 0; dt < A::NDT; ++dt)
@@ -359,9 +385,9 @@ __global__ __launch_bounds__(64) void pm_attn_f32_dkv_kernel(const T* __restrict
   float4 rq[A::PER], rd[A::PER], ro[A::PER];
   float L = 0.f;
   auto load = [&](int it) __attribute__((always_inline)) {
-    pm_af_load<T, DH>(q + base, d, it * 32, S, lane, rq);
-    pm_af_load<T, DH>(dO + base, d, it * 32, S, lane, rd);
-    pm_af_load<T, DH>(o + base, d, it * 32, S, lane, ro);
+    pm_af_load<T, DH, VEC>(q + base, d, it * 32, S, lane, rq);
+    pm_af_load<T, DH, VEC>(dO + base, d, it * 32, S, lane, rd);
+    pm_af_load<T, DH, VEC>(o + base, d, it * 32, S, lane, ro);
     const int row = it * 32 + kl;
     L = lse[((int64_t)b * H + h) * S + (row < S ? row : S - 1)];
   };
@@ -410,7 +436,7 @@ __global__ __launch_bounds__(64) void pm_attn_f32_dkv_kernel(const T* __restrict
     __syncthreads();
   }
   if (ki < S) {
-    pm_af_store<T, DH>(dk + base + (int64_t)ki * d, ak, lane);
-    pm_af_store<T, DH>(dv + base + (int64_t)ki * d, av, lane);
+    pm_af_store<T, DH, VEC>(dk + base + (int64_t)ki * d, ak, lane);
+    pm_af_store<T, DH, VEC>(dv + base + (int64_t)ki * d, av, lane);
   }
 }

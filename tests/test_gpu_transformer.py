@@ -303,6 +303,40 @@ def test_attention_mask_stops_infinities_and_nans(torch_cuda, dtype, S, dh, bad)
             assert not torch.isfinite(dkb[:first]).all()
 
 
+@pytest.mark.parametrize("shift", [1, 4])
+@pytest.mark.parametrize("dtype,S,dh", [("f32", 33, 64), ("f32", 40, 8), ("bf16", 45, 64), ("bf16", 70, 32), ("bf16", 40, 16), ("bf16", 21, 4)])
+def test_attention_takes_tensors_that_start_anywhere(torch_cuda, dtype, S, dh, shift):
+    """Outside whole bf16 tiles the tensors may start at any element: the same results as from aligned ones.  fp32 arithmetic
+    on both sides gives the same bits; 32- and 64-wide bf16 heads differ in the kernel, so by one rounding of the output."""
+    import paper_1910_05124_amd as pm
+    torch = torch_cuda
+    tdt = _tdt(torch, dtype)
+    rng = np.random.default_rng(S + dh)
+    B, H = 2, 3
+    n = B * S * H * dh
+    data = [torch.from_numpy(rng.standard_normal(n).astype(np.float32)).cuda().to(tdt) for _ in range(4)]
+    st = torch.cuda.current_stream().cuda_stream
+
+    def run(at):
+        def place(x=None):
+            t = torch.zeros(n + 16, dtype=tdt, device="cuda")[at:at + n]
+            return t if x is None else t.copy_(x)
+
+        q, k, v, do = (place(x) for x in data)
+        o, dq, dk, dv = (place() for _ in range(4))
+        lse = torch.empty(B * H * S, dtype=torch.float32, device="cuda")
+        pm.pm_attention_fwd(st, dtype, B, S, H, dh, q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), lse.data_ptr())
+        pm.pm_attention_bwd(st, dtype, B, S, H, dh, q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), do.data_ptr(),
+                            lse.data_ptr(), dq.data_ptr(), dk.data_ptr(), dv.data_ptr())
+        return [t.float().cpu().numpy() for t in (o, dq, dk, dv)]
+
+    for got, want in zip(run(shift), run(0)):
+        if dtype == "f32" or dh < 32:
+            assert np.array_equal(got, want)
+        else:
+            assert np.max(np.abs(got - want)) <= 2.0 ** -8 * np.max(np.abs(want))
+
+
 # ------------------------------------------------------------------------------- whole training runs
 def run_pair(torch, w, steps, tau=None, N=1, gpu_kw=None, check_tables=True, **kw):
     params = wl.init_params(w)
