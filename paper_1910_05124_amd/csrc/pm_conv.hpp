@@ -494,18 +494,18 @@ __device__ __forceinline__ void pm_cv_split(int64_t p, int W, int H, int& b, int
   }
 }
 
-// Product of one wave: 32 pixels (lane % 32) x the 32 channels rows[.] of the weights, contraction over 9 taps
-// of 16 KC channels.  BWD: the source is dz and the weights are [ci][tap][co].  All loads are unconditional (a tap
-// outside the map reads pixel 0 and is masked when it arrives) and are requested ahead of the products: all of
-// them up to 32 channels, a tap row ahead with more (registers).  Under a predicate each load came out with a wait
-// of its own, 9 KC round trips to memory one behind the other, and the kernels spent nearly all their time there.
-template <int KC, bool BWD>
-__device__ __forceinline__ void pm_cv_core(const PmConvGeom& g, const bf16_t* __restrict__ src, const bf16_t* __restrict__ wrow,
-                                           bool pv, int b, int y, int x, int kg, pm_f32x16& acc) {
-  constexpr int C = 16 * KC, AHEAD = KC <= 2 ? 3 : 2;     // tap rows in registers
+// Product of one wave: 32 pixels (lane % 32) x NCT tiles of 32 channels, rows wrow[.] of the weights, contraction over 9
+// taps of 16 KC channels.  BWD: the source is dz and the weights are [ci][tap][co].  All loads are unconditional (a tap
+// outside the map reads pixel 0 and is masked when it arrives) and are requested ahead of the products, AHEAD tap rows
+// of them (registers).  Under a predicate each load came out with a wait of its own, 9 KC round trips to memory one
+// behind the other, and the kernels spent nearly all their time there.
+template <int KC, bool BWD, int NCT, int AHEAD>
+__device__ __forceinline__ void pm_cv_core(const PmConvGeom& g, const bf16_t* __restrict__ src, const bf16_t* const (&wrow)[NCT],
+                                           bool pv, int b, int y, int x, int kg, pm_f32x16 (&acc)[NCT]) {
+  constexpr int C = 16 * KC;
   const int SH = BWD ? g.Ho : g.H, SW = BWD ? g.Wo : g.W;
   union Frag { pm_bf16x8 v; uint4 q; };
-  Frag fx[AHEAD][3][KC], fw[AHEAD][3][KC];
+  Frag fx[AHEAD][3][KC], fw[AHEAD][3][KC][NCT];
   unsigned m[AHEAD][3];
   auto load = [&](int r, int at) __attribute__((always_inline)) {
 #pragma unroll
@@ -527,11 +527,11 @@ __device__ __forceinline__ void pm_cv_core(const PmConvGeom& g, const bf16_t* __
       }
       m[at][c] = ok ? 0xffffffffu : 0u;
       const bf16_t* sp = src + (ok ? (((int64_t)b * SH + iy) * SW + ix) * C : (int64_t)0) + 8 * kg;
-      const bf16_t* wp = wrow + (r * 3 + c) * C + 8 * kg;
 #pragma unroll
       for (int k = 0; k < KC; ++k) {
         fx[at][c][k].q = *reinterpret_cast<const uint4*>(sp + 16 * k);
-        fw[at][c][k].q = *reinterpret_cast<const uint4*>(wp + 16 * k);
+#pragma unroll
+        for (int t = 0; t < NCT; ++t) fw[at][c][k][t].q = *reinterpret_cast<const uint4*>(wrow[t] + (r * 3 + c) * C + 8 * kg + 16 * k);
       }
     }
   };
@@ -543,21 +543,30 @@ __device__ __forceinline__ void pm_cv_core(const PmConvGeom& g, const bf16_t* __
         Frag f = fx[at][c][k];
         const unsigned w = m[at][c];
         f.q = make_uint4(f.q.x & w, f.q.y & w, f.q.z & w, f.q.w & w);
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[at][c][k].v, f.v, acc, 0, 0, 0);
+#pragma unroll
+        for (int t = 0; t < NCT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[at][c][k][t].v, f.v, acc[t], 0, 0, 0);
       }
   };
-  // (scheduling barriers: left to itself the compiler moves each load down to its use)
-  load(0, 0);
-  load(1, 1);
-  if (AHEAD == 3) load(2, 2 % AHEAD);
-  __builtin_amdgcn_sched_barrier(0);
-  mma(0);
-  if (AHEAD == 2) {
-    load(2, 0);
+  if constexpr (AHEAD == 1) {
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+      load(r, 0);
+      mma(0);
+    }
+  } else {
+    // (scheduling barriers: left to itself the compiler moves each load down to its use)
+    load(0, 0);
+    load(1, 1);
+    if (AHEAD == 3) load(2, 2 % AHEAD);
     __builtin_amdgcn_sched_barrier(0);
+    mma(0);
+    if (AHEAD == 2) {
+      load(2, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    mma(1);
+    mma(2 % AHEAD);
   }
-  mma(1);
-  mma(2 % AHEAD);
 }
 __device__ __forceinline__ float4 pm_cv_unpack(uint2 a) {
   return make_float4(__uint_as_float(a.x << 16), __uint_as_float(a.x & 0xffff0000u), __uint_as_float(a.y << 16),
@@ -568,55 +577,69 @@ __device__ __forceinline__ uint2 pm_cv_mask(uint2 a, bool on) {
   return make_uint2(a.x & m, a.y & m);
 }
 
-// forward.  One wave = 32 output pixels x 32 output channels (blockIdx.y: which 32); blockDim.x / 64 waves per
-// block, no LDS.  What the epilogue reads is requested before the contraction.
-// 128 x 32 x 32 x 16 channels 10.4 -> 7.8 us, 128 x 8 x 8 x 64 channels 19.0 -> 7.5 us.
-template <int KC>    // Cin = 16 KC
+// forward.  One wave = 32 output pixels x NCT x 32 output channels (blockIdx.y: which); blockDim.x / 64 waves per
+// block, no LDS.  What the epilogue reads is requested before the contraction where loads go ahead.
+// 128 x 32 x 32 x 16 channels 10.4 -> 7.0 us, 128 x 8 x 8 x 64 channels 19.0 -> 7.0 us; large maps 512 x 64 x 64 x 16 83 -> 76,
+// 256 x 16 x 16 x 64 34 -> 32 us, against loads under predicates with one load in flight per wave.
+template <int KC, int NCT, int AHEAD>    // Cin = 16 KC
 __global__ __launch_bounds__(256) void pm_conv_fwd_mfma_kernel(PmConvGeom g, const bf16_t* __restrict__ x,
                                                                PmWLoc<bf16_t> wloc, PmShortcut<bf16_t> sc,
                                                                bf16_t* __restrict__ z, bf16_t* __restrict__ y) {
   const bf16_t* Wt = wloc.get();
   const bf16_t* scale = Wt + (int64_t)g.Cout * 9 * g.Cin;
   const bf16_t* shift = scale + g.Cout;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, pl = lane & 31, kg = lane >> 5, c0 = blockIdx.y * 32;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, pl = lane & 31, kg = lane >> 5, c0 = blockIdx.y * 32 * NCT;
   const int64_t npix = (int64_t)g.B * g.Ho * g.Wo;
   const int64_t p = ((int64_t)blockIdx.x * (blockDim.x >> 6) + wave) * 32 + pl;
   const bool pv = p < npix;
   int b, oy, ox;
   pm_cv_split(pv ? p : 0, g.Wo, g.Ho, b, oy, ox);
-  // a lane's channels: c0 + 8 a + 4 kg + 0 .. 3.  Groups past Cout read the first group's values and store nothing.
-  uint2 rs[4], rt[4], rc[4];
-  // (no shortcut: the shift's address, masked)
-  const bf16_t* sp = sc.src ? sc.src + (((int64_t)b * sc.Hs + oy * sc.stride) * sc.Ws + ox * sc.stride) * sc.Cs : shift;
+  // a lane's channels: c0 + 32 t + 8 a + 4 kg + 0 .. 3; groups past Cout are left out (uniform: Cout is a multiple of 16)
+  uint2 rs[NCT][4], rt[NCT][4], rc[NCT][4];
+  const bf16_t* sp = sc.src ? sc.src + (((int64_t)b * sc.Hs + oy * sc.stride) * sc.Ws + ox * sc.stride) * sc.Cs : nullptr;
+  auto affine = [&]() __attribute__((always_inline)) {
 #pragma unroll
-  for (int a = 0; a < 4; ++a) {
-    const int co = c0 + 8 * a + 4 * kg, cc = co < g.Cout ? co : 0;
-    rs[a] = *reinterpret_cast<const uint2*>(scale + cc);
-    rt[a] = *reinterpret_cast<const uint2*>(shift + cc);
-    // whole groups lie inside or outside the shortcut's channels (Cs is a multiple of 8)
-    rc[a] = *reinterpret_cast<const uint2*>(sp + (co < sc.Cs ? co : 0));
+    for (int t = 0; t < NCT; ++t)
+#pragma unroll
+      for (int a = 0; a < 4; ++a) {
+        if (c0 + 32 * t + 8 * a >= g.Cout) continue;
+        const int co = c0 + 32 * t + 8 * a + 4 * kg;
+        rs[t][a] = *reinterpret_cast<const uint2*>(scale + co);
+        rt[t][a] = *reinterpret_cast<const uint2*>(shift + co);
+        rc[t][a] = make_uint2(0u, 0u);
+        // whole groups of 8 lie inside or outside the shortcut's channels (Cs is a multiple of 8)
+        if (sp && c0 + 32 * t + 8 * a < sc.Cs) rc[t][a] = *reinterpret_cast<const uint2*>(sp + co);
+      }
+  };
+  if (AHEAD > 1) affine();
+  pm_f32x16 acc[NCT];
+  const bf16_t* wrow[NCT];
+#pragma unroll
+  for (int t = 0; t < NCT; ++t) {
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[t][e] = 0.f;
+    wrow[t] = Wt + (int64_t)min(c0 + 32 * t + pl, g.Cout - 1) * 9 * g.Cin;      // channels past Cout repeat the last one: not stored
   }
-  pm_f32x16 acc;
-#pragma unroll
-  for (int e = 0; e < 16; ++e) acc[e] = 0.f;
-  // channels past Cout repeat the last one: their products are not stored
-  pm_cv_core<KC, false>(g, x, Wt + (int64_t)min(c0 + pl, g.Cout - 1) * 9 * g.Cin, pv, b, oy, ox, kg, acc);
+  pm_cv_core<KC, false, NCT, AHEAD>(g, x, wrow, pv, b, oy, ox, kg, acc);
+  if (AHEAD == 1) affine();
   if (!pv) return;
 #pragma unroll
-  for (int a = 0; a < 4; ++a) {
-    const int co = c0 + 8 * a + 4 * kg;
-    if (co >= g.Cout) continue;
-    const float4 s4 = pm_cv_unpack(rs[a]), t4 = pm_cv_unpack(rt[a]), c4 = pm_cv_unpack(pm_cv_mask(rc[a], sc.src && co < sc.Cs));
-    const float ss[4] = {s4.x, s4.y, s4.z, s4.w}, tt[4] = {t4.x, t4.y, t4.z, t4.w}, cc[4] = {c4.x, c4.y, c4.z, c4.w};
-    float yy[4];
+  for (int t = 0; t < NCT; ++t)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const float av = ss[j] * acc[4 * a + j] + tt[j] + cc[j];
-      yy[j] = av > 0.f ? av : 0.f;
+    for (int a = 0; a < 4; ++a) {
+      if (c0 + 32 * t + 8 * a >= g.Cout) continue;
+      const int co = c0 + 32 * t + 8 * a + 4 * kg;
+      const float4 s4 = pm_cv_unpack(rs[t][a]), t4 = pm_cv_unpack(rt[t][a]), c4 = pm_cv_unpack(rc[t][a]);
+      const float ss[4] = {s4.x, s4.y, s4.z, s4.w}, tt[4] = {t4.x, t4.y, t4.z, t4.w}, cc[4] = {c4.x, c4.y, c4.z, c4.w};
+      float yy[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float av = ss[j] * acc[t][4 * a + j] + tt[j] + cc[j];
+        yy[j] = av > 0.f ? av : 0.f;
+      }
+      pm_st4(z + p * g.Cout + co, make_float4(acc[t][4 * a], acc[t][4 * a + 1], acc[t][4 * a + 2], acc[t][4 * a + 3]));
+      pm_st4(y + p * g.Cout + co, make_float4(yy[0], yy[1], yy[2], yy[3]));
     }
-    pm_st4(z + p * g.Cout + co, make_float4(acc[4 * a], acc[4 * a + 1], acc[4 * a + 2], acc[4 * a + 3]));
-    pm_st4(y + p * g.Cout + co, make_float4(yy[0], yy[1], yy[2], yy[3]));
-  }
 }
 
 // The kernel tensors of the backward weights, transposed for the data gradient: [co][tap][ci] -> [ci][tap][co],
@@ -681,10 +704,12 @@ __global__ __launch_bounds__(256, KC == 1 ? 4 : 1) void pm_conv_dgrad_affine_ker
     rz[a] = *reinterpret_cast<const uint2*>(z + row + cc);
     rc[a] = *reinterpret_cast<const uint2*>(sp + cc);      // (no shortcut: the scale's address, masked)
   }
-  pm_f32x16 acc;
+  pm_f32x16 acc1[1];
+  pm_f32x16& acc = acc1[0];
 #pragma unroll
   for (int e = 0; e < 16; ++e) acc[e] = 0.f;
-  pm_cv_core<KC, true>(g, dz, wt + (int64_t)min(c0 + pl, g.Cin - 1) * 9 * g.Cout, pv, b, iy, ix, kg, acc);
+  const bf16_t* wrow[1] = {wt + (int64_t)min(c0 + pl, g.Cin - 1) * 9 * g.Cout};
+  pm_cv_core<KC, true, 1, KC <= 2 ? 3 : 2>(g, dz, wrow, pv, b, iy, ix, kg, acc1);
   float v[32];                                           // [which sum][a][j]
 #pragma unroll
   for (int a = 0; a < 4; ++a) {
@@ -979,13 +1004,22 @@ inline void pm_conv_fwd_launch(hipStream_t st, const PmConvGeom& g, const T* x, 
   if constexpr (sizeof(T) == 2) {
     if (pm_conv_mfma_fits(g.Cin, g.Cout)) {
       const int wpb = pm_conv_waves(npix, g.Cout);
-      const dim3 grid((unsigned)((npix + 32 * wpb - 1) / (32 * wpb)), (g.Cout + 31) / 32), blk(64 * wpb);
-#define PM_CF(K) hipLaunchKernelGGL((pm_conv_fwd_mfma_kernel<K>), grid, blk, 0, st, g, x, w, sc, z, y)
-      if (g.Cin == 16) PM_CF(1);
-      else if (g.Cin == 32) PM_CF(2);
-      else if (g.Cin == 48) PM_CF(3);
-      else PM_CF(4);
-#undef PM_CF
+      auto go = [&](auto kc, auto nct, auto ahead) {
+        const dim3 grid((unsigned)((npix + 32 * wpb - 1) / (32 * wpb)), (g.Cout + 32 * nct - 1) / (32 * nct)), blk(64 * wpb);
+        hipLaunchKernelGGL((pm_conv_fwd_mfma_kernel<kc, nct, ahead>), grid, blk, 0, st, g, x, w, sc, z, y);
+      };
+      using std::integral_constant;
+      auto with = [&](auto kc) {
+        constexpr int KC = decltype(kc)::value;
+        // many wide pixels: both channel tiles in one wave, so that the gathered operand is read once, and few registers
+        // (128 x 16 x 16 x 64 channels 21.1 -> 17.5 us, 2048 x 8 x 8 73 -> 58; 128 x 8 x 8 7.0 against 8.2 the other way)
+        if (KC > 2 && g.Cout > 32 && wpb == 4) go(kc, integral_constant<int, 2>(), integral_constant<int, 1>());
+        else go(kc, integral_constant<int, 1>(), integral_constant<int, (KC <= 2 ? 3 : 2)>());
+      };
+      if (g.Cin == 16) with(integral_constant<int, 1>());
+      else if (g.Cin == 32) with(integral_constant<int, 2>());
+      else if (g.Cin == 48) with(integral_constant<int, 3>());
+      else with(integral_constant<int, 4>());
       return;
     }
   }
