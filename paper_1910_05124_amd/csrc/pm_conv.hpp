@@ -1081,13 +1081,18 @@ inline void pm_conv_transpose_launch(hipStream_t st, const PmCvTransposeJob* v, 
   }
 }
 
-// Chunks of 32 pixels per wave and blocks of the MFMA weight-gradient kernel: at most 64 blocks (times three tap
-// rows, times the units that share the launch) write a partial, 32 of the wide tensors, whose partials are 147 KB
-// each and are written and read once more.
-inline void pm_conv_wgrad_plan(const PmConvGeom& g, int* blocks, int* nch) {
+// Chunks of 32 pixels per wave and blocks of the MFMA weight-gradient kernel.  Each block (times three tap rows) writes a
+// partial that is read once more.  In a step, whose units share launches: at most 64, 32 of the wide tensors, whose
+// partials are 147 KB each.  A unit by itself (ALONE) has to fill the chip: up to 256 and 64 where that leaves a wave four
+// chunks.  Us with 64 (32) blocks, now, and with twice as many: 512 x 64 x 64 x 16 channels 184, 77, 81; 512 x 32 x 32 x 32 68,
+// 34, 42; 256 x 32 x 32 x 64 137, 76, 107; 128 x 16 x 16 x 32, below four chunks, 12, 12, 15.  Never more partials than
+// pm_conv_wgrad_scratch_elems has room for: one per 16 chunks from 2048 chunks on, one per 4 below.
+inline void pm_conv_wgrad_plan(const PmConvGeom& g, bool alone, int* blocks, int* nch) {
   const int64_t chunks = ((int64_t)g.B * g.Ho * g.Wo + 31) / 32;
-  const int64_t top = 4 * (g.Cin * g.Cout > 1024 ? 32 : 64);
-  const int64_t c = (chunks + top - 1) / top;
+  const bool wide = g.Cin * g.Cout > 1024;
+  int64_t most = wide ? 32 : 64;
+  if (alone) most = std::max<int64_t>(most, std::min<int64_t>(wide ? 64 : 256, chunks / 16));
+  const int64_t c = (chunks + 4 * most - 1) / (4 * most);
   *nch = (int)c;
   *blocks = (int)((chunks + c * 4 - 1) / (c * 4));
 }
@@ -1101,11 +1106,11 @@ inline bool pm_conv_wgrad_mfma_fits(const PmConvGeom& g) {       // 32-bit index
 }
 // partial vectors of Cout * 9 * Cin floats that the weight gradient writes (0: the plain path is used)
 template <typename T>
-inline int pm_conv_wgrad_parts(const PmConvGeom& g) {
+inline int pm_conv_wgrad_parts(const PmConvGeom& g, bool alone = false) {
   if (pm_conv_thin_fits(g)) return PM_CONV_THIN_GROUPS;
   if (!pm_conv_wgrad_mfma_fits<T>(g)) return 0;
   int blocks, nch;
-  pm_conv_wgrad_plan(g, &blocks, &nch);
+  pm_conv_wgrad_plan(g, alone, &blocks, &nch);
   return blocks;
 }
 // fp32 scratch elements that the entry points ask for: a partial per 128 pixels, per 512 on large maps.  The
@@ -1119,7 +1124,7 @@ inline size_t pm_conv_wgrad_scratch_elems(const PmConvGeom& g) {
 }
 
 // The MFMA weight gradients of a list of units, one launch per pair of channel tiles and PM_CONV_JOBS units
-inline void pm_conv_wgrad_group_launch(hipStream_t st, const PmCvWgradJob* v, int count) {
+inline void pm_conv_wgrad_group_launch(hipStream_t st, const PmCvWgradJob* v, int count, bool alone = false) {
   for (int cls = 0; cls < 5; ++cls) {
     PmCvWgradList l{};
     int blocks = 0;
@@ -1137,7 +1142,7 @@ inline void pm_conv_wgrad_group_launch(hipStream_t st, const PmCvWgradJob* v, in
       const bool thin = v[i].g.Cin == 16 && v[i].g.Cout == 16;
       if ((thin ? 4 : (v[i].g.Cout > 32 ? 2 : 0) + (v[i].g.Cin > 32 ? 1 : 0)) != cls) continue;
       int nb, nch;
-      pm_conv_wgrad_plan(v[i].g, &nb, &nch);
+      pm_conv_wgrad_plan(v[i].g, alone, &nb, &nch);
       l.job[l.count] = v[i];
       l.job[l.count].nch = nch;
       l.end[l.count++] = blocks += nb;
@@ -1159,7 +1164,7 @@ inline void pm_conv_wgrad_plain_launch(hipStream_t st, const PmConvGeom& g, cons
 // pm_conv_wgrad_scratch_elems floats (unused by the plain path).
 template <typename T>
 inline void pm_conv_wgrad_launch(hipStream_t st, const PmConvGeom& g, const T* dz, const T* x, float* dW, float* scratch) {
-  const int parts = pm_conv_wgrad_parts<T>(g);
+  const int parts = pm_conv_wgrad_parts<T>(g, true);
   if (!parts) {
     pm_conv_wgrad_plain_launch<T>(st, g, dz, x, dW, 0);
     return;
@@ -1168,7 +1173,7 @@ inline void pm_conv_wgrad_launch(hipStream_t st, const PmConvGeom& g, const T* d
     pm_conv_wgrad_thin_launch<T>(st, g, dz, x, scratch);
   } else if constexpr (sizeof(T) == 2) {
     const PmCvWgradJob jb{g, dz, x, scratch, 0};
-    pm_conv_wgrad_group_launch(st, &jb, 1);
+    pm_conv_wgrad_group_launch(st, &jb, 1, true);
   }
   const PmReduceJob r{scratch, parts, g.Cout * 9 * g.Cin, dW, 0};
   pm_conv_reduce_launch(st, &r, 1);

@@ -130,11 +130,11 @@ def test_bf16_backward_chain_edges(torch_cuda, batch, image, blocks, N, segment)
 
 
 @pytest.mark.parametrize("shape", [(1, 1, 1, 16, 16, 1), (3, 7, 5, 32, 16, 2), (9, 31, 33, 16, 32, 1), (2, 200, 180, 16, 16, 1),
-                                   (40, 16, 16, 48, 64, 1), (130, 16, 16, 64, 64, 1), (9, 61, 60, 48, 48, 1)])
+                                   (40, 16, 16, 48, 64, 1), (130, 16, 16, 64, 64, 1), (9, 61, 60, 48, 48, 1), (35, 64, 61, 16, 16, 1)])
 def test_conv_primitives_at_tile_edges(torch_cuda, shape):
     """Pixel counts around a wave's 32 and a block's 128, several chunks per wave in the weight gradient, four waves
-    per block in the forward product (with 64 and 48 channels: both channel tiles in one wave); references and tolerances as
-    above."""
+    per block in the forward product (with 64 and 48 channels: both channel tiles in one wave), the most blocks of a
+    weight gradient by itself (4270 chunks); references and tolerances as above."""
     test_conv_primitives_against_numpy(torch_cuda, "bf16", shape)
 
 
