@@ -484,3 +484,47 @@ def test_fp32_products_sum_in_index_order(torch_cuda, M, n_in, n_out):
     for m in range(M):
         chains[m % 4] = chains[m % 4] + dz[m]
     assert np.array_equal(db.cpu().numpy(), ((chains[0] + chains[1]) + chains[2]) + chains[3])
+
+
+@pytest.mark.parametrize("rows,widths,N", [(129, (64, 64), 1), (200, (72, 136, 200, 40), 2), (255, (24, 520, 8), 1),
+                                           (200, (1000,) * 9, 1), (1000, (1000,) * 9, 1), (131, (1024,) * 9, 2)])
+def test_bf16_chain_weight_gradients_of_many_rows(torch_cuda, rows, widths, N):
+    """More than 128 rows: the weight and bias gradients of all units in one pipelined launch, on tiles of 64 and (eight
+    units of 1000 or 1024) of 128, ragged in every extent.  Weights with at most one entry of +-1 per row and
+    column, integer inputs and no activation keep every activation and data gradient exact (a data gradient is a rounded
+    value of the loss passed on), so what is left are the fp32 sums: |error| <= 2 K 2^-24 sum |dz a|."""
+    from workloads import Layer, Workload
+    torch = torch_cuda
+    rng = np.random.default_rng(rows + len(widths))
+    L = len(widths) - 1
+    w = Workload(name="chain", layers=tuple(Layer("linear", widths[l], widths[l + 1], "none", l + 1) for l in range(L)), P=L, N=N,
+                 loss="mse", dtype="bf16", microbatch=rows, n_classes=widths[-1])
+    Ws, params = [], []
+    for a, b in zip(widths, widths[1:]):
+        n = min(a, b)
+        W = np.zeros((b, a), dtype=np.float32)
+        W[rng.permutation(b)[:n], rng.permutation(a)[:n]] = rng.choice([-1, 1], n)
+        Ws.append(W)
+        params.append(np.concatenate([W.ravel(), np.zeros(b, dtype=np.float32)]))
+    g = make_gpu(w, params, *po.pipeline_delays(L, N), N=N, opt="sgdm", lr=0.0, K=6)
+    want = [(0.0, 0.0, 0.0, 0.0)] * L
+    for _ in range(N):
+        x = rng.integers(-4, 5, (rows, widths[0])).astype(np.float32)
+        y = rng.integers(-4, 5, (rows, widths[-1])).astype(np.float32)
+        g.step(torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda(), want_loss=True)
+        acts = [x]
+        for W in Ws:
+            acts.append(acts[-1] @ W.T)
+        inv = np.float32(1) / (np.float32(rows) * np.float32(widths[-1]))
+        dz = torch.from_numpy(np.float32(2) * (acts[-1] - y) * inv).bfloat16().float().numpy()
+        for l in range(L - 1, -1, -1):
+            dz64, a64 = dz.astype(np.float64), acts[l].astype(np.float64)
+            want[l] = tuple(p + q for p, q in zip(want[l], (dz64.T @ a64, np.abs(dz64).T @ np.abs(a64), dz64.sum(0), np.abs(dz64).sum(0))))
+            dz = dz @ Ws[l]
+    tol = 2 * N * rows * 2.0 ** -24
+    for l in range(L):
+        got = g.state(4, l).astype(np.float64)
+        dW, W_terms, db, b_terms = want[l]
+        assert np.all(np.abs(got[:dW.size].reshape(dW.shape) - dW) <= tol * W_terms), l
+        assert np.all(np.abs(got[dW.size:] - db) <= tol * b_terms), l
+    g.close()

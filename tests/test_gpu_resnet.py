@@ -100,7 +100,8 @@ def test_bf16_backward_chain_edges(torch_cuda, batch, image, blocks, N, segment)
     waves per block), microbatches that accumulate, recomputation that overwrites the outputs between them.
     Odd channels are shifted far above and even ones far below zero and the kernels are small, so that no rounding
     flips a ReLU; what is left is 2^-9 per stored tensor and weight, two of them in each of up to 13 convolutions,
-    2^-9 sqrt(26) = 1 % of a part's norm.  The bound is three times that."""
+    2^-9 sqrt(26) = 1 % of a part's norm.  The bound is three times that.  (What it leaves open - a few pixels of a large
+    map, the mask - the two tests below cover.)"""
     torch = torch_cuda
     w = wl.resnet(blocks, batch, dtype="bf16", image=image)
     params = wl.init_params(w)
@@ -127,6 +128,92 @@ def test_bf16_backward_chain_edges(torch_cuda, batch, image, blocks, N, segment)
             err = float(np.linalg.norm(a - b) / np.linalg.norm(b))
             assert err <= 3e-2, (u, name, err)
     g.close()
+
+
+def _conv_affine(m, u, p, f):
+    """Pre-activation of unit u without its shift: scale * z (+ shortcut)."""
+    ci, co, _ = m.specs[u]
+    nw = co * 9 * ci
+    a = m._conv_forward(u, p, f.__getitem__)[f"z{u}"] * p[nw:nw + co]
+    if u >= 2 and (u - 1) % 2 == 1:
+        a = a + ro._shortcut(f[m._in_name(u - 1)], co, m.specs[u - 1][2])
+    return a
+
+
+def _check_gradients(torch, w, params, x, y, bound):
+    """All convolutions' gradients of one step against the oracle, per part and by norm."""
+    kw = dict(opt="sgdm", lr=0.02, beta=0.9, D=0.5, K=6)
+    tf, tb = po.pipeline_delays(w.P, 1)
+    o, g = make_oracle(w, params, tf, tb, **kw), make_gpu(w, params, tf, tb, **kw)
+    o.step((x, y))
+    g.step(torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda(), want_loss=True)
+    for u, L in enumerate(w.layers[:-1]):
+        nw = L.n_out * 9 * L.n_in
+        for name, part in (("W", slice(0, nw)), ("scale", slice(nw, nw + L.n_out)), ("shift", slice(nw + L.n_out, None))):
+            a, b = g.state(4, u)[part].astype(np.float64), o.last_grads[u][part]
+            err = float(np.linalg.norm(a - b) / np.linalg.norm(b))
+            assert err <= bound, (u, name, err)
+    g.close()
+
+
+@pytest.mark.parametrize("batch,image,seed", [(3, 8, 6), (4, 4, 1), (2, 12, 16)])
+def test_bf16_backward_chain_where_the_mask_changes_from_pixel_to_pixel(torch_cuda, batch, image, seed):
+    """The ReLU mask of the fused data gradient, half of the pixels on in every channel: images of +-1, kernels that mostly
+    pass one channel through, and each channel's shift in the middle of the widest gap between its pre-activations, so
+    that no rounding moves one across zero (at least 3 % of their spread away, seven convolutions of about 2^-9 each).  A
+    mask taken from another pixel changes a gradient by its own size; the bound is that of the test above."""
+    rng = np.random.default_rng(seed)
+    w = wl.resnet(1, batch, dtype="bf16", image=image)
+    params = wl.init_params(w)
+    m = ro.ResNetModel(1, 10, image)
+    x = (rng.choice([-1, 1], (batch, 3, image, image)) * rng.uniform(1, 1.1, (batch, 3, image, image))).astype(np.float32)
+    f = {"img": x.transpose(0, 2, 3, 1).astype(np.float64)}
+    for u, (ci, co, _) in enumerate(m.specs):
+        nw = co * 9 * ci
+        W = 0.03 * rng.standard_normal((co, 9, ci))
+        W[np.arange(co), 4, rng.permutation(co) % ci] += rng.choice([-1, 1], co)
+        p = params[u]
+        p[:nw], p[nw:nw + co], p[nw + co:] = W.ravel(), rng.uniform(0.8, 1.2, co), 0
+        a = _conv_affine(m, u, p.astype(np.float64), f).reshape(-1, co)
+        for c in range(co):
+            v = np.sort(a[:, c])
+            lo, hi = len(v) // 5, max(len(v) - len(v) // 5, len(v) // 5 + 2)
+            i = lo + int(np.argmax(np.diff(v[lo:hi])))
+            p[nw + co + c] = -(v[i] + v[i + 1]) / 2
+            assert (v[i + 1] - v[i]) / 2 >= 0.03 * np.std(v)
+        f.update(m._conv_forward(u, p.astype(np.float64), f.__getitem__))
+    y = rng.integers(0, 10, batch).astype(np.int32)
+    _check_gradients(torch_cuda, w, params, x, y, 3e-2)
+
+
+@pytest.mark.parametrize("batch,image,blocks,segment", [(51, 36, 1, 0), (33, 32, 2, 0), (5, 12, 2, 3), (37, 28, 1, 0)])
+def test_bf16_gradients_do_not_depend_on_where_an_image_lies(torch_cuda, batch, image, blocks, segment):
+    """A batch and the same batch rotated: every pixel's values are the same bits wherever its image lies, so the gradients of
+    all convolutions differ by the order of their fp32 sums, 1e-5 of the norm at most.  What a block's edge loses, doubles
+    or takes from elsewhere does not rotate with the images: the last block of 51 x 36 x 36 pixels has 48 of 66096, a
+    norm of 2.7 % of the whole."""
+    torch = torch_cuda
+    w = wl.resnet(blocks, batch, dtype="bf16", image=image)
+    params = wl.init_params(w)
+    tf, tb = po.pipeline_delays(w.P, 1)
+    kw = dict(opt="sgdm", lr=0.02, beta=0.9, D=0.5, K=6)
+    if segment:
+        kw.update(tau_recomp=po.recompute_delays(w.P, segment, 1, tb), segment=segment)
+    x, y = wl.ImageStream(w).batch(0)
+
+    def gradients(by):
+        g = make_gpu(w, params, tf, tb, **kw)
+        g.step(torch.from_numpy(np.roll(x, by, 0)).cuda(), torch.from_numpy(np.roll(y, by)).cuda(), want_loss=True)
+        out = [g.state(4, u).astype(np.float64) for u in range(len(w.layers) - 1)]
+        g.close()
+        return out
+
+    want = gradients(0)
+    for by in (1, batch // 2, batch - 1):
+        for u, (a, b) in enumerate(zip(gradients(by), want)):
+            nw = w.layers[u].n_out * 9 * w.layers[u].n_in
+            for part in (slice(0, nw), slice(nw, None)):
+                assert np.linalg.norm(a[part] - b[part]) <= 1e-5 * np.linalg.norm(b[part]), (by, u, part)
 
 
 @pytest.mark.parametrize("shape", [(1, 1, 1, 16, 16, 1), (3, 7, 5, 32, 16, 2), (9, 31, 33, 16, 32, 1), (2, 200, 180, 16, 16, 1),

@@ -625,3 +625,34 @@ def test_wide_vocabulary_transformer_large_tile_paths_live_oracle(torch_cuda):
     assert err <= TOL["bf16"], errs
     assert max(m for u, m in enumerate(mvs) if u not in key_bias_entries(w)) <= 0.15, mvs
     g.close()
+
+
+@pytest.mark.parametrize("d,heads,vocab,seq,batch", [(128, 2, 4099, 50, 3), (64, 1, 2053, 40, 5), (128, 2, 4096, 64, 4), (192, 3, 10007, 33, 7),
+                                                     (256, 4, 3000, 32, 16)])
+def test_vocabulary_data_gradient_in_parts(torch_cuda, d, heads, vocab, seq, batch):
+    """The data gradient through the vocabulary projection cut into parts of the vocabulary (2 to 8, the last one ragged or not).
+    With Wo and W2 zero the only layer passes the gradient on, so the gradient of a token's embedding row is the final
+    LayerNorm's backward of that token's sum over the vocabulary, in which its target stands out; targets lie at both ends of
+    the vocabulary and on both sides of multiples of 64 (every boundary between parts is one).  Bound per token: the
+    bf16 roundings of the loss gradient, the LayerNorm output and the stored weights, 2^-9 each of a sum whose terms
+    mostly add up: 2^-6 of the row.  A lost or doubled target would be all of it."""
+    torch = torch_cuda
+    w = wl.transformer(1, d, heads, 2 * d, vocab, seq, batch, dtype="bf16")
+    rng = np.random.default_rng(vocab + d)
+    params = wl.init_params(w)
+    params[5][:], params[8][:] = 0, 0
+    params = [torch.from_numpy(p).bfloat16().float().numpy() for p in params]
+    tf, tb = po.pipeline_delays(w.P, 1)
+    kw = dict(opt="sgdm", lr=0.01, beta=0.9, D=0.5, K=6)
+    o, g = make_oracle(w, params, tf, tb, **kw), make_gpu(w, params, tf, tb, **kw)
+    n = seq * batch
+    x = rng.permutation(vocab)[:n].astype(np.int32).reshape(batch, seq)
+    edges = np.unique(np.concatenate([np.arange(64, vocab, 64), np.arange(63, vocab, 64), [0, 1, vocab - 2, vocab - 1]]))
+    y = np.concatenate([[0, vocab - 1, vocab - 2, (vocab - 1) // 64 * 64], rng.permutation(edges)])
+    y = np.resize(y, n).astype(np.int32).reshape(batch, seq)
+    o.step((x, y))
+    g.step(torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda(), want_loss=True)
+    got, want = (np.asarray(v, dtype=np.float64).reshape(vocab, d)[x.ravel()] for v in (g.state(4, 0), o.last_grads[0]))
+    err = np.linalg.norm(got - want, axis=1) / np.linalg.norm(want, axis=1)
+    assert np.max(err) <= 2.0 ** -6, (int(np.argmax(err)), float(np.max(err)))
+    g.close()
