@@ -780,34 +780,27 @@ pm_status launch_fwd_bwd(pm_ctx* c, const void* x_dev, const void* y_dev, int ac
   }
   // ---- weight gradients from the stored forward activations: dW[n_out, n_in] = dz^T . a_in,
   // db = column sums of dz.  They depend only on stored tensors, so all units go out as ONE
-  // grouped launch (bias gradients fused) when every unit fits the MFMA kernel.
-  bool grouped = false;
-  if constexpr (sizeof(T) == 2) {
-    if (c->dw_grouped) {
-      ProfSpan span(c, PM_CLS_GEMM);
-      const auto* tab = c->at<PmGemmProb<PmEpiBwdWeight>>(lay.probs_off) + (accumulate ? L : 0);
-      if (M <= 128)
-        hipLaunchKernelGGL((pm_gemm_mfma_grouped_kernel<PmCfgShortK, false, false, PmEpiBwdWeight>),
-                           dim3((c->dw_maxJ + 63) / 64, (c->dw_maxI + 63) / 64, L), dim3(256), 0, st, tab);
-      else if (c->dw_tile == 128)
-        hipLaunchKernelGGL((pm_gemm_big_table_kernel<PmBig128, false, false, PmEpiBwdWeight>), dim3(c->dw_ntiles, L),
-                           dim3(PmBig128::NT), 0, st, tab);
-      else
-        hipLaunchKernelGGL((pm_gemm_big_table_kernel<PmBig64, false, false, PmEpiBwdWeight>), dim3(c->dw_ntiles, L),
-                           dim3(PmBig64::NT), 0, st, tab);
-      grouped = true;
-    }
-  } else {
+  // grouped launch, bias gradients with it (bf16: when every unit fits the MFMA kernel).
+  if constexpr (sizeof(T) == 4) {
     launch_f32_wgrads(c, accumulate);
-    grouped = true;
-  }
-  if (!grouped) {
+  } else if (c->dw_grouped) {
+    ProfSpan span(c, PM_CLS_GEMM);
+    const auto* tab = c->at<PmGemmProb<PmEpiBwdWeight>>(lay.probs_off) + (accumulate ? L : 0);
+    if (M <= 128)
+      hipLaunchKernelGGL((pm_gemm_mfma_grouped_kernel<PmCfgShortK, false, false, PmEpiBwdWeight>),
+                         dim3((c->dw_maxJ + 63) / 64, (c->dw_maxI + 63) / 64, L), dim3(256), 0, st, tab);
+    else if (c->dw_tile == 128)
+      hipLaunchKernelGGL((pm_gemm_big_table_kernel<PmBig128, false, false, PmEpiBwdWeight>), dim3(c->dw_ntiles, L),
+                         dim3(PmBig128::NT), 0, st, tab);
+    else
+      hipLaunchKernelGGL((pm_gemm_big_table_kernel<PmBig64, false, false, PmEpiBwdWeight>), dim3(c->dw_ntiles, L),
+                         dim3(PmBig64::NT), 0, st, tab);
+  } else {
     for (int l = L - 1; l >= 0; --l) {
       const Unit& u = lay.units[l];
       const T* a_in = l == 0 ? c->at<T>(lay.x_off) : c->at<T>(lay.units[l - 1].a_off);
-      const T* dz = c->at<T>(u.dz_off);
       ProfSpan span(c, PM_CLS_GEMM);
-      launch_wgrad<T>(st, M, u.d.n_out, u.d.n_in, dz, u.ld_out, a_in, u.ld_in, g + u.off, g + u.off + u.boff, accumulate);
+      launch_wgrad<T>(st, M, u.d.n_out, u.d.n_in, c->at<T>(u.dz_off), u.ld_out, a_in, u.ld_in, g + u.off, g + u.off + u.boff, accumulate);
     }
   }
   PM_HIP(hipGetLastError());

@@ -242,7 +242,7 @@ __global__ __launch_bounds__(256) void pm_conv_wgrad_plain_kernel(PmConvGeom g, 
 // weight gradient of a convolution with very few input channels (the 3-channel input layer), any T.
 // grid (pixel groups, 9 taps); a thread walks pixels of its group and keeps the CO x CI outer-product
 // sums of its pixels in registers; wave shuffles, then LDS across the four waves; the block writes
-// its partial of the tap to scratch [group][co][tap][ci] for pm_conv_wgrad_reduce_kernel.
+// its partial of the tap to scratch [group][co][tap][ci] for pm_conv_reduce_kernel.
 template <typename T, int CO, int CI>
 __global__ __launch_bounds__(256) void pm_conv_wgrad_thin_kernel(PmConvGeom g, const T* __restrict__ dz,
                                                                  const T* __restrict__ x, float* __restrict__ part) {

@@ -189,7 +189,7 @@ __global__ __launch_bounds__(256) void pm_ln_fwd_kernel(const float* __restrict_
 // Block = 8 waves x 4 rows; lane l owns columns 256 c + 4 l .. + 3 (16-byte accesses), d <= 256 NC,
 // d a multiple of 4.
 // ---------------------------------------------------------------------------------------------
-template <typename T, int NC, int R>
+template <typename T, int NC>
 __global__ __launch_bounds__(512) void pm_ln_bwd_kernel(const float* __restrict__ dy, const float* __restrict__ x,
                                                         const float* __restrict__ mean, const float* __restrict__ rstd,
                                                         PmWLoc<T> gain_bkwd, const float* dx_res, float* dx_out,
@@ -207,13 +207,13 @@ __global__ __launch_bounds__(512) void pm_ln_bwd_kernel(const float* __restrict_
     ag[c] = zero4;
     ab[c] = zero4;
   }
-  // all loads of the wave's R rows go out first (rows past the end re-read the last row and are
+  // all loads of the wave's four rows go out first (rows past the end re-read the last row and are
   // masked out below), so the wave pays the memory latency once instead of once per row
-  float4 dyr[R][NC], xr[R][NC], rrr[R][NC];
-  float mur[R], rsr[R];
+  float4 dyr[4][NC], xr[4][NC], rrr[4][NC];
+  float mur[4], rsr[4];
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int row = blockIdx.x * (8 * R) + wave * R + r;
+  for (int r = 0; r < 4; ++r) {
+    const int row = blockIdx.x * 32 + wave * 4 + r;
     const int rowc = row < rows ? row : rows - 1;
     const int64_t ro = (int64_t)rowc * d;
     mur[r] = mean[rowc];
@@ -228,9 +228,9 @@ __global__ __launch_bounds__(512) void pm_ln_bwd_kernel(const float* __restrict_
     }
   }
 #pragma unroll
-  for (int r = 0; r < R; ++r)
+  for (int r = 0; r < 4; ++r)
     for (int p = 1; p < parts; ++p) {                         // the gradient arrives as several addends
-      const int row = blockIdx.x * (8 * R) + wave * R + r;
+      const int row = blockIdx.x * 32 + wave * 4 + r;
       const float* dyp = dy + p * part_stride + (int64_t)(row < rows ? row : rows - 1) * d;
 #pragma unroll
       for (int c = 0; c < NC; ++c) {
@@ -240,8 +240,8 @@ __global__ __launch_bounds__(512) void pm_ln_bwd_kernel(const float* __restrict_
       }
     }
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int row = blockIdx.x * (8 * R) + wave * R + r;
+  for (int r = 0; r < 4; ++r) {
+    const int row = blockIdx.x * 32 + wave * 4 + r;
     if (row >= rows) break;                                   // wave-uniform
     const float mu = mur[r], rs = rsr[r];
     const int64_t ro = (int64_t)row * d;
@@ -332,15 +332,13 @@ inline bool pm_ln_bwd_launch(hipStream_t st, const float* dy, const float* x, co
                              PmWLoc<T> gain_bkwd, const float* dx_res, float* dx_out, T* dx_out_t, float* dgain,
                              float* dbias, int rows, int d, int parts = 1, int64_t part_stride = 0) {
   if (d & 3) return false;
-  const dim3 blk(512);
-#define PM_LNB(NC, R) hipLaunchKernelGGL((pm_ln_bwd_kernel<T, NC, R>), dim3((rows + 8 * R - 1) / (8 * R)), blk, 0, st, dy, x, mean, rstd, gain_bkwd, dx_res, dx_out, dx_out_t, dgain, dbias, rows, d, parts, part_stride)
-#define PM_LNR(NC) PM_LNB(NC, 4)
-  if (d <= 256) PM_LNR(1);
-  else if (d <= 512) PM_LNR(2);
-  else if (d <= 768) PM_LNR(3);
-  else if (d <= 1024) PM_LNR(4);
+  const dim3 grid((rows + 31) / 32), blk(512);
+#define PM_LNB(NC) hipLaunchKernelGGL((pm_ln_bwd_kernel<T, NC>), grid, blk, 0, st, dy, x, mean, rstd, gain_bkwd, dx_res, dx_out, dx_out_t, dgain, dbias, rows, d, parts, part_stride)
+  if (d <= 256) PM_LNB(1);
+  else if (d <= 512) PM_LNB(2);
+  else if (d <= 768) PM_LNB(3);
+  else if (d <= 1024) PM_LNB(4);
   else return false;
-#undef PM_LNR
 #undef PM_LNB
   return true;
 }
