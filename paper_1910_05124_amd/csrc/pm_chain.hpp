@@ -2,7 +2,7 @@
 // persistent launch (bf16, gfx950).
 //
 // With 128 rows a stage product (128 x 1024 x 1024) takes about a microsecond of work, a dependent
-// kernel launch 4.4 us, and a step has two such products per stage in sequence (the per-stage forward
+// launch of it 5.4 us with its loads, and a step has two such products per stage in sequence (the per-stage forward
 // and backward of Sec. 2.1).  Here one grid of co-resident blocks walks the whole chain.  A block owns
 // 32 x 32 output tiles; it stages the 32 input rows of a tile in LDS (panels of up to 1024 columns), its
 // 16 waves split the contraction in slices of 64 and sum their partial tiles through LDS.  The tile of

@@ -13,8 +13,8 @@
 // instruction adds its four products to the accumulator one after the other, each addition rounded (checked bit for bit
 // against fmaf chains, with wide exponents and denormal products).  A network with ReLU units turns a difference of one
 // rounding in a pre-activation next to zero into a gradient that differs in the third digit, so the order is part of
-// what a caller can rely on: splitting the contraction over waves or permuting it inside a piece made 1 seed in 6 of a
-// 2-layer Transformer 256 wide differ by 5e-6 .. 1e-4 in its gradients, and is left out.  For the same reason a bias
+// what a caller can rely on: splitting the contraction over waves or permuting it inside a piece made a 2-layer Transformer
+// 256 wide differ by 5e-6 .. 1e-4 in its gradients on some inputs (4 of 24 seeds in a simulation), and is left out.  For the same reason a bias
 // gradient adds rows m, m + 4, m + 8, ... in four chains and the chains in order.
 //
 // One lane of a 16 x 16 x 4 step s holds row lane % 16 and contraction index 4 s + lane / 16 of each operand.  A KC
