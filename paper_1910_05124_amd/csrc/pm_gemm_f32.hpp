@@ -3,11 +3,12 @@
 //   C[i, j] = sum_k A(i, k) * B(j, k),   v_mfma_f32_16x16x4_f32 (fp32 operands, fp32 accumulation).
 //
 // Operands are "KC" (contraction index contiguous) or "RC" (row index contiguous) as in pm_gemm_mfma.hpp.  The networks
-// trained in fp32 are small: a product has 10^5 .. 10^9 multiply-adds, and what bounds it is the latency of its chain of
-// additions - about 28 ns per dependent 16 x 16 x 4 step, 7 ns per index (100 x 4096 x 33: 31 us) - and of its first
-// loads, not the matrix rate.  So the operands go from memory to the matrix instruction's registers without a stop in
-// LDS (no barrier in the main loop), several 16-deep pieces of the contraction in flight ahead of those being multiplied.
-// (Staged through LDS, 32 x 32 outputs and 128 indices at a time: 6.5 -> 7.7 us on 100 x 512 x 512, 31 -> 43 us there.)
+// trained in fp32 are small: a product has 10^5 .. 10^9 multiply-adds, and what bounds it is the latency of its first loads
+// and of its chain of additions, not the matrix rate.  So the operands go from memory to the matrix instruction's
+// registers without a stop in LDS (no barrier in the main loop), several 16-deep pieces of the contraction in flight ahead
+// of those being multiplied.  A dependent 16 x 16 x 4 step takes 12.9 ns from registers, 3.2 ns per index; here an
+// index costs 7 ns (100 x 4096 x 33: 31 us), a third of it the lane exchanges below (21 us without them), the rest loads.
+// Staged through LDS, 32 x 32 outputs and 128 indices at a time, it was slower: 6.5 -> 7.7 us on 100 x 512 x 512, 31 -> 43.
 //
 // Order of the sums.  Every output is ONE chain of fused multiply-adds over k = 0, 1, 2, ... starting at zero: the
 // instruction adds its four products to the accumulator one after the other, each addition rounded (checked bit for bit
