@@ -10,13 +10,12 @@
 #include "pm_attn_mfma.hpp"
 
 namespace {
-// bf16 matrix instructions: whole tiles of 64-wide heads, or (ragged lengths, 32-wide heads) with the probabilities in
-// three terms
-template <int DH, bool RAGGED, bool SPLIT>
+// bf16 matrix instructions: forward whole tiles of 64-wide heads; backward those, or (ragged lengths, 32-wide heads) with
+// the probabilities in three terms
 void mfma_fwd(hipStream_t st, int B, int S, int H, const bf16_t* q, const bf16_t* k, const bf16_t* v, bf16_t* o, float* lse) {
   const int qblocks = (S + 127) / 128;
-  hipLaunchKernelGGL((pm_attn_mfma_fwd_kernel<DH, RAGGED, SPLIT>), dim3(B * H * qblocks), dim3(256), 0, st, q, k, v, o, lse, S, H,
-                     B * H, 1.f / sqrtf((float)DH));
+  hipLaunchKernelGGL((pm_attn_mfma_fwd_kernel<64>), dim3(B * H * qblocks), dim3(256), 0, st, q, k, v, o, lse, S, H, B * H,
+                     1.f / sqrtf(64.f));
 }
 template <int DH, bool RAGGED, bool SPLIT>
 void mfma_bwd(hipStream_t st, int B, int S, int H, const bf16_t* q, const bf16_t* k, const bf16_t* v, const bf16_t* o,
@@ -48,11 +47,8 @@ void f32_fwd_any(int dh, P... p) {
     case 4: f32_fwd<T, 4, VEC>(p...); break;
     case 8: f32_fwd<T, 8, VEC>(p...); break;
     case 16: f32_fwd<T, 16, VEC>(p...); break;
-    default:
-      if constexpr (sizeof(T) == 4 || !VEC) {
-        if (dh == 32) f32_fwd<T, 32, VEC>(p...);
-        else f32_fwd<T, 64, VEC>(p...);
-      }
+    case 32: f32_fwd<T, 32, VEC>(p...); break;
+    default: f32_fwd<T, 64, VEC>(p...); break;
   }
 }
 template <typename T, bool VEC, class... P>
@@ -72,16 +68,15 @@ template <class... P>
 bool aligned(size_t n, P... p) { return ((... | (uintptr_t)p) & (n - 1)) == 0; }
 }  // namespace
 
-// Heads of 32 and 64 outside whole tiles: the bf16 kernels read 16 bytes at a time; tensors that start anywhere else go
-// through the fp32 kernels, element by element (24 x 100 tokens, 5 heads of 64: forward 14 us against 8, backward 59 against 20).
+// Outside whole tiles the forward pass is fp32 arithmetic (see pm_attn_mfma.hpp).  Backward of heads of 32 and 64: the bf16
+// kernels read 16 bytes at a time; tensors that start anywhere else go through the fp32 kernels, element by element
+// (24 x 100 tokens, 5 heads of 64: 59 us against 20).
 bool pm_attn_fwd_launch(hipStream_t st, int B, int S, int H, int dh, const bf16_t* q, const bf16_t* k, const bf16_t* v, bf16_t* o,
                         float* lse) {
-  if (pm_attn_whole_tiles(S, dh)) { mfma_fwd<64, false, false>(st, B, S, H, q, k, v, o, lse); return true; }
+  if (pm_attn_whole_tiles(S, dh)) { mfma_fwd(st, B, S, H, q, k, v, o, lse); return true; }
   if (!pm_attn_short_fits(S, dh)) return false;
-  if (!aligned(dh < 32 ? 8 : 16, q, k, v, o)) f32_fwd_any<bf16_t, false>(dh, st, B, S, H, q, k, v, o, lse);
-  else if (dh == 32) mfma_fwd<32, true, true>(st, B, S, H, q, k, v, o, lse);
-  else if (dh == 64) mfma_fwd<64, true, true>(st, B, S, H, q, k, v, o, lse);
-  else f32_fwd_any<bf16_t, true>(dh, st, B, S, H, q, k, v, o, lse);
+  if (aligned(8, q, k, v, o)) f32_fwd_any<bf16_t, true>(dh, st, B, S, H, q, k, v, o, lse);
+  else f32_fwd_any<bf16_t, false>(dh, st, B, S, H, q, k, v, o, lse);
   return true;
 }
 bool pm_attn_fwd_launch(hipStream_t st, int B, int S, int H, int dh, const float* q, const float* k, const float* v, float* o,

@@ -1,5 +1,5 @@
-// Causal attention core in fp32 arithmetic, for fp32 contexts and for bf16 tensors with heads narrower than 32
-// or off the alignment of the bf16 kernels, gfx950.
+// Causal attention core in fp32 arithmetic, for fp32 contexts, for the forward pass of bf16 tensors outside whole
+// tiles of 64-wide heads, and for the backward pass of bf16 heads narrower than 32 or off the bf16 kernels' alignment, gfx950.
 // T: element type of the tensors in memory; everything inside is fp32.  VEC: see pm_af_ld4.
 //
 // Order of the sums.  Scores are one chain of fused multiply-adds over the head dimension, the forward pass takes its keys
@@ -24,6 +24,8 @@
 // and these shapes (a few dozen heads, sequences of at most 8192 / (DH + 1) rows) need the blocks to fill the chip.
 // A masked row has probability zero, and zero times an infinity or NaN of its is NaN: where a tile with masked rows holds such
 // a value, its rows are added by hand (pm_at_add_row), each for the owned rows that see it.
+// 24 sequences of 100 tokens, 5 heads of 64 in bf16: forward 496 -> 12 us (8 on the bf16 matrix kernel); 82 x 100 tokens, 16
+// heads of 64: 1213 -> 82 us (23).
 // 8 sequences of 64 tokens, 8 heads of 32: forward 85 -> 6 us, backward 161 -> 16 us per layer against one thread per row.
 #pragma once
 #include "pm_common.hpp"

@@ -18,22 +18,27 @@
 // v of lane group g = l / 32 the streamed row 16 (v / 8) + 8 g + v % 8, i.e. values 8 s .. 8 s + 7 are
 // exactly the k-slots of lane group g in k-step s of the second MFMA.
 //
-// A sequence that is no multiple of 32 rows (RAGGED, a template argument so that whole tiles keep their plain loads):
-// loads past the end re-read the last row, so every value stays finite.  Owned rows past the end are not stored.
-// Streamed keys past the end lie behind every query that is stored and fall to the causal mask; only the dK/dV
-// kernel, whose streamed index is the query, masks its last tile explicitly.
-// (24 x 100 tokens, 5 heads of 64, on the one-thread-per-row kernels that these lengths took before: forward 511 us,
-// backward 2090 us per layer, one wave per 64 rows walking 100 dependent keys; here 8 us and 20 us.)
+// The forward kernel takes whole tiles of 64-wide heads only: outside them (32-wide heads, lengths that are no multiple of
+// 32) the forward pass runs on fp32 arithmetic in index order (pm_attn_f32.hpp), whose rounding the ReLU units behind it
+// hang on.  A deep network of few tokens (6 layers, 125 tokens, heads of 32) moved by 1 % of its gradients with this
+// kernel in its place.  The backward kernels take both, with these template arguments:
+//
+// RAGGED, a sequence that is no multiple of 32 rows (an argument so that whole tiles keep their plain loads): loads past the
+// end re-read the last row, so every value stays finite.  Owned rows past the end are not stored.  Streamed keys past
+// the end lie behind every query that is stored and fall to the causal mask; only the dK/dV kernel, whose streamed
+// index is the query, masks its last tile explicitly.
+// (24 x 100 tokens, 5 heads of 64, backward: 2090 us per layer on the one-thread-per-row kernels that these lengths took
+// before, one wave per 64 rows walking 100 dependent keys; here 20 us.)
 //
 // SPLIT: the second products take the probabilities (and dS) as three bf16 terms instead of one.  Whole tiles of 64-wide
-// heads round them to one bf16 value; the shapes that run on fp32 arithmetic otherwise (32-wide heads, ragged lengths)
-// keep all 24 mantissa bits through these products, for four more matrix instructions per tile and head half.  Two terms
-// (16 bits) took 6.6 + 16.2 us per layer of the example above against 7.1 + 17.7 and lost bits where a sum cancels.
+// heads round them to one bf16 value; the shapes that run on fp32 arithmetic otherwise keep all 24 mantissa bits
+// through these products, for four more matrix instructions per tile and head half.  Two terms (16 bits) took 16.2 us per
+// layer of the example above against 17.7 and lost bits where a sum cancels.
 //
 // A masked row has probability zero, and zero times an infinity or NaN of its is NaN.  The SPLIT shapes keep such a value from
 // rows that the mask keeps it from: where a tile with masked rows holds one, its second product is left out and its rows
 // are added by hand at the end (pm_at_add_row), each for the owned rows that see it.  (The look at those tiles and the
-// code behind it: 7.1 + 17.7 -> 7.7 + 19.7 us per layer of the example above.)
+// code behind it: 17.7 -> 19.7 us per layer of the example above.)
 //
 // Probabilities are recomputed in the backward from q, k and the stored log-sum-exp of the scaled
 // scores; D_i = sum_c dO[i, c] O[i, c].  Two backward kernels (dQ; dK and dV) so that every output
@@ -147,10 +152,9 @@ __device__ __forceinline__ void pm_at_store_t(bf16_t* out_row, const pm_f32x16* 
 // double-buffered in LDS (one barrier per tile).
 // ---------------------------------------------------------------------------------------------
 // (register budget of four waves per SIMD: two values spill, and the fourth wave is worth more - 26.2 -> 24.7 us on
-// 16 x 512 tokens, 16 heads; the dQ kernel would spill 34 and is left at three.  SPLIT, 64 wide: three as well, 9.3 -> 7.7 us
-// on 24 x 100 tokens, 5 heads; 32 wide four, 15.4 -> 12.9 us on 256 x 32 tokens, 16 heads)
-template <int DH, bool RAGGED, bool SPLIT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SPLIT && DH == 64 ? 3 : 4, SPLIT && DH == 64 ? 3 : 4))) void pm_attn_mfma_fwd_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
+// 16 x 512 tokens, 16 heads; the dQ kernel would spill 34 and is left at three.)
+template <int DH>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void pm_attn_mfma_fwd_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
                                                                const bf16_t* __restrict__ v, bf16_t* __restrict__ o,
                                                                float* __restrict__ lse, int S, int H, int BH, float scale) {
   __shared__ __attribute__((aligned(16))) bf16_t sK[2][32 * PM_AT_ST<DH>];
@@ -163,13 +167,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SPLIT && DH
   const int q0 = qb * 128 + wave * 32;
   const bool active = q0 < S;
   const int my_last = q0 >> 5;
-  const int qr = RAGGED && q0 + ql >= S ? S - 1 : q0 + ql;                 // the row this lane reads
   const int n_tiles = ((S < qb * 128 + 128 ? S : qb * 128 + 128) + 31) >> 5;
 
   pm_bf16x8 fq[DH / 16];
 #pragma unroll
   for (int kk = 0; kk < DH / 16; ++kk)
-    fq[kk] = active ? *reinterpret_cast<const pm_bf16x8*>(q + base + (int64_t)qr * d + kk * 16 + 8 * g) : pm_at_zero8();
+    fq[kk] = active ? *reinterpret_cast<const pm_bf16x8*>(q + base + (int64_t)(q0 + ql) * d + kk * 16 + 8 * g) : pm_at_zero8();
   pm_f32x16 acc[DH / 32];
 #pragma unroll
   for (int dt = 0; dt < DH / 32; ++dt)
@@ -184,8 +187,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SPLIT && DH
   // so a load has more than a whole iteration to arrive.
   uint4 rk0, rv0, rk1 = make_uint4(0, 0, 0, 0), rv1 = rk1;
   auto gload = [&](int t, uint4& rk, uint4& rv) __attribute__((always_inline)) {
-    int r = t * 32 + lrow;
-    if (RAGGED) r = r < S ? r : S - 1;
+    const int r = t * 32 + lrow;
     rk = *reinterpret_cast<const uint4*>(k + base + (int64_t)r * d + lcol);
     rv = *reinterpret_cast<const uint4*>(v + base + (int64_t)r * d + lcol);
   };
@@ -199,7 +201,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SPLIT && DH
   __syncthreads();
   const int prow = pm_at_perm(ql);
   const float c2 = scale * 1.44269504f;            // scores in base-2 units: exp(x) = exp2(x log2 e)
-  bool odd = false;
   auto tile = [&](int jt, int cur) __attribute__((always_inline)) {
     if (active && jt <= my_last) {
       pm_f32x16 s;
@@ -215,8 +216,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SPLIT && DH
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
           const int kidx = jt * 32 + 16 * (e >> 3) + 8 * g + (e & 7);
-          // (SPLIT: minus infinity, so that a row whose scores are all of them minus infinity takes nothing from it)
-          if (kidx > q0 + ql) p[e] = SPLIT ? -__builtin_inff() : -3.0e38f;
+          if (kidx > q0 + ql) p[e] = -3.0e38f;
         }
       }
 #pragma unroll
@@ -238,8 +238,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SPLIT && DH
           for (int e = 0; e < 16; ++e) acc[dt][e] *= corr;
       }
       m = mn;
-      if (SPLIT && jt == my_last) odd = pm_at_odd<DH>(sV[cur], lane);
-      if (!SPLIT || !odd) pm_at_second<DH, SPLIT>(acc, sV[cur], p, lane);
+      pm_at_second<DH, false>(acc, sV[cur], p, lane);
     }
   };
   // steady part: the loads are unconditional, so the compiler counts outstanding loads exactly and the
@@ -269,15 +268,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SPLIT && DH
   }
   if (active) {
     lsum += __shfl_xor(lsum, 32, 64);
-    if (SPLIT && odd) {
-#pragma unroll 1
-      for (int j = q0; j < S && j < q0 + 32; ++j) {
-        const int64_t rj = base + (int64_t)j * d;
-        const float pj = __builtin_amdgcn_exp2f(pm_at_dot<bf16_t, DH>(q + base + (int64_t)qr * d, k + rj) * c2 - m);
-        pm_at_add_row<bf16_t, DH>(acc, v + rj, pj, j <= q0 + ql, lane);
-      }
-    }
-    if (RAGGED && q0 + ql >= S) return;
     pm_at_store_t<DH>(o + base + (int64_t)(q0 + ql) * d, acc, 1.f / lsum, lane);
     if (g == 0) lse[((int64_t)b * H + h) * S + q0 + ql] = m * 0.693147181f + __logf(lsum);   // m is in base-2 units
   }

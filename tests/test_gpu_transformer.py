@@ -138,12 +138,13 @@ def _fma(a, b, c):
 
 
 @pytest.mark.parametrize("dtype,B,S,H,dh", [("f32", 2, 5, 2, 64), ("f32", 1, 16, 2, 32), ("f32", 2, 33, 1, 16), ("f32", 1, 50, 2, 8),
-                                            ("f32", 1, 67, 1, 4), ("f32", 1, 70, 1, 64), ("bf16", 2, 35, 1, 16), ("bf16", 1, 18, 3, 4)])
+                                            ("f32", 1, 67, 1, 4), ("f32", 1, 70, 1, 64), ("bf16", 2, 35, 1, 16), ("bf16", 1, 18, 3, 4),
+                                            ("bf16", 1, 45, 2, 64), ("bf16", 2, 32, 1, 32), ("bf16", 1, 99, 1, 32)])
 def test_fp32_attention_arithmetic_keeps_its_order(torch_cuda, dtype, B, S, H, dh):
     """The fp32 core bit for bit: scores are chains of fused multiply-adds over the head dimension, the forward pass takes a
     row's keys one after the other with a running maximum and sum, a gradient row is one chain over its keys or queries.
-    (In an fp32 network a ReLU input next to zero turns one rounding into another gradient.)  The exponentials are the
-    device's own; every argument lies in its normal range."""
+    (A ReLU input next to zero turns one rounding into another gradient; bf16 tensors outside whole tiles of 64-wide heads
+    share the forward pass.)  The exponentials are the device's own; every argument lies in its normal range."""
     import paper_1910_05124_amd as pm
     torch = torch_cuda
     if np.finfo(np.longdouble).nmant < 63:
@@ -187,6 +188,8 @@ def test_fp32_attention_arithmetic_keeps_its_order(torch_cuda, dtype, B, S, H, d
         acc = np.where(on[:, None], _fma(acc, corr[..., None], p[..., None] * V[..., j, None, :]), acc)
         m = np.where(on, mn, m)
     assert np.array_equal(O, stored(acc * (f(1.0) / l)[..., None]))
+    if dtype == "bf16" and dh >= 32:                        # backward on the bf16 matrix kernels
+        return
     D = np.zeros((B, H, S), dtype=f)
     for c in range(dh):
         D = _fma(DO[..., c], O[..., c], D)
@@ -307,7 +310,8 @@ def test_attention_mask_stops_infinities_and_nans(torch_cuda, dtype, S, dh, bad)
 @pytest.mark.parametrize("dtype,S,dh", [("f32", 33, 64), ("f32", 40, 8), ("bf16", 45, 64), ("bf16", 70, 32), ("bf16", 40, 16), ("bf16", 21, 4)])
 def test_attention_takes_tensors_that_start_anywhere(torch_cuda, dtype, S, dh, shift):
     """Outside whole bf16 tiles the tensors may start at any element: the same results as from aligned ones.  fp32 arithmetic
-    on both sides gives the same bits; 32- and 64-wide bf16 heads differ in the kernel, so by one rounding of the output."""
+    on both sides gives the same bits; the backward pass of 32- and 64-wide
+    bf16 heads differs in the kernel, so by one rounding of the output."""
     import paper_1910_05124_amd as pm
     torch = torch_cuda
     tdt = _tdt(torch, dtype)
@@ -330,8 +334,8 @@ def test_attention_takes_tensors_that_start_anywhere(torch_cuda, dtype, S, dh, s
                             lse.data_ptr(), dq.data_ptr(), dk.data_ptr(), dv.data_ptr())
         return [t.float().cpu().numpy() for t in (o, dq, dk, dv)]
 
-    for got, want in zip(run(shift), run(0)):
-        if dtype == "f32" or dh < 32:
+    for name, got, want in zip(("o", "dq", "dk", "dv"), run(shift), run(0)):
+        if dtype == "f32" or dh < 32 or name == "o":
             assert np.array_equal(got, want)
         else:
             assert np.max(np.abs(got - want)) <= 2.0 ** -8 * np.max(np.abs(want))
