@@ -19,6 +19,7 @@
 #include "pm_elem.hpp"
 #include "pm_gemm_f32.hpp"
 #include "pm_gemm_mfma.hpp"
+#include "pm_gemm_async.hpp"
 #include "pm_update.hpp"
 #include "pm_chain.hpp"
 #include "pm_transformer.hpp"

@@ -312,14 +312,10 @@ __device__ __forceinline__ void pm_prefetch_block(const PmPrefetch& pf, int bx, 
   asm volatile("" ::"v"(acc));                            // the reads have no other use: keep them
 }
 
-// one problem, passed by value.  Grid (column tiles, row tiles + extra rows of prefetching blocks).
+// one problem, passed by value.  Grid (column tiles, row tiles).
 template <class Cfg, bool AKC, bool BKC, class Epi>
-__global__ __launch_bounds__(Cfg::NT) void pm_gemm_mfma_kernel(PmGemmProb<Epi> pr, PmPrefetch pf, int tiles_i) {
+__global__ __launch_bounds__(Cfg::NT) void pm_gemm_mfma_kernel(PmGemmProb<Epi> pr) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[PmGemmLds<Cfg, AKC, BKC>::bytes];
-  if ((int)blockIdx.y >= tiles_i) {
-    pm_prefetch_block(pf, blockIdx.x, blockIdx.y - tiles_i, gridDim.x, gridDim.y - tiles_i);
-    return;
-  }
   // XCD k (blocks with x % 8 == k) takes the k-th eighth of the column tiles: its L2 then holds one
   // contiguous part of the B operand
   int bx = blockIdx.x;
@@ -336,14 +332,9 @@ __global__ __launch_bounds__(Cfg::NT) void pm_gemm_mfma_grouped_kernel(const PmG
 }
 
 template <class Cfg, bool AKC, bool BKC, class Epi>
-inline void pm_mfma_launch(hipStream_t st, const PmGemmProb<Epi>& pr, const PmPrefetch* pf = nullptr) {
-  dim3 grid((pr.J + Cfg::BJ - 1) / Cfg::BJ, (pr.I + Cfg::BI - 1) / Cfg::BI);
-  const int tiles_i = (int)grid.y;
-  PmPrefetch none{nullptr, nullptr, 0, 0, 0, 0, 0, 0};
-  // prefetching blocks only where the product leaves compute units idle, as many as are idle
-  if (pf && pf->base && (grid.x & 7) == 0 && grid.x * grid.y < 256) grid.y += (256 - grid.x * grid.y) / grid.x;
-  else pf = &none;
-  hipLaunchKernelGGL((pm_gemm_mfma_kernel<Cfg, AKC, BKC, Epi>), grid, dim3(Cfg::NT), 0, st, pr, *pf, tiles_i);
+inline void pm_mfma_launch(hipStream_t st, const PmGemmProb<Epi>& pr) {
+  const dim3 grid((pr.J + Cfg::BJ - 1) / Cfg::BJ, (pr.I + Cfg::BI - 1) / Cfg::BI);
+  hipLaunchKernelGGL((pm_gemm_mfma_kernel<Cfg, AKC, BKC, Epi>), grid, dim3(Cfg::NT), 0, st, pr);
 }
 
 using PmCfgBig = PmGemmCfg<128, 128, 2, 2, 1, 64>;      // MFMA-bound shapes
@@ -358,6 +349,8 @@ using PmCfgSkinny256 = PmGemmCfg<32, 32, 1, 1, 8, 256>;
 using PmCfgSkinny512 = PmGemmCfg<32, 32, 1, 1, 16, 512>;
 using PmCfgSkinny1K = PmGemmCfg<32, 32, 1, 1, 16, 1024>;
 
+template <class Epi>
+inline bool pm_async_try(hipStream_t st, const PmGemmProb<Epi>& pr, const PmPrefetch* pf);
 template <bool AKC, bool BKC, class Epi>
 inline bool pm_big_try(hipStream_t st, const PmGemmProb<Epi>& pr);
 template <bool AKC, bool BKC, class Epi>
@@ -365,16 +358,20 @@ inline bool pm_mid_try(hipStream_t st, const PmGemmProb<Epi>& pr);
 
 template <bool AKC, bool BKC, class Epi>
 inline void pm_mfma_pick(hipStream_t st, const PmGemmProb<Epi>& pr, const PmPrefetch* pf = nullptr) {
-  if (pm_big_try<AKC, BKC>(st, pr)) return;
-  const long tiles128 = (long)((pr.I + 127) / 128) * ((pr.J + 127) / 128);
-  const long tiles64 = (long)((pr.I + 63) / 64) * ((pr.J + 63) / 64);
-  if (pm_mid_try<AKC, BKC>(st, pr)) return;
-  if (tiles128 >= 512) pm_mfma_launch<PmCfgBig, AKC, BKC>(st, pr);
-  else if (pr.K <= 128) pm_mfma_launch<PmCfgShortK, AKC, BKC>(st, pr, pf);
-  else if (tiles64 >= 192 || pr.K <= 256) pm_mfma_launch<PmCfgMid, AKC, BKC>(st, pr, pf);
-  else if (pr.K >= 768) pm_mfma_launch<PmCfgSkinny1K, AKC, BKC>(st, pr, pf);
-  else if (pr.K >= 384) pm_mfma_launch<PmCfgSkinny512, AKC, BKC>(st, pr, pf);
-  else pm_mfma_launch<PmCfgSkinny256, AKC, BKC>(st, pr, pf);
+  if constexpr (AKC) {                                    // forward and data gradient
+    if (!pm_async_try(st, pr, pf)) pm_mfma_launch<PmCfgMid, AKC, BKC>(st, pr);      // (rows of millions of elements)
+  } else {                                                // weight gradient
+    if (pm_big_try<AKC, BKC>(st, pr)) return;
+    const long tiles128 = (long)((pr.I + 127) / 128) * ((pr.J + 127) / 128);
+    const long tiles64 = (long)((pr.I + 63) / 64) * ((pr.J + 63) / 64);
+    if (pm_mid_try<AKC, BKC>(st, pr)) return;
+    if (tiles128 >= 512) pm_mfma_launch<PmCfgBig, AKC, BKC>(st, pr);
+    else if (pr.K <= 128) pm_mfma_launch<PmCfgShortK, AKC, BKC>(st, pr);
+    else if (tiles64 >= 192 || pr.K <= 256) pm_mfma_launch<PmCfgMid, AKC, BKC>(st, pr);
+    else if (pr.K >= 768) pm_mfma_launch<PmCfgSkinny1K, AKC, BKC>(st, pr);
+    else if (pr.K >= 384) pm_mfma_launch<PmCfgSkinny512, AKC, BKC>(st, pr);
+    else pm_mfma_launch<PmCfgSkinny256, AKC, BKC>(st, pr);
+  }
 }
 
 // Alignment rules of the MFMA path for one problem given element strides (exactly one of
@@ -515,22 +512,9 @@ struct PmBigLds {
 // the other register set into the other LDS stage, a part behind each k-step.  A load therefore has
 // more than a slab of MFMA time to arrive before it is waited for; one barrier per slab.
 //
-// Seg: PmNoSeg, or PmKSeg3 = the contraction runs over three operand pairs of Kseg indices each
-// (out = A0 B0 + A1 B1 + A2 B2 as ONE product with K = 3 Kseg: the slab loader switches base pointers
-// at the segment boundaries, which fall on slab boundaries since Kseg is a multiple of 64).
-struct PmNoSeg {
-  static constexpr bool on = false;
-};
-struct PmKSeg3 {                     // pair 0 is the problem's own A and B
-  static constexpr bool on = true;
-  const bf16_t* A1;
-  const bf16_t* A2;
-  PmWLoc<bf16_t> B1, B2;
-  int Kseg;
-};
-template <class Cfg, bool AKC, bool BKC, bool CHECK, class Epi, class Seg = PmNoSeg>
+template <class Cfg, bool AKC, bool BKC, bool CHECK, class Epi>
 __device__ __forceinline__ void pm_gemm_big_body(const PmGemmProb<Epi>& pr, int id, int tiles_i, int tiles_j, bf16_t* smem,
-                                                 bool xcd_remap = true, const Seg& sg = Seg()) {
+                                                 bool xcd_remap = true) {
   constexpr int BI = Cfg::BI, BJ = Cfg::BJ, WI = Cfg::WI, WJ = Cfg::WJ, NT = Cfg::NT, BK = PM_SLAB;
   constexpr int TI = BI / WI / 32, TJ = BJ / WJ / 32;
   using SA = PmBigTile<BI, AKC>;
@@ -577,37 +561,11 @@ __device__ __forceinline__ void pm_gemm_big_body(const PmGemmProb<Epi>& pr, int 
   LA la0, la1;
   LB lb0, lb1;
   const int nk = (K + BK - 1) / BK;
-  // segment p > 0 is addressed with the running contraction index through a base pointer moved back by
-  // p * Kseg contraction steps, so the loader's address arithmetic is the same as for a single pair
-  const bf16_t* As1 = A;
-  const bf16_t* As2 = A;
-  const bf16_t* Bs1 = B;
-  const bf16_t* Bs2 = B;
-  int Kseg = K;
-  if constexpr (Seg::on) {
-    Kseg = sg.Kseg;
-    const int64_t ka = AKC ? 1 : lda, kb = BKC ? 1 : ldb;
-    As1 = sg.A1 - (int64_t)Kseg * ka;
-    As2 = sg.A2 - 2 * (int64_t)Kseg * ka;
-    Bs1 = sg.B1.get() - (int64_t)Kseg * kb;
-    Bs2 = sg.B2.get() - 2 * (int64_t)Kseg * kb;
-  }
-  // global loads of slab kt into a register set.  (The selects work on copies of the pointers: a
-  // conditional between the captured variables themselves is a conditional between their addresses,
-  // which keeps every captured variable in memory.)
+  // global loads of slab kt into a register set
   auto load_slab = [&](auto tail, LA& sa, LB& sb, int kt_) __attribute__((always_inline)) {
     constexpr bool TAIL = decltype(tail)::value;
-    const int k_ = kt_ * BK;
-    const bf16_t* Xa_ = A;
-    const bf16_t* Xb_ = B;
-    if constexpr (Seg::on) {
-      const bf16_t *a1_ = As1, *a2_ = As2, *b1_ = Bs1, *b2_ = Bs2;
-      const int ks_ = Kseg;
-      if (k_ >= ks_) Xa_ = a1_, Xb_ = b1_;
-      if (k_ >= 2 * ks_) Xa_ = a2_, Xb_ = b2_;
-    }
-    sa.template load<CHECK, TAIL>(Xa_, lda, i0, k_, I, K);
-    sb.template load<CHECK, TAIL>(Xb_, ldb, j0, k_, J, K);
+    sa.template load<CHECK, TAIL>(A, lda, i0, kt_ * BK, I, K);
+    sb.template load<CHECK, TAIL>(B, ldb, j0, kt_ * BK, J, K);
   };
   load_slab(std::true_type{}, la0, lb0, 0);
   la0.template store<CHECK, true>(smem, 0, K);
@@ -773,40 +731,6 @@ __global__ __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(Cfg::WP
   pm_gemm_big_body<Cfg, AKC, BKC, CHECK, Epi>(pr, blockIdx.x, tiles_i, tiles_j, smem);
 }
 
-// Three products of equal shape in one launch (the query / key / value projections share their
-// input): block b works on problem b / (tiles_i * tiles_j).  One launch instead of three keeps the
-// chip filled across the problems' first and last waves of tiles.
-template <class Cfg, bool AKC, bool BKC, bool CHECK, class Epi>
-__global__ __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(Cfg::WPE, Cfg::WPE))) void pm_gemm_big_multi3_kernel(PmGemmProb<Epi> p0, PmGemmProb<Epi> p1, PmGemmProb<Epi> p2, int tiles_i, int tiles_j) {
-  __shared__ __attribute__((aligned(16))) bf16_t smem[PmBigLds<Cfg, AKC, BKC>::elems];
-  const int nt = tiles_i * tiles_j;
-  const int p = blockIdx.x / nt, id = blockIdx.x - p * nt;      // uniform over the block
-  pm_gemm_big_body<Cfg, AKC, BKC, CHECK, Epi>(p == 0 ? p0 : p == 1 ? p1 : p2, id, tiles_i, tiles_j, smem);
-}
-
-// One product with a long contraction and too few output tiles to fill the chip, its contraction cut into parts that
-// run side by side: block b works on part b / (tiles_i * tiles_j), indices part * kpart on, and writes that part's fp32
-// output at part * part_stride; the consumer adds the parts in order.  kpart is a multiple of 64.
-template <class Cfg, bool CHECK, class Epi>
-__global__ __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(Cfg::WPE, Cfg::WPE))) void pm_gemm_big_ksplit_kernel(PmGemmProb<Epi> pr, int kpart, int64_t part_stride, int tiles_i, int tiles_j) {
-  __shared__ __attribute__((aligned(16))) bf16_t smem[PmBigLds<Cfg, Epi::kAKC, Epi::kBKC>::elems];
-  const int nt = tiles_i * tiles_j;
-  const int p = blockIdx.x / nt, id = blockIdx.x - p * nt;      // uniform over the block
-  const int k0 = p * kpart;
-  pr.A += (int64_t)k0 * (Epi::kAKC ? 1 : pr.lda);
-  pr.B.base += (int64_t)k0 * (Epi::kBKC ? 1 : pr.ldb);
-  pr.K = pr.K - k0 < kpart ? pr.K - k0 : kpart;
-  pr.epi.out += p * part_stride;
-  pm_gemm_big_body<Cfg, Epi::kAKC, Epi::kBKC, CHECK, Epi>(pr, id, tiles_i, tiles_j, smem);
-}
-
-// One product whose contraction runs over three operand pairs (PmKSeg3); pr.K = 3 * Kseg, pr.A / pr.B = pair 0.
-template <class Cfg, bool AKC, bool BKC, bool CHECK, class Epi>
-__global__ __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(Cfg::WPE, Cfg::WPE))) void pm_gemm_big_kseg3_kernel(PmGemmProb<Epi> pr, PmKSeg3 sg, int tiles_i, int tiles_j) {
-  __shared__ __attribute__((aligned(16))) bf16_t smem[PmBigLds<Cfg, AKC, BKC>::elems];
-  pm_gemm_big_body<Cfg, AKC, BKC, CHECK, Epi, PmKSeg3>(pr, blockIdx.x, tiles_i, tiles_j, smem, true, sg);
-}
-
 // Many problems in one launch, scheduled per XCD.  Consecutive block ids land on consecutive XCDs
 // (8 of them, each with its own L2), so block b works for XCD b % 8 at position b / 8 of that XCD's
 // own work list: a list of segments (problem, first tile, tile count) built by the host so that the
@@ -865,30 +789,9 @@ using PmBig256 = PmBigCfg<256, 256, 2, 4>;
 // software pipeline hides the memory latency that a load - store - compute loop pays once per slab.
 using PmBig64 = PmBigCfg<64, 64, 2, 2>;
 
-// 256 x 128 and 128 x 256 blocks, 8 waves x (64 x 64), one block per compute unit: the operand tile with 256 rows is
-// written to LDS once for two of the other's (a quarter less LDS write traffic and global load issue than two
-// 128 x 128 blocks), with the same eight waves per compute unit.  Measured stand-alone on the token-rich products of
-// the 12-layer workload (8192 rows; one block per compute unit or a few rounds, operands warm) against 128 x 128:
-// K = 4096 forward 78 -> 73 us, feed-forward expansion 88 -> 81 us (256 x 128); data gradients 23 -> 21 us (K = 1024),
-// 79 -> 74 us (K = 4096), 92 -> 87 us (4096 columns; 128 x 256); the vocabulary projection (hundreds of rounds, fp32
-// output) is slower on them.  Inside a step only some of these gains remain (pm_rect_tiles says which epilogues
-// take the rectangular blocks).
-using PmBigTall = PmBigCfg<256, 128, 4, 2>;
-using PmBigWide = PmBigCfg<128, 256, 2, 4>;
-// a problem for these blocks: whole tiles, at least one per compute unit and at most a few rounds, K >= 1024
-template <class Cfg>
-inline bool pm_big_rect_suits(int I, int J, int K);
-
 // true if no tile of the problem needs a bounds test
 template <class Cfg>
 inline bool pm_big_aligned(int I, int J, int K) { return I % Cfg::BI == 0 && J % Cfg::BJ == 0 && K % 64 == 0; }
-
-template <class Cfg>
-inline bool pm_big_rect_suits(int I, int J, int K) {
-  if (!pm_big_aligned<Cfg>(I, J, K) || K < 1024) return false;
-  const long t = (long)(I / Cfg::BI) * (J / Cfg::BJ);
-  return t >= 256 && t <= 2048;
-}
 
 template <class Cfg, bool AKC, bool BKC, class Epi>
 inline void pm_big_launch(hipStream_t st, const PmGemmProb<Epi>& pr) {
@@ -929,118 +832,6 @@ inline bool pm_big_try(hipStream_t st, const PmGemmProb<Epi>& pr) {
     pm_big_launch<PmBig256, AKC, BKC>(st, pr);
     return true;
   }
-  // activations times weights with whole rectangular tiles: the tall block where the weights are read along the
-  // contraction (forward), the wide one where they are read across it (data gradient)
-  if constexpr (AKC && pm_rect_tiles<Epi>::value) {
-    using Rect = std::conditional_t<BKC, PmBigTall, PmBigWide>;
-    if (pm_big_rect_suits<Rect>(pr.I, pr.J, pr.K)) {
-      const int ti = pr.I / Rect::BI, tj = pr.J / Rect::BJ;
-      hipLaunchKernelGGL((pm_gemm_big_kernel<Rect, AKC, BKC, false, Epi>), dim3(ti * tj), dim3(Rect::NT), 0, st, pr, ti, tj);
-      return true;
-    }
-  }
   pm_big_launch<PmBig128, AKC, BKC>(st, pr);
-  return true;
-}
-
-
-// Which pipelined block tile a problem with `tiles128` / `tiles64` block tiles in total gets: 0 none, 128, 64.
-inline int pm_big_choice(long tiles128, long tiles64, int K) {
-  if (K < 256) return 0;
-  if (tiles128 >= 200) return 128;
-  if (tiles64 >= 256) return 64;
-  return 0;
-}
-
-// Three products of equal shape and layout (A row-major over the contraction, B likewise) in one launch.
-// False (nothing launched) if the shapes do not suit the pipelined kernels.
-template <class Epi>
-inline bool pm_gemm_multi3_try(hipStream_t st, const PmGemmProb<Epi> (&pr)[3]) {
-  const int I = pr[0].I, J = pr[0].J, K = pr[0].K;
-  for (int p = 0; p < 3; ++p) {
-    if (pr[p].I != I || pr[p].J != J || pr[p].K != K) return false;
-    if (!pm_mfma_fits(I, J, K, pr[p].A, pr[p].lda, 1, pr[p].B.base, pr[p].B.stride, pr[p].ldb, 1)) return false;
-  }
-  const long t128 = (long)((I + 127) / 128) * ((J + 127) / 128), t64 = (long)((I + 63) / 64) * ((J + 63) / 64);
-  const int pick = pm_big_choice(3 * t128, 3 * t64, K);
-  auto go = [&](auto cfg) {
-    using Cfg = decltype(cfg);
-    const int ti = (I + Cfg::BI - 1) / Cfg::BI, tj = (J + Cfg::BJ - 1) / Cfg::BJ;
-    if (pm_big_aligned<Cfg>(I, J, K))
-      hipLaunchKernelGGL((pm_gemm_big_multi3_kernel<Cfg, true, true, false, Epi>), dim3(3 * ti * tj), dim3(Cfg::NT), 0, st,
-                         pr[0], pr[1], pr[2], ti, tj);
-    else
-      hipLaunchKernelGGL((pm_gemm_big_multi3_kernel<Cfg, true, true, true, Epi>), dim3(3 * ti * tj), dim3(Cfg::NT), 0, st,
-                         pr[0], pr[1], pr[2], ti, tj);
-  };
-  if (pick == 128) go(PmBig128());
-  else if (pick == 64) go(PmBig64());
-  else return false;
-  return true;
-}
-
-// out = sum over p of A_p B_p with A_p (I x Kseg, row-major) and B_p (Kseg x J, row-major) as one product.
-template <class Epi>
-inline bool pm_gemm_kseg3_try(hipStream_t st, int I, int J, int Kseg, const bf16_t* const (&A)[3], int64_t lda,
-                              const PmWLoc<bf16_t> (&B)[3], int64_t ldb, const Epi& epi) {
-  if (Kseg % 64) return false;
-  for (int p = 0; p < 3; ++p)
-    if (!pm_mfma_fits(I, J, Kseg, A[p], lda, 1, B[p].base, B[p].stride, 1, ldb)) return false;
-  const long t128 = (long)((I + 127) / 128) * ((J + 127) / 128), t64 = (long)((I + 63) / 64) * ((J + 63) / 64);
-  const int pick = pm_big_choice(t128, t64, 3 * Kseg);
-  PmGemmProb<Epi> pr{I, J, 3 * Kseg, A[0], lda, B[0], ldb, epi};
-  PmKSeg3 sg{A[1], A[2], B[1], B[2], Kseg};
-  if (pm_big_rect_suits<PmBigTall>(I, J, Kseg)) {      // (measured 56.6 us tall, 58.0 wide, 60.5 on 128 x 128)
-    const int ti = I / 256, tj = J / 128;
-    hipLaunchKernelGGL((pm_gemm_big_kseg3_kernel<PmBigTall, true, false, false, Epi>), dim3(ti * tj), dim3(PmBigTall::NT), 0, st, pr,
-                       sg, ti, tj);
-    return true;
-  }
-  auto go = [&](auto cfg) {
-    using Cfg = decltype(cfg);
-    const int ti = (I + Cfg::BI - 1) / Cfg::BI, tj = (J + Cfg::BJ - 1) / Cfg::BJ;
-    if (pm_big_aligned<Cfg>(I, J, Kseg))
-      hipLaunchKernelGGL((pm_gemm_big_kseg3_kernel<Cfg, true, false, false, Epi>), dim3(ti * tj), dim3(Cfg::NT), 0, st, pr,
-                         sg, ti, tj);
-    else
-      hipLaunchKernelGGL((pm_gemm_big_kseg3_kernel<Cfg, true, false, true, Epi>), dim3(ti * tj), dim3(Cfg::NT), 0, st, pr,
-                         sg, ti, tj);
-  };
-  if (pick == 128) go(PmBig128());
-  else if (pick == 64) go(PmBig64());
-  else return false;
-  return true;
-}
-
-// How a product with K >> I, J is cut (pm_gemm_big_ksplit_kernel): block tile, parts and indices per part; parts = 1: not
-// at all.  Two halves on 256 x 256 tiles where those fill half to all of the chip (their main loop is the fastest from
-// 8192 indices on: 502 us on 8192 x 1024 x 32000); else as many parts on 128 x 128 tiles as give every compute unit two
-// blocks, of at least 512 indices each (below that the parts' start and the extra outputs cost
-// what they gain): 4096 x 512 x 8192 110 -> 49 us, 2048 x 768 x 16000 170 -> 68, 2400 x 320 x 10007 174 -> 42.
-struct PmKSplit { int tile, parts, kpart; };
-inline PmKSplit pm_ksplit_plan(int I, int J, int K, int max_parts) {
-  const PmKSplit none{0, 1, K};
-  if (K < 2048 || max_parts < 2) return none;
-  const int t256 = (I / 256) * (J / 256);
-  if (pm_big_aligned<PmBig256>(I, J, K) && K % 128 == 0 && K >= 16384 && 2 * t256 <= 256 && 2 * t256 >= 128) return {256, 2, K / 2};
-  const int t128 = ((I + 127) / 128) * ((J + 127) / 128);
-  int parts = std::min({8, max_parts, 512 / t128, K / 512});
-  if (parts < 2) return none;
-  const int kpart = (K + 64 * parts - 1) / (64 * parts) * 64;
-  parts = (K + kpart - 1) / kpart;
-  return {128, parts, kpart};
-}
-template <class Epi>
-inline bool pm_gemm_ksplit_try(hipStream_t st, const PmGemmProb<Epi>& pr, const PmKSplit& s, int64_t part_stride) {
-  if (s.parts < 2 || !pm_mfma_fits(pr.I, pr.J, pr.K, pr.A, pr.lda, 1, pr.B.base, pr.B.stride, 1, pr.ldb)) return false;
-  auto go = [&](auto cfg, auto check) {
-    using Cfg = decltype(cfg);
-    const int ti = (pr.I + Cfg::BI - 1) / Cfg::BI, tj = (pr.J + Cfg::BJ - 1) / Cfg::BJ;
-    hipLaunchKernelGGL((pm_gemm_big_ksplit_kernel<Cfg, decltype(check)::value, Epi>), dim3(s.parts * ti * tj), dim3(Cfg::NT), 0, st,
-                       pr, s.kpart, part_stride, ti, tj);
-  };
-  if (s.tile == 256) go(PmBig256(), std::false_type());
-  else if (pm_big_aligned<PmBig128>(pr.I, pr.J, pr.K)) go(PmBig128(), std::false_type());
-  else go(PmBig128(), std::true_type());
   return true;
 }

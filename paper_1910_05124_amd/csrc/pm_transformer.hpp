@@ -80,12 +80,6 @@ struct PmEpiF32 {
   }
 };
 
-// Inside a step of the 12-layer workload (kernel trace, same box): residual products 54.0 -> 51.8 us, fp32 data gradient
-// with K = 4096 77.2 -> 75.0 us on the rectangular blocks; the bf16 data gradients (58.2 -> 59.1 us) and the feed-forward
-// expansion (87.1 -> 88.3 us) lose what they gain stand-alone, the three projections in one launch stay the same.
-template <typename T> struct pm_rect_tiles<PmEpiFwdRes<T>> : std::true_type {};
-template <> struct pm_rect_tiles<PmEpiF32> : std::true_type {};
-
 // zero a list of regions of a flat fp32 array: region r = [reg[2r], reg[2r] + reg[2r+1]); grid (x, regions)
 __global__ __launch_bounds__(256) void pm_zero_regions_kernel(float* base, const int64_t* __restrict__ reg) {
   const int64_t off = reg[2 * blockIdx.y], n = reg[2 * blockIdx.y + 1];

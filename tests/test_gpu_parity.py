@@ -528,3 +528,51 @@ def test_bf16_chain_weight_gradients_of_many_rows(torch_cuda, rows, widths, N):
         assert np.all(np.abs(got[:dW.size].reshape(dW.shape) - dW) <= tol * W_terms), l
         assert np.all(np.abs(got[dW.size:] - db) <= tol * b_terms), l
     g.close()
+
+
+@pytest.mark.parametrize("M,n_in,n_out", [(1, 24, 8), (33, 40, 1032), (31, 1024, 72), (130, 1032, 200), (300, 1288, 200), (129, 72, 1000),
+                                          (700, 776, 776), (1500, 328, 1288), (2000, 200, 520), (1300, 1000, 2056), (3000, 1032, 1032),
+                                          (4097, 264, 2056), (8200, 264, 4104), (8192, 256, 4096)])
+def test_bf16_products_at_the_edges_of_every_block_shape(torch_cuda, M, n_in, n_out):
+    """Forward and data gradient for every block shape of the dispatch, with rows, columns and contractions that end inside a
+    tile and inside a slab.  A row of NaN stays in its row, whatever lies around the operands (NaN here) stays out, and
+    nothing behind the outputs is written.  Bound per output: one bf16 rounding, and K fp32 additions of terms whose absolute
+    values sum to S: (K + 4) 2^-24 S."""
+    import paper_1910_05124_amd as pm
+    torch = torch_cuda
+    gen = torch.Generator(device="cuda").manual_seed(M * 7 + n_in * 3 + n_out)
+
+    def guarded(rows, cols, fill=None):
+        buf = torch.full((rows * cols + 4096,), float("nan"), device="cuda", dtype=torch.bfloat16)
+        t = buf[2048:2048 + rows * cols].view(rows, cols)
+        if fill is None:
+            t.copy_(torch.randn(rows, cols, device="cuda", generator=gen))
+        return buf, t
+
+    _, x = guarded(M, n_in)
+    _, W = guarded(n_out, n_in)
+    _, b = guarded(1, n_out)
+    _, dz = guarded(M, n_out)
+    _, zp = guarded(M, n_in)
+    bad = M // 2 if M > 1 else None
+    if bad is not None:
+        x[bad] = float("nan")
+        dz[bad] = float("nan")
+    st = torch.cuda.current_stream().cuda_stream
+    zbuf, z = guarded(M, n_out, "nan")
+    abuf, a = guarded(M, n_out, "nan")
+    dbuf, dp = guarded(M, n_in, "nan")
+    pm.pm_linear_fwd(st, "bf16", M, n_in, n_out, x.data_ptr(), W.data_ptr(), b.data_ptr(), "relu", z.data_ptr(), a.data_ptr())
+    pm.pm_linear_bwd_data(st, "bf16", M, n_in, n_out, dz.data_ptr(), W.data_ptr(), zp.data_ptr(), "relu", dp.data_ptr())
+    torch.cuda.synchronize()
+    keep = [m for m in range(M) if m != bad]
+    Wd = W.double()
+    for got, ref, S, K in ((z, x.double() @ Wd.T + b.double(), x.double().abs() @ Wd.abs().T + b.double().abs(), n_in),
+                           (dp, (dz.double() @ Wd) * (zp.double() > 0), dz.double().abs() @ Wd.abs(), n_out)):
+        tol = 2.0 ** -8 * ref.abs() + (K + 4) * 2.0 ** -24 * S
+        assert bool(((got.double() - ref).abs() <= tol)[keep].all())
+        if bad is not None and got is z:
+            assert bool(torch.isnan(got[bad]).all())
+    assert torch.equal(a[keep], torch.relu(z[keep]))
+    for buf, t in ((zbuf, z), (abuf, a), (dbuf, dp)):
+        assert bool(torch.isnan(buf[:2048]).all()) and bool(torch.isnan(buf[2048 + t.numel():]).all())
