@@ -118,6 +118,7 @@ struct Layout {
   size_t t_xf, t_muf, t_rsf, t_nf, t_logits, t_dlogits;      // final LayerNorm and head
   size_t t_dx, t_dn, t_do;                                   // backward scratch, reused by every layer
   size_t t_pos, t_zero;                                      // positions fp32 [S, d]; zero-region table
+  size_t t_lnpart, t_lnwhere;                                // LayerNorm backward: tables of column sums, where the sums go
   size_t t_fuse, t_ublocks;                                  // update in the weight-gradient epilogue: problem table of that launch, blocks left to the update pass
   size_t t_wprobs, t_wtiles, t_wsegs;                        // grouped weight-gradient launch: problems (2 sets), tiles per XCD, segments
   int n_zero = 0;
@@ -323,6 +324,8 @@ void make_layout(int32_t L, const pm_layer_desc* layers, const int32_t* tau_fwd,
     for (int l = 0; l < L; ++l)
       if (lay.units[l].d.kind != PM_LINEAR) { lay.n_zero += 1; lay.zero_max = std::max(lay.zero_max, lay.units[l].n_pad); }
     lay.t_zero = take(sizeof(int64_t) * 2 * lay.n_zero);
+    lay.t_lnpart = take(sizeof(float) * (2 * nl + 1) * (size_t)pm_ln_part_blocks(Tk) * 2 * d);
+    lay.t_lnwhere = take(sizeof(int64_t) * 2 * (2 * nl + 1));
   } else if (o->arch == PM_ARCH_RESNET) {
     const size_t e = lay.esz;
     const int nconv = L - 1;
@@ -909,9 +912,15 @@ pm_status launch_tfm(pm_ctx* c, const void* x_dev, const void* y_dev, int accumu
   auto ln_fwd = [&](int u, const float* x, T* out, float* mu, float* rs) {
     pm_ln_fwd_launch<T>(st, x, Wx(u, 0), (int)U(u).boff, out, mu, rs, Tk, d);
   };
+  const int ln_rows = (int)pm_ln_part_blocks(Tk);
+  auto ln_table = [&](int u) -> float* {                      // unit u's table of column sums (null: atomics)
+    const int n = u == L - 2 ? 2 * nl : 2 * ((u - 1) / 8) + ((u - 1) % 8 ? 1 : 0);
+    return ln_rows ? c->at<float>(lay.t_lnpart) + (int64_t)n * ln_rows * 2 * d : nullptr;
+  };
   auto ln_bwd = [&](int u, const float* dy, const float* x, const float* mu, const float* rs, const float* dx_res,
                     float* dx_out, T* dx_t) {
-    pm_ln_bwd_launch<T>(st, dy, x, mu, rs, Wb(u, 0), dx_res, dx_out, dx_t, g + U(u).off, g + U(u).off + U(u).boff, Tk, d);
+    pm_ln_bwd_launch<T>(st, dy, x, mu, rs, Wb(u, 0), dx_res, dx_out, dx_t, g + U(u).off, g + U(u).off + U(u).boff, Tk, d, 1, 0,
+                        ln_table(u));
   };
   auto F = [&](size_t off) { return c->at<float>(off); };
   auto TT = [&](size_t off) { return c->at<T>(off); };
@@ -1037,7 +1046,7 @@ pm_status launch_tfm(pm_ctx* c, const void* x_dev, const void* y_dev, int accumu
   if (dn_parts == 1) dgrad_f32(L - 1, TT(lay.t_dlogits), ldV, V, d, dn, 0);
   PM_ENTER(L - 2);
   pm_ln_bwd_launch<T>(st, dnf, F(lay.t_xf), F(lay.t_muf), F(lay.t_rsf), Wb(L - 2, 0), nullptr, dx, nl ? TT(lay.tl[nl - 1].dz2) : nullptr,
-                      g + U(L - 2).off, g + U(L - 2).off + U(L - 2).boff, Tk, d, dn_parts, (int64_t)Tk * d);
+                      g + U(L - 2).off, g + U(L - 2).off + U(L - 2).boff, Tk, d, dn_parts, (int64_t)Tk * d, ln_table(L - 2));
   for (int l = nl - 1; l >= 0; --l) {
     const Layout::TfmLayer& b = lay.tl[l];
     const int u = 1 + 8 * l;
@@ -1108,8 +1117,9 @@ pm_status launch_tfm(pm_ctx* c, const void* x_dev, const void* y_dev, int accumu
   }
   {
     const int64_t tot = (int64_t)Tk * d;
-    hipLaunchKernelGGL(pm_embed_bwd_kernel, dim3((unsigned)std::min<int64_t>(4096, (tot + 255) / 256)), dim3(256), 0, st,
-                       tokens, dx, g + U(0).off, Tk, d, V);
+    const int ne = (int)std::min<int64_t>(4096, (tot + 255) / 256), nb = ln_rows ? (2 * nl + 1) * ((2 * d + 63) / 64) : 0;
+    hipLaunchKernelGGL(pm_embed_bwd_kernel, dim3(ne + nb), dim3(256), 0, st, tokens, dx, g + U(0).off, Tk, d, V, ne,
+                       c->at<float>(lay.t_lnpart), c->at<int64_t>(lay.t_lnwhere), g, ln_rows);
   }
   PM_HIP(hipGetLastError());
   return PM_OK;
@@ -1576,7 +1586,7 @@ pm_status pm_create(int32_t P, int32_t L, const pm_layer_desc* layers, const int
   }
   std::vector<PmGemmProb<PmEpiBwdWeight>> probs;
   std::vector<float> pos;
-  std::vector<int64_t> zero_tab;
+  std::vector<int64_t> zero_tab, ln_where;
   if (c->o.arch == PM_ARCH_TRANSFORMER) {
     // fixed sinusoidal positions pos[s, 2i] = sin(s / 10000^(2i/d)), pos[s, 2i+1] = cos(same)
     const int S = c->o.seq_len, d = lay.units[0].d.n_out;
@@ -1588,6 +1598,9 @@ pm_status pm_create(int32_t P, int32_t L, const pm_layer_desc* layers, const int
       }
     for (int l = 0; l < L; ++l)
       if (lay.units[l].d.kind != PM_LINEAR) { zero_tab.push_back(lay.units[l].off); zero_tab.push_back(lay.units[l].n_pad); }
+    for (int l = 0; l < L; ++l)                              // in unit order: two per layer, then the last one
+      if (lay.units[l].d.kind == PM_LAYERNORM) { ln_where.push_back(lay.units[l].off); ln_where.push_back(lay.units[l].off + lay.units[l].boff); }
+    if ((e = hipMemcpyAsync(c->arena + lay.t_lnwhere, ln_where.data(), ln_where.size() * 8, hipMemcpyHostToDevice, st)) != hipSuccess) return bail(e, "copy LayerNorm table");
     if ((e = hipMemcpyAsync(c->arena + lay.t_pos, pos.data(), pos.size() * 4, hipMemcpyHostToDevice, st)) != hipSuccess) return bail(e, "copy positions");
     if ((e = hipMemcpyAsync(c->arena + lay.t_zero, zero_tab.data(), zero_tab.size() * 8, hipMemcpyHostToDevice, st)) != hipSuccess) return bail(e, "copy region table");
     // Which weight gradients can wait for the grouped launch: all, but those whose forward input another segment of a

@@ -114,19 +114,6 @@ __global__ __launch_bounds__(256) void pm_embed_fwd_kernel(const int32_t* __rest
   }
 }
 
-// dE[token[t], :] += dx[t, :]   (fp32 atomics; the caller zeroes dE first unless accumulating)
-__global__ __launch_bounds__(256) void pm_embed_bwd_kernel(const int32_t* __restrict__ tokens,
-                                                           const float* __restrict__ dx, float* __restrict__ dE,
-                                                           int tokens_n, int d, int vocab) {
-  const int64_t total = (int64_t)tokens_n * d;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
-    const int t = (int)(i / d), j = (int)(i % d);
-    int tok = tokens[t];
-    tok = tok < 0 ? 0 : (tok >= vocab ? vocab - 1 : tok);
-    atomicAdd(dE + (int64_t)tok * d + j, dx[i]);
-  }
-}
-
 // ---------------------------------------------------------------------------------------------
 // LayerNorm forward: one wavefront per row, the row held in registers (lane l owns columns
 // 256 c + 4 l .. + 3, d <= 256 NC, d a multiple of 4).  Stores mean and 1/sqrt(var + eps) for the
@@ -177,13 +164,26 @@ __global__ __launch_bounds__(256) void pm_ln_fwd_kernel(const float* __restrict_
 // ---------------------------------------------------------------------------------------------
 // LayerNorm backward.  dy fp32 [rows, d] is the gradient w.r.t. the LayerNorm output.
 //   dx_out = dx_res + rstd * (dxh - mean(dxh) - xhat * mean(dxh * xhat)),  dxh = dy * gain_bkwd
-//   dgain += sum_rows dy * xhat,  dbias += sum_rows dy      (fp32 atomics, one set per block)
+//   dgain += sum_rows dy * xhat,  dbias += sum_rows dy
 // dx_res is the gradient already on the residual stream (same shape); dx_out may alias it.
 // dx_out_t (optional) receives a copy in the compute dtype for the GEMMs that consume it.
-// Block = 8 waves x 4 rows; lane l owns columns 256 c + 4 l .. + 3 (16-byte accesses), d <= 256 NC,
+// Block = 8 waves x RPW rows; lane l owns columns 256 c + 4 l .. + 3 (16-byte accesses), d <= 256 NC,
 // d a multiple of 4.
+//
+// The column sums of a block go to dgain / dbias by fp32 atomics, or (PART) to its own row of a table that
+// pm_ln_params_block adds up for all LayerNorms of the step at once.  With atomics fewer, larger blocks win (each
+// block's 2 d atomics meet those of all others on the same addresses), which left 64 blocks of 2048 rows on 256 compute units;
+// with the table, blocks of 8 rows: 2048 x 768 10.9 -> 7.6 us, 4096 x 512 12.1 -> 9.3 (16 rows), 2400 x 320 8.6 -> 5.7, 512 x 256
+// 4.9 -> 2.7.  8192 x 1024 is bound by its 151 MB (35 us either way, 5 TB/s inside a step) and the table would be 2 MB more to
+// write and read, so beyond 4096 rows the atomics stay.
 // ---------------------------------------------------------------------------------------------
-template <typename T, int NC>
+constexpr int PM_LN_PART_ROWS = 4096;
+inline int pm_ln_part_rpw(int64_t rows) { return rows <= 2048 ? 1 : 2; }              // at most 256 blocks
+inline int64_t pm_ln_part_blocks(int64_t rows) {                                     // rows of the table; 0: atomics
+  const int64_t per = 8 * pm_ln_part_rpw(rows);
+  return rows <= PM_LN_PART_ROWS ? (rows + per - 1) / per : 0;
+}
+template <typename T, int NC, int RPW, bool PART>
 __global__ __launch_bounds__(512) void pm_ln_bwd_kernel(const float* __restrict__ dy, const float* __restrict__ x,
                                                         const float* __restrict__ mean, const float* __restrict__ rstd,
                                                         PmWLoc<T> gain_bkwd, const float* dx_res, float* dx_out,
@@ -201,13 +201,13 @@ __global__ __launch_bounds__(512) void pm_ln_bwd_kernel(const float* __restrict_
     ag[c] = zero4;
     ab[c] = zero4;
   }
-  // all loads of the wave's four rows go out first (rows past the end re-read the last row and are
+  // all loads of the wave's rows go out first (rows past the end re-read the last row and are
   // masked out below), so the wave pays the memory latency once instead of once per row
-  float4 dyr[4][NC], xr[4][NC], rrr[4][NC];
-  float mur[4], rsr[4];
+  float4 dyr[RPW][NC], xr[RPW][NC], rrr[RPW][NC];
+  float mur[RPW], rsr[RPW];
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int row = blockIdx.x * 32 + wave * 4 + r;
+  for (int r = 0; r < RPW; ++r) {
+    const int row = blockIdx.x * (8 * RPW) + wave * RPW + r;
     const int rowc = row < rows ? row : rows - 1;
     const int64_t ro = (int64_t)rowc * d;
     mur[r] = mean[rowc];
@@ -222,9 +222,9 @@ __global__ __launch_bounds__(512) void pm_ln_bwd_kernel(const float* __restrict_
     }
   }
 #pragma unroll
-  for (int r = 0; r < 4; ++r)
+  for (int r = 0; r < RPW; ++r)
     for (int p = 1; p < parts; ++p) {                         // the gradient arrives as several addends
-      const int row = blockIdx.x * 32 + wave * 4 + r;
+      const int row = blockIdx.x * (8 * RPW) + wave * RPW + r;
       const float* dyp = dy + p * part_stride + (int64_t)(row < rows ? row : rows - 1) * d;
 #pragma unroll
       for (int c = 0; c < NC; ++c) {
@@ -234,8 +234,8 @@ __global__ __launch_bounds__(512) void pm_ln_bwd_kernel(const float* __restrict_
       }
     }
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int row = blockIdx.x * 32 + wave * 4 + r;
+  for (int r = 0; r < RPW; ++r) {
+    const int row = blockIdx.x * (8 * RPW) + wave * RPW + r;
     if (row >= rows) break;                                   // wave-uniform
     const float mu = mur[r], rs = rsr[r];
     const int64_t ro = (int64_t)row * d;
@@ -274,7 +274,7 @@ __global__ __launch_bounds__(512) void pm_ln_bwd_kernel(const float* __restrict_
     }
   }
   // block sum of the per-wave partials (plain LDS stores and loads: LDS float atomics were measured
-  // several times slower), then one fp32 atomic per column and block
+  // several times slower)
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
     red[wave][0][64 * c + lane] = ag[c];
@@ -291,8 +291,52 @@ __global__ __launch_bounds__(512) void pm_ln_bwd_kernel(const float* __restrict_
       sg += pg[e];
       sb += pb[e];
     }
-    atomicAdd(dgain + j, sg);
-    atomicAdd(dbias + j, sb);
+    if (PART) {                                               // dgain: the table [blocks][2][d]
+      dgain[(int64_t)blockIdx.x * 2 * d + j] = sg;
+      dgain[(int64_t)blockIdx.x * 2 * d + d + j] = sb;
+    } else {
+      atomicAdd(dgain + j, sg);
+      atomicAdd(dbias + j, sb);
+    }
+  }
+}
+
+// Adds up the tables of all LayerNorms of a step: block b takes 64 of the 2 d columns of LayerNorm b / blocks per LayerNorm,
+// four groups of threads a quarter of the rows each.  where[2 n], where[2 n + 1]: offsets of LayerNorm n's gain and bias gradients in g.
+__device__ __forceinline__ void pm_ln_params_block(int b, const float* __restrict__ part, const int64_t* __restrict__ where, float* __restrict__ g,
+                                                   int rows, int d) {
+  __shared__ float sum[4][64];
+  const int cb = (2 * d + 63) / 64, n = b / cb, col = (b - n * cb) * 64 + (threadIdx.x & 63), rg = threadIdx.x >> 6;
+  float acc = 0.f;
+  if (col < 2 * d) {
+    const float* p = part + (int64_t)n * rows * 2 * d + col;
+#pragma unroll 8
+    for (int r = rg; r < rows; r += 4) acc += p[(int64_t)r * 2 * d];
+  }
+  sum[rg][threadIdx.x & 63] = acc;
+  __syncthreads();
+  if (rg == 0 && col < 2 * d) {
+    float* o = g + (col < d ? where[2 * n] + col : where[2 * n + 1] + col - d);
+    *o += (sum[0][threadIdx.x] + sum[1][threadIdx.x]) + (sum[2][threadIdx.x] + sum[3][threadIdx.x]);
+  }
+}
+
+// Last launch of a backward pass: dE[token[t], :] += dx[t, :] (fp32 atomics; the caller zeroes dE first unless accumulating) in
+// the first n_embed blocks, and in the others the sums of the LayerNorms' tables.
+__global__ __launch_bounds__(256) void pm_embed_bwd_kernel(const int32_t* __restrict__ tokens, const float* __restrict__ dx,
+                                                           float* __restrict__ dE, int tokens_n, int d, int vocab, int n_embed,
+                                                           const float* __restrict__ part, const int64_t* __restrict__ where,
+                                                           float* __restrict__ g, int part_rows) {
+  if ((int)blockIdx.x >= n_embed) {
+    pm_ln_params_block(blockIdx.x - n_embed, part, where, g, part_rows, d);
+    return;
+  }
+  const int64_t total = (int64_t)tokens_n * d;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (int64_t)n_embed * blockDim.x) {
+    const int t = (int)(i / d), j = (int)(i % d);
+    int tok = tokens[t];
+    tok = tok < 0 ? 0 : (tok >= vocab ? vocab - 1 : tok);
+    atomicAdd(dE + (int64_t)tok * d + j, dx[i]);
   }
 }
 
@@ -321,18 +365,22 @@ inline bool pm_ln_fwd_launch(hipStream_t st, const float* x, PmWLoc<T> gb, int b
   return true;
 }
 
+// table: null (the sums meet in dgain / dbias by atomics), or pm_ln_part_blocks(rows) rows of 2 d values to be added up later
 template <typename T>
 inline bool pm_ln_bwd_launch(hipStream_t st, const float* dy, const float* x, const float* mean, const float* rstd,
                              PmWLoc<T> gain_bkwd, const float* dx_res, float* dx_out, T* dx_out_t, float* dgain,
-                             float* dbias, int rows, int d, int parts = 1, int64_t part_stride = 0) {
+                             float* dbias, int rows, int d, int parts = 1, int64_t part_stride = 0, float* table = nullptr) {
   if (d & 3) return false;
-  const dim3 grid((rows + 31) / 32), blk(512);
-#define PM_LNB(NC) hipLaunchKernelGGL((pm_ln_bwd_kernel<T, NC>), grid, blk, 0, st, dy, x, mean, rstd, gain_bkwd, dx_res, dx_out, dx_out_t, dgain, dbias, rows, d, parts, part_stride)
-  if (d <= 256) PM_LNB(1);
-  else if (d <= 512) PM_LNB(2);
-  else if (d <= 768) PM_LNB(3);
-  else if (d <= 1024) PM_LNB(4);
+  const int rpw = table ? pm_ln_part_rpw(rows) : 4;
+  const dim3 grid((rows + 8 * rpw - 1) / (8 * rpw)), blk(512);
+#define PM_LNB(NC, RPW, PART) hipLaunchKernelGGL((pm_ln_bwd_kernel<T, NC, RPW, PART>), grid, blk, 0, st, dy, x, mean, rstd, gain_bkwd, dx_res, dx_out, dx_out_t, PART ? table : dgain, dbias, rows, d, parts, part_stride)
+#define PM_LNB_ROWS(NC) do { if (!table) PM_LNB(NC, 4, false); else if (rpw == 1) PM_LNB(NC, 1, true); else PM_LNB(NC, 2, true); } while (0)
+  if (d <= 256) PM_LNB_ROWS(1);
+  else if (d <= 512) PM_LNB_ROWS(2);
+  else if (d <= 768) PM_LNB_ROWS(3);
+  else if (d <= 1024) PM_LNB_ROWS(4);
   else return false;
+#undef PM_LNB_ROWS
 #undef PM_LNB
   return true;
 }

@@ -660,3 +660,29 @@ def test_vocabulary_data_gradient_in_parts(torch_cuda, d, heads, vocab, seq, bat
     err = np.linalg.norm(got - want, axis=1) / np.linalg.norm(want, axis=1)
     assert np.max(err) <= 2.0 ** -6, (int(np.argmax(err)), float(np.max(err)))
     g.close()
+
+
+@pytest.mark.parametrize("seq,batch,N", [(7, 1, 1), (8, 1, 2), (9, 7, 1), (8, 256, 1), (3, 683, 2), (16, 256, 1), (17, 241, 1)])
+def test_layernorm_gradients_over_the_row_counts_of_the_block_rule(torch_cuda, seq, batch, N):
+    """Gain and bias gradients of every LayerNorm where the backward kernel changes its rows per block (up to 2048 rows, up
+    to 4096) and from the table of column sums to atomics (beyond), with one and two microbatches per step, against the
+    live oracle.  Per unit max |dg| / max |g| at the first step: a gradient is a sum over `rows` terms of one size, each with
+    the error of about 40 fp32 operations before it, so 40 x 2^-24 of the terms' root sum of squares; 1e-4 leaves ten times
+    that where the terms cancel to 1 / 4.  A block left out of 2 .. 256 would be 4e-3 and more."""
+    w = wl.transformer(2, 24, 3, 40, 30, seq, batch, dtype="f32")
+    kw = dict(opt="sgdm", lr=0.02, beta=0.9, D=0.5, K=4, N=N)
+    params = wl.init_params(w)
+    tf, tb = po.pipeline_delays(w.P, N)
+    o = make_oracle(w, params, tf, tb, **kw)
+    g = make_gpu(w, params, tf, tb, **kw)
+    stream = wl.TokenStream(w)
+    batches = [stream.batch(k) for k in range(N)]
+    o.step(batches if N > 1 else batches[0])
+    for x, y in batches:
+        g.step(torch_cuda.from_numpy(x).cuda(), torch_cuda.from_numpy(y).cuda())
+    for u, unit in enumerate(w.layers):
+        if unit.kind == "layernorm":
+            gg, go = g.state(4, u).astype(np.float64) / N, o.last_grads[u]        # (the buffer holds the microbatches' sum)
+            rel = float(np.max(np.abs(gg - go)) / np.max(np.abs(go)))
+            assert rel <= 1e-4, (u, rel)
+    g.close()
