@@ -19,7 +19,7 @@
 #include "pm_elem.hpp"
 #include "pm_gemm_f32.hpp"
 #include "pm_gemm_mfma.hpp"
-#include "pm_gemm_async.hpp"
+#include "pm_gemm_async_api.hpp"
 #include "pm_update.hpp"
 #include "pm_chain.hpp"
 #include "pm_transformer.hpp"
@@ -1092,17 +1092,14 @@ pm_status launch_tfm(pm_ctx* c, const void* x_dev, const void* y_dev, int accumu
       ProfSpan span(c, PM_CLS_GEMM);
       const auto* tab = c->at<PmGemmProb<PmEpiBwdWeight>>(lay.t_wprobs) + (accumulate ? c->dw_nprob : 0);
       if (c->fuse_upd && c->dw_tile == 256)
-        hipLaunchKernelGGL((pm_gemm_big_grouped_kernel<PmBig256, false, false, false, PmEpiBwdWeightUpd>), dim3(c->dw_ntiles),
-                           dim3(PmBig256::NT), 0, st, c->at<PmGemmProb<PmEpiBwdWeightUpd>>(lay.t_fuse),
-                           c->at<PmXcdSeg>(lay.t_wsegs), c->at<int32_t>(lay.t_wtiles), c->dw_max_segs);
+        pm_wgrad_grouped256_launch(st, c->at<PmGemmProb<PmEpiBwdWeightUpd>>(lay.t_fuse), c->at<PmXcdSeg>(lay.t_wsegs),
+                                   c->at<int32_t>(lay.t_wtiles), c->dw_max_segs, c->dw_ntiles);
       else if (c->fuse_upd)
         hipLaunchKernelGGL((pm_gemm_big_grouped_kernel<PmBig128, false, false, false, PmEpiBwdWeightUpd>), dim3(c->dw_ntiles),
                            dim3(PmBig128::NT), 0, st, c->at<PmGemmProb<PmEpiBwdWeightUpd>>(lay.t_fuse),
                            c->at<PmXcdSeg>(lay.t_wsegs), c->at<int32_t>(lay.t_wtiles), c->dw_max_segs);
       else if (c->dw_tile == 256)
-        hipLaunchKernelGGL((pm_gemm_big_grouped_kernel<PmBig256, false, false, false, PmEpiBwdWeight>), dim3(c->dw_ntiles),
-                           dim3(PmBig256::NT), 0, st, tab, c->at<PmXcdSeg>(lay.t_wsegs), c->at<int32_t>(lay.t_wtiles),
-                           c->dw_max_segs);
+        pm_wgrad_grouped256_launch(st, tab, c->at<PmXcdSeg>(lay.t_wsegs), c->at<int32_t>(lay.t_wtiles), c->dw_max_segs, c->dw_ntiles);
       else if (c->dw_aligned)
         hipLaunchKernelGGL((pm_gemm_big_grouped_kernel<PmBig128, false, false, false, PmEpiBwdWeight>), dim3(c->dw_ntiles),
                            dim3(PmBig128::NT), 0, st, tab, c->at<PmXcdSeg>(lay.t_wsegs), c->at<int32_t>(lay.t_wtiles),

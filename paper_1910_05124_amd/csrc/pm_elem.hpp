@@ -216,7 +216,7 @@ __global__ __launch_bounds__(256) void pm_act_bwd_apply_kernel(T* __restrict__ d
   }
 }
 
-__global__ __launch_bounds__(256) void pm_zero_f32_kernel(float* p, int64_t n) {
+static __global__ __launch_bounds__(256) void pm_zero_f32_kernel(float* p, int64_t n) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = 0.f;
 }
 
@@ -332,7 +332,7 @@ struct PmEpiBwdWeight {
 // Sec. 3.2, with the arithmetic of pm_fused_update_kernel - while other tiles of the launch still multiply.
 // The update pass then leaves these parameters out.
 struct PmEpiBwdWeightUpd {
-  static constexpr bool kColSumA = true;
+  static constexpr bool kColSumA = true, kAKC = false, kBKC = false;
   static constexpr bool kTileUpdate = true;
   float* g; int ld;
   float* db;

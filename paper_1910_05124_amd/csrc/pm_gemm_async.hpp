@@ -1,6 +1,7 @@
-// bf16 products whose first operand is read along the contraction (forward and data gradient of the Linear units):
+// bf16 products of the Linear units, from a few rows to many thousands:
 //
-//   C[i, j] = sum_k A(i, k) * B(j, k),   A along the contraction (KC), B along it (forward) or across it (RC, data gradient)
+//   C[i, j] = sum_k A(i, k) * B(j, k),   each operand read along the contraction (KC) or across it (RC):
+//   forward KC, KC; data gradient KC, RC; weight gradient RC, RC
 //
 // What bounds such a product is how fast a compute unit gets its operand tiles: measured, 83 bytes per ns reach the LDS of
 // one unit whatever the tile (64 x 64, 128 x 64, 32 x 32 outputs per block, alone on the chip or with all units busy), and
@@ -19,7 +20,7 @@
 //
 // The sum over the contraction is cut by WK (see PmAsyncCfg) and otherwise in index order, fp32 accumulation throughout.
 #pragma once
-#include "pm_gemm_mfma.hpp"
+#include "pm_gemm_async_api.hpp"
 
 // BI x BJ outputs per block; WI x WJ waves tile them, WK groups of such waves share every slab of BK contraction indices
 // (each takes BK / WK of them; the groups' sums meet in LDS at the end); ST slabs in LDS.
@@ -149,9 +150,10 @@ __device__ __forceinline__ void pm_block_sync() {            // a barrier withou
   __builtin_amdgcn_sched_barrier(0);
 }
 
-template <class Cfg, bool BKC>
+template <class Cfg, class Epi>
 struct PmAsyncLds {
-  static constexpr int stage = PmAsyncTile<Cfg::BI, true, Cfg::BK>::bytes + PmAsyncTile<Cfg::BJ, BKC, Cfg::BK>::bytes;
+  static constexpr bool AKC = Epi::kAKC, BKC = Epi::kBKC;
+  static constexpr int stage = PmAsyncTile<Cfg::BI, AKC, Cfg::BK>::bytes + PmAsyncTile<Cfg::BJ, BKC, Cfg::BK>::bytes;
   // what the epilogue passes through LDS.  WK > 1: the groups' whole tiles; else a 32-row stripe per wave
   static constexpr int red = Cfg::WK > 1 ? Cfg::WK * Cfg::BI * (Cfg::BJ + 4) * 4 : Cfg::WI * Cfg::WJ * 32 * (Cfg::TJ * 32 + 4) * 4;
   static constexpr int bytes = Cfg::ST * stage > red ? Cfg::ST * stage : red;
@@ -159,9 +161,11 @@ struct PmAsyncLds {
 
 // Block ids go round the 8 XCDs: XCD x takes the x-th eighth of the tiles, walked in panels of 8 row tiles, so that the
 // blocks that share operand panels share an L2.
+__device__ __forceinline__ int pm_async_xcd_order(int id, int nblk) {
+  const int x = id & 7, part = nblk >> 3, more = nblk & 7;
+  return x * part + (x < more ? x : more) + (id >> 3);
+}
 __device__ __forceinline__ void pm_async_tile_of(int id, int tiles_i, int tiles_j, int& by, int& bx) {
-  const int nblk = tiles_i * tiles_j, x = id & 7, part = nblk >> 3, more = nblk & 7;
-  id = x * part + (x < more ? x : more) + (id >> 3);
   constexpr int GROUP = 8;
   const int panel = id / (GROUP * tiles_j), first = panel * GROUP, at = id % (GROUP * tiles_j);
   const int rows = tiles_i - first < GROUP ? tiles_i - first : GROUP;
@@ -172,34 +176,24 @@ __device__ __forceinline__ void pm_async_tile_of(int id, int tiles_i, int tiles_
 struct PmNoSeg {
   static constexpr bool on = false;
 };
-struct PmKSeg3 {                     // pair 0 is the problem's own A and B
-  static constexpr bool on = true;
-  const bf16_t* A1;
-  const bf16_t* A2;
-  PmWLoc<bf16_t> B1, B2;
-  int Kseg;
-};
 
-// Tile id of tiles_i x tiles_j.  CHECK false: whole tiles and whole slabs only.  Seg: PmNoSeg, or PmKSeg3 = three operand pairs
+// Tile (by, bx).  CHECK false: whole tiles and whole slabs only.  Seg: PmNoSeg, or PmKSeg3 = three operand pairs
 // of Kseg indices each, one behind the other.
 template <class Cfg, bool CHECK, class Epi, class Seg = PmNoSeg>
-__device__ __forceinline__ void pm_gemm_async_body(const PmGemmProb<Epi>& pr, int id, int tiles_i, int tiles_j, unsigned char* smem,
+__device__ __forceinline__ void pm_gemm_async_body(const PmGemmProb<Epi>& pr, int by, int bx, unsigned char* smem,
                                                    const Seg& sg = Seg()) {
-  constexpr bool BKC = Epi::kBKC;
-  static_assert(Epi::kAKC, "A is read along the contraction");
+  constexpr bool AKC = Epi::kAKC, BKC = Epi::kBKC;
   constexpr int BI = Cfg::BI, BJ = Cfg::BJ, WI = Cfg::WI, WJ = Cfg::WJ, WK = Cfg::WK, BK = Cfg::BK, ST = Cfg::ST, NT = Cfg::NT;
   constexpr int TI = Cfg::TI, TJ = Cfg::TJ, KS = Cfg::KS;
-  using SA = PmAsyncTile<BI, true, BK>;
-  constexpr int STAGE = PmAsyncLds<Cfg, BKC>::stage;
-  int by, bx;
-  pm_async_tile_of(id, tiles_i, tiles_j, by, bx);
+  using SA = PmAsyncTile<BI, AKC, BK>;
+  constexpr int STAGE = PmAsyncLds<Cfg, Epi>::stage;
   const int I = pr.I, J = pr.J;
   const int i0 = by * BI, j0 = bx * BJ;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int wj = wave % WJ, wi = (wave / WJ) % WI, wk = wave / (WJ * WI);
   const int lr = lane & 31, kg = lane >> 5;
 
-  PmAsyncLoader<BI, true, BK, NT> la;
+  PmAsyncLoader<BI, AKC, BK, NT> la;
   PmAsyncLoader<BJ, BKC, BK, NT> lb;
   la.init(pr.A, pr.lda, i0, I, threadIdx.x);
   lb.init(pr.B.get(), pr.ldb, j0, J, threadIdx.x);
@@ -234,7 +228,7 @@ __device__ __forceinline__ void pm_gemm_async_body(const PmGemmProb<Epi>& pr, in
 #pragma unroll
   for (int s = 0; s < ST; ++s)
     if (s < nk) issue(s * STAGE);
-  PmAsyncFrag<BI, true, BK> ra;
+  PmAsyncFrag<BI, AKC, BK> ra;
   PmAsyncFrag<BJ, BKC, BK> rb;
   ra.init(lane);
   rb.init(lane);
@@ -258,7 +252,22 @@ __device__ __forceinline__ void pm_gemm_async_body(const PmGemmProb<Epi>& pr, in
       for (int b = 0; b < TJ; ++b) f.b[ks][b] = rb.read(s + SA::bytes, (wj * TJ + b) * 32, kb);
     }
   };
+  // bias gradient: column sums of A, from the fragments of the first column of tiles; of the WJ waves that hold the same rows
+  // each sums a share of the 32-row tiles (one register of sums: with all four tiles per wave the 256 x 256 block spilled)
+  constexpr bool COLSUM = Epi::kColSumA && !AKC;
+  float cs[(TI + WJ - 1) / WJ] = {};
+  const bool do_colsum = COLSUM && bx == 0 && pr.epi.wants_colsum();
   auto mul = [&](const Frags& f) __attribute__((always_inline)) {
+    if constexpr (COLSUM) {
+      if (do_colsum) {
+#pragma unroll
+        for (int a = 0; a < TI; ++a)
+          if (a % WJ == wj) {
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) cs[a / WJ] += pm_frag_sum(f.a[ks][a]);
+          }
+      }
+    }
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
@@ -306,6 +315,25 @@ __device__ __forceinline__ void pm_gemm_async_body(const PmGemmProb<Epi>& pr, in
 
   Epi epi = pr.epi;
   epi.begin();
+  if constexpr (COLSUM) {
+    if (do_colsum) {                                     // uniform over the block
+      float* part = reinterpret_cast<float*>(smem);      // [WK][BI]
+      __syncthreads();
+#pragma unroll
+      for (int a = 0; a < TI; ++a)
+        if (a % WJ == wj) {
+          const float half = cs[a / WJ] + __shfl_xor(cs[a / WJ], 32, 64);
+          if (lane < 32) part[wk * BI + (wi * TI + a) * 32 + lane] = half;
+        }
+      __syncthreads();
+      if ((int)threadIdx.x < BI && i0 + (int)threadIdx.x < I) {
+        float sum = 0.f;
+#pragma unroll
+        for (int w = 0; w < WK; ++w) sum += part[w * BI + threadIdx.x];
+        epi.colsum(i0 + threadIdx.x, sum);
+      }
+    }
+  }
   auto store = [&](auto check_) __attribute__((always_inline)) {
   constexpr bool CHECKED = decltype(check_)::value;
   float* red = reinterpret_cast<float*>(smem);
@@ -391,6 +419,19 @@ __device__ __forceinline__ void pm_gemm_async_body(const PmGemmProb<Epi>& pr, in
   };
   if (CHECK && (i0 + BI > I || j0 + BJ > J)) store(std::true_type());
   else store(std::false_type());
+  if constexpr (pm_has_tile_update<Epi>::value) {
+    static_assert(!CHECK, "whole tiles only");
+    __syncthreads();      // the block's stores of the tile are visible to all its waves
+    epi.template update_tile<BI, BJ, NT>(i0, j0);
+  }
+}
+// tile `id` of tiles_i x tiles_j, spread over the XCDs
+template <class Cfg, bool CHECK, class Epi, class Seg = PmNoSeg>
+__device__ __forceinline__ void pm_gemm_async_tile(const PmGemmProb<Epi>& pr, int id, int tiles_i, int tiles_j, unsigned char* smem,
+                                                   const Seg& sg = Seg()) {
+  int by, bx;
+  pm_async_tile_of(pm_async_xcd_order(id, tiles_i * tiles_j), tiles_i, tiles_j, by, bx);
+  pm_gemm_async_body<Cfg, CHECK>(pr, by, bx, smem, sg);
 }
 
 #define PM_ASYNC_KERNEL __global__ __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(2))) void
@@ -398,13 +439,13 @@ __device__ __forceinline__ void pm_gemm_async_body(const PmGemmProb<Epi>& pr, in
 // one product; blocks from tiles_i * tiles_j on read ahead the next product's weights (see PmPrefetch)
 template <class Cfg, bool CHECK, class Epi>
 PM_ASYNC_KERNEL pm_gemm_async_kernel(PmGemmProb<Epi> pr, PmPrefetch pf, int tiles_i, int tiles_j) {
-  __shared__ __attribute__((aligned(16))) unsigned char smem[PmAsyncLds<Cfg, Epi::kBKC>::bytes];
+  __shared__ __attribute__((aligned(16))) unsigned char smem[PmAsyncLds<Cfg, Epi>::bytes];
   const int nt = tiles_i * tiles_j;
   if ((int)blockIdx.x >= nt) {
     pm_prefetch_block(pf, blockIdx.x - nt, 0, gridDim.x - nt, 1);
     return;
   }
-  pm_gemm_async_body<Cfg, CHECK>(pr, blockIdx.x, tiles_i, tiles_j, smem);
+  pm_gemm_async_tile<Cfg, CHECK>(pr, blockIdx.x, tiles_i, tiles_j, smem);
 }
 
 // A product of few outputs and at most 1024 indices (the layers of a chain at 16 .. 256 rows): 32 x 32 outputs per block, wave w
@@ -417,7 +458,7 @@ __device__ __forceinline__ void pm_gemm_once_body(const PmGemmProb<Epi>& pr, int
   constexpr int PART = SA::bytes + PmAsyncTile<32, BKC, 64>::bytes;
   static_assert(PART == 8192, "a wave's part of LDS");
   int by, bx;
-  pm_async_tile_of(id, tiles_i, tiles_j, by, bx);
+  pm_async_tile_of(pm_async_xcd_order(id, tiles_i * tiles_j), tiles_i, tiles_j, by, bx);
   const int I = pr.I, J = pr.J, K = pr.K, i0 = by * 32, j0 = bx * 32;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int k0 = wave * 64, nw = (K + 63) >> 6;          // waves with a share
@@ -483,16 +524,16 @@ __global__ __launch_bounds__(1024) void pm_gemm_once_kernel(PmGemmProb<Epi> pr, 
 // three products of equal shape in one launch (the query / key / value projections share their input)
 template <class Cfg, bool CHECK, class Epi>
 PM_ASYNC_KERNEL pm_gemm_async_multi3_kernel(PmGemmProb<Epi> p0, PmGemmProb<Epi> p1, PmGemmProb<Epi> p2, int tiles_i, int tiles_j) {
-  __shared__ __attribute__((aligned(16))) unsigned char smem[PmAsyncLds<Cfg, Epi::kBKC>::bytes];
+  __shared__ __attribute__((aligned(16))) unsigned char smem[PmAsyncLds<Cfg, Epi>::bytes];
   const int nt = tiles_i * tiles_j, p = blockIdx.x / nt;          // uniform over the block
-  pm_gemm_async_body<Cfg, CHECK>(p == 0 ? p0 : p == 1 ? p1 : p2, blockIdx.x - p * nt, tiles_i, tiles_j, smem);
+  pm_gemm_async_tile<Cfg, CHECK>(p == 0 ? p0 : p == 1 ? p1 : p2, blockIdx.x - p * nt, tiles_i, tiles_j, smem);
 }
 
 // one product over three operand pairs, out = A0 B0 + A1 B1 + A2 B2 (their data gradients meet in one tensor)
 template <class Cfg, bool CHECK, class Epi>
 PM_ASYNC_KERNEL pm_gemm_async_kseg3_kernel(PmGemmProb<Epi> pr, PmKSeg3 sg, int tiles_i, int tiles_j) {
-  __shared__ __attribute__((aligned(16))) unsigned char smem[PmAsyncLds<Cfg, Epi::kBKC>::bytes];
-  pm_gemm_async_body<Cfg, CHECK>(pr, blockIdx.x, tiles_i, tiles_j, smem, sg);
+  __shared__ __attribute__((aligned(16))) unsigned char smem[PmAsyncLds<Cfg, Epi>::bytes];
+  pm_gemm_async_tile<Cfg, CHECK>(pr, blockIdx.x, tiles_i, tiles_j, smem, sg);
 }
 
 // One product with a long contraction and too few output tiles to fill the chip, its contraction cut into parts that
@@ -500,13 +541,36 @@ PM_ASYNC_KERNEL pm_gemm_async_kseg3_kernel(PmGemmProb<Epi> pr, PmKSeg3 sg, int t
 // output at part * part_stride; the consumer adds the parts in order.  kpart is a multiple of 64.
 template <class Cfg, bool CHECK, class Epi>
 PM_ASYNC_KERNEL pm_gemm_async_ksplit_kernel(PmGemmProb<Epi> pr, int kpart, int64_t part_stride, int tiles_i, int tiles_j) {
-  __shared__ __attribute__((aligned(16))) unsigned char smem[PmAsyncLds<Cfg, Epi::kBKC>::bytes];
+  __shared__ __attribute__((aligned(16))) unsigned char smem[PmAsyncLds<Cfg, Epi>::bytes];
   const int nt = tiles_i * tiles_j, p = blockIdx.x / nt, k0 = p * kpart;       // uniform over the block
   pr.A += k0;
   pr.B.base += (int64_t)k0 * (Epi::kBKC ? 1 : pr.ldb);
   pr.K = pr.K - k0 < kpart ? pr.K - k0 : kpart;
   pr.epi.out += p * part_stride;
-  pm_gemm_async_body<Cfg, CHECK>(pr, blockIdx.x - p * nt, tiles_i, tiles_j, smem);
+  pm_gemm_async_tile<Cfg, CHECK>(pr, blockIdx.x - p * nt, tiles_i, tiles_j, smem);
+}
+
+// Weight gradients of whole tiles, many problems in one launch, by per-XCD work lists as in pm_gemm_big_grouped_kernel.  12 x 1024
+// layers, 8192 rows, with the update of the parameters inside: 3801 us with the operands through registers, 3640 here; 6 x 512
+// layers, 4096 rows: 264 -> 239.  (Ragged problems and accumulating ones stay on 128 x 128 blocks there, two of which share a compute
+// unit: what bounds those is the gradient's read and write, and 16000 x 768 and twelve smaller ones took 192 us there, 206 here.)
+template <class Cfg, class Epi>
+PM_ASYNC_KERNEL pm_gemm_async_grouped_kernel(const PmGemmProb<Epi>* __restrict__ probs, const PmXcdSeg* __restrict__ segs, const int32_t* __restrict__ xcd_tiles, int max_segs) {
+  __shared__ __attribute__((aligned(16))) unsigned char smem[PmAsyncLds<Cfg, Epi>::bytes];
+  const int x = blockIdx.x & 7, pos = blockIdx.x >> 3;
+  if (pos >= xcd_tiles[x]) return;
+  const PmXcdSeg* list = segs + (size_t)x * max_segs;
+  int lo = 0, hi = max_segs - 1;                 // last segment with start <= pos
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (list[mid].start <= pos) lo = mid; else hi = mid - 1;
+  }
+  const PmXcdSeg sg = list[lo];
+  const PmGemmProb<Epi> pr = probs[sg.prob];
+  const int ti = (pr.I + Cfg::BI - 1) / Cfg::BI, tj = (pr.J + Cfg::BJ - 1) / Cfg::BJ;
+  int by, bx;
+  pm_async_tile_of(sg.tile0 + (pos - sg.start), ti, tj, by, bx);
+  pm_gemm_async_body<Cfg, false>(pr, by, bx, smem);
 }
 
 // Block shapes, and what a launch on each costs: us = start + rounds * (per1k * K / 1000 + round), rounds = blocks over 256
@@ -536,12 +600,15 @@ template <> struct PmAsyncShape<PmAsync256> { static constexpr PmAsyncCost cost{
 
 inline int64_t pm_async_tiles(int I, int J, int BI, int BJ) { return (int64_t)((I + BI - 1) / BI) * ((J + BJ - 1) / BJ); }
 
+template <class Cfg>
+inline float pm_async_rounds_us(int64_t blocks, float slabs) {
+  constexpr PmAsyncCost c = PmAsyncShape<Cfg>::cost;
+  return c.start + (float)((blocks + 255) / 256) * (c.per1k * 1e-3f * slabs + c.round);
+}
 // the rule for one block shape; n products of I x J outputs over `segs` operand pairs of K indices each
 template <class Cfg>
 inline float pm_async_us(int n, int I, int J, int K, int segs) {
-  constexpr PmAsyncCost c = PmAsyncShape<Cfg>::cost;
-  const float slabs = (float)segs * ((K + Cfg::BK - 1) / Cfg::BK) * Cfg::BK;
-  return c.start + (float)((n * pm_async_tiles(I, J, Cfg::BI, Cfg::BJ) + 255) / 256) * (c.per1k * 1e-3f * slabs + c.round);
+  return pm_async_rounds_us<Cfg>(n * pm_async_tiles(I, J, Cfg::BI, Cfg::BJ), (float)segs * ((K + Cfg::BK - 1) / Cfg::BK) * Cfg::BK);
 }
 template <class F>
 inline void pm_async_each(F&& f) {
@@ -573,7 +640,7 @@ inline bool pm_async_pick(int n, int I, int J, int K, int segs, int64_t lda, int
 }
 
 template <class Epi>
-inline bool pm_async_try(hipStream_t st, const PmGemmProb<Epi>& pr, const PmPrefetch* pf) {
+bool pm_async_try(hipStream_t st, const PmGemmProb<Epi>& pr, const PmPrefetch* pf) {
   const int64_t t32 = pm_async_tiles(pr.I, pr.J, 32, 32);
   if (t32 <= 256 && pr.K <= 1024 && pm_async_fits<PmAsync64>(pr.lda, pr.ldb)) {
     const int ti = (pr.I + 31) / 32, tj = (pr.J + 31) / 32, nt = (int)t32;
@@ -594,7 +661,7 @@ inline bool pm_async_try(hipStream_t st, const PmGemmProb<Epi>& pr, const PmPref
 
 // Three products of equal shape and layout in one launch.  False (nothing launched) if the operands do not suit.
 template <class Epi>
-inline bool pm_gemm_multi3_try(hipStream_t st, const PmGemmProb<Epi> (&pr)[3]) {
+bool pm_gemm_multi3_try(hipStream_t st, const PmGemmProb<Epi> (&pr)[3]) {
   const int I = pr[0].I, J = pr[0].J, K = pr[0].K;
   for (int p = 0; p < 3; ++p) {
     if (pr[p].I != I || pr[p].J != J || pr[p].K != K || pr[p].lda != pr[0].lda || pr[p].ldb != pr[0].ldb) return false;
@@ -610,7 +677,7 @@ inline bool pm_gemm_multi3_try(hipStream_t st, const PmGemmProb<Epi> (&pr)[3]) {
 
 // out = sum over p of A_p B_p with A_p (I x Kseg, row-major) and B_p (Kseg x J, row-major) as one product.
 template <class Epi>
-inline bool pm_gemm_kseg3_try(hipStream_t st, int I, int J, int Kseg, const bf16_t* const (&A)[3], int64_t lda,
+bool pm_gemm_kseg3_try(hipStream_t st, int I, int J, int Kseg, const bf16_t* const (&A)[3], int64_t lda,
                               const PmWLoc<bf16_t> (&B)[3], int64_t ldb, const Epi& epi) {
   for (int p = 0; p < 3; ++p)
     if (!pm_mfma_takes(I, J, Kseg, A[p], lda, 1, B[p].base, B[p].stride, 1, ldb)) return false;
@@ -623,25 +690,8 @@ inline bool pm_gemm_kseg3_try(hipStream_t st, int I, int J, int Kseg, const bf16
   });
 }
 
-// How a product with K >> I, J is cut (pm_gemm_async_ksplit_kernel): as many parts, of at least 512 indices each, as the rule
-// finds fastest with the parts' outputs written and read once more at 4 bytes per ps; parts = 1: not at all.
-struct PmKSplit { int parts, kpart; };
-inline PmKSplit pm_ksplit_plan(int I, int J, int K, int max_parts) {
-  PmKSplit plan{1, K};
-  if (K < 2048) return plan;
-  float best = 3e38f;
-  for (int parts = 1; parts <= std::min({8, max_parts, K / 512}); ++parts) {
-    const int kpart = (K + 64 * parts - 1) / (64 * parts) * 64;
-    if ((K + kpart - 1) / kpart != parts) continue;
-    float us = 3e38f;
-    pm_async_each([&](auto cfg) { us = std::min(us, pm_async_us<decltype(cfg)>(parts, I, J, kpart, 1)); });
-    us += (parts - 1) * 2e-6f * (float)I * (float)J;
-    if (us < best) best = us, plan = PmKSplit{parts, kpart};
-  }
-  return plan;
-}
 template <class Epi>
-inline bool pm_gemm_ksplit_try(hipStream_t st, const PmGemmProb<Epi>& pr, const PmKSplit& s, int64_t part_stride) {
+bool pm_gemm_ksplit_try(hipStream_t st, const PmGemmProb<Epi>& pr, const PmKSplit& s, int64_t part_stride) {
   if (s.parts < 2 || !pm_mfma_takes(pr.I, pr.J, pr.K, pr.A, pr.lda, 1, pr.B.base, pr.B.stride, 1, pr.ldb)) return false;
   return pm_async_pick(s.parts, pr.I, pr.J, s.kpart, 1, pr.lda, pr.ldb, [&](auto cfg, auto whole) {
     using Cfg = decltype(cfg);

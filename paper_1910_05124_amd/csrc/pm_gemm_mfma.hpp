@@ -350,7 +350,7 @@ using PmCfgSkinny512 = PmGemmCfg<32, 32, 1, 1, 16, 512>;
 using PmCfgSkinny1K = PmGemmCfg<32, 32, 1, 1, 16, 1024>;
 
 template <class Epi>
-inline bool pm_async_try(hipStream_t st, const PmGemmProb<Epi>& pr, const PmPrefetch* pf);
+bool pm_async_try(hipStream_t st, const PmGemmProb<Epi>& pr, const PmPrefetch* pf);      // pm_gemm_async_api.hpp
 template <bool AKC, bool BKC, class Epi>
 inline bool pm_big_try(hipStream_t st, const PmGemmProb<Epi>& pr);
 template <bool AKC, bool BKC, class Epi>

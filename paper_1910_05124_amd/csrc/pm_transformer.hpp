@@ -81,7 +81,7 @@ struct PmEpiF32 {
 };
 
 // zero a list of regions of a flat fp32 array: region r = [reg[2r], reg[2r] + reg[2r+1]); grid (x, regions)
-__global__ __launch_bounds__(256) void pm_zero_regions_kernel(float* base, const int64_t* __restrict__ reg) {
+static __global__ __launch_bounds__(256) void pm_zero_regions_kernel(float* base, const int64_t* __restrict__ reg) {
   const int64_t off = reg[2 * blockIdx.y], n = reg[2 * blockIdx.y + 1];
   float4* p = reinterpret_cast<float4*>(base + off);          // regions are chunk-aligned and chunk-sized
   const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -91,7 +91,7 @@ __global__ __launch_bounds__(256) void pm_zero_regions_kernel(float* base, const
 // First kernel of a Transformer microbatch: refreshes the step table at the start of a minibatch
 // (L > 0) and clears the loss accumulator.  A launch of its own because the next kernel (the
 // embedding lookup) already reads its ring slot from the table.
-__global__ void pm_begin_tokens_kernel(PmStepHdr* hdr, const PmLayerStatic* ls, PmLayerStep* ld, int L, PmSchedDev sc,
+static __global__ void pm_begin_tokens_kernel(PmStepHdr* hdr, const PmLayerStatic* ls, PmLayerStep* ld, int L, PmSchedDev sc,
                                        int par) {
   if (L > 0) pm_prologue_block(hdr, ls, ld, L, sc, par);
   if (threadIdx.x == 0) hdr->loss = 0.f;
@@ -323,7 +323,7 @@ __device__ __forceinline__ void pm_ln_params_block(int b, const float* __restric
 
 // Last launch of a backward pass: dE[token[t], :] += dx[t, :] (fp32 atomics; the caller zeroes dE first unless accumulating) in
 // the first n_embed blocks, and in the others the sums of the LayerNorms' tables.
-__global__ __launch_bounds__(256) void pm_embed_bwd_kernel(const int32_t* __restrict__ tokens, const float* __restrict__ dx,
+static __global__ __launch_bounds__(256) void pm_embed_bwd_kernel(const int32_t* __restrict__ tokens, const float* __restrict__ dx,
                                                            float* __restrict__ dE, int tokens_n, int d, int vocab, int n_embed,
                                                            const float* __restrict__ part, const int64_t* __restrict__ where,
                                                            float* __restrict__ g, int part_rows) {

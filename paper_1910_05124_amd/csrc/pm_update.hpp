@@ -73,7 +73,7 @@ __device__ __forceinline__ void pm_prologue_block(PmStepHdr* hdr, const PmLayerS
   }
 }
 
-__global__ void pm_prologue_kernel(PmStepHdr* hdr, const PmLayerStatic* ls, PmLayerStep* ld, int L, PmSchedDev sc,
+static __global__ void pm_prologue_kernel(PmStepHdr* hdr, const PmLayerStatic* ls, PmLayerStep* ld, int L, PmSchedDev sc,
                                    int par) {
   pm_prologue_block(hdr, ls, ld, L, sc, par);
 }
@@ -105,7 +105,7 @@ __global__ __launch_bounds__(256) void pm_begin_step_kernel(const float* __restr
 // Sum of squares over a flat fp32 array (global gradient norm for clipping, parameter norm for
 // the divergence monitor): wavefront shuffles, one LDS stage, one atomic per block.
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void pm_sumsq_kernel(const float* __restrict__ x, int64_t n, float* out) {
+static __global__ __launch_bounds__(256) void pm_sumsq_kernel(const float* __restrict__ x, int64_t n, float* out) {
   float acc = 0.f;
   const int64_t n4 = n >> 2;
   const float4* x4 = reinterpret_cast<const float4*>(x);
@@ -121,7 +121,7 @@ __global__ __launch_bounds__(256) void pm_sumsq_kernel(const float* __restrict__
 }
 
 // gscale <- (1/N) * min(1, clip / ||g/N||)
-__global__ void pm_clip_scale_kernel(PmStepHdr* hdr, float clip, int par) {
+static __global__ void pm_clip_scale_kernel(PmStepHdr* hdr, float clip, int par) {
   const float gn = sqrtf(hdr->gnorm2[par]) * hdr->gscale[par];
   if (gn > clip) hdr->gscale[par] *= clip / gn;
 }
