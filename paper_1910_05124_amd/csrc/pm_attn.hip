@@ -10,6 +10,11 @@
 #include "pm_attn_mfma.hpp"
 
 namespace {
+// Backward passes of up to this many blocks a half go out as one launch (two blocks per compute unit: beyond that the halves fill
+// the chip by themselves, and dQ alone has three).  dQ + dK / dV, us: 32 x 128 tokens, 8 heads 10.6 + 10.2 -> 16.2, 8 x 256, 12 heads
+// 11.5 + 12.6 -> 17.4, 24 x 100, 5 heads 9.7 + 12.4 -> 14.0, fp32 8 x 64, 8 heads of 32 8.3 + 9.1 -> 10.1.
+constexpr unsigned PM_AT_JOIN = 512;
+
 // bf16 matrix instructions: forward whole tiles of 64-wide heads; backward those, or (ragged lengths, 32-wide heads) with
 // the probabilities in three terms
 void mfma_fwd(hipStream_t st, int B, int S, int H, const bf16_t* q, const bf16_t* k, const bf16_t* v, bf16_t* o, float* lse) {
@@ -22,9 +27,14 @@ void mfma_bwd(hipStream_t st, int B, int S, int H, const bf16_t* q, const bf16_t
               const bf16_t* dO, const float* lse, bf16_t* dq, bf16_t* dk, bf16_t* dv) {
   const int qblocks = (S + 127) / 128;
   const float scale = 1.f / sqrtf((float)DH);
-  hipLaunchKernelGGL((pm_attn_mfma_dq_kernel<DH, RAGGED, SPLIT>), dim3(B * H * qblocks), dim3(256), 0, st, q, k, v, o, dO, lse, dq,
+  const unsigned n = B * H * qblocks;
+  if (n <= PM_AT_JOIN) {
+    hipLaunchKernelGGL((pm_attn_mfma_bwd_kernel<DH, RAGGED, SPLIT>), dim3(2 * n), dim3(256), 0, st, q, k, v, o, dO, lse, dq, dk, dv, S, H, B * H, scale);
+    return;
+  }
+  hipLaunchKernelGGL((pm_attn_mfma_dq_kernel<DH, RAGGED, SPLIT>), dim3(n), dim3(256), 0, st, q, k, v, o, dO, lse, dq,
                      S, H, B * H, scale);
-  hipLaunchKernelGGL((pm_attn_mfma_dkv_kernel<DH, RAGGED, SPLIT>), dim3(B * H * qblocks), dim3(256), 0, st, q, k, v, o, dO, lse,
+  hipLaunchKernelGGL((pm_attn_mfma_dkv_kernel<DH, RAGGED, SPLIT>), dim3(n), dim3(256), 0, st, q, k, v, o, dO, lse,
                      dk, dv, S, H, B * H, scale);
 }
 template <typename T, int DH, bool VEC>
@@ -37,6 +47,10 @@ void f32_bwd(hipStream_t st, int B, int S, int H, const T* q, const T* k, const 
              T* dq, T* dk, T* dv) {
   const dim3 grid(B * H * ((S + 31) / 32)), blk(64);
   const float scale = 1.f / sqrtf((float)DH);
+  if (grid.x <= PM_AT_JOIN) {
+    hipLaunchKernelGGL((pm_attn_f32_bwd_kernel<T, DH, VEC>), dim3(2 * grid.x), blk, 0, st, q, k, v, o, dO, lse, dq, dk, dv, S, H, B * H, scale);
+    return;
+  }
   hipLaunchKernelGGL((pm_attn_f32_dq_kernel<T, DH, VEC>), grid, blk, 0, st, q, k, v, o, dO, lse, dq, S, H, B * H, scale);
   hipLaunchKernelGGL((pm_attn_f32_dkv_kernel<T, DH, VEC>), grid, blk, 0, st, q, k, v, o, dO, lse, dk, dv, S, H, B * H, scale);
 }

@@ -298,13 +298,13 @@ __device__ __forceinline__ void pm_af_store(T* out_row, const pm_f32x16* acc, in
 
 // blockIdx.x = block of 32 owned rows * BH + (sequence, head)
 template <typename T, int DH, bool VEC>
-__global__ __launch_bounds__(64) void pm_attn_f32_dq_kernel(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
-                                                            const T* __restrict__ o, const T* __restrict__ dO,
-                                                            const float* __restrict__ lse, T* __restrict__ dq, int S, int H, int BH,
-                                                            float scale) {
+__device__ __forceinline__ void pm_attn_f32_dq_block(float* smem, int block, const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
+                                                     const T* __restrict__ o, const T* __restrict__ dO,
+                                                     const float* __restrict__ lse, T* __restrict__ dq, int S, int H, int BH,
+                                                     float scale) {
   using A = PmAf<DH>;
-  __shared__ __attribute__((aligned(16))) float sK[A::ELEMS], sV[A::ELEMS];
-  const int bh = blockIdx.x % BH, qb = (S + 31) / 32 - 1 - blockIdx.x / BH;      // long blocks first
+  float *sK = smem, *sV = smem + A::ELEMS;
+  const int bh = block % BH, qb = (S + 31) / 32 - 1 - block / BH;                // long blocks first
   const int b = bh / H, h = bh % H, d = H * DH, lane = threadIdx.x, ql = lane & 31, g = lane >> 5;
   const int64_t base = (int64_t)b * S * d + (int64_t)h * DH;
   const int q0 = qb * 32, qi = q0 + ql, qr = qi < S ? qi : S - 1;
@@ -361,14 +361,16 @@ __global__ __launch_bounds__(64) void pm_attn_f32_dq_kernel(const T* __restrict_
   if (qi < S) pm_af_store<T, DH, VEC>(dq + base + (int64_t)qi * d, acc, lane);
 }
 
+template <int DH>
+constexpr int PM_AF_BWD_LDS = 2 * PmAf<DH>::ELEMS + 32 * PmAf<DH>::ST + 64;      // floats of LDS of a block of either kernel
 template <typename T, int DH, bool VEC>
-__global__ __launch_bounds__(64) void pm_attn_f32_dkv_kernel(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
-                                                             const T* __restrict__ o, const T* __restrict__ dO,
-                                                             const float* __restrict__ lse, T* __restrict__ dk, T* __restrict__ dv,
-                                                             int S, int H, int BH, float scale) {
+__device__ __forceinline__ void pm_attn_f32_dkv_block(float* smem, int block, const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
+                                                      const T* __restrict__ o, const T* __restrict__ dO,
+                                                      const float* __restrict__ lse, T* __restrict__ dk, T* __restrict__ dv,
+                                                      int S, int H, int BH, float scale) {
   using A = PmAf<DH>;
-  __shared__ __attribute__((aligned(16))) float sQ[A::ELEMS], sO[A::ELEMS], sX[32 * A::ST], sL[32], sD[32];
-  const int bh = blockIdx.x % BH, kb = blockIdx.x / BH;                          // long blocks (early keys) first
+  float *sQ = smem, *sO = sQ + A::ELEMS, *sX = sO + A::ELEMS, *sL = sX + 32 * A::ST, *sD = sL + 32;
+  const int bh = block % BH, kb = block / BH;                                    // long blocks (early keys) first
   const int b = bh / H, h = bh % H, d = H * DH, lane = threadIdx.x, kl = lane & 31, g = lane >> 5;
   const int64_t base = (int64_t)b * S * d + (int64_t)h * DH;
   const int ki = kb * 32 + kl, kr = ki < S ? ki : S - 1;
@@ -441,4 +443,26 @@ __global__ __launch_bounds__(64) void pm_attn_f32_dkv_kernel(const T* __restrict
     pm_af_store<T, DH, VEC>(dk + base + (int64_t)ki * d, ak, lane);
     pm_af_store<T, DH, VEC>(dv + base + (int64_t)ki * d, av, lane);
   }
+}
+
+// As launches of their own, and as one with the dK / dV blocks first (see pm_attn_mfma_bwd_kernel).
+template <typename T, int DH, bool VEC>
+__global__ __launch_bounds__(64) void pm_attn_f32_dq_kernel(const T* q, const T* k, const T* v, const T* o, const T* dO, const float* lse, T* dq,
+                                                            int S, int H, int BH, float scale) {
+  __shared__ __attribute__((aligned(16))) float smem[2 * PmAf<DH>::ELEMS];
+  pm_attn_f32_dq_block<T, DH, VEC>(smem, blockIdx.x, q, k, v, o, dO, lse, dq, S, H, BH, scale);
+}
+template <typename T, int DH, bool VEC>
+__global__ __launch_bounds__(64) void pm_attn_f32_dkv_kernel(const T* q, const T* k, const T* v, const T* o, const T* dO, const float* lse, T* dk, T* dv,
+                                                             int S, int H, int BH, float scale) {
+  __shared__ __attribute__((aligned(16))) float smem[PM_AF_BWD_LDS<DH>];
+  pm_attn_f32_dkv_block<T, DH, VEC>(smem, blockIdx.x, q, k, v, o, dO, lse, dk, dv, S, H, BH, scale);
+}
+template <typename T, int DH, bool VEC>
+__global__ __launch_bounds__(64) void pm_attn_f32_bwd_kernel(const T* q, const T* k, const T* v, const T* o, const T* dO, const float* lse, T* dq, T* dk, T* dv,
+                                                             int S, int H, int BH, float scale) {
+  __shared__ __attribute__((aligned(16))) float smem[PM_AF_BWD_LDS<DH>];
+  const int n = gridDim.x / 2;
+  if ((int)blockIdx.x < n) pm_attn_f32_dkv_block<T, DH, VEC>(smem, blockIdx.x, q, k, v, o, dO, lse, dk, dv, S, H, BH, scale);
+  else pm_attn_f32_dq_block<T, DH, VEC>(smem, blockIdx.x - n, q, k, v, o, dO, lse, dq, S, H, BH, scale);
 }

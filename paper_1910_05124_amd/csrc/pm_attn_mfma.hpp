@@ -277,15 +277,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
 // backward, dQ: block = 4 waves x 32 queries; streams key / value tiles.
 //   S^T = K Q^T, dP^T = V dO^T, dS^T = P^T (dP^T - D) / sqrt(dh), dQ^T += K^T dS^T
 // ---------------------------------------------------------------------------------------------
+template <int DH>
+constexpr int PM_AT_BWD_LDS = 4 * 32 * PM_AT_ST<DH> * 2 + 4 * 32 * 4;      // bytes of LDS of a block of either backward kernel
 template <int DH, bool RAGGED, bool SPLIT>
-__global__ __launch_bounds__(256) void pm_attn_mfma_dq_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
-                                                              const bf16_t* __restrict__ v, const bf16_t* __restrict__ o,
-                                                              const bf16_t* __restrict__ dO, const float* __restrict__ lse,
-                                                              bf16_t* __restrict__ dq, int S, int H, int BH, float scale) {
-  __shared__ __attribute__((aligned(16))) bf16_t sK[2][32 * PM_AT_ST<DH>];
-  __shared__ __attribute__((aligned(16))) bf16_t sV[2][32 * PM_AT_ST<DH>];
+__device__ __forceinline__ void pm_attn_mfma_dq_block(unsigned char* smem, int block, const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
+                                                      const bf16_t* __restrict__ v, const bf16_t* __restrict__ o,
+                                                      const bf16_t* __restrict__ dO, const float* __restrict__ lse,
+                                                      bf16_t* __restrict__ dq, int S, int H, int BH, float scale) {
+  auto sK = reinterpret_cast<bf16_t (*)[32 * PM_AT_ST<DH>]>(smem);         // two tiles each
+  auto sV = sK + 2;
   const int qblocks = (S + 127) / 128;
-  const int bh = blockIdx.x % BH, qb = qblocks - 1 - blockIdx.x / BH;
+  const int bh = block % BH, qb = qblocks - 1 - block / BH;
   const int b = bh / H, h = bh % H, d = H * DH;
   const int64_t base = (int64_t)b * S * d + (int64_t)h * DH;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, ql = lane & 31, g = lane >> 5;
@@ -412,16 +414,16 @@ __global__ __launch_bounds__(256) void pm_attn_mfma_dq_kernel(const bf16_t* __re
 //   S = Q K^T, dP = dO V^T, dS = P (dP - D) / sqrt(dh), dV^T += dO^T P, dK^T += Q^T dS
 // ---------------------------------------------------------------------------------------------
 template <int DH, bool RAGGED, bool SPLIT>
-__global__ __launch_bounds__(256) void pm_attn_mfma_dkv_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
-                                                               const bf16_t* __restrict__ v, const bf16_t* __restrict__ o,
-                                                               const bf16_t* __restrict__ dO, const float* __restrict__ lse,
-                                                               bf16_t* __restrict__ dk, bf16_t* __restrict__ dv, int S, int H,
-                                                               int BH, float scale) {
-  __shared__ __attribute__((aligned(16))) bf16_t sQ[2][32 * PM_AT_ST<DH>];
-  __shared__ __attribute__((aligned(16))) bf16_t sO[2][32 * PM_AT_ST<DH>];     // dO
-  __shared__ __attribute__((aligned(16))) float sL[2][32];
-  __shared__ __attribute__((aligned(16))) float sD[2][32];
-  const int bh = blockIdx.x % BH, kb = blockIdx.x / BH;                    // long blocks (early keys) first
+__device__ __forceinline__ void pm_attn_mfma_dkv_block(unsigned char* smem, int block, const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
+                                                       const bf16_t* __restrict__ v, const bf16_t* __restrict__ o,
+                                                       const bf16_t* __restrict__ dO, const float* __restrict__ lse,
+                                                       bf16_t* __restrict__ dk, bf16_t* __restrict__ dv, int S, int H,
+                                                       int BH, float scale) {
+  auto sQ = reinterpret_cast<bf16_t (*)[32 * PM_AT_ST<DH>]>(smem);
+  auto sO = sQ + 2;                                                        // dO
+  auto sL = reinterpret_cast<float (*)[32]>(sO + 2);
+  auto sD = sL + 2;
+  const int bh = block % BH, kb = block / BH;                              // long blocks (early keys) first
   const int b = bh / H, h = bh % H, d = H * DH;
   const int64_t base = (int64_t)b * S * d + (int64_t)h * DH;
   const int64_t lbase = ((int64_t)b * H + h) * S;
@@ -583,3 +585,27 @@ __global__ __launch_bounds__(256) void pm_attn_mfma_dkv_kernel(const bf16_t* __r
   }
 }
 
+// The two halves as launches of their own, and as one launch with the dK / dV blocks (the longer ones) first.  Together they overlap
+// where neither fills the chip, at the register budget of the larger one (two blocks per compute unit; dQ alone: three).
+#define PM_AT_BWD_SMEM __shared__ __attribute__((aligned(16))) unsigned char smem[PM_AT_BWD_LDS<DH>]
+template <int DH, bool RAGGED, bool SPLIT>
+__global__ __launch_bounds__(256) void pm_attn_mfma_dq_kernel(const bf16_t* q, const bf16_t* k, const bf16_t* v, const bf16_t* o, const bf16_t* dO,
+                                                              const float* lse, bf16_t* dq, int S, int H, int BH, float scale) {
+  PM_AT_BWD_SMEM;
+  pm_attn_mfma_dq_block<DH, RAGGED, SPLIT>(smem, blockIdx.x, q, k, v, o, dO, lse, dq, S, H, BH, scale);
+}
+template <int DH, bool RAGGED, bool SPLIT>
+__global__ __launch_bounds__(256) void pm_attn_mfma_dkv_kernel(const bf16_t* q, const bf16_t* k, const bf16_t* v, const bf16_t* o, const bf16_t* dO,
+                                                               const float* lse, bf16_t* dk, bf16_t* dv, int S, int H, int BH, float scale) {
+  PM_AT_BWD_SMEM;
+  pm_attn_mfma_dkv_block<DH, RAGGED, SPLIT>(smem, blockIdx.x, q, k, v, o, dO, lse, dk, dv, S, H, BH, scale);
+}
+template <int DH, bool RAGGED, bool SPLIT>
+__global__ __launch_bounds__(256) void pm_attn_mfma_bwd_kernel(const bf16_t* q, const bf16_t* k, const bf16_t* v, const bf16_t* o, const bf16_t* dO,
+                                                               const float* lse, bf16_t* dq, bf16_t* dk, bf16_t* dv, int S, int H, int BH, float scale) {
+  PM_AT_BWD_SMEM;
+  const int n = gridDim.x / 2;
+  if ((int)blockIdx.x < n) pm_attn_mfma_dkv_block<DH, RAGGED, SPLIT>(smem, blockIdx.x, q, k, v, o, dO, lse, dk, dv, S, H, BH, scale);
+  else pm_attn_mfma_dq_block<DH, RAGGED, SPLIT>(smem, blockIdx.x - n, q, k, v, o, dO, lse, dq, S, H, BH, scale);
+}
+#undef PM_AT_BWD_SMEM

@@ -686,3 +686,31 @@ def test_layernorm_gradients_over_the_row_counts_of_the_block_rule(torch_cuda, s
             rel = float(np.max(np.abs(gg - go)) / np.max(np.abs(go)))
             assert rel <= 1e-4, (u, rel)
     g.close()
+
+
+@pytest.mark.parametrize("dtype,S,H,dh", [("bf16", 32, 8, 64), ("bf16", 20, 8, 64), ("bf16", 40, 8, 32), ("f32", 20, 8, 16), ("f32", 40, 4, 64)])
+def test_attention_backward_in_one_launch_and_in_two(torch_cuda, dtype, S, H, dh):
+    """Above 512 blocks a half the backward pass goes out as two launches, below as one: a batch of 66 sequences (two) against
+    its halves (one), bit for bit."""
+    import paper_1910_05124_amd as pm
+    torch = torch_cuda
+    B, gen = 66, torch.Generator(device="cuda").manual_seed(S * dh)
+    t = _tdt(torch, dtype)
+    q, k, v, do = (torch.randn(B, S, H * dh, device="cuda", generator=gen).to(t) for _ in range(4))
+    st = torch.cuda.current_stream().cuda_stream
+
+    def run(lo, hi):
+        n = hi - lo
+        ins = [x[lo:hi].contiguous() for x in (q, k, v)]
+        o, lse = torch.empty_like(ins[0]), torch.empty(n, H, S, device="cuda")
+        outs = [torch.full_like(ins[0], float("nan")) for _ in range(3)]
+        g = do[lo:hi].contiguous()
+        pm.pm_attention_fwd(st, dtype, n, S, H, dh, *(x.data_ptr() for x in ins), o.data_ptr(), lse.data_ptr())
+        pm.pm_attention_bwd(st, dtype, n, S, H, dh, *(x.data_ptr() for x in ins), o.data_ptr(), g.data_ptr(), lse.data_ptr(),
+                            *(x.data_ptr() for x in outs))
+        return outs
+
+    whole, first, second = run(0, B), run(0, B // 2), run(B // 2, B)
+    torch.cuda.synchronize()
+    for w, a, b in zip(whole, first, second):
+        assert torch.equal(w, torch.cat([a, b])) and not bool(torch.isnan(w).any())
