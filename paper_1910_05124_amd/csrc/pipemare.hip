@@ -513,8 +513,7 @@ template <typename T>
 pm_status launch_update(pm_ctx* c, hipStream_t st, int par, bool all_params = false) {
   const Layout& lay = c->lay;
   if (c->o.clip_norm > 0.0) {
-    int blocks = (int)std::min<int64_t>(2048, (lay.n_flat / 4 + 255) / 256);
-    hipLaunchKernelGGL(pm_sumsq_kernel, dim3(blocks), dim3(256), 0, st, c->at<float>(lay.g_off), lay.n_flat,
+    hipLaunchKernelGGL(pm_sumsq_kernel, dim3(pm_sumsq_blocks(lay.n_flat)), dim3(PM_SUMSQ_NT), 0, st, c->at<float>(lay.g_off), lay.n_flat,
                        &c->hdr()->gnorm2[par]);
     hipLaunchKernelGGL(pm_clip_scale_kernel, dim3(1), dim3(1), 0, st, c->hdr(), (float)c->o.clip_norm, par);
   }
@@ -1113,8 +1112,7 @@ pm_status launch_tfm(pm_ctx* c, const void* x_dev, const void* y_dev, int accumu
     launch_f32_wgrads(c, accumulate);
   }
   {
-    const int64_t tot = (int64_t)Tk * d;
-    const int ne = (int)std::min<int64_t>(4096, (tot + 255) / 256), nb = ln_rows ? (2 * nl + 1) * ((2 * d + 63) / 64) : 0;
+    const int ne = pm_embed_bwd_blocks(Tk, d), nb = ln_rows ? (2 * nl + 1) * ((2 * d + 63) / 64) : 0;
     hipLaunchKernelGGL(pm_embed_bwd_kernel, dim3(ne + nb), dim3(256), 0, st, tokens, dx, g + U(0).off, Tk, d, V, ne,
                        c->at<float>(lay.t_lnpart), c->at<int64_t>(lay.t_lnwhere), g, ln_rows);
   }
@@ -1951,7 +1949,7 @@ pm_status pm_step(pm_ctx* c, const void* x_dev, const void* y_dev, float* loss_o
     PmStepHdr h;
     PM_HIP(hipMemcpyAsync(&h, c->hdr(), sizeof h, hipMemcpyDeviceToHost, c->stream));
     PM_HIP(hipStreamSynchronize(c->stream));
-    *loss_out_host = c->last_loss = h.loss;
+    *loss_out_host = c->last_loss = (float)pm_loss_sum(h);
     if (h.chain_err) return fail(PM_EHIP, "a chained launch gave up waiting for its producers (results of this context are invalid)");
     if (h.diverged) { c->diverged = true; return fail(PM_EDIVERGED, "non-finite weight after step %lld", (long long)h.t_used); }
   }
@@ -2054,14 +2052,13 @@ pm_status pm_stats(pm_ctx* c, double* loss, double* grad_norm, double* param_nor
   const Layout& lay = c->lay;
   if (param_norm) {
     PM_HIP(hipMemsetAsync(&c->hdr()->pnorm2, 0, sizeof(float), c->stream));
-    int blocks = (int)std::min<int64_t>(2048, (lay.n_flat / 4 + 255) / 256);
-    hipLaunchKernelGGL(pm_sumsq_kernel, dim3(blocks), dim3(256), 0, c->stream, c->at<float>(lay.w_off), lay.n_flat,
+    hipLaunchKernelGGL(pm_sumsq_kernel, dim3(pm_sumsq_blocks(lay.n_flat)), dim3(PM_SUMSQ_NT), 0, c->stream, c->at<float>(lay.w_off), lay.n_flat,
                        &c->hdr()->pnorm2);
   }
   PmStepHdr h;
   PM_HIP(hipMemcpyAsync(&h, c->hdr(), sizeof h, hipMemcpyDeviceToHost, c->stream));
   PM_HIP(hipStreamSynchronize(c->stream));
-  if (loss) *loss = h.loss;
+  if (loss) *loss = (float)pm_loss_sum(h);
   if (grad_norm) *grad_norm = c->o.clip_norm > 0.0 ? std::sqrt((double)h.gnorm2[c->last_par]) / c->o.n_microbatches : 0.0;
   if (param_norm) *param_norm = std::sqrt((double)h.pnorm2);
   if (t) *t = h.t_next;
@@ -2506,7 +2503,7 @@ pm_status pm_checkpoint_load(pm_ctx* c, const void* src, size_t bytes) {
   dh.t_next = h.t;
   dh.t_used = h.t > 0 ? h.t - 1 : 0;
   dh.diverged = h.diverged;
-  dh.loss = 0.f;
+  for (auto& part : dh.loss) part[0] = 0.f;
   PM_HIP(hipMemcpy(c->hdr(), &dh, sizeof dh, hipMemcpyHostToDevice));
   c->t_host = h.t;
   c->micro = 0;

@@ -9,7 +9,7 @@
 template <typename T>
 __global__ __launch_bounds__(256) void pm_stage_input_kernel(const float* __restrict__ x, T* __restrict__ out,
                                                              int M, int n, int ld, PmStepHdr* hdr) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) hdr->loss = 0.f;
+  if (blockIdx.x == 0) pm_loss_clear(hdr);
   const int64_t total = (int64_t)M * ld;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
     const int m = (int)(i / ld), c = (int)(i % ld);
@@ -19,7 +19,7 @@ __global__ __launch_bounds__(256) void pm_stage_input_kernel(const float* __rest
 
 // Softmax cross-entropy, mean over rows.  One wavefront per row; logits fp32 [M, ld], ld a multiple
 // of 8.  Writes dz = (softmax - onehot)/M in the compute dtype (pad columns zero) and adds the row's
-// loss / M to hdr->loss.  Two passes over the row: running (max, sum of exponentials) per lane,
+// loss / M to the loss.  Two passes over the row: running (max, sum of exponentials) per lane,
 // merged across the wave; then the gradient, eight columns per lane and access.
 template <typename T>
 __global__ __launch_bounds__(256) void pm_xent_kernel(const float* __restrict__ logits, const int32_t* __restrict__ y,
@@ -60,7 +60,7 @@ __global__ __launch_bounds__(256) void pm_xent_kernel(const float* __restrict__ 
       o[e] = (c + e < C) ? (__expf(v[e] - mall) * inv - (c + e == label ? 1.f : 0.f)) * invM : 0.f;
     pm_st8(dz + (int64_t)row * ld + c, o);
   }
-  if (lane == 0 && label_ok) atomicAdd(&hdr->loss, (logf(se) + mall - z[label]) * invM);
+  if (lane == 0 && label_ok) pm_loss_add(hdr, row, (logf(se) + mall - z[label]) * invM);
 }
 
 // The same for wide rows (thousands of classes): one block of 512 threads per row keeps the whole row
@@ -129,16 +129,21 @@ __global__ __launch_bounds__(512) void pm_xent_row_kernel(const float* __restric
       pm_st4(dz + (int64_t)row * ld + c, o);
     }
   }
-  if (tid == 0 && label_ok) atomicAdd(&hdr->loss, (logf(se) + mall - z[label]) * invM);
+  if (tid == 0 && label_ok) pm_loss_add(hdr, row, (logf(se) + mall - z[label]) * invM);
 }
 
 // softmax cross-entropy of M rows: row-resident kernel for wide rows, one wavefront per row otherwise
 template <typename T>
 inline void pm_xent_launch(hipStream_t st, const float* logits, const int32_t* y, T* dz, int M, int C, int ld,
                            PmStepHdr* hdr) {
-  constexpr int NV = 16;
-  if (C >= 2048 && (ld >> 2) <= NV * 512)
-    hipLaunchKernelGGL((pm_xent_row_kernel<T, NV>), dim3(M), dim3(512), 0, st, logits, y, dz, M, C, ld, hdr);
+  // registers for the row length at hand: more waves where rows are short
+  const int ld4 = ld >> 2;
+  if (C >= 2048 && ld4 <= 4 * 512)
+    hipLaunchKernelGGL((pm_xent_row_kernel<T, 4>), dim3(M), dim3(512), 0, st, logits, y, dz, M, C, ld, hdr);
+  else if (C >= 2048 && ld4 <= 8 * 512)
+    hipLaunchKernelGGL((pm_xent_row_kernel<T, 8>), dim3(M), dim3(512), 0, st, logits, y, dz, M, C, ld, hdr);
+  else if (C >= 2048 && ld4 <= 16 * 512)
+    hipLaunchKernelGGL((pm_xent_row_kernel<T, 16>), dim3(M), dim3(512), 0, st, logits, y, dz, M, C, ld, hdr);
   else
     hipLaunchKernelGGL((pm_xent_kernel<T>), dim3((M + 3) / 4), dim3(256), 0, st, logits, y, dz, M, C, ld, hdr);
 }
@@ -161,7 +166,7 @@ __global__ __launch_bounds__(256) void pm_mse_kernel(const float* __restrict__ o
     stf(dz + i, v);
   }
   acc = pm_wave_sum(acc);
-  if ((threadIdx.x & 63) == 0 && acc != 0.f) atomicAdd(&hdr->loss, acc * inv);
+  if ((threadIdx.x & 63) == 0 && acc != 0.f) pm_loss_add(hdr, blockIdx.x, acc * inv);
 }
 
 // Bias gradient db[n] = sum_m dz[m, n] into the fp32 gradient buffer (optionally accumulating).

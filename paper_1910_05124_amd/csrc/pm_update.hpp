@@ -88,7 +88,7 @@ __global__ __launch_bounds__(256) void pm_begin_step_kernel(const float* __restr
                                                             uint4* shared_fill, int64_t n_shared_fill) {
   if (blockIdx.x == 0) {
     if (L > 0) pm_prologue_block(hdr, ls, ld, L, sc, par);
-    if (threadIdx.x == 0) hdr->loss = 0.f;
+    pm_loss_clear(hdr);
   }
   // the tensors that the chained forward / data-gradient launches of this microbatch pass from block to block
   // start as all-ones words ("not written yet", see pm_chain.hpp)
@@ -103,21 +103,36 @@ __global__ __launch_bounds__(256) void pm_begin_step_kernel(const float* __restr
 
 // ---------------------------------------------------------------------------------------------
 // Sum of squares over a flat fp32 array (global gradient norm for clipping, parameter norm for
-// the divergence monitor): wavefront shuffles, one LDS stage, one atomic per block.
+// the divergence monitor): wavefront shuffles, one LDS stage, one atomic per block.  The atomics meet on one address and follow each
+// other at 16 ns, so: one block of 1024 threads per compute unit, four loads each in flight (46 M gradients: 51 us with 2048 blocks of
+// 256, 32 now).
 // ---------------------------------------------------------------------------------------------
-static __global__ __launch_bounds__(256) void pm_sumsq_kernel(const float* __restrict__ x, int64_t n, float* out) {
+constexpr int PM_SUMSQ_NT = 1024, PM_SUMSQ_BLOCKS = 256;
+static __global__ __launch_bounds__(PM_SUMSQ_NT) void pm_sumsq_kernel(const float* __restrict__ x, int64_t n, float* out) {
   float acc = 0.f;
   const int64_t n4 = n >> 2;
   const float4* x4 = reinterpret_cast<const float4*>(x);
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n4; i += (int64_t)gridDim.x * blockDim.x) {
-    const float4 v = x4[i];
-    acc += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+  const int64_t step = (int64_t)gridDim.x * PM_SUMSQ_NT;
+  int64_t i = (int64_t)blockIdx.x * PM_SUMSQ_NT + threadIdx.x;
+  auto square = [](const float4& v) { return v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w; };
+  for (; i + 3 * step < n4; i += 4 * step) {
+    const float4 a = x4[i], b = x4[i + step], c = x4[i + 2 * step], d = x4[i + 3 * step];
+    acc += (square(a) + square(b)) + (square(c) + square(d));
   }
+  for (; i < n4; i += step) acc += square(x4[i]);
   acc = pm_wave_sum(acc);
-  __shared__ float part[4];
+  __shared__ float part[PM_SUMSQ_NT / 64];
   if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = acc;
   __syncthreads();
-  if (threadIdx.x == 0) atomicAdd(out, part[0] + part[1] + part[2] + part[3]);
+  if (threadIdx.x < 64) {
+    acc = pm_wave_sum(threadIdx.x < PM_SUMSQ_NT / 64 ? part[threadIdx.x] : 0.f);
+    if (threadIdx.x == 0) atomicAdd(out, acc);
+  }
+}
+
+inline int pm_sumsq_blocks(int64_t n) {
+  const int64_t b = (n / 4 + PM_SUMSQ_NT - 1) / PM_SUMSQ_NT;
+  return (int)(b < 1 ? 1 : b < PM_SUMSQ_BLOCKS ? b : PM_SUMSQ_BLOCKS);
 }
 
 // gscale <- (1/N) * min(1, clip / ||g/N||)
