@@ -843,21 +843,22 @@ struct PmCvWgradList {
 // With 16 channels a transposed read of 32 columns runs into the next row; those rows of the product are not
 // stored.  That takes 24 KB of LDS a block instead of 40, and half the loads.
 template <int PA, int PB>
-__global__ __launch_bounds__(256) void pm_conv_wgrad_mfma_kernel(PmCvWgradList list) {
-  constexpr int NTO = (PA + 1) / 2, NTI = (PB + 1) / 2;   // channel tiles of 32
-  constexpr int SA = PA * 16 + 8, SB = PB * 16 + 8;       // LDS row strides (elements)
-  constexpr int RW = NTI * 32;                            // row width of the block's reduction tile
-  constexpr int WAVE = 32 * SA + 3 * 32 * SB + (PB == 1 ? 16 : 0);   // elements of a wave's region, with what a read of the last row runs into
-  constexpr size_t BYTES = sizeof(bf16_t) * 4 * WAVE > sizeof(float) * 4 * NTO * 32 * RW ? sizeof(bf16_t) * 4 * WAVE
-                                                                                         : sizeof(float) * 4 * NTO * 32 * RW;
-  __shared__ __attribute__((aligned(16))) unsigned char lds[BYTES];
-  int k = 0;
-  while (k + 1 < list.count && (int)blockIdx.x >= list.end[k]) ++k;
-  const PmCvWgradJob& jb = list.job[k];
+struct PmCvWgradLds {
+  static constexpr int NTO = (PA + 1) / 2, NTI = (PB + 1) / 2;   // channel tiles of 32
+  static constexpr int SA = PA * 16 + 8, SB = PB * 16 + 8;       // LDS row strides (elements)
+  static constexpr int RW = NTI * 32;                            // row width of the block's reduction tile
+  static constexpr int WAVE = 32 * SA + 3 * 32 * SB + (PB == 1 ? 16 : 0);   // elements of a wave's region, with what a read of the last row runs into
+  static constexpr size_t BYTES = sizeof(bf16_t) * 4 * WAVE > sizeof(float) * 4 * NTO * 32 * RW ? sizeof(bf16_t) * 4 * WAVE
+                                                                                                : sizeof(float) * 4 * NTO * 32 * RW;
+};
+template <int PA, int PB>
+__device__ __forceinline__ void pm_conv_wgrad_block(const PmCvWgradJob& jb, int bid, unsigned char* lds) {
+  using S = PmCvWgradLds<PA, PB>;
+  constexpr int NTO = S::NTO, NTI = S::NTI, SA = S::SA, SB = S::SB, RW = S::RW, WAVE = S::WAVE;
   const PmConvGeom g = jb.g;
   const bf16_t* __restrict__ dz = jb.dz;
   const bf16_t* __restrict__ x = jb.x;
-  const int bid = (int)blockIdx.x - (k ? list.end[k - 1] : 0), dy = (int)blockIdx.y - 1, nch = jb.nch;
+  const int dy = (int)blockIdx.y - 1, nch = jb.nch;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   bf16_t* wa = reinterpret_cast<bf16_t*>(lds) + wave * WAVE;
   bf16_t* wb = wa + 32 * SA;
@@ -980,10 +981,43 @@ __global__ __launch_bounds__(256) void pm_conv_wgrad_mfma_kernel(PmCvWgradList l
         for (int v = 0; v < 16; ++v)
           red[wave * IMG + (a * 32 + 8 * (v >> 2) + 4 * kg + (v & 3)) * RW + bb * 32 + cl] = acc[t][a][bb][v];
     __syncthreads();
-    for (int e = threadIdx.x; e < g.Cout * g.Cin; e += 256) {
-      const int co = e / g.Cin, ci = e - co * g.Cin, o = co * RW + ci;
-      my_part[(co * 9 + blockIdx.y * 3 + t) * g.Cin + ci] = red[o] + red[IMG + o] + red[2 * IMG + o] + red[3 * IMG + o];
+    const int c4 = g.Cin / 4;
+    for (int e = threadIdx.x; e < g.Cout * c4; e += 256) {
+      const int co = e / c4, ci = (e - co * c4) * 4, o = co * RW + ci;
+      float4 sum = *reinterpret_cast<const float4*>(red + o);
+#pragma unroll
+      for (int w = 1; w < 4; ++w) {
+        const float4 v = *reinterpret_cast<const float4*>(red + w * IMG + o);
+        sum.x += v.x; sum.y += v.y; sum.z += v.z; sum.w += v.w;
+      }
+      *reinterpret_cast<float4*>(my_part + (co * 9 + blockIdx.y * 3 + t) * g.Cin + ci) = sum;
     }
+  }
+}
+
+template <int PA, int PB>
+__global__ __launch_bounds__(256) void pm_conv_wgrad_mfma_kernel(PmCvWgradList list) {
+  __shared__ __attribute__((aligned(16))) unsigned char lds[PmCvWgradLds<PA, PB>::BYTES];
+  int k = 0;
+  while (k + 1 < list.count && (int)blockIdx.x >= list.end[k]) ++k;
+  pm_conv_wgrad_block<PA, PB>(list.job[k], (int)blockIdx.x - (k ? list.end[k - 1] : 0), lds);
+}
+// Units of more than 16 channels, all pairs of channel tiles in one launch (at the LDS and registers of the widest: two
+// blocks per compute unit).  The launches per pair are short and each leaves much of the chip idle: 32 us for the 8 units of
+// ResNet-14 on 37 images in three launches, 25 in one.  The 16-channel units keep a launch of their own, whose blocks are smaller
+// and share a compute unit in sixes.
+__global__ __launch_bounds__(256) void pm_conv_wgrad_wide_kernel(PmCvWgradList list) {
+  __shared__ __attribute__((aligned(16))) unsigned char lds[PmCvWgradLds<4, 4>::BYTES];
+  int k = 0;
+  while (k + 1 < list.count && (int)blockIdx.x >= list.end[k]) ++k;
+  const PmCvWgradJob& jb = list.job[k];
+  const int bid = (int)blockIdx.x - (k ? list.end[k - 1] : 0);
+  if (jb.g.Cout > 32) {
+    if (jb.g.Cin > 32) pm_conv_wgrad_block<4, 4>(jb, bid, lds);
+    else pm_conv_wgrad_block<4, 2>(jb, bid, lds);
+  } else {
+    if (jb.g.Cin > 32) pm_conv_wgrad_block<2, 4>(jb, bid, lds);
+    else pm_conv_wgrad_block<2, 2>(jb, bid, lds);
   }
 }
 
@@ -1083,7 +1117,9 @@ inline void pm_conv_transpose_launch(hipStream_t st, const PmCvTransposeJob* v, 
 
 // Chunks of 32 pixels per wave and blocks of the MFMA weight-gradient kernel.  Each block (times three tap rows) writes a
 // partial that is read once more.  In a step, whose units share launches: at most 64, 32 of the wide tensors, whose
-// partials are 147 KB each.  A unit by itself (ALONE) has to fill the chip: up to 256 and 64 where that leaves a wave four
+// partials are 147 KB each, and eight chunks a wave where the map has them (a block's start and the sums of its waves cost as
+// much as two or three chunks: ResNet-20 on 128 images 476 us a step with as few as one, 469 from 4, 461 from 8; ResNet-14 on 37
+// of 28 x 28: 215, 210 and, where that leaves too few blocks, 216).  A unit by itself (ALONE) has to fill the chip: up to 256 and 64 where that leaves a wave four
 // chunks.  Us with 64 (32) blocks, now, and with twice as many: 512 x 64 x 64 x 16 channels 184, 77, 81; 512 x 32 x 32 x 32 68,
 // 34, 42; 256 x 32 x 32 x 64 137, 76, 107; 128 x 16 x 16 x 32, below four chunks, 12, 12, 15.  Never more partials than
 // pm_conv_wgrad_scratch_elems has room for: one per 16 chunks from 2048 chunks on, one per 4 below.
@@ -1092,7 +1128,8 @@ inline void pm_conv_wgrad_plan(const PmConvGeom& g, bool alone, int* blocks, int
   const bool wide = g.Cin * g.Cout > 1024;
   int64_t most = wide ? 32 : 64;
   if (alone) most = std::max<int64_t>(most, std::min<int64_t>(wide ? 64 : 256, chunks / 16));
-  const int64_t c = (chunks + 4 * most - 1) / (4 * most);
+  int64_t c = (chunks + 4 * most - 1) / (4 * most);
+  if (!alone) c = std::max(c, std::min<int64_t>(8, (chunks + 27) / 28));
   *nch = (int)c;
   *blocks = (int)((chunks + c * 4 - 1) / (c * 4));
 }
@@ -1123,31 +1160,36 @@ inline size_t pm_conv_wgrad_scratch_elems(const PmConvGeom& g) {
   return (size_t)((chunks + c - 1) / c) * g.Cout * 9 * g.Cin;
 }
 
-// The MFMA weight gradients of a list of units, one launch per pair of channel tiles and PM_CONV_JOBS units
+// The MFMA weight gradients of a list of units: one launch for those of 16 channels and one for all others, per PM_CONV_JOBS units
 inline void pm_conv_wgrad_group_launch(hipStream_t st, const PmCvWgradJob* v, int count, bool alone = false) {
-  for (int cls = 0; cls < 5; ++cls) {
+  auto class_of = [](const PmConvGeom& g) { return g.Cin == 16 && g.Cout == 16 ? 4 : (g.Cout > 32 ? 2 : 0) + (g.Cin > 32 ? 1 : 0); };
+  for (int thin = 0; thin < 2; ++thin) {
     PmCvWgradList l{};
-    int blocks = 0;
+    int blocks = 0, classes = 0;                          // (bit per class)
     auto flush = [&]() {
       if (!l.count) return;
       const dim3 grid((unsigned)blocks, 3), blk(256);
-      if (cls == 0) hipLaunchKernelGGL((pm_conv_wgrad_mfma_kernel<2, 2>), grid, blk, 0, st, l);
-      else if (cls == 1) hipLaunchKernelGGL((pm_conv_wgrad_mfma_kernel<2, 4>), grid, blk, 0, st, l);
-      else if (cls == 2) hipLaunchKernelGGL((pm_conv_wgrad_mfma_kernel<4, 2>), grid, blk, 0, st, l);
-      else if (cls == 3) hipLaunchKernelGGL((pm_conv_wgrad_mfma_kernel<4, 4>), grid, blk, 0, st, l);
-      else hipLaunchKernelGGL((pm_conv_wgrad_mfma_kernel<1, 1>), grid, blk, 0, st, l);
-      l.count = blocks = 0;
+      switch (classes) {
+        case 1 << 0: hipLaunchKernelGGL((pm_conv_wgrad_mfma_kernel<2, 2>), grid, blk, 0, st, l); break;
+        case 1 << 1: hipLaunchKernelGGL((pm_conv_wgrad_mfma_kernel<2, 4>), grid, blk, 0, st, l); break;
+        case 1 << 2: hipLaunchKernelGGL((pm_conv_wgrad_mfma_kernel<4, 2>), grid, blk, 0, st, l); break;
+        case 1 << 3: hipLaunchKernelGGL((pm_conv_wgrad_mfma_kernel<4, 4>), grid, blk, 0, st, l); break;
+        case 1 << 4: hipLaunchKernelGGL((pm_conv_wgrad_mfma_kernel<1, 1>), grid, blk, 0, st, l); break;
+        default: hipLaunchKernelGGL(pm_conv_wgrad_wide_kernel, grid, blk, 0, st, l);
+      }
+      l.count = blocks = classes = 0;
     };
-    for (int i = 0; i < count; ++i) {
-      const bool thin = v[i].g.Cin == 16 && v[i].g.Cout == 16;
-      if ((thin ? 4 : (v[i].g.Cout > 32 ? 2 : 0) + (v[i].g.Cin > 32 ? 1 : 0)) != cls) continue;
-      int nb, nch;
-      pm_conv_wgrad_plan(v[i].g, alone, &nb, &nch);
-      l.job[l.count] = v[i];
-      l.job[l.count].nch = nch;
-      l.end[l.count++] = blocks += nb;
-      if (l.count == PM_CONV_JOBS) flush();
-    }
+    for (int cls = thin ? 4 : 3; cls >= (thin ? 4 : 0); --cls)      // the widest, and so the longest, blocks first
+      for (int i = 0; i < count; ++i) {
+        if (class_of(v[i].g) != cls) continue;
+        int nb, nch;
+        pm_conv_wgrad_plan(v[i].g, alone, &nb, &nch);
+        l.job[l.count] = v[i];
+        l.job[l.count].nch = nch;
+        l.end[l.count++] = blocks += nb;
+        classes |= 1 << class_of(v[i].g);
+        if (l.count == PM_CONV_JOBS) flush();
+      }
     flush();
   }
 }
