@@ -409,17 +409,52 @@ struct PmReduceJob {
   int cin, cpad;     // rows of cin elements lie cpad apart in the partials (0: they lie as in the output)
 };
 constexpr int PM_CONV_JOBS = 24;       // jobs of one launch (they travel as kernel arguments)
+constexpr int PM_REDUCE_JOBS = 64;     // (3.4 KB of arguments)
 struct PmReduceList {
-  PmReduceJob job[PM_CONV_JOBS];
-  int end[PM_CONV_JOBS];               // first block behind each job
+  PmReduceJob job[PM_REDUCE_JOBS];
+  int end[PM_REDUCE_JOBS];             // first block behind each job
   int count;
 };
+// A job of few elements and many partials (the channel sums of the affine backward: 32 .. 128 elements, up to 1024 partials) has
+// one block, whose chain of loads the whole launch waits for: there a thread takes four neighbouring elements of every 256 / (n / 4)-th
+// partial.
+inline __host__ __device__ bool pm_conv_reduce_narrow(const PmReduceJob& jb) { return jb.n <= 128 && jb.n % 4 == 0 && !jb.cpad && jb.nparts >= 64; }
 // Block = 16 slices of the partial range x 64 elements, four per thread: many short chains of independent
 // loads instead of a few long ones (the arrays are small; what matters is the latency of the longest chain).
 __global__ __launch_bounds__(256) void pm_conv_reduce_kernel(PmReduceList list) {
   int k = 0;
   while (k + 1 < list.count && (int)blockIdx.x >= list.end[k]) ++k;
   const PmReduceJob jb = list.job[k];
+  __shared__ __attribute__((aligned(16))) float s[16][64];
+  if (pm_conv_reduce_narrow(jb)) {                           // uniform over the block
+    const int n4 = jb.n >> 2, slices = 256 / n4, slice = (int)threadIdx.x / n4, c = ((int)threadIdx.x - slice * n4) * 4;
+    float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+    auto add = [&](const float4& v) __attribute__((always_inline)) { sum.x += v.x; sum.y += v.y; sum.z += v.z; sum.w += v.w; };
+    if (slice < slices) {
+      const float* p = jb.part + c;
+      int r = slice;
+      for (; r + 7 * slices < jb.nparts; r += 8 * slices) {
+        float4 v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const float4*>(p + (int64_t)(r + u * slices) * jb.n);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) add(v[u]);
+      }
+      for (; r < jb.nparts; r += slices) add(*reinterpret_cast<const float4*>(p + (int64_t)r * jb.n));
+    }
+    float4* all = reinterpret_cast<float4*>(&s[0][0]);
+    all[threadIdx.x] = sum;
+    __syncthreads();
+    if ((int)threadIdx.x < n4) {
+#pragma unroll 8
+      for (int q = 1; q < slices; ++q) add(all[q * n4 + threadIdx.x]);
+      float* o = jb.out + c;
+      const float out[4] = {sum.x, sum.y, sum.z, sum.w};
+#pragma unroll
+      for (int q = 0; q < 4; ++q) o[q] = jb.accumulate ? o[q] + out[q] : out[q];
+    }
+    return;
+  }
   const int el = threadIdx.x & 15, sl = threadIdx.x >> 4;
   const int e0 = ((int)blockIdx.x - (k ? list.end[k - 1] : 0)) * 64;
   float acc[4] = {0.f, 0.f, 0.f, 0.f};
@@ -448,7 +483,6 @@ __global__ __launch_bounds__(256) void pm_conv_reduce_kernel(PmReduceList list) 
 #pragma unroll 1
   for (; p + 16 < jb.nparts; p += 32) rows(std::integral_constant<int, 2>());
   if (p < jb.nparts) rows(std::integral_constant<int, 1>());
-  __shared__ float s[16][64];
 #pragma unroll
   for (int q = 0; q < 4; ++q) s[sl][16 * q + el] = acc[q];
   __syncthreads();
@@ -460,15 +494,15 @@ __global__ __launch_bounds__(256) void pm_conv_reduce_kernel(PmReduceList list) 
     *o = jb.accumulate ? *o + v : v;
   }
 }
-// the jobs of `v`, in launches of up to PM_CONV_JOBS
+// the jobs of `v`, in launches of up to PM_REDUCE_JOBS
 inline void pm_conv_reduce_launch(hipStream_t st, const PmReduceJob* v, int count) {
-  for (int at = 0; at < count; at += PM_CONV_JOBS) {
+  for (int at = 0; at < count; at += PM_REDUCE_JOBS) {
     PmReduceList l{};
-    l.count = std::min(PM_CONV_JOBS, count - at);
+    l.count = std::min(PM_REDUCE_JOBS, count - at);
     int blocks = 0;
     for (int k = 0; k < l.count; ++k) {
       l.job[k] = v[at + k];
-      l.end[k] = blocks += (v[at + k].n + 63) / 64;
+      l.end[k] = blocks += pm_conv_reduce_narrow(v[at + k]) ? 1 : (v[at + k].n + 63) / 64;
     }
     hipLaunchKernelGGL(pm_conv_reduce_kernel, dim3((unsigned)blocks), dim3(256), 0, st, l);
   }
