@@ -250,3 +250,26 @@ def test_small_resnet_modes(torch_cuda, case):
     print(case, "max-rel", err)
     assert err <= TOL[dtype], errs
     g.close()
+
+
+@pytest.mark.parametrize("batch", [126, 128, 130, 511, 1025])
+def test_channel_sums_of_many_partials(torch_cuda, batch):
+    """Scale and shift gradients of the image layer in fp32, whose 32 sums come from 63, 64, 65, 256 and 513 partials: the reduction
+    changes its walk from 64 on, in whole and partial turns of 32 slices and eight loads.  A ReLU whose input
+    rounds across zero (one in 10^6) moves a sum by one of its up to 65600 terms, 2e-5 of it; the bound is ten of those, a
+    partial left out is ten times the bound."""
+    torch = torch_cuda
+    w = wl.resnet(1, batch, dtype="f32", image=8)
+    params = wl.init_params(w)
+    kw = dict(opt="sgdm", lr=0.02, beta=0.9, D=0.5, K=6)
+    tf, tb = po.pipeline_delays(w.P, 1)
+    o, g = make_oracle(w, params, tf, tb, **kw), make_gpu(w, params, tf, tb, **kw)
+    x, y = wl.ImageStream(w).batch(0)
+    o.step((x, y))
+    g.step(torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda(), want_loss=True)
+    nw = w.layers[0].n_out * 9 * w.layers[0].n_in
+    for part in (slice(nw, nw + 16), slice(nw + 16, None)):
+        a, b = g.state(4, 0)[part].astype(np.float64), o.last_grads[0][part]
+        err = float(np.max(np.abs(a - b)) / np.max(np.abs(b)))
+        assert err <= 2e-4, err
+    g.close()
