@@ -908,8 +908,23 @@ pm_status launch_tfm(pm_ctx* c, const void* x_dev, const void* y_dev, int accumu
     dgrad_f32(u + 2, dzk, d, d, d, out, 1);
     dgrad_f32(u + 3, dzv, d, d, d, out, 1);
   };
+  // The matrices of units first .. last, to be read ahead by a LayerNorm's launch.  Not beyond 4096 rows: the products are bound by the matrix
+  // units there and the LayerNorms by memory.
+  auto ahead = [&](bool backward, int first, int last) {
+    PmReadAhead ra{};
+    if (sizeof(T) != 2 || Tk > 4096) return ra;
+    for (int u = first; u <= last; ++u) {
+      const PmWLoc<T> W = backward ? Wb(u, 0) : Wx(u, 0);
+      ra.m[ra.count++] = PmReadAhead::Span{reinterpret_cast<const unsigned char*>(W.base), W.slot, W.stride * (int64_t)sizeof(T),
+                                           (int64_t)U(u).d.n_in * U(u).d.n_out * (int64_t)sizeof(T)};
+    }
+    ra.blocks = 64;
+    return ra;
+  };
   auto ln_fwd = [&](int u, const float* x, T* out, float* mu, float* rs) {
-    pm_ln_fwd_launch<T>(st, x, Wx(u, 0), (int)U(u).boff, out, mu, rs, Tk, d);
+    const int j = (u - 1) % 8;                     // first LayerNorm of a layer: its projections; second: the feed-forward pair
+    pm_ln_fwd_launch<T>(st, x, Wx(u, 0), (int)U(u).boff, out, mu, rs, Tk, d,
+                        u == L - 2 ? PmReadAhead{} : j == 0 ? ahead(false, u + 1, u + 4) : ahead(false, u + 1, u + 2));
   };
   const int ln_rows = (int)pm_ln_part_blocks(Tk);
   auto ln_table = [&](int u) -> float* {                      // unit u's table of column sums (null: atomics)
@@ -919,7 +934,7 @@ pm_status launch_tfm(pm_ctx* c, const void* x_dev, const void* y_dev, int accumu
   auto ln_bwd = [&](int u, const float* dy, const float* x, const float* mu, const float* rs, const float* dx_res,
                     float* dx_out, T* dx_t) {
     pm_ln_bwd_launch<T>(st, dy, x, mu, rs, Wb(u, 0), dx_res, dx_out, dx_t, g + U(u).off, g + U(u).off + U(u).boff, Tk, d, 1, 0,
-                        ln_table(u));
+                        ln_table(u), (u - 1) % 8 ? ahead(true, u - 4, u - 1) : u > 1 ? ahead(true, u - 2, u - 1) : PmReadAhead{});
   };
   auto F = [&](size_t off) { return c->at<float>(off); };
   auto TT = [&](size_t off) { return c->at<T>(off); };
@@ -1045,7 +1060,7 @@ pm_status launch_tfm(pm_ctx* c, const void* x_dev, const void* y_dev, int accumu
   if (dn_parts == 1) dgrad_f32(L - 1, TT(lay.t_dlogits), ldV, V, d, dn, 0);
   PM_ENTER(L - 2);
   pm_ln_bwd_launch<T>(st, dnf, F(lay.t_xf), F(lay.t_muf), F(lay.t_rsf), Wb(L - 2, 0), nullptr, dx, nl ? TT(lay.tl[nl - 1].dz2) : nullptr,
-                      g + U(L - 2).off, g + U(L - 2).off + U(L - 2).boff, Tk, d, dn_parts, (int64_t)Tk * d, ln_table(L - 2));
+                      g + U(L - 2).off, g + U(L - 2).off + U(L - 2).boff, Tk, d, dn_parts, (int64_t)Tk * d, ln_table(L - 2), nl ? ahead(true, L - 4, L - 3) : PmReadAhead{});
   for (int l = nl - 1; l >= 0; --l) {
     const Layout::TfmLayer& b = lay.tl[l];
     const int u = 1 + 8 * l;

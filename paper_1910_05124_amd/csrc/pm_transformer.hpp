@@ -114,6 +114,25 @@ __global__ __launch_bounds__(256) void pm_embed_fwd_kernel(const int32_t* __rest
   }
 }
 
+// Weights of the products that follow a LayerNorm, read while it runs, by the first `blocks` blocks of its launch: a weight matrix was last
+// touched many steps ago (a ring slot) or by the update of the step before, so a product that finds it in memory waits 1.5 to 3 us longer
+// than one that finds it in the last-level cache.
+struct PmReadAhead {
+  struct Span { const unsigned char* base; const int32_t* slot; int64_t stride_bytes; int64_t bytes; };
+  Span m[4];
+  int count, blocks;
+};
+__device__ __forceinline__ void pm_read_ahead(const PmReadAhead& ra) {
+  uint32_t acc = 0;
+  for (int k = 0; k < ra.count; ++k) {
+    const PmReadAhead::Span& s = ra.m[k];
+    const unsigned char* base = s.base + (s.slot ? (int64_t)(*s.slot) * s.stride_bytes : 0);
+    for (int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 128; i < s.bytes; i += (int64_t)ra.blocks * blockDim.x * 128)
+      acc |= *reinterpret_cast<const uint32_t*>(base + i);
+  }
+  asm volatile("" ::"v"(acc));                            // the reads have no other use: keep them
+}
+
 // ---------------------------------------------------------------------------------------------
 // LayerNorm forward: one wavefront per row, the row held in registers (lane l owns columns
 // 256 c + 4 l .. + 3, d <= 256 NC, d a multiple of 4).  Stores mean and 1/sqrt(var + eps) for the
@@ -122,8 +141,12 @@ __global__ __launch_bounds__(256) void pm_embed_fwd_kernel(const int32_t* __rest
 template <typename T, int NC>
 __global__ __launch_bounds__(256) void pm_ln_fwd_kernel(const float* __restrict__ x, PmWLoc<T> gb, int boff,
                                                         T* __restrict__ out, float* __restrict__ mean,
-                                                        float* __restrict__ rstd, int rows, int d) {
-  const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+                                                        float* __restrict__ rstd, int rows, int d, PmReadAhead ra) {
+  if ((int)blockIdx.x < ra.blocks) {
+    pm_read_ahead(ra);
+    return;
+  }
+  const int row = ((int)blockIdx.x - ra.blocks) * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (row >= rows) return;
   const int64_t ro = (int64_t)row * d;
   float4 xv[NC];
@@ -188,7 +211,12 @@ __global__ __launch_bounds__(512) void pm_ln_bwd_kernel(const float* __restrict_
                                                         const float* __restrict__ mean, const float* __restrict__ rstd,
                                                         PmWLoc<T> gain_bkwd, const float* dx_res, float* dx_out,
                                                         T* dx_out_t, float* __restrict__ dgain, float* __restrict__ dbias,
-                                                        int rows, int d, int parts, int64_t part_stride) {
+                                                        int rows, int d, int parts, int64_t part_stride, PmReadAhead ra) {
+  if ((int)blockIdx.x < ra.blocks) {
+    pm_read_ahead(ra);
+    return;
+  }
+  const int block = (int)blockIdx.x - ra.blocks;
   __shared__ float4 red[8][2][64 * NC];                       // per wave: gain and bias partial sums
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const T* g = gain_bkwd.get();
@@ -207,7 +235,7 @@ __global__ __launch_bounds__(512) void pm_ln_bwd_kernel(const float* __restrict_
   float mur[RPW], rsr[RPW];
 #pragma unroll
   for (int r = 0; r < RPW; ++r) {
-    const int row = blockIdx.x * (8 * RPW) + wave * RPW + r;
+    const int row = block * (8 * RPW) + wave * RPW + r;
     const int rowc = row < rows ? row : rows - 1;
     const int64_t ro = (int64_t)rowc * d;
     mur[r] = mean[rowc];
@@ -224,7 +252,7 @@ __global__ __launch_bounds__(512) void pm_ln_bwd_kernel(const float* __restrict_
 #pragma unroll
   for (int r = 0; r < RPW; ++r)
     for (int p = 1; p < parts; ++p) {                         // the gradient arrives as several addends
-      const int row = blockIdx.x * (8 * RPW) + wave * RPW + r;
+      const int row = block * (8 * RPW) + wave * RPW + r;
       const float* dyp = dy + p * part_stride + (int64_t)(row < rows ? row : rows - 1) * d;
 #pragma unroll
       for (int c = 0; c < NC; ++c) {
@@ -235,7 +263,7 @@ __global__ __launch_bounds__(512) void pm_ln_bwd_kernel(const float* __restrict_
     }
 #pragma unroll
   for (int r = 0; r < RPW; ++r) {
-    const int row = blockIdx.x * (8 * RPW) + wave * RPW + r;
+    const int row = block * (8 * RPW) + wave * RPW + r;
     if (row >= rows) break;                                   // wave-uniform
     const float mu = mur[r], rs = rsr[r];
     const int64_t ro = (int64_t)row * d;
@@ -292,8 +320,8 @@ __global__ __launch_bounds__(512) void pm_ln_bwd_kernel(const float* __restrict_
       sb += pb[e];
     }
     if (PART) {                                               // dgain: the table [blocks][2][d]
-      dgain[(int64_t)blockIdx.x * 2 * d + j] = sg;
-      dgain[(int64_t)blockIdx.x * 2 * d + d + j] = sb;
+      dgain[(int64_t)block * 2 * d + j] = sg;
+      dgain[(int64_t)block * 2 * d + d + j] = sb;
     } else {
       atomicAdd(dgain + j, sg);
       atomicAdd(dbias + j, sb);
@@ -380,10 +408,10 @@ __global__ __launch_bounds__(256) void pm_cast_kernel(const float* __restrict__ 
 // ---------------------------------------------------------------------------------------------
 template <typename T>
 inline bool pm_ln_fwd_launch(hipStream_t st, const float* x, PmWLoc<T> gb, int boff, T* out, float* mean, float* rstd,
-                             int rows, int d) {
+                             int rows, int d, const PmReadAhead& ra = PmReadAhead{}) {
   if ((d & 3) || (boff & 3)) return false;
-  const dim3 grid((rows + 3) / 4), blk(256);
-#define PM_LNF(NC) hipLaunchKernelGGL((pm_ln_fwd_kernel<T, NC>), grid, blk, 0, st, x, gb, boff, out, mean, rstd, rows, d)
+  const dim3 grid(ra.blocks + (rows + 3) / 4), blk(256);
+#define PM_LNF(NC) hipLaunchKernelGGL((pm_ln_fwd_kernel<T, NC>), grid, blk, 0, st, x, gb, boff, out, mean, rstd, rows, d, ra)
   if (d <= 256) PM_LNF(1);
   else if (d <= 512) PM_LNF(2);
   else if (d <= 768) PM_LNF(3);
@@ -397,11 +425,12 @@ inline bool pm_ln_fwd_launch(hipStream_t st, const float* x, PmWLoc<T> gb, int b
 template <typename T>
 inline bool pm_ln_bwd_launch(hipStream_t st, const float* dy, const float* x, const float* mean, const float* rstd,
                              PmWLoc<T> gain_bkwd, const float* dx_res, float* dx_out, T* dx_out_t, float* dgain,
-                             float* dbias, int rows, int d, int parts = 1, int64_t part_stride = 0, float* table = nullptr) {
+                             float* dbias, int rows, int d, int parts = 1, int64_t part_stride = 0, float* table = nullptr,
+                             const PmReadAhead& ra = PmReadAhead{}) {
   if (d & 3) return false;
   const int rpw = table ? pm_ln_part_rpw(rows) : 4;
-  const dim3 grid((rows + 8 * rpw - 1) / (8 * rpw)), blk(512);
-#define PM_LNB(NC, RPW, PART) hipLaunchKernelGGL((pm_ln_bwd_kernel<T, NC, RPW, PART>), grid, blk, 0, st, dy, x, mean, rstd, gain_bkwd, dx_res, dx_out, dx_out_t, PART ? table : dgain, dbias, rows, d, parts, part_stride)
+  const dim3 grid(ra.blocks + (rows + 8 * rpw - 1) / (8 * rpw)), blk(512);
+#define PM_LNB(NC, RPW, PART) hipLaunchKernelGGL((pm_ln_bwd_kernel<T, NC, RPW, PART>), grid, blk, 0, st, dy, x, mean, rstd, gain_bkwd, dx_res, dx_out, dx_out_t, PART ? table : dgain, dbias, rows, d, parts, part_stride, ra)
 #define PM_LNB_ROWS(NC) do { if (!table) PM_LNB(NC, 4, false); else if (rpw == 1) PM_LNB(NC, 1, true); else PM_LNB(NC, 2, true); } while (0)
   if (d <= 256) PM_LNB_ROWS(1);
   else if (d <= 512) PM_LNB_ROWS(2);
