@@ -918,7 +918,7 @@ pm_status launch_tfm(pm_ctx* c, const void* x_dev, const void* y_dev, int accumu
       ra.m[ra.count++] = PmReadAhead::Span{reinterpret_cast<const unsigned char*>(W.base), W.slot, W.stride * (int64_t)sizeof(T),
                                            (int64_t)U(u).d.n_in * U(u).d.n_out * (int64_t)sizeof(T)};
     }
-    ra.blocks = 64;
+    ra.spread(backward ? 512 : 256);
     return ra;
   };
   auto ln_fwd = [&](int u, const float* x, T* out, float* mu, float* rs) {
