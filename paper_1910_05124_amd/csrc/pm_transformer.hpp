@@ -116,7 +116,7 @@ __global__ __launch_bounds__(256) void pm_embed_fwd_kernel(const int32_t* __rest
 
 // Weights of the products that follow a LayerNorm, read while it runs, by the first `blocks` blocks of its launch: a weight matrix was last
 // touched many steps ago (a ring slot) or by the update of the step before, so a product that finds it in memory waits 1.5 to 3 us longer
-// than one that finds it in the last-level cache.  Step on one box without, with 64 blocks a launch, and with a line for each thread: 6 x 512
+// than one that finds it in the last-level cache.  Step time without, with 64 blocks a launch, and with a line for each thread: 6 x 512
 // layers, 4096 rows 1683, 1657, 1626 us; 3 x 768, four times 2048 rows 4411, 4311, 4227; 4 x 320, 2400 rows 787, 773, 761.
 struct PmReadAhead {
   struct Span { const unsigned char* base; const int32_t* slot; int64_t stride_bytes; int64_t bytes; };
